@@ -165,11 +165,11 @@ SHPLB_API int32_t shplb_sparse_attn_prefill(const shplb_problem* p, const void* 
 
 /* For callers that cannot allocate device memory or hand over a workspace (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the attention step of
- * shplb_sparse_attn_prefill with its scratch (ordering histograms, work-item queues, tickets)
- * in a static device array of SHPLB_STATIC_SCRATCH_BYTES inside the library instead of a
- * workspace argument.  Same kernels, same results, bit for bit.  It allocates and frees
- * nothing.  The scratch needed is about 100 bytes per (sequence, head, query block) row: the
- * array covers about 80 000 rows (a 128K-token layer of 32 heads has 32 768); a larger
+ * shplb_sparse_attn_prefill with its scratch (work-item queues, tickets) in a static
+ * device array of SHPLB_STATIC_SCRATCH_BYTES inside the library instead of a workspace
+ * argument.  Same kernels, same results, bit for bit.  It allocates and frees
+ * nothing.  The scratch needed is 64 bytes per (sequence, head, query block) row: the
+ * array covers about 131 000 rows (a 128K-token layer of 32 heads has 32 768); a larger
  * problem is refused with SHPLB_E_WORKSPACE before any device work.
  * Every GPU the library is used on holds its own copy of the array until the process ends.
  * All calls on one GPU share it: the kernels rewrite everything they read, so calls in

@@ -76,20 +76,14 @@ WorkspaceLayout make_layout(const Geometry& g, int32_t split_slots, bool with_po
   int64_t off = 0;
   w.qbar = off; off += with_pooled ? align256(int64_t(g.meta.n_q_heads) * g.total_blocks * kHeadDim * 6) : 0;
   w.kbar = off; off += with_pooled ? align256(int64_t(g.meta.n_kv_heads) * g.total_blocks * kHeadDim * 6) : 0;
-  w.order_by_cost = off; off += align256(g.rows * 4);
   // Items: one per row plus the extra pieces of split rows.  split_length() keeps the pieces
   // within whatever number of slots it is given.
   w.slot_capacity = std::max<int32_t>(split_slots, 0);
   w.item_capacity = g.rows + w.slot_capacity;
   w.items = off; off += align256(w.item_capacity * int64_t(sizeof(ItemRec)));
   w.split_done = off; off += align256((w.slot_capacity / 2 + 1) * int64_t(sizeof(uint32_t)));
-  w.split_count = off; off += 256;
   w.part_o = off; off += align256(w.slot_capacity * kSlotFloatsO * 4);
   w.part_ml = off; off += align256(w.slot_capacity * kSlotFloatsML * 4);
-  const int64_t n_chunks = (g.rows + kOrderChunk - 1) / kOrderChunk;
-  w.hist = off; off += align256(n_chunks * kCostBins * 4);
-  w.bin_start = off; off += align256(int64_t(kCostBins) * 4);
-  w.xcd_hist = off; off += align256(n_chunks * kXcds * 4);
   w.queue_begin = off; off += 256;
   w.tickets = off; off += align256(int64_t(kXcds) * kTicketStride * 4);
   w.total = off;
@@ -116,8 +110,7 @@ int32_t persistent_workgroups(int block) {
 using namespace shplb;
 
 // Scratch of the entry point that allocates nothing (shplb_sparse_attn_prefill_static): the
-// ordering kernels' histograms, the work-item queues and their tickets live here instead of in
-// a caller's workspace.  The array's name is only a host-side handle; its device address is
+// work-item queues and their tickets live here instead of in a caller's workspace.  The array's name is only a host-side handle; its device address is
 // asked for once per device (every device holds its own copy) and that pointer is what the
 // kernels get.
 static __device__ __align__(256) unsigned char scratch[SHPLB_STATIC_SCRATCH_BYTES];
@@ -259,14 +252,15 @@ int32_t attention_entry(const shplb_problem* p, const void* q, const void* k, co
   const WorkspaceLayout w = make_layout(g, split_slots, !static_scratch_call);
   char* ws = static_cast<char*>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (int32_t rc = launch_order(g, sel_ptr, w, ws, n_wg, st)) return rc;
-  const WorkQueues wq{reinterpret_cast<const ItemRec*>(ws + w.items),
+  const AttentionPlan plan = plan_attention(g, n_wg, w.slot_capacity);
+  if (plan.ordered)
+    if (int32_t rc = launch_order(g, sel_ptr, sel_idx, w, ws, n_wg, plan.grid, st)) return rc;
+  const WorkQueues wq{plan.ordered ? reinterpret_cast<const ItemRec*>(ws + w.items) : nullptr,
                       reinterpret_cast<const int32_t*>(ws + w.queue_begin),
                       reinterpret_cast<uint32_t*>(ws + w.tickets)};
   const SplitBuffers sb{reinterpret_cast<float*>(ws + w.part_o), reinterpret_cast<float*>(ws + w.part_ml),
-                        reinterpret_cast<uint32_t*>(ws + w.split_done),
-                        reinterpret_cast<SplitCounters*>(ws + w.split_count), int32_t(w.slot_capacity)};
-  return launch_attention(g, q, k, v, sel_ptr, sel_idx, out, lse_out, static_cast<shplb_wg_stats*>(sched_stats_out),
+                        reinterpret_cast<uint32_t*>(ws + w.split_done), int32_t(w.slot_capacity)};
+  return launch_attention(g, plan, q, k, v, sel_ptr, sel_idx, out, lse_out, static_cast<shplb_wg_stats*>(sched_stats_out),
                           wq, sb, n_wg, st);
 }
 

@@ -44,6 +44,9 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const char* p) {
 }
 
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
+// Wait until at most N (< 16) of the wave's vector memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vmem_but(std::integral_constant<int, N>) { __builtin_amdgcn_s_waitcnt(0x0f70 | N); }
 
 // One wave copies 64 x 16 bytes from global memory (uniform base + per-lane byte
 // offset) to the 1 KB of LDS starting at lds_base: lane l's 16 bytes land at
@@ -140,7 +143,7 @@ constexpr int kDeferredMerges = 1024;   // rows a workgroup can owe a merge (it 
 // waits until its stores are done, the workgroup meets at a barrier, one thread counts the piece with
 // a device-scope atomic.  Returns (to all threads) whether this piece completed its row.
 __device__ __forceinline__ bool count_piece(const SplitBuffers& sb, int pieces, int split_index, int32_t* s_flag) {
-  // item records come from the ordering kernels; a malformed one must not index out of bounds
+  // item records come from the ordering kernel; a malformed one must not index out of bounds
   if (pieces < 2 || pieces > kMaxPieces || split_index < 0 || split_index > sb.slot_capacity / 2) return false;
   wait_vmem_all();
   __syncthreads();

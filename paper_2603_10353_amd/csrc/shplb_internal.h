@@ -3,13 +3,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "shplb.h"
 
 namespace shplb {
 
 constexpr int kHeadDim = 128;
 constexpr int kCostBins = 4100;       // selected-block counts 0..SHPLB_MAX_BLOCKS, rounded up
-constexpr int kOrderChunk = 256;      // rows per workgroup in the ordering kernels
 constexpr int kXcds = 8;              // accelerator dies (XCDs) of an MI355X, each with its own L2
 constexpr int kTicketStride = 16;     // uint32 slots between two queue tickets (one 64-byte line each)
 constexpr int kSplitSlotsMax = 1 << 16;   // most partial-result slots a caller may ask for (64 KB + 1 KB each)
@@ -51,16 +52,11 @@ struct Geometry {
 // Workspace carve-up (byte offsets, each 256-byte aligned).
 struct WorkspaceLayout {
   int64_t qbar, kbar;        // pooled blocks as three bf16 planes, each [H][total_blocks][128]
-  int64_t order_by_cost;     // int32 [rows]: rows by descending cost (intermediate)
   int64_t items;             // ItemRec [item_capacity]: the work items, one queue per XCD after the other
   int64_t split_done;        // uint32 [slot_capacity / 2 + 1]: pieces finished, per split row
-  int64_t split_count;       // SplitCounters
   int64_t part_o;            // float [slot_capacity][128][kHeadDim]: partial results of the pieces
   int64_t part_ml;           // float [slot_capacity][2][128]
   int64_t item_capacity, slot_capacity;   // counts, not offsets
-  int64_t hist;              // int32 [n_chunks][kCostBins]
-  int64_t bin_start;         // int32 [kCostBins]
-  int64_t xcd_hist;          // int32 [n_chunks][kXcds]
   int64_t queue_begin;       // int32 [kXcds + 1]: queue x is items[queue_begin[x] .. queue_begin[x+1])
   int64_t tickets;           // uint32 [kXcds * kTicketStride]
   int64_t total;
@@ -79,15 +75,16 @@ int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, floa
                            uint16_t* q_planes, uint16_t* k_planes, int n_compute_units, hipStream_t stream);
 int32_t launch_select(const Geometry& g, const float* scores, const int64_t* sel_ptr,
                       int32_t* sel_idx, hipStream_t stream);
-int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const WorkspaceLayout& w,
-                     char* workspace, int32_t n_wg, hipStream_t stream);
+int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* sel_idx, const WorkspaceLayout& w,
+                     char* workspace, int32_t n_wg, int32_t grid, hipStream_t stream);
 int32_t launch_mfma_rate(int random_operands, int iters, int n_workgroups, void* scratch, hipStream_t stream);
 int32_t launch_block_mass(const Geometry& g, const void* q, const void* k, float* mass, hipStream_t stream);
 int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, const int32_t* budgets,
                               int32_t n_budgets, float* recovery, hipStream_t stream);
 // One work item of an attention launch: a row, or one piece of a row that was split along
-// its selected key blocks (positions [first, first + n_sel) of the row's selection).
-struct alignas(32) ItemRec {
+// its selected key blocks (positions [first, first + n_sel) of the row's selection).  It carries
+// everything a workgroup needs to start: sixteen words, one scalar load.
+struct alignas(64) ItemRec {
   int32_t row;
   int32_t n_sel;        // selected key blocks this item covers
   int64_t sel_begin;    // index of its first one in sel_idx
@@ -95,10 +92,10 @@ struct alignas(32) ItemRec {
   int32_t pieces;       // pieces of its row (1: whole row)
   int32_t first_slot;   // slot of the row's first piece; the row's pieces hold slots first_slot .. + pieces - 1
   int32_t split_index;  // the row's entry in the finished-pieces counters
-};
-
-struct SplitCounters {
-  uint32_t n_slots, n_rows;   // slots handed out, rows split (zeroed by the ordering kernels)
+  int32_t seq_begin, seq_end;         // tokens of the row's sequence
+  int32_t head, kv_head, query_block;
+  int32_t n_blocks;                   // blocks of the sequence
+  int32_t first_block, second_block;  // the item's first two selected blocks (the same one twice if it has one)
 };
 
 // Longest item, in key blocks, of a launch whose rows select total_cost blocks in all, run by
@@ -128,23 +125,30 @@ __host__ __device__ inline int pieces_of(int64_t n_sel, int64_t split_len) {
 // piece c of a row of n selected blocks cut into p pieces covers [piece_begin(c), piece_begin(c + 1))
 __host__ __device__ inline int64_t piece_begin(int64_t n_sel, int p, int c) { return n_sel * c / p; }
 
-// The per-XCD work queues the ordering kernels build (device pointers into the workspace).
+// The per-XCD work queues the ordering kernel builds (device pointers into the workspace).
 struct WorkQueues {
   const ItemRec* items;        // items, queue after queue, each by descending row cost
   const int32_t* queue_begin;  // [kXcds + 1]
-  uint32_t* tickets;           // [kXcds * kTicketStride], zeroed by the ordering kernels
+  uint32_t* tickets;           // [kXcds * kTicketStride]: items taken, set by the ordering kernel to those that
+                               // the attention launch's workgroups start with (see order_kernel)
 };
 
 // Where the pieces of split rows leave their results, and the per-row counts of finished pieces.
 struct SplitBuffers {
   float* part_o;
   float* part_ml;
-  uint32_t* done;              // [slot_capacity / 2 + 1], zeroed by the ordering kernels
-  SplitCounters* count;
+  uint32_t* done;              // [slot_capacity / 2 + 1], zeroed by the ordering kernel
   int32_t slot_capacity;
 };
 
-int32_t launch_attention(const Geometry& g, const void* q, const void* k, const void* v,
+// How an attention launch is laid out.
+struct AttentionPlan {
+  int32_t key_groups;   // groups of waves of a workgroup that share a row
+  int32_t grid;         // workgroups
+  bool ordered;         // items come from queues; else every row has a workgroup
+};
+AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capacity);
+int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const void* q, const void* k, const void* v,
                          const int64_t* sel_ptr, const int32_t* sel_idx, void* out, float* lse,
                          shplb_wg_stats* stats, WorkQueues wq, SplitBuffers sb, int32_t n_wg, hipStream_t stream);
 
@@ -163,27 +167,12 @@ __device__ __forceinline__ void decode_row(const SeqMeta& m, int32_t row, int& s
   i = local - h * nb;
 }
 
-// Home XCD of a row.  All rows that stream the same K/V (one KV head of one sequence) go to
-// the same die, so its L2 sees one K/V stream per resident head instead of all of them;
-// with fewer streams than dies a stream is spread over several dies by query block.
-__device__ __forceinline__ int xcd_of_row(const SeqMeta& m, int32_t row) {
-  int s, h, i, nb;
-  decode_row(m, row, s, h, i, nb);
-  const int stream = s * m.n_kv_heads + kv_head_of(m, h);
-  const int n_streams = m.n_seq * m.n_kv_heads;
-  if (n_streams >= kXcds) return stream % kXcds;
-  const int per = kXcds / n_streams;
-  return stream * per + i % per;
-}
-
 // The queue with the most items left, other than those in empty_mask (ties: the first one
-// after home), or -1.  Counts are read with device-scope loads and may be a little old.
-// Kept out of line: it runs a few times per workgroup, at the end of a launch, and inlined
-// it costs the attention kernels registers across their whole item loop.
-__device__ __attribute__((noinline)) int fullest_queue(const int32_t* queue_begin, const uint32_t* tickets,
+// from home on), or -1.  Counts are read with device-scope loads and may be a little old.
+__device__ __forceinline__ int fullest_queue(const int32_t* queue_begin, const uint32_t* tickets,
                                                        int home, int empty_mask) {
   int most = 0, pick = -1;
-  for (int d = 1; d < kXcds; ++d) {
+  for (int d = 0; d < kXcds; ++d) {
     const int x = (home + d) % kXcds;
     if (empty_mask & 1 << x) continue;
     const uint32_t size = uint32_t(queue_begin[x + 1] - queue_begin[x]);
@@ -197,26 +186,28 @@ __device__ __attribute__((noinline)) int fullest_queue(const int32_t* queue_begi
   return pick;
 }
 
-// Next work item for a persistent workgroup (called by one thread).  A workgroup draws from
-// its home die's queue until that is empty; from then on every item comes from the queue
-// that has the most items left at that moment.  Helpers so spread over the dies that still
-// have work in proportion to what is left there, and no queue is left for last with its
-// heavy items still in it.  An old count only affects which queue is tried, the ticket
-// decides.  A queue whose ticket came back past its end is never tried again, so the loop
-// ends after at most kXcds misses.  Returns the item's position in wq.items, or -1 when
-// every queue is empty.
-__device__ __forceinline__ int32_t next_item(const WorkQueues& wq, int home, int& empty_mask) {
-  int pick = home;
+// An item from another die's queue for a persistent workgroup whose own is empty (called by one
+// thread).  Every item comes from the queue that has the most items left at that moment.
+// Helpers so spread over the dies that still have work in proportion to what is left there,
+// and no queue is left for last with its heavy items still in it.  An old count only affects
+// which queue is tried, the ticket decides.  A queue whose ticket came back past its end is
+// never tried again (*empty_mask), so the loop ends after at most kXcds misses.  Returns the
+// item's place in the queues, or -1 when every queue is empty.
+__device__ __attribute__((noinline)) int help_item(const int32_t* queue_begin, uint32_t* tickets, int home, int* empty_mask) {
+  int empty = *empty_mask, pos = -1;
   for (;;) {
-    if (empty_mask & 1 << home) {
-      pick = fullest_queue(wq.queue_begin, wq.tickets, home, empty_mask);
-      if (pick < 0) return -1;
+    const int pick = fullest_queue(queue_begin, tickets, home, empty);
+    if (pick < 0) break;
+    const int begin = queue_begin[pick], end = queue_begin[pick + 1];
+    const uint32_t t = atomicAdd(tickets + pick * kTicketStride, 1u);
+    if (t < uint32_t(end - begin)) {
+      pos = begin + int(t);
+      break;
     }
-    const int begin = wq.queue_begin[pick], end = wq.queue_begin[pick + 1];
-    const uint32_t t = atomicAdd(wq.tickets + pick * kTicketStride, 1u);
-    if (t < uint32_t(end - begin)) return begin + int(t);
-    empty_mask |= 1 << pick;
+    empty |= 1 << pick;
   }
+  *empty_mask = empty;
+  return pos;
 }
 
 __device__ __forceinline__ int my_xcd() {
