@@ -47,6 +47,9 @@
 // issued in pairs).  LDS operands are fetched kLook groups ahead of their use.  Fully
 // masked sub-tiles are computed like any other (their probabilities are exact zeros).
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
+//
+// KS = 2: two groups of waves share a row, each with every other selected block, and combine their
+// results in LDS (launches of few 64-token rows, see plan_attention()).
 #include <type_traits>
 
 #include "attn_common.h"
@@ -80,6 +83,13 @@ __device__ __forceinline__ ArgsPtr reload(ArgsPtr a) {
   return a;
 }
 
+// A pointer that is the same in all lanes, said explicitly: in scalar registers.
+__device__ __forceinline__ const char* uniform(const char* p) {
+  const uint64_t x = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<const char*>(uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(x)))) |
+                                       uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(x >> 32)))) << 32);
+}
+
 // What a wave keeps of the item it works on (uniform values).
 struct Item {
   int pos;                            // its place in the queues
@@ -97,21 +107,23 @@ __device__ __forceinline__ bool row_item(ArgsPtr a, int b, Item& it) {
   // sequence: how many of them end at or before the row (one lane per sequence)
   const int lane = threadIdx.x & 63;
   const int s = __builtin_popcountll(__ballot(lane < n_seq && row >= a->meta.blk_begin[min(lane, n_seq - 1) + 1] * hq));
+  auto scalar = [](int x) { return int(__builtin_amdgcn_readfirstlane(x)); };
   const int b0 = a->meta.blk_begin[s], local = row - b0 * hq;
   it.pos = row;
-  it.n_blocks = a->meta.blk_begin[s + 1] - b0;
+  it.n_blocks = scalar(a->meta.blk_begin[s + 1] - b0);
   it.head = local / it.n_blocks;
   it.q_block = local - it.head * it.n_blocks;
-  it.kv_head = a->meta.kv_map ? int(a->meta.kv_of[it.head >> 2] >> (8 * (it.head & 3)) & 0xff)
-                              : it.head / (hq / a->meta.n_kv_heads);
-  it.seq_begin = a->meta.tok_begin[s];
-  it.seq_end = a->meta.tok_begin[s + 1];
+  it.kv_head = scalar(a->meta.kv_map ? int(a->meta.kv_of[it.head >> 2] >> (8 * (it.head & 3)) & 0xff)
+                                     : it.head / (hq / a->meta.n_kv_heads));
+  it.seq_begin = scalar(a->meta.tok_begin[s]);
+  it.seq_end = scalar(a->meta.tok_begin[s + 1]);
   it.slot = -1;
-  it.sel_begin = a->sel_ptr[row];
-  it.n_sel = int(a->sel_ptr[row + 1] - it.sel_begin);
+  const int64_t first = a->sel_ptr[row];
+  it.sel_begin = int64_t(uint32_t(scalar(int(first)))) | int64_t(scalar(int(first >> 32))) << 32;
+  it.n_sel = scalar(int(a->sel_ptr[row + 1] - first));
   if (it.n_sel <= 0) return false;
-  it.first_block = a->sel_idx[it.sel_begin];
-  it.second_block = a->sel_idx[it.sel_begin + min(1, it.n_sel - 1)];
+  it.first_block = scalar(a->sel_idx[it.sel_begin]);
+  it.second_block = scalar(a->sel_idx[it.sel_begin + min(1, it.n_sel - 1)]);
   return true;
 }
 
@@ -119,6 +131,7 @@ __device__ __forceinline__ bool row_item(ArgsPtr a, int b, Item& it) {
 template <int BQ, int KS>
 __global__ __launch_bounds__(64 * KS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
+  static_assert(KS == 1 || KS == 2, "an item's record names its first two blocks");
   constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each
   constexpr int kThreads = 64 * KS * kWaves;
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
@@ -261,7 +274,7 @@ void attn_pipe_kernel(AttnArgs) {
   };
   // Copy the K or V rows of the located tile into an LDS stage.
   auto issue = [&](const char* head, uint32_t dst) {
-    const char* tile = head + next_off;
+    const char* tile = uniform(head + next_off);
     if (next_last >= KT - 1) {
 #pragma unroll
       for (int rd = 0; rd < kRounds; ++rd) {
@@ -286,7 +299,6 @@ void attn_pipe_kernel(AttnArgs) {
     v_head = reinterpret_cast<const char*>(a->v + int64_t(it.kv_head) * a->st.kv_h);
     int j0 = it.first_block;
     if (KS > 1 && grp == 1) j0 = it.second_block;
-    if (KS > 2 && grp > 1) j0 = a->sel_idx[it.sel_begin + min(grp, it.n_sel - 1)];
     it.first_block = j0;
     const int tok = min(it.seq_begin + it.q_block * BQ + wave * 32 + n, it.seq_end - 1);
     const uint16_t* src = a->q + int64_t(tok) * a->st.q_t + int64_t(it.head) * a->st.q_h + 8 * hi;
@@ -685,8 +697,14 @@ void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
 
 AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capacity) {
   AttentionPlan plan;
-  plan.key_groups = 1;
-  plan.grid = n_wg;
+  const int cus = n_wg / (g.meta.block == 64 ? 4 : 2);
+  // A launch of few 64-token rows leaves half of every compute unit's SIMDs without a wave (a row is two
+  // waves), and its length is that of the chain of tiles of the longest row: two groups of waves per row
+  // halve that chain.  256 rows of up to 16 blocks 24.6 -> 18.1 us, 512 rows 28.2 -> 21.6 us, 64 rows of up to
+  // 8 blocks 14.8 -> 11.8 us; at 1024 rows, where the chip is full without them, 54 -> 57 and 38 -> 51 us.
+  // 128-token rows fill the SIMDs by themselves: 224 rows 19.5 -> 20.6 us, 512 rows 41 -> 48 us.
+  plan.key_groups = g.meta.block == 64 && g.rows <= 2 * cus ? 2 : 1;
+  plan.grid = n_wg / plan.key_groups;
   // No more rows than workgroups and none to be cut: there is nothing to order, every row gets a workgroup
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).
   plan.ordered = slot_capacity > 0 || g.rows > plan.grid - plan.grid % kXcds;
@@ -712,8 +730,12 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.wq = wq;
   args.sb = sb;
   args.meta = g.meta;
-  if (g.meta.block == 128) launch_one<128, 1>(args, plan.grid, stream);
-  else launch_one<64, 1>(args, plan.grid, stream);
+  if (g.meta.block == 128) {
+    launch_one<128, 1>(args, plan.grid, stream);
+  } else {
+    if (plan.key_groups == 2) launch_one<64, 2>(args, plan.grid, stream);
+    else launch_one<64, 1>(args, plan.grid, stream);
+  }
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;
 }

@@ -29,3 +29,12 @@ def test_pieces_of_split_rows(heads):
     hq, hkv = heads
     wl = make_custom([64 * 140 + 21, 64 * 3], hq, hkv, 64, [999, 3] * hq, seed=62 + hq, name="order_split_%d" % hkv)
     _split_against_whole_rows(wl, 2048, 5 if hq == 2 else 3)
+
+
+@pytest.mark.parametrize("n_blocks, budgets", [(1, [2, 2]), (64, [2, 3, 4, 5, 999, 7, 64, 33]), (65, [2, 3, 4, 5, 999, 7, 64, 33])])
+def test_rows_shared_by_two_groups_of_waves(n_blocks, budgets):
+    # 64-token rows of launches of up to two rows per compute unit (512) are worked on by two groups of
+    # waves, each with every other selected block: rows of one block (a group with nothing), of odd and
+    # even numbers, ragged tails; 520 rows go the other way.
+    wl = make_custom([64 * n_blocks - 27], len(budgets), 1, 64, budgets, seed=500 + n_blocks, name="groups_%d" % n_blocks)
+    full_parity(wl)
