@@ -239,9 +239,10 @@ SHPLB_API int32_t shplb_recovery_curves(const shplb_problem* p, const float* mas
  * (Eq. 1), recovery_out[b][h][t] = the sum of the budgets[b] largest attention
  * weights of query token t of head h; a query that sees at most budgets[b] keys
  * recovers exactly 1.  Exact selection (the k-th largest weight of every query is
- * found by a bitwise search over dense sweeps, ties at the k-th place counted at
- * that weight), fp32 softmax statistics, bf16 MFMA products; a dense pass of some
- * 20 to 33 sweeps over the causal triangle: an offline tool.
+ * found by counting the scores in the bins of an interval that holds it, ties at the
+ * k-th place counted at that weight), fp32 softmax statistics, bf16 MFMA products; a
+ * dense pass of one sweep over the causal triangle and one more per budget (more where
+ * scores crowd): an offline tool.
  *   q, k: device bf16.  budgets: host [n_budgets], tokens, each >= 1;
  *   n_budgets: 1..SHPLB_MAX_TOKEN_BUDGETS.
  *   recovery_out: device fp32 [n_budgets][n_q_heads][T], T = cu_seqlens[n_seq].

@@ -9,7 +9,7 @@
 //  * token_recovery_kernel: at the paper's own granularity, for every query token the sum of its
 //    k largest attention weights, for up to eight budgets k at once.
 //
-// Both share the first contraction of the attention kernels (64-key K tiles copied global->LDS
+// Both use the first contraction of the attention kernels (64-key K tiles copied global->LDS
 // into swizzled 256-byte rows, S^T = K Q^T with Q in registers, a lane owns one query column) and
 // have no second one.  One workgroup = one (sequence, head, query block) row, all key blocks
 // 0 .. i, in several sweeps over the row's keys; the scores are recomputed in every sweep (the
@@ -229,130 +229,509 @@ struct TokenBudgets {
   int32_t k[SHPLB_MAX_TOKEN_BUDGETS];
 };
 
+// 128 consecutive queries of one (sequence, head) swept over their keys in tiles of kTile; a wave owns 32
+// queries.  Unlike DenseRow the tiles are software-pipelined: the MFMAs of the next tile are issued before
+// the work on the present one's scores, which depends on none of them, and a tile is copied one whole step
+// ahead of its use.
+struct QueryRun {
+  static constexpr int kQueries = 128, kWaves = kQueries / 32;
+  static constexpr int kTile = 64, MT = kTile / 32;                  // keys of a tile
+  static constexpr int kStageBytes = kTile * kRowBytes;
+  static constexpr int kRoundRows = 4 * kWaves;                      // key rows one copy instruction per wave moves
+  static constexpr int kRounds = kTile / kRoundRows;
+  typedef f32x16 Scores[MT];
+  static constexpr int kLook = 8;                                    // operand fetches ahead of the MFMA that uses them
+  // Steps between sampled keys are multiples of 1/kOne.  (The largest products fit: all keys, kOne apart, are up
+  // to 2^19 x 2^12; of those sampled, 2^11 at most, the last is one of these keys; a step is below 2^24.)
+  static constexpr uint32_t kOne = 4096;
+
+  int s, h, i, tid, lane, wave, n, hi;
+  int seq_begin, seq_end, n_tiles, q_tok;
+  int cp_row, k_rd0;
+  uint32_t k_stage0;
+  int64_t row_bytes;
+  const char* k_head;
+  const char* k_lds;                                // two stages of kStageBytes
+  bf16x8 qf[8];                                     // B operand of S^T = K Q^T: dims 16ks + 8hi.. of the lane's query
+
+  // blockIdx.x = level * (sequences * heads) + place of the (sequence, head); level 0 is the end of the longest
+  // sequence.  Workgroups go to the dies in turn: places x, x + 8, .. are given consecutive heads, so that a
+  // die works on few K streams (32 heads, 8 KV heads: on one).  False: this sequence is shorter.
+  __device__ __forceinline__ bool init(const SeqMeta& meta, const Strides& st, const uint16_t* __restrict__ k,
+                                       int levels, const char* lds) {
+    const int per_level = meta.n_seq * meta.n_q_heads;
+    const int level = blockIdx.x / per_level, place = blockIdx.x - level * per_level;
+    const int die = place % kXcds;
+    const int sh = die * (per_level / kXcds) + min(die, per_level % kXcds) + place / kXcds;
+    s = sh / meta.n_q_heads;
+    h = sh - s * meta.n_q_heads;
+    i = levels - 1 - level;
+    seq_begin = meta.tok_begin[s];
+    seq_end = meta.tok_begin[s + 1];
+    if (i * kQueries >= seq_end - seq_begin) return false;
+    tid = threadIdx.x;
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    n = lane & 31;
+    hi = lane >> 5;
+    n_tiles = (i + 1) * (kQueries / kTile);
+    row_bytes = st.kv_t * 2;
+    k_head = reinterpret_cast<const char*>(k + int64_t(kv_head_of(meta, h)) * st.kv_h);
+    k_lds = lds;
+    cp_row = 4 * wave + (lane >> 4);
+    k_rd0 = n * kRowBytes + ((hi ^ swz(n)) << 4);
+    k_stage0 = __builtin_amdgcn_readfirstlane(lds_offset_of(lds) + 4 * wave * kRowBytes);
+    q_tok = seq_begin + i * kQueries + wave * 32 + n;
+    return true;
+  }
+  __device__ __forceinline__ bool live() const { return q_tok < seq_end; }   // not past the end of the sequence
+
+  __device__ __forceinline__ void load_queries(const Strides& st, const uint16_t* __restrict__ q) {
+    const uint16_t* src = q + int64_t(min(q_tok, seq_end - 1)) * st.q_t + int64_t(h) * st.q_h + 8 * hi;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
+  }
+
+  // Copy a tile into LDS stage `buf`: keys kTile x .. of the row's, or of those that are left when only every
+  // (stride / kOne)-th is taken.  Rows past the end of the sequence re-read its last key; they are masked.
+  __device__ __forceinline__ void issue_tile(int x, uint32_t stride, int buf) const {
+    const int first = int(uint32_t(kTile * x) * stride / kOne);
+    const int key_base = min(seq_begin + first, seq_end - 1);
+    const int last = seq_end - 1 - key_base;
+    const char* k_tile = k_head + int64_t(key_base) * row_bytes;
+#pragma unroll
+    for (int rd = 0; rd < kRounds; ++rd) {
+      const int r = rd * kRoundRows + cp_row;
+      const int key = int(__umul24(r, stride) / kOne);
+      const uint32_t off = uint32_t(min(key, last)) * uint32_t(row_bytes) + (((lane & 15) ^ swz(r)) << 4);
+      copy_g2l_16(k_tile, off, __builtin_amdgcn_readfirstlane(k_stage0 + buf * kStageBytes + rd * kRoundRows * kRowBytes));
+    }
+  }
+
+  // raw scores (q . k, unscaled) of the tile in stage `buf`
+  __device__ __forceinline__ void scores_of(int buf, Scores& sc) const {
+    const char* kt = k_lds + buf * kStageBytes;
+    auto read_k = [&](int gi) {
+      return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ ((gi / MT) << 5)) + (gi % MT) * 32 * kRowBytes);
+    };
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[mt][r] = 0.0f;
+    bf16x8 kf[8 * MT];
+#pragma unroll
+    for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(gi);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int gi = 0; gi < 8 * MT; ++gi) {
+      if (gi + kLook < 8 * MT) kf[gi + kLook] = read_k(gi + kLook);
+      sc[gi % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[gi], qf[gi / MT], sc[gi % MT], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // keys above the lane's query to -inf (tiles of the diagonal only)
+  __device__ __forceinline__ void mask(int it, Scores& sc) const {
+    int d = kTile * it - kQueries * i + 4 * hi - (wave * 32 + n);   // key position minus query position, per register below
+    asm volatile("" : "+v"(d));                                           // keep the 32 comparisons here, not hoisted as masks
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (d + (32 * mt + 8 * (r >> 2) + (r & 3)) > 0) sc[mt][r] = -INFINITY;
+  }
+
+  // A sweep over the row's keys, or over `count` tiles' worth of them evenly spread (a stretch of keys alike
+  // must not come in or stay out as a whole), in two parts: start() sends the first tiles on their way (the
+  // stages are free after its barrier), sweep() calls per_tile(sc) with the raw scores of tile after tile;
+  // masked (all keys only): keys above the lane's query are -inf.
+  __device__ __forceinline__ uint32_t stride_of(int count) const {
+    return __builtin_amdgcn_readfirstlane(uint32_t(n_tiles) * kOne / uint32_t(count));
+  }
+  __device__ __forceinline__ void start(int count, uint32_t stride) const {
+    __syncthreads();
+    issue_tile(0, stride, 0);
+    if (count > 1) issue_tile(1, stride, 1);
+  }
+  template <class F>
+  __device__ __forceinline__ void sweep(int count, uint32_t stride, bool masked, F&& per_tile) const {
+    Scores sa, sb;
+    wait_vmem_all();
+    __syncthreads();
+    scores_of(0, sa);
+    auto step = [&](int x, int buf, Scores& cur, Scores& nxt) {
+      if (x + 1 < count) {
+        wait_vmem_all();                            // own copies of tile x + 1 have landed
+        __syncthreads();                            // everyone's have; the stage of tile x is free
+        if (x + 2 < count) issue_tile(x + 2, stride, buf);
+        scores_of(buf ^ 1, nxt);
+      }
+      if (masked && x >= n_tiles - kQueries / kTile) mask(x, cur);
+      per_tile(cur);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int x = 0; x < count; x += 2) {
+      step(x, 0, sa, sb);
+      if (x + 1 < count) step(x + 1, 1, sb, sa);
+    }
+  }
+};
+
 // Sum of the k largest attention weights of every query, for M budgets k at once.
 //
-// A weight is p = 2^-y with y = log2(denominator) - score * scale * log2(e) >= 0, so the k largest
-// weights are the k smallest y, and the bit pattern of a non-negative float orders like the float.
-// After the denominators (first sweep) the k-th smallest y of every query is found bit by bit, one
-// sweep per bit: v grows from 0; with probe = v | bit, the number of the query's keys with y < probe
-// is counted (a compare and an add-with-carry per score and budget; the two lanes that share a query
-// add their counts); fewer than k means the k-th smallest is at least probe.  A count of exactly k
-// settles the query early (its k best are the keys below probe), and the search ends when every query
-// of the workgroup is settled; with distinct weights that happens once the probes separate the k-th
-// from the (k+1)-th, in 20 to 25 sweeps instead of 31.  A last sweep sums the weights below v and
-// adds the remainder of the budget at the weight of v itself (ties at the k-th place).  A y that
-// rounding made slightly negative (one dominant key, p = 1 + a few ulp) is negative as an integer
-// too and counts as smallest, which it is.  Queries that see at most k keys recover exactly 1.
-template <int BQ, int M>
-__global__ __launch_bounds__(2 * BQ) void token_recovery_kernel(SeqMeta meta, Strides st,
+// The weight of a key grows with its raw score, so the k largest weights belong to the k largest scores.
+// The triangle of scores fits nowhere: every question about it is a sweep over the keys that computes them
+// again, and the kernel is bound by the number of sweeps.  Per query it needs two, and a little sampling:
+//
+//   1. a few tiles, evenly spread, give the range of the query's scores, then a histogram of a few more tiles
+//      over that range gives an interval that should hold the k-th largest score;
+//   2. a sweep counts the scores in kBins bins over the interval, the outermost ones open: the bin that holds
+//      the k-th largest is known, and how many scores lie above it.  With more keys in the bin than there
+//      is room for, or with the k-th largest in an open bin, the sweep is done again over that bin or over
+//      what lies beyond.  A bin no wider than the resolution of a score (ties) needs no more division;
+//   3. the last sweep takes the exponentials: their sum, the sum of those above the bin, and the scores in
+//      the bin to a list.  The list gives the few weights that are missing.
+//
+// Counters are a word per (bin, query) in LDS, private to the query's wave, in the bank of its lane: an
+// LDS atomic without a result, and nothing of the search is held in registers but the map from scores to
+// bins.  Bins are taken as x = fma(score, a, b) around 2^23, where a float is a whole number and its low bits
+// are the bin: rounding keeps the order of the scores, so bins are exact intervals whatever a and b are.
+// The list takes the counters' place; the two lanes of a query fill it from its two ends.
+// Sums are per tile first, then over tiles, always in the same order: results repeat bit for bit.
+//
+// 32 heads x 32K tokens, k = 4096: 12.7 ms, against 131 ms with the threshold found bit by bit in 27 to 29
+// sweeps; three budgets at 9.7K tokens 7.5 -> 1.7 ms.  Of the 12.7 ms an empty sweep (the MFMAs) takes 2.9, the
+// counting 2.6, the exponentials and sums 1.9 and looking for the bin's scores 1.9: the VALU is busy 60% of the
+// time and the matrix pipe 29%, two waves per SIMD not being enough to hide either behind the other.  Three
+// (tiles of 32 keys, 74 bins) were slower, 16.4 ms.
+constexpr int kBins = 95;                          // and the longest list: 128 queries x 95 words leave room for
+                                                   // two workgroups per compute unit beside the tiles
+constexpr int kInner = 85, kFirst = 5;             // an interval is spread over bins kFirst .. kFirst + kInner
+constexpr float kWhole = 8388608.0f;               // 2^23
+constexpr int kRangeTiles = 256 / QueryRun::kTile, kSampleTiles = 2048 / QueryRun::kTile;  // tiles sampled for the range, and at most for the interval
+// Tiles of a row that is searched over its whole range at once: sampling costs such rows as much as the sweep it
+// would save (384 and 768 keys alike; with 1536, 1391 tokens x 28 heads, three budgets, take 365 instead of 262 us)
+constexpr int kSmallRow = 768 / QueryRun::kTile;
+constexpr int kSearchRounds = 64;                  // never reached: a round divides the interval by kInner
+
+template <int M>
+__global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, Strides st,
                                                                 const uint16_t* __restrict__ q,
                                                                 const uint16_t* __restrict__ k,
                                                                 float* __restrict__ recovery, TokenBudgets budgets,
-                                                                int n_out, int max_nb, float scale_log2,
+                                                                int n_out, int levels, float scale_log2,
                                                                 int total_tokens) {
-  using Row = DenseRow<BQ>;
-  __shared__ __attribute__((aligned(1024))) char k_lds[2][kTileBytes];
-  __shared__ int s_open[2][Row::kWaves];
+  typedef __attribute__((address_space(3))) uint32_t LdsWord;
+  typedef __attribute__((address_space(3))) float LdsFloat;
+  constexpr int MT = QueryRun::MT;
+  constexpr uint32_t kBinBytes = 32 * 4;           // a word for each of a wave's queries
+  __shared__ __attribute__((aligned(1024))) char k_lds[2][QueryRun::kStageBytes];
+  __shared__ __attribute__((aligned(16))) uint32_t s_bins[QueryRun::kWaves][kBins][32];
+  __shared__ int s_open[2][QueryRun::kWaves];
 
-  Row row;
-  if (!row.init(meta, st, q, k, max_nb, &k_lds[0][0])) return;
-  row.issue_tile(0, 0);
-  const float lse2 = row.log2_denominator(scale_log2);
-  const float neg_scale = -scale_log2;
+  QueryRun row;
+  if (!row.init(meta, st, k, levels, &k_lds[0][0])) return;
   const int visible = row.q_tok - row.seq_begin + 1;          // keys the lane's query sees
-
-  int v[M], want[M];
-  bool settled[M];
+  int fewest = budgets.k[0];
 #pragma unroll
-  for (int b = 0; b < M; ++b) {
-    want[b] = budgets.k[b];
-    v[b] = 0;
-    settled[b] = !row.live() || visible <= want[b];           // nothing to search
-  }
-
-  for (int bit = 30, round = 0;; --bit, ++round) {
-    bool open = false;
-#pragma unroll
-    for (int b = 0; b < M; ++b) open |= !settled[b];
-    // does any query of the workgroup still search?  (two flag sets: a wave may write the next
-    // round's flag while another still reads this round's; a sweep's barriers separate the rounds)
-    if (row.lane == 0) s_open[round & 1][row.wave] = 0;
-    if (__any(open) && row.lane == 0) s_open[round & 1][row.wave] = 1;
-    __syncthreads();
-    int any_open = 0;
-#pragma unroll
-    for (int w = 0; w < Row::kWaves; ++w) any_open |= s_open[round & 1][w];
-    if (!any_open || bit < 0) break;
-
-    int probe[M], below[M];
-#pragma unroll
-    for (int b = 0; b < M; ++b) {
-      probe[b] = v[b] | (1 << bit);
-      below[b] = 0;
-    }
-    row.sweep(true, [&](int, f32x16 (&sc)[2]) {
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int y = __float_as_int(__builtin_fmaf(sc[mt][r], neg_scale, lse2));   // masked: +inf, above every probe
-#pragma unroll
-          for (int b = 0; b < M; ++b) below[b] += y < probe[b] ? 1 : 0;
-        }
-    });
-#pragma unroll
-    for (int b = 0; b < M; ++b) {
-      float lo, up;
-      pair_values(__int_as_float(below[b]), lo, up);
-      const int cnt = __float_as_int(lo) + __float_as_int(up);
-      if (!settled[b]) {
-        if (cnt <= want[b]) v[b] = probe[b];
-        if (cnt == want[b]) settled[b] = true;
-      }
-    }
-  }
-
-  float sum[M];
-  int below[M];
-#pragma unroll
-  for (int b = 0; b < M; ++b) {
-    sum[b] = 0.0f;
-    below[b] = 0;
-  }
-  row.sweep(false, [&](int, f32x16 (&sc)[2]) {
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float yf = __builtin_fmaf(sc[mt][r], neg_scale, lse2);
-        const float p = __builtin_amdgcn_exp2f(-yf);
-        const int y = __float_as_int(yf);
-#pragma unroll
-        for (int b = 0; b < M; ++b) {
-          sum[b] += y < v[b] ? p : 0.0f;
-          below[b] += y < v[b] ? 1 : 0;
-        }
-      }
-  });
-  if (!row.live()) return;
-#pragma unroll
-  for (int b = 0; b < M; ++b) {
-    float lo, up;
-    pair_values(__int_as_float(below[b]), lo, up);
-    const int rest = want[b] - (__float_as_int(lo) + __float_as_int(up));
-    float r = pair_sum(sum[b]);
-    if (rest > 0) r += float(rest) * __builtin_amdgcn_exp2f(-__int_as_float(v[b]));
-    if (visible <= want[b]) r = 1.0f;
-    if (b < n_out && row.hi == 0)
+  for (int b = 1; b < M; ++b) fewest = min(fewest, budgets.k[b]);
+  auto store = [&](int b, float r) {
+    if (b < n_out && row.hi == 0 && row.live())
       recovery[(int64_t(b) * meta.n_q_heads + row.h) * total_tokens + row.q_tok] = r;
+  };
+  if ((row.i + 1) * QueryRun::kQueries <= fewest) {           // no query sees more keys than any budget
+#pragma unroll
+    for (int b = 0; b < M; ++b) store(b, 1.0f);
+    return;
+  }
+  const int all = row.n_tiles;
+  const int n_range = all <= kSmallRow ? all : kRangeTiles;
+  const int n_sample = all <= kSmallRow ? 0 : max(kRangeTiles, min(all / 16, kSampleTiles));
+  uint32_t stride = row.stride_of(n_range);
+  row.start(n_range, stride);
+  row.load_queries(st, q);
+
+  const uint32_t column = lds_offset_of(&s_bins[row.wave][0][0]) + 4 * row.n;      // the query's words, kBinBytes apart
+  const uint32_t bin_base = column - (__builtin_bit_cast(uint32_t, kWhole) << 7);  // + bits of kWhole + bin << 7
+  static_assert(kBinBytes == 1 << 7, "shifts above and below");
+  auto word = [&](int x) { return reinterpret_cast<LdsWord*>(column + x * kBinBytes); };
+  auto entry = [&](int x) { return reinterpret_cast<LdsFloat*>(column + x * kBinBytes); };
+  auto fence = [] { asm volatile("" ::: "memory"); };         // the words of a wave are its own: order in the program is enough
+  auto clear = [&] {
+    fence();
+    for (int x = row.hi; x < kBins; x += 2) *word(x) = 0;
+    fence();
+  };
+  // least useful width of a bin around scores lo .. hi: half the distance of neighbouring floats, or what
+  // changes a weight by 2^-26 of itself
+  auto finest = [&](float lo, float hi) {
+    return fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 0x1p-26f / scale_log2);
+  };
+  float bin_lo, bin_w, map_a, map_b;                          // interval's begin, width of a bin, x = fma(score, map_a, map_b)
+  bool ties;                                                  // bins hold one score each (as far as a weight can tell)
+  auto spread = [&](float lo, float hi) {
+    const float least = finest(lo, hi);
+    bin_lo = lo;
+    bin_w = fmaxf((hi - lo) * (1.0f / kInner), least);
+    ties = bin_w <= least;
+    map_a = fminf(fmaxf(1.0f / bin_w, 1e-30f), 1e30f);
+    map_b = (kWhole + kFirst) - map_a * lo;
+  };
+  auto bin_begin = [&](int u) { return bin_lo + (float(u - kFirst) - 0.5f) * bin_w; };
+  float top_score = -INFINITY;
+  auto count_bins = [&](QueryRun::Scores& sc) {
+#pragma unroll
+    for (int r = 0; r < 16 * MT; ++r) {
+      const float s = sc[r / 16][r % 16];
+      top_score = fmaxf(top_score, s);
+      const float x = __builtin_amdgcn_fmed3f(__builtin_fmaf(s, map_a, map_b), kWhole, kWhole + (kBins - 1));
+      __hip_atomic_fetch_add(reinterpret_cast<LdsWord*>((__builtin_bit_cast(uint32_t, x) << 7) + bin_base), 1u,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  };
+  // the bin that holds the rank-th largest score: how many scores lie above it and in it
+  auto find = [&](int rank, int& bin, int& above, int& inside) {
+    fence();
+    int c = 0;
+    bin = above = inside = 0;
+#pragma unroll 5
+    for (int x = kBins - 1; x >= 0; --x) {
+      const int here = int(*word(x));
+      if (c < rank && c + here >= rank) {
+        bin = x;
+        above = c;
+        inside = here;
+      }
+      c += here;
+    }
+  };
+
+  // ---- 1. where to look
+  float lo = INFINITY, hi = -INFINITY;
+  row.sweep(n_range, stride, false, [&](QueryRun::Scores& sc) {
+#pragma unroll
+    for (int r = 0; r < 16 * MT; ++r) {
+      hi = fmaxf(hi, sc[r / 16][r % 16]);
+      lo = fminf(lo, sc[r / 16][r % 16]);
+    }
+  });
+  hi = pair_max(hi);
+  lo = -pair_max(-lo);
+  float from[M], to[M];
+#pragma unroll
+  for (int b = 0; b < M; ++b) {
+    from[b] = lo;
+    to[b] = hi;
+  }
+  if (n_sample > 0) {
+    stride = row.stride_of(n_sample);
+    row.start(n_sample, stride);
+    clear();
+    spread(lo, hi);
+    row.sweep(n_sample, stride, false, count_bins);
+    const float n_keys = float(n_sample * QueryRun::kTile), share = n_keys / float(visible);
+    top_score = pair_max(top_score);
+#pragma unroll
+    for (int b = 0; b < M; ++b) {
+      // the rank in the sample is off by its standard deviation; four of them
+      const float rank = fminf(float(budgets.k[b]) * share, n_keys);
+      const float off = 4.0f * __builtin_sqrtf(fmaxf(rank * (1.0f - rank / n_keys), 0.0f)) + 4.0f;
+      int bin, above, inside;
+      find(max(1, int(rank - off)), bin, above, inside);
+      to[b] = bin < kBins - 1 && rank > off ? bin_begin(bin + 1) : top_score;
+      find(min(n_sample * QueryRun::kTile, int(rank + off)), bin, above, inside);
+      from[b] = bin > 0 ? bin_begin(bin) : bin_begin(0) - kInner * bin_w;
+    }
+  }
+
+  // ---- 2. the bin of the k-th largest score, budget after budget
+  float above_from[M], list_from[M];                          // scores from which on: above the bin, in the bin or above
+  int rest[M], listed[M], list_at[M];                         // keys wanted from the bin, entries and place of its list
+  bool tied[M];                                               // all scores of the bin count as one: the list is that one
+  int used = 0, round = 0;
+#pragma unroll
+  for (int b = 0; b < M; ++b) {
+    above_from[b] = list_from[b] = INFINITY;
+    rest[b] = listed[b] = list_at[b] = 0;
+    tied[b] = false;
+  }
+  stride = QueryRun::kOne;
+  for (int b = 0; b < n_out; ++b) {
+    int want = 0;
+    float f = 0.0f, t = 0.0f;
+#pragma unroll
+    for (int x = 0; x < M; ++x)
+      if (x == b) {
+        want = budgets.k[x];
+        f = from[x];
+        t = to[x];
+      }
+    bool open = row.live() && visible > want;
+    const bool search = open;
+    const int room = (kBins - used) / (n_out - b);
+    int bin = 0, above = 0, inside = 0;
+    spread(f, t);
+    for (int tries = 0;; ++tries, ++round) {
+      // does any query of the workgroup still search?  (two flag sets: a wave may write the next
+      // round's flag while another still reads this round's; the sweep's barriers separate the rounds)
+      if (row.lane == 0) s_open[round & 1][row.wave] = 0;
+      if (__any(open) && row.lane == 0) s_open[round & 1][row.wave] = 1;
+      __syncthreads();
+      int any_open = 0;
+#pragma unroll
+      for (int w = 0; w < QueryRun::kWaves; ++w) any_open |= s_open[round & 1][w];
+      if (!__builtin_amdgcn_readfirstlane(any_open) || tries == kSearchRounds) break;
+      row.start(all, stride);
+      clear();
+      top_score = -INFINITY;                                  // (the samples' may be a key the query does not see)
+      row.sweep(all, stride, true, count_bins);
+      top_score = pair_max(top_score);
+      if (open) {
+        find(want, bin, above, inside);
+        // beyond the interval: most often just beyond
+        const float reach = (tries == 0 ? 2.0f : 32.0f) * kInner * bin_w;
+        if (bin == 0) {
+          spread(bin_begin(1) - reach, bin_begin(1) + bin_w);
+        } else if (bin == kBins - 1) {
+          spread(bin_begin(kBins - 1) - bin_w, tries == 0 ? fminf(bin_begin(kBins - 1) + reach, top_score) : top_score);
+        } else if (inside <= room || ties) {
+          open = false;
+        } else {
+          const float low = bin_begin(bin) - 0.5f * bin_w, high = bin_begin(bin + 1) + 0.5f * bin_w;
+          spread(low, high);
+        }
+      }
+    }
+    ++round;
+    // the least scores that fall on bins `bin` and `bin + 1`: the map keeps the order, so by bisection
+    auto least_score = [&](float x) {
+      int low = int(0x80800000), high = 0x7f7fffff;           // floats as integers of the same order
+      while (low < high) {
+        const int mid = int((int64_t(low) + high) >> 1);
+        const float s = __builtin_bit_cast(float, mid ^ ((mid >> 31) & 0x7fffffff));
+        if (__builtin_fmaf(s, map_a, map_b) >= x) high = mid;
+        else low = mid + 1;
+      }
+      return __builtin_bit_cast(float, low ^ ((low >> 31) & 0x7fffffff));
+    };
+    const float least_in = search ? least_score(kWhole + float(bin)) : INFINITY;
+    const float least_above = search ? least_score(kWhole + float(bin + 1)) : INFINITY;
+    const bool tie = inside > room;
+    const int entries = tie ? 1 : inside;
+#pragma unroll
+    for (int x = 0; x < M; ++x)
+      if (x == b) {
+        list_from[x] = least_in;
+        above_from[x] = least_above;
+        rest[x] = want - above;
+        listed[x] = search ? entries : 0;
+        list_at[x] = used;
+        tied[x] = tie;
+      }
+    if (search) used += entries;
+  }
+
+  // ---- 3. weights
+  row.start(all, stride);
+  const float ref = top_score * scale_log2;
+  auto weight = [&](float s) { return __builtin_amdgcn_exp2f(__builtin_fmaf(s, scale_log2, -ref)); };
+  uint32_t put[M];                                            // where the lane's next entry goes
+  float sum = 0.0f, top[M];
+#pragma unroll
+  for (int b = 0; b < M; ++b) {
+    put[b] = column + (list_at[b] + (row.hi == 0 || tied[b] ? 0 : listed[b] - 1)) * kBinBytes;
+    top[b] = 0.0f;
+  }
+  fence();
+  row.sweep(all, stride, true, [&](QueryRun::Scores& sc) {
+    float sum0 = 0.0f, sum1 = 0.0f, part[M];
+#pragma unroll
+    for (int b = 0; b < M; ++b) part[b] = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16 * MT; ++r) {
+      const float s = sc[r / 16][r % 16], p = weight(s);
+      if (r & 1) sum1 += p;
+      else sum0 += p;
+#pragma unroll
+      for (int b = 0; b < M; ++b) {
+        const bool over = s >= above_from[b];
+        part[b] += over ? p : 0.0f;
+        asm volatile("" : "+v"(part[b]));                     // here, and not all comparisons first: their masks fit no registers
+        if (s >= list_from[b] && !over) {
+          if (put[b] - column < kBins * kBinBytes) *reinterpret_cast<LdsFloat*>(put[b]) = s;
+          if (!tied[b]) put[b] += row.hi == 0 ? kBinBytes : 0u - kBinBytes;
+        }
+      }
+    }
+    sum += sum0 + sum1;
+#pragma unroll
+    for (int b = 0; b < M; ++b) top[b] += part[b];
+  });
+  fence();
+  const float total = pair_sum(sum);
+
+  // ---- the rest of the budget from the list: its rest-th largest entry, halving the range of floats until the
+  // entries from there on are as many as wanted (or all equal there)
+  auto both = [](int c) {
+    float x, y;
+    pair_values(__int_as_float(c), x, y);
+    return __float_as_int(x) + __float_as_int(y);
+  };
+  auto ordered = [](float s) {
+    const int v = __float_as_int(s);
+    return v ^ ((v >> 31) & 0x7fffffff);
+  };
+#pragma unroll
+  for (int b = 0; b < M; ++b) {
+    const bool search = listed[b] > 0;
+    const int end = listed[b];
+    int low = search ? ordered(list_from[b]) : 0, high = search ? ordered(above_from[b]) : 0;   // [low, high)
+    auto from_on = [&](int v) {
+      int c = 0;
+      for (int x = row.hi; x < end; x += 2) c += ordered(*entry(list_at[b] + x)) >= v ? 1 : 0;
+      return both(c);
+    };
+    bool open = search && !tied[b] && rest[b] < end;
+    while (__any(open)) {
+      const int mid = low + int((uint32_t(high) - uint32_t(low)) >> 1);
+      const int c = from_on(mid);
+      if (open) {
+        if (c >= rest[b]) low = mid;
+        else high = mid;
+        if (c == rest[b] || uint32_t(high) - uint32_t(low) <= 1u) open = false;
+      }
+    }
+    float part = 0.0f;
+    int more = 0;
+    float at = 0.0f;
+    for (int x = row.hi; x < end; x += 2) {
+      const float s = *entry(list_at[b] + x);
+      at = weight(s);
+      if (tied[b] || ordered(s) >= low) {
+        part += at;
+        more += 1;
+      }
+    }
+    // ties at the place of the k-th: as many as wanted of entries that are all alike
+    more = both(more);
+    float r = pair_sum(top[b]) + pair_sum(part);
+    if (search && more != rest[b]) {
+      float w = 0.0f;
+      // entries equal to the smallest one taken
+      w = tied[b] ? weight(*entry(list_at[b])) : weight(__builtin_bit_cast(float, low ^ ((low >> 31) & 0x7fffffff)));
+      r += float(rest[b] - more) * w;
+    }
+    r /= total;
+    if (visible <= budgets.k[b]) r = 1.0f;
+    store(b, r);
   }
 }
 
-template <int BQ, int M>
+template <int M>
 void launch_token_recovery_as(const Geometry& g, const uint16_t* q, const uint16_t* k, float* recovery,
-                              const TokenBudgets& budgets, int n_out, uint32_t n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((token_recovery_kernel<BQ, M>), dim3(n_wg), dim3(2 * BQ), 0, stream, g.meta, g.st, q, k,
-                     recovery, budgets, n_out, g.max_nb, g.scale * 1.4426950408889634f, int(g.total_tokens));
+                              const TokenBudgets& budgets, int n_out, int levels, uint32_t n_wg, hipStream_t stream) {
+  hipLaunchKernelGGL((token_recovery_kernel<M>), dim3(n_wg), dim3(2 * QueryRun::kQueries), 0, stream, g.meta, g.st, q, k,
+                     recovery, budgets, n_out, levels, g.scale * 1.4426950408889634f, int(g.total_tokens));
 }
 
 }  // namespace
@@ -375,25 +754,18 @@ int32_t launch_block_mass(const Geometry& g, const void* q, const void* k, float
 int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, const int32_t* budgets,
                               int32_t n_budgets, float* recovery, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  const int64_t n_wg = int64_t(g.max_nb) * m.n_seq * m.n_q_heads;
+  const int levels = (g.max_nb * m.block + QueryRun::kQueries - 1) / QueryRun::kQueries;
+  const int64_t n_wg = int64_t(levels) * m.n_seq * m.n_q_heads;
   if (n_wg > 0x7fffffff) return SHPLB_E_UNSUPPORTED;
   TokenBudgets kb;
   for (int b = 0; b < SHPLB_MAX_TOKEN_BUDGETS; ++b) kb.k[b] = budgets[std::min(b, n_budgets - 1)];
   const uint16_t* qp = static_cast<const uint16_t*>(q);
   const uint16_t* kp = static_cast<const uint16_t*>(k);
   const uint32_t wg = uint32_t(n_wg);
-  const int width = n_budgets <= 1 ? 1 : n_budgets <= 2 ? 2 : n_budgets <= 4 ? 4 : 8;
-  if (m.block == 128) {
-    if (width == 1) launch_token_recovery_as<128, 1>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-    else if (width == 2) launch_token_recovery_as<128, 2>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-    else if (width == 4) launch_token_recovery_as<128, 4>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-    else launch_token_recovery_as<128, 8>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-  } else {
-    if (width == 1) launch_token_recovery_as<64, 1>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-    else if (width == 2) launch_token_recovery_as<64, 2>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-    else if (width == 4) launch_token_recovery_as<64, 4>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-    else launch_token_recovery_as<64, 8>(g, qp, kp, recovery, kb, n_budgets, wg, stream);
-  }
+  if (n_budgets <= 1) launch_token_recovery_as<1>(g, qp, kp, recovery, kb, n_budgets, levels, wg, stream);
+  else if (n_budgets <= 2) launch_token_recovery_as<2>(g, qp, kp, recovery, kb, n_budgets, levels, wg, stream);
+  else if (n_budgets <= 4) launch_token_recovery_as<4>(g, qp, kp, recovery, kb, n_budgets, levels, wg, stream);
+  else launch_token_recovery_as<8>(g, qp, kp, recovery, kb, n_budgets, levels, wg, stream);
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;
 }

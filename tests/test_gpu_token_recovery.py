@@ -63,6 +63,32 @@ def test_one_dominant_key_and_a_custom_scale():
     assert np.median(got[0]) > 0.9
 
 
+@pytest.mark.parametrize("shape", ["ties_beside_others", "all_scores_zero", "heavy_tailed", "rising_keys", "two_levels"])
+@pytest.mark.parametrize("T", [768, 769, 2600])
+def test_search_on_unfavourable_scores(shape, T):
+    # rows on both sides of the length from which the search samples first; runs of equal scores longer than
+    # the list of a bin, a tail far outside what a sample shows, keys above the query unlike those it sees
+    rng = np.random.default_rng(T)
+    wl = make_custom([T], 2, 1, 128, [2, 2], seed=3, name="token_recovery_" + shape)
+    q, k = rng.standard_normal((T, 2, 128)).astype(np.float32), rng.standard_normal((T, 1, 128)).astype(np.float32)
+    if shape == "ties_beside_others":
+        k[rng.permutation(T)[:T // 2]] = k[0]
+    elif shape == "all_scores_zero":
+        q[:] = 0.0
+    elif shape == "heavy_tailed":
+        k *= np.exp(1.5 * rng.standard_normal((T, 1, 1))).astype(np.float32)
+    elif shape == "rising_keys":
+        k = 0.05 * k + np.linspace(-3, 12, T, dtype=np.float32)[:, None, None] * q.mean(axis=(0, 1))
+        q += 40.0 * q.mean(axis=(0, 1))
+    else:
+        k[:] = np.where(rng.uniform(size=(T, 1, 1)) < 0.4, k[0], k[1])
+    wl.q, wl.k = bf16_bits_from_f32(q), bf16_bits_from_f32(k)
+    budgets = [1, 97, T // 2, T - 1]
+    _, got = _run(wl, budgets)
+    want = orc.token_recovery(wl.q, wl.k, wl.cu_seqlens, budgets)
+    np.testing.assert_allclose(got, want, rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
+
+
 def test_is_deterministic():
     wl = make_workload(1, seqlens=[3000])
     run, a = _run(wl, [256])
