@@ -11,228 +11,18 @@
 //
 // Both use the first contraction of the attention kernels (64-key K tiles copied global->LDS
 // into swizzled 256-byte rows, S^T = K Q^T with Q in registers, a lane owns one query column) and
-// have no second one.  One workgroup = one (sequence, head, query block) row, all key blocks
-// 0 .. i, in several sweeps over the row's keys; the scores are recomputed in every sweep (the
-// triangle of probabilities does not fit anywhere).  Rows are launched heaviest first (largest i
-// first), so the tail of the launch is short rows.
+// have no second one.  One workgroup = 128 consecutive queries of a (sequence, head), whatever the
+// block size, in one or a few sweeps over their keys; the scores are recomputed in every sweep (the
+// triangle of scores does not fit anywhere).  The longest are launched first, so that the tail of
+// the launch is short.
 #include "attn_common.h"
 
 namespace shplb {
 namespace {
 
-// One (sequence, head, query block) row swept over its keys: tile copies, Q fragments, raw scores.
-template <int BQ>
-struct DenseRow {
-  static constexpr int kWaves = BQ / 32;
-  static constexpr int SUB = BQ / kKeysPerTile;            // 64-key tiles per key block
-  static constexpr int kRoundRows = 4 * kWaves;
-  static constexpr int kRounds = kKeysPerTile / kRoundRows;
-
-  int s, h, i, nb, tid, lane, wave, n, hi;
-  int seq_begin, seq_end, n_tiles, q_tok, n_valid;
-  int cp_row, k_rd0;
-  int step;                                         // tiles handled so far over all sweeps: stage = step & 1
-  uint32_t k_stage0;
-  int64_t row_bytes;
-  const char* k_head;
-  const char* k_lds;                                // two stages of kTileBytes
-  bf16x8 qf[8];                                     // B operand of S^T = K Q^T: dims 16ks + 8hi.. of the lane's query
-
-  // blockIdx.x = level * (sequences * heads) + (s * heads + h); level 0 is the last query block.
-  // False: this sequence of a varlen batch has no such block.
-  __device__ __forceinline__ bool init(const SeqMeta& meta, const Strides& st, const uint16_t* __restrict__ q,
-                                       const uint16_t* __restrict__ k, int max_nb, const char* lds) {
-    const int per_level = meta.n_seq * meta.n_q_heads;
-    const int level = blockIdx.x / per_level, sh = blockIdx.x - level * per_level;
-    s = sh / meta.n_q_heads;
-    h = sh - s * meta.n_q_heads;
-    nb = meta.blk_begin[s + 1] - meta.blk_begin[s];
-    i = max_nb - 1 - level;
-    if (i >= nb) return false;
-    tid = threadIdx.x;
-    lane = tid & 63;
-    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    n = lane & 31;
-    hi = lane >> 5;
-    seq_begin = meta.tok_begin[s];
-    seq_end = meta.tok_begin[s + 1];
-    n_tiles = (i + 1) * SUB;
-    row_bytes = st.kv_t * 2;
-    k_head = reinterpret_cast<const char*>(k + int64_t(kv_head_of(meta, h)) * st.kv_h);
-    k_lds = lds;
-    cp_row = 4 * wave + (lane >> 4);
-    k_rd0 = n * kRowBytes + ((hi ^ swz(n)) << 4);
-    k_stage0 = __builtin_amdgcn_readfirstlane(lds_offset_of(lds) + 4 * wave * kRowBytes);
-    step = 0;
-    q_tok = seq_begin + i * BQ + wave * 32 + n;
-    n_valid = min(BQ, seq_end - seq_begin - i * BQ);
-    const uint16_t* src = q + int64_t(min(q_tok, seq_end - 1)) * st.q_t + int64_t(h) * st.q_h + 8 * hi;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
-    return true;
-  }
-  __device__ __forceinline__ bool live() const { return q_tok < seq_end; }   // not a padding query of a ragged last block
-
-  // Copy the 64 keys of tile `it` (block it / SUB) into LDS stage `buf`.
-  __device__ __forceinline__ void issue_tile(int it, int buf) const {
-    const int j = it / SUB, sub = it - j * SUB;
-    // a tile that starts past the end of a ragged last block is moved back onto the last token
-    const int key_base = min(seq_begin + j * BQ + kKeysPerTile * sub, seq_end - 1);
-    const int last = seq_end - 1 - key_base;
-    const char* k_tile = k_head + int64_t(key_base) * row_bytes;
-#pragma unroll
-    for (int rd = 0; rd < kRounds; ++rd) {
-      const int r = rd * kRoundRows + cp_row;
-      // rows past the end of the sequence re-read the last valid key; they are masked
-      const uint32_t off = uint32_t(min(r, last)) * uint32_t(row_bytes) + (((lane & 15) ^ swz(r)) << 4);
-      // (the LDS base goes into M0: a scalar, said explicitly because it is derived from struct members)
-      copy_g2l_16(k_tile, off, __builtin_amdgcn_readfirstlane(k_stage0 + buf * kTileBytes + rd * kRoundRows * kRowBytes));
-    }
-  }
-
-  // raw scores (q . k, unscaled) of tile `it` from stage `buf`; on the diagonal block the keys above the
-  // query are set to -inf (only there: the test is uniform, so other tiles pay nothing for it)
-  __device__ __forceinline__ void scores_of(int it, int buf, f32x16 (&sc)[2]) const {
-    const char* kt = k_lds + buf * kTileBytes;
-    bf16x8 kf[2][8];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        kf[mt][ks] = *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ (ks << 5)) + mt * 32 * kRowBytes);
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sc[mt][r] = 0.0f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-        sc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mt][ks], qf[ks], sc[mt], 0, 0, 0);
-    const int j = it / SUB, sub = it - j * SUB;
-    if (j == i) {
-      int d = kKeysPerTile * sub + 4 * hi - (wave * 32 + n);      // key position minus query position, per register below
-      asm volatile("" : "+v"(d));                                  // keep the 32 comparisons here, not hoisted as masks
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (d + (32 * mt + 8 * (r >> 2) + (r & 3)) > 0) sc[mt][r] = -INFINITY;
-    }
-  }
-
-  // One sweep over the row's tiles: per_tile(it, sc) sees the raw scores of tile `it`.  The first tile
-  // must be on its way into stage step & 1; with `another` the last iteration starts the first tile
-  // of the next sweep.  (A sweep that is the kernel's last must not: a copy that lands after the
-  // workgroup has ended writes into LDS that is no longer its own.)
-  template <class F>
-  __device__ __forceinline__ void sweep(bool another, F&& per_tile) {
-    for (int it = 0; it < n_tiles; ++it, ++step) {
-      wait_vmem_all();
-      __syncthreads();
-      if (it + 1 < n_tiles) issue_tile(it + 1, (step + 1) & 1);
-      else if (another) issue_tile(0, (step + 1) & 1);
-      f32x16 sc[2];
-      scores_of(it, step & 1, sc);
-      per_tile(it, sc);
-    }
-  }
-
-  // First sweep: log2 of the softmax denominator of the lane's query, exact fp32 statistics (nothing
-  // rounded to bf16).  The sum runs against a reference exponent that is only raised when a tile's
-  // maximum exceeds it by more than 2^8 (then the sum so far is rescaled): exact in real arithmetic,
-  // and most tiles cost one fused multiply-add, one exponential and one addition per score, plus the
-  // maximum.  The two lanes of a query hold disjoint halves of its keys and are merged at the end.
-  __device__ __forceinline__ float log2_denominator(float scale_log2) {
-    float m_run = -INFINITY, l_run = 0.0f;
-    sweep(true, [&](int, f32x16 (&sc)[2]) {
-      float mx = fmaxf(sc[0][0], sc[1][0]);
-#pragma unroll
-      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(sc[0][r], sc[1][r]));
-      mx *= scale_log2;
-      if (mx > m_run + kRescaleSlack) {             // per lane: a lane's reference follows its own keys
-        l_run *= m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - mx);
-        m_run = mx;
-      }
-      if (m_run != -INFINITY) {                     // all keys of the lane masked so far: nothing to add
-        float sum0 = 0.0f, sum1 = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sum0 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][r], scale_log2, -m_run));
-          sum1 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][r], scale_log2, -m_run));
-        }
-        l_run += sum0 + sum1;
-      }
-    });
-    float m_lo, m_hi, l_lo, l_hi;
-    pair_values(m_run, m_lo, m_hi);
-    pair_values(l_run, l_lo, l_hi);
-    const float m_all = fmaxf(m_lo, m_hi);
-    const float l_all = (m_lo == -INFINITY ? 0.0f : l_lo * __builtin_amdgcn_exp2f(m_lo - m_all)) +
-                        (m_hi == -INFINITY ? 0.0f : l_hi * __builtin_amdgcn_exp2f(m_hi - m_all));
-    return m_all + __builtin_amdgcn_logf(l_all);    // v_log_f32 is a base-2 logarithm
-  }
-};
-
-// Two sweeps: the softmax denominators, then the probabilities exp2(s - lse) summed over the lane's
-// keys, the tiles of a key block, the wave (shuffles) and the waves (LDS, fixed order): one number
-// per key block, bit-identical from run to run.
-template <int BQ>
-__global__ __launch_bounds__(2 * BQ) void mass_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
-                                                      const uint16_t* __restrict__ k, float* __restrict__ mass,
-                                                      int max_nb, float scale_log2) {
-  using Row = DenseRow<BQ>;
-  __shared__ __attribute__((aligned(1024))) char k_lds[2][kTileBytes];
-  __shared__ float s_part[2][Row::kWaves];
-
-  Row row;
-  if (!row.init(meta, st, q, k, max_nb, &k_lds[0][0])) return;
-  row.issue_tile(0, 0);
-  float* out_row = mass + meta.score_off[row.s] + (int64_t(row.h) * row.nb + row.i) * row.nb;
-  const float lse2 = row.log2_denominator(scale_log2);
-  const bool live = row.live();
-  const float per_query = 1.0f / float(row.n_valid);
-
-  float acc = 0.0f;
-  row.sweep(false, [&](int it, f32x16 (&sc)[2]) {
-    const int j = it / Row::SUB, sub = it - j * Row::SUB;
-    if (sub == 0 && j > 0 && row.tid == 0) {        // block j-1 is complete and visible: fixed-order sum
-      float tot = 0.0f;
-#pragma unroll
-      for (int w = 0; w < Row::kWaves; ++w) tot += s_part[(j - 1) & 1][w];
-      out_row[j - 1] = tot * per_query;
-    }
-    float sum0 = 0.0f, sum1 = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      sum0 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][r], scale_log2, -lse2));
-      sum1 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][r], scale_log2, -lse2));
-    }
-    acc += live ? sum0 + sum1 : 0.0f;
-    if (sub == Row::SUB - 1) {
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d);
-      if (row.lane == 0) s_part[j & 1][row.wave] = acc;
-      acc = 0.0f;
-    }
-  });
-  __syncthreads();
-  if (row.tid == 0) {
-    float tot = 0.0f;
-#pragma unroll
-    for (int w = 0; w < Row::kWaves; ++w) tot += s_part[row.i & 1][w];
-    out_row[row.i] = tot * per_query;
-  }
-}
-
-struct TokenBudgets {
-  int32_t k[SHPLB_MAX_TOKEN_BUDGETS];
-};
-
 // 128 consecutive queries of one (sequence, head) swept over their keys in tiles of kTile; a wave owns 32
-// queries.  Unlike DenseRow the tiles are software-pipelined: the MFMAs of the next tile are issued before
-// the work on the present one's scores, which depends on none of them, and a tile is copied one whole step
-// ahead of its use.
+// queries.  The tiles are software-pipelined: the MFMAs of the next tile are issued before the work on the
+// present one's scores, which depends on none of them, and a tile is copied one whole step ahead of its use.
 struct QueryRun {
   static constexpr int kQueries = 128, kWaves = kQueries / 32;
   static constexpr int kTile = 64, MT = kTile / 32;                  // keys of a tile
@@ -343,38 +133,201 @@ struct QueryRun {
 
   // A sweep over the row's keys, or over `count` tiles' worth of them evenly spread (a stretch of keys alike
   // must not come in or stay out as a whole), in two parts: start() sends the first tiles on their way (the
-  // stages are free after its barrier), sweep() calls per_tile(sc) with the raw scores of tile after tile;
-  // masked (all keys only): keys above the lane's query are -inf.
+  // stages are free after its barrier), sweep() calls per_tile(x, sc) with the raw scores of tile after tile,
+  // x = first ..; masked (all keys only): keys above the lane's query are -inf.
   __device__ __forceinline__ uint32_t stride_of(int count) const {
     return __builtin_amdgcn_readfirstlane(uint32_t(n_tiles) * kOne / uint32_t(count));
   }
-  __device__ __forceinline__ void start(int count, uint32_t stride) const {
+  __device__ __forceinline__ void start(int first, int count, uint32_t stride) const {
     __syncthreads();
-    issue_tile(0, stride, 0);
-    if (count > 1) issue_tile(1, stride, 1);
+    issue_tile(first, stride, 0);
+    if (count > 1) issue_tile(first + 1, stride, 1);
   }
   template <class F>
-  __device__ __forceinline__ void sweep(int count, uint32_t stride, bool masked, F&& per_tile) const {
+  __device__ __forceinline__ void sweep(int first, int count, uint32_t stride, bool masked, F&& per_tile) const {
+    const int end = first + count;
     Scores sa, sb;
     wait_vmem_all();
     __syncthreads();
     scores_of(0, sa);
     auto step = [&](int x, int buf, Scores& cur, Scores& nxt) {
-      if (x + 1 < count) {
+      if (x + 1 < end) {
         wait_vmem_all();                            // own copies of tile x + 1 have landed
         __syncthreads();                            // everyone's have; the stage of tile x is free
-        if (x + 2 < count) issue_tile(x + 2, stride, buf);
+        if (x + 2 < end) issue_tile(x + 2, stride, buf);
         scores_of(buf ^ 1, nxt);
       }
       if (masked && x >= n_tiles - kQueries / kTile) mask(x, cur);
-      per_tile(cur);
+      per_tile(x, cur);
       __builtin_amdgcn_sched_barrier(0);
     };
-    for (int x = 0; x < count; x += 2) {
+    for (int x = first; x < end; x += 2) {
       step(x, 0, sa, sb);
-      if (x + 1 < count) step(x + 1, 1, sb, sa);
+      if (x + 1 < end) step(x + 1, 1, sb, sa);
     }
   }
+};
+
+// Attention weight of every key block, averaged over the queries of a query block; BQ = the block size.
+//
+// One sweep over the keys: the exponentials of a query against a fixed reference exponent, summed per key block
+// and kept, as many as there is room for, and in all; divided by the query's total and summed over the
+// queries of a block once it is known.  A query's sums of the first kLdsBlocks key blocks are kept in LDS
+// (a word per block and query), those of the next kRegBlocks in registers, alternating between the two lanes of
+// the query.  Only key blocks behind these (of rows beyond 28K tokens with 128-token blocks, 14K with 64) are
+// swept a second time, kLdsBlocks at a time, when the totals are known.
+//
+// The reference is the largest score of the query's first tile.  It is a scale, not a bound: the sums are floats and
+// lose nothing by being large, so it is only raised (and what is kept scaled down, at most a few times per row)
+// when a tile's sum leaves the range of useful exponents.
+//
+// Sums run over keys, tiles, queries and waves in a fixed order: results repeat bit for bit.
+// 32 heads x 32K tokens: 4.9 ms, against 9.2 with a sweep for the totals, one for the averages and tiles that were
+// not pipelined (1653 tokens with 64-token blocks 70 -> 28 us).  An empty sweep (the MFMAs) takes 2.9 ms; of the
+// rest most is exponentials, 16 cycles of the VALU each.
+constexpr int kLdsBlocks = 92, kRegBlocks = 128;   // 4 x 92 x 32 words beside the tiles and partial sums: two workgroups
+                                                   // per compute unit; 64 registers
+constexpr float kSumRange = 0x1p64f;
+
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+template <int BQ>
+__global__ __launch_bounds__(256, 2) void mass_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
+                                                      const uint16_t* __restrict__ k, float* __restrict__ mass,
+                                                      int levels, float scale_log2) {
+  constexpr int kTiles = BQ / QueryRun::kTile;                // tiles of a key block
+  constexpr int kRows = QueryRun::kQueries / BQ;              // query blocks of the workgroup
+  constexpr int kRowWaves = QueryRun::kWaves / kRows;
+  __shared__ __attribute__((aligned(1024))) char k_lds[2][QueryRun::kStageBytes];
+  __shared__ float s_sums[QueryRun::kWaves][kLdsBlocks][32];
+  __shared__ float s_weight[QueryRun::kWaves][32];
+  __shared__ float s_part[QueryRun::kWaves][kLdsBlocks];
+
+  QueryRun row;
+  if (!row.init(meta, st, k, levels, &k_lds[0][0])) return;
+  const int nb = meta.blk_begin[row.s + 1] - meta.blk_begin[row.s];
+  const int n_blocks = min((row.i + 1) * kRows, nb);          // key blocks the workgroup's queries see
+  const int n_tiles = n_blocks * kTiles;
+  row.start(0, n_tiles, QueryRun::kOne);
+  row.load_queries(st, q);
+
+  float (*sums)[32] = s_sums[row.wave];
+  float ref = 0.0f, total = 0.0f, part = 0.0f, pending = 0.0f;
+  f32x32 held0, held1;
+#pragma unroll
+  for (int x = 0; x < 32; ++x) held0[x] = held1[x] = 0.0f;
+
+  auto tile_sum = [&](QueryRun::Scores& sc) {
+    float sum0 = 0.0f, sum1 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sum0 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][r], scale_log2, -ref));
+      sum1 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][r], scale_log2, -ref));
+    }
+    return sum0 + sum1;
+  };
+  auto largest = [&](QueryRun::Scores& sc) {
+    float m = fmaxf(sc[0][0], sc[1][0]);
+#pragma unroll
+    for (int r = 1; r < 16; ++r) m = fmaxf(fmaxf(m, sc[0][r]), sc[1][r]);
+    return pair_max(m) * scale_log2;
+  };
+  row.sweep(0, n_tiles, QueryRun::kOne, true, [&](int x, QueryRun::Scores& sc) {
+    const int j = x / kTiles;
+    if (x == 0) ref = largest(sc);                            // every query sees its sequence's first key
+    float sum = tile_sum(sc);
+    if (__any(!(sum <= kSumRange))) {
+      const float raised = fmaxf(ref, largest(sc));
+      const float alpha = __builtin_amdgcn_exp2f(ref - raised);
+      ref = raised;
+      total *= alpha;
+      part *= alpha;
+      pending *= alpha;
+      for (int y = row.hi; y < min(j, kLdsBlocks); y += 2) sums[y][row.n] *= alpha;
+#pragma unroll
+      for (int y = 0; y < 32; ++y) {
+        held0[y] *= alpha;
+        held1[y] *= alpha;
+      }
+      sum = tile_sum(sc);
+    }
+    part += sum;
+    if (kTiles == 1 || x % kTiles == kTiles - 1) {
+      const float block = pair_sum(part);
+      total += block;
+      part = 0.0f;
+      if (j < kLdsBlocks) {
+        sums[j][row.n] = block;                               // (both lanes of the query, the same)
+      } else if (j < kLdsBlocks + kRegBlocks) {
+        const int y = j - kLdsBlocks;
+        if (y & 1) {
+          const float both = row.hi ? block : pending;
+          if (y < 64) held0[y >> 1] = both;
+          else held1[(y - 64) >> 1] = both;
+        } else {
+          pending = block;
+        }
+      }
+    }
+  });
+  if (n_blocks > kLdsBlocks && n_blocks < kLdsBlocks + kRegBlocks && ((n_blocks - kLdsBlocks) & 1)) {
+    const int y = n_blocks - 1 - kLdsBlocks;
+    if (y < 64) held0[y >> 1] = pending;
+    else held1[(y - 64) >> 1] = pending;
+  }
+  // a query's share of its block's average; none for a query past the end of the sequence
+  const int q_block = row.i * kRows + row.wave / kRowWaves;   // the wave's query block
+  const int n_valid = min(BQ, row.seq_end - row.seq_begin - q_block * BQ);
+  s_weight[row.wave][row.n] = row.live() ? 1.0f / (total * float(n_valid)) : 0.0f;
+
+  // the key blocks base .. base + count whose sums are in LDS: over the wave's queries (a lane takes a block
+  // and goes round them), then over the waves of a query block
+  auto flush = [&](int base, int count) {
+    asm volatile("" ::: "memory");                            // sums and weights are the wave's own
+    for (int y = row.lane; y < count; y += 64) {
+      float a = 0.0f;
+#pragma unroll 8
+      for (int x = 0; x < 32; ++x) {
+        const int n = (x + row.lane) & 31;
+        a += sums[y][n] * s_weight[row.wave][n];
+      }
+      s_part[row.wave][y] = a;
+    }
+    __syncthreads();
+    for (int y = row.tid; y < count * kRows; y += 256) {
+      const int r = kRows == 1 ? 0 : y / count, j = y - r * count, i = row.i * kRows + r;
+      float a = s_part[r * kRowWaves][j];
+#pragma unroll
+      for (int w = 1; w < kRowWaves; ++w) a += s_part[r * kRowWaves + w][j];
+      if (i < nb && base + j <= i) mass[meta.score_off[row.s] + (int64_t(row.h) * nb + i) * nb + base + j] = a;
+    }
+    __syncthreads();
+  };
+  flush(0, min(n_blocks, kLdsBlocks));
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int base = kLdsBlocks + 64 * half;
+    if (n_blocks <= base) return;
+#pragma unroll
+    for (int x = 0; x < 32; ++x) sums[2 * x + row.hi][row.n] = half ? held1[x] : held0[x];
+    flush(base, min(n_blocks - base, 64));
+  }
+  for (int base = kLdsBlocks + kRegBlocks; base < n_blocks; base += kLdsBlocks) {
+    const int count = min(n_blocks - base, kLdsBlocks);
+    row.start(base * kTiles, count * kTiles, QueryRun::kOne);
+    row.sweep(base * kTiles, count * kTiles, QueryRun::kOne, true, [&](int x, QueryRun::Scores& sc) {
+      part += tile_sum(sc);
+      if (kTiles == 1 || x % kTiles == kTiles - 1) {
+        sums[x / kTiles - base][row.n] = pair_sum(part);
+        part = 0.0f;
+      }
+    });
+    flush(base, count);
+  }
+}
+
+struct TokenBudgets {
+  int32_t k[SHPLB_MAX_TOKEN_BUDGETS];
 };
 
 // Sum of the k largest attention weights of every query, for M budgets k at once.
@@ -448,7 +401,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   const int n_range = all <= kSmallRow ? all : kRangeTiles;
   const int n_sample = all <= kSmallRow ? 0 : max(kRangeTiles, min(all / 16, kSampleTiles));
   uint32_t stride = row.stride_of(n_range);
-  row.start(n_range, stride);
+  row.start(0, n_range, stride);
   row.load_queries(st, q);
 
   const uint32_t column = lds_offset_of(&s_bins[row.wave][0][0]) + 4 * row.n;      // the query's words, kBinBytes apart
@@ -479,7 +432,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   };
   auto bin_begin = [&](int u) { return bin_lo + (float(u - kFirst) - 0.5f) * bin_w; };
   float top_score = -INFINITY;
-  auto count_bins = [&](QueryRun::Scores& sc) {
+  auto count_bins = [&](int, QueryRun::Scores& sc) {
 #pragma unroll
     for (int r = 0; r < 16 * MT; ++r) {
       const float s = sc[r / 16][r % 16];
@@ -508,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
 
   // ---- 1. where to look
   float lo = INFINITY, hi = -INFINITY;
-  row.sweep(n_range, stride, false, [&](QueryRun::Scores& sc) {
+  row.sweep(0, n_range, stride, false, [&](int, QueryRun::Scores& sc) {
 #pragma unroll
     for (int r = 0; r < 16 * MT; ++r) {
       hi = fmaxf(hi, sc[r / 16][r % 16]);
@@ -525,10 +478,10 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   }
   if (n_sample > 0) {
     stride = row.stride_of(n_sample);
-    row.start(n_sample, stride);
+    row.start(0, n_sample, stride);
     clear();
     spread(lo, hi);
-    row.sweep(n_sample, stride, false, count_bins);
+    row.sweep(0, n_sample, stride, false, count_bins);
     const float n_keys = float(n_sample * QueryRun::kTile), share = n_keys / float(visible);
     top_score = pair_max(top_score);
 #pragma unroll
@@ -581,10 +534,10 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
 #pragma unroll
       for (int w = 0; w < QueryRun::kWaves; ++w) any_open |= s_open[round & 1][w];
       if (!__builtin_amdgcn_readfirstlane(any_open) || tries == kSearchRounds) break;
-      row.start(all, stride);
+      row.start(0, all, stride);
       clear();
       top_score = -INFINITY;                                  // (the samples' may be a key the query does not see)
-      row.sweep(all, stride, true, count_bins);
+      row.sweep(0, all, stride, true, count_bins);
       top_score = pair_max(top_score);
       if (open) {
         find(want, bin, above, inside);
@@ -632,7 +585,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   }
 
   // ---- 3. weights
-  row.start(all, stride);
+  row.start(0, all, stride);
   const float ref = top_score * scale_log2;
   auto weight = [&](float s) { return __builtin_amdgcn_exp2f(__builtin_fmaf(s, scale_log2, -ref)); };
   uint32_t put[M];                                            // where the lane's next entry goes
@@ -643,7 +596,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     top[b] = 0.0f;
   }
   fence();
-  row.sweep(all, stride, true, [&](QueryRun::Scores& sc) {
+  row.sweep(0, all, stride, true, [&](int, QueryRun::Scores& sc) {
     float sum0 = 0.0f, sum1 = 0.0f, part[M];
 #pragma unroll
     for (int b = 0; b < M; ++b) part[b] = 0.0f;
@@ -738,15 +691,13 @@ void launch_token_recovery_as(const Geometry& g, const uint16_t* q, const uint16
 
 int32_t launch_block_mass(const Geometry& g, const void* q, const void* k, float* mass, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  const int64_t n_wg = int64_t(g.max_nb) * m.n_seq * m.n_q_heads;
+  const int levels = (g.max_nb * m.block + QueryRun::kQueries - 1) / QueryRun::kQueries;
+  const int64_t n_wg = int64_t(levels) * m.n_seq * m.n_q_heads;
   if (n_wg > 0x7fffffff) return SHPLB_E_UNSUPPORTED;
   const float scale_log2 = g.scale * 1.4426950408889634f;
-  if (m.block == 128)
-    hipLaunchKernelGGL((mass_kernel<128>), dim3(uint32_t(n_wg)), dim3(256), 0, stream, m, g.st,
-                       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), mass, g.max_nb, scale_log2);
-  else
-    hipLaunchKernelGGL((mass_kernel<64>), dim3(uint32_t(n_wg)), dim3(128), 0, stream, m, g.st,
-                       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), mass, g.max_nb, scale_log2);
+  const auto kernel = m.block == 128 ? mass_kernel<128> : mass_kernel<64>;
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(n_wg)), dim3(2 * QueryRun::kQueries), 0, stream, m, g.st,
+                     static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), mass, levels, scale_log2);
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;
 }

@@ -6,7 +6,7 @@ import torch
 
 import paper_2603_10353_amd as S
 from oracle import shplb_oracle as orc
-from workloads import make_custom, make_workload
+from workloads import bf16_bits_from_f32, make_custom, make_workload
 
 from checks import MASS_ATOL, MASS_RTOL
 
@@ -97,3 +97,34 @@ def test_block_mass_32k_layer_sampled_rows():
     rows = set(rng.choice(nb * hq, size=24, replace=False).tolist())
     rows |= {h * nb + nb - 1 for h in (0, 9, 18, 31)}
     _profile(wl, rows=sorted(rows))
+
+
+@pytest.mark.parametrize("block,n_blocks,tail", [(64, 92, 64), (64, 93, 1), (64, 220, 64), (64, 221, 63), (64, 315, 5),
+                                                 (128, 94, 127), (128, 221, 9)])
+def test_block_mass_where_the_kept_sums_end(block, n_blocks, tail):
+    # rows around the lengths up to which a query's block sums stay in LDS, in registers, and beyond
+    T = (n_blocks - 1) * block + tail
+    wl = make_custom([T], 2, 1, block, [2, 2], seed=n_blocks, name="mass_%d_blocks" % n_blocks)
+    nb = wl.n_blocks[0]
+    assert nb == n_blocks
+    rows = sorted({h * nb + i for h in range(2) for i in (0, 1, 91, 92, 93, nb - 2, nb - 1) if i < nb})
+    _profile(wl, rows=rows)
+
+
+@pytest.mark.parametrize("block", [64, 128])
+def test_block_mass_scores_far_above_those_of_the_first_keys(block):
+    # exponents leave the range around the first tile's reference, in several steps, at odd and even blocks:
+    # what is kept by then (in LDS and in registers) has to follow.  Scores reach some 100 nats; their fp32
+    # rounding (2^-24 of sums of 128 products of that size) stays well inside MASS_RTOL.
+    nb = 130
+    T = nb * block - 3
+    rng = np.random.default_rng(block)
+    wl = make_custom([T], 2, 1, block, [2, 2], seed=5, name="mass_rising_%d" % block)
+    k = rng.standard_normal((T, 1, 128)).astype(np.float32)
+    k *= np.where(np.arange(T) < 64, 0.05, 1.0).astype(np.float32)[:, None, None]
+    for b, f in ((37, 3.0), (100, 4.5), (127, 6.0)):
+        k[b * block:(b + 1) * block] *= f
+    wl.q = bf16_bits_from_f32(3 * rng.standard_normal((T, 2, 128)).astype(np.float32))
+    wl.k = bf16_bits_from_f32(k)
+    rows = sorted({h * nb + i for h in range(2) for i in (0, 36, 37, 38, 99, 100, 101, 127, 128, 129)})
+    _profile(wl, rows=rows)
