@@ -37,11 +37,12 @@
 //
 // Between items.  An item used to cost about 21 000 cycles beside its tiles (an atomic ticket that waited
 // for the output stores in front of it, the record, the first selected blocks, the first tile copies and
-// the Q rows, one dependent memory round trip after the other).  Now the ticket is asked for in the last
-// step but one and the record fetched in the last one, and the next item's copies and Q loads are issued
-// before the finished item's output is normalised and stored; the copies are waited for by count, without
-// the stores behind them.  About 10 700 cycles are left.  (4.9 tiles an item, 48 sequences x 28 heads:
-// 135 -> 123 us; 62 tiles, 32K: 1.84 -> 1.81 ms; the 128K layer, 270 tiles, 0.7%.)
+// the Q rows, one dependent memory round trip after the other).  Now the ticket is asked for three steps before
+// the end (in items of two tiles: at their start), its record is fetched in the last step but one, and the last
+// step issues the next item's copies and Q loads as soon as its barrier says that the stages are free; the copies
+// are waited for after the output stores, by count, without the stores.  (4.9 tiles an item, 48 sequences x 28
+// heads: the launch 135 -> 121 us; 62 tiles, 32K: 1.84 -> 1.80 ms; the 128K layer, 270 tiles, 1.4%.)  With the copies
+// started one step later, between the last step and the output, these were 125 us, 1.81 ms and 0.7%.
 //
 // The two score buffers swap roles from step to step (the tile count is even, steps are
 // issued in pairs).  LDS operands are fetched kLook groups ahead of their use.  Fully
@@ -372,6 +373,22 @@ void attn_pipe_kernel(AttnArgs) {
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
     };
 
+    // a workgroup that owes (nearly) as many merges as it can note stops taking items; the others carry on
+    // (there are far fewer split rows in a launch than the workgroups together can note)
+    const bool more = n_merge < kDeferredMerges - 1 && reload(args)->wq.items != nullptr;
+    home_open = more && home_open;
+    // The next item is asked for two steps before the last one (an item of two tiles: here).
+    uint32_t ticket = 0, words = 0;
+    int pos = -1;
+    auto ask = [&]() {
+      if (home_open && tid == 0) {
+        int at = home * kTicketStride;               // (in a vector register: for a uniform address the compiler
+        asm volatile("" : "+v"(at));                 // would add a use of the result right behind the atomic)
+        ticket = __hip_atomic_fetch_add(reload(args)->wq.tickets + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    };
+    if (n_pairs == 1) ask();
+
     // ---- S(0).  (The item's copies have landed in this wave: see the end of the loop.)
     f32x16 sc_a[MT], sc_b[MT];
     __syncthreads();
@@ -393,18 +410,18 @@ void attn_pipe_kernel(AttnArgs) {
     // One step: tile t's softmax and PV from sc_cur, tile t+1's scores into sc_nxt.
     //   stage: t & 1.  jk: block of tile t+2 (kMid only).  mask: tile t+1 is (in) the diagonal block, or `all`
     //   of its keys are to be masked.
-    // kPlace: kMid inside the item; kTicket the last step but one, kFinal the last one.
-    enum { kMid, kTicket, kFinal };
-    uint32_t ticket = 0, words = 0;
-    int pos = -1;
-    auto step = [&](auto place_c, auto stage_c, f32x16 (&sc_cur)[MT], f32x16 (&sc_nxt)[MT], int jk, bool mask, bool all) {
+    // kPlace: kMid inside the item; kRecord the last step but one, kFinal the last one.
+    enum { kMid, kRecord, kFinal };
+    const Item cur = it;                             // (the last step starts the next item)
+    auto step = [&](auto place_c, auto stage_c, f32x16 (&sc_cur)[MT], f32x16 (&sc_nxt)[MT], int jk, bool mask, bool all,
+                    bool ask_now) {
       constexpr int kPlace = decltype(place_c)::value, kStage = decltype(stage_c)::value;
       constexpr bool kHasNext = kPlace != kFinal;
       // Take turns with the other workgroup of this compute unit (see kTurnShift).
       if (((uint32_t(wall_clock64()) >> kTurnShift) & 1) ^ second_wg) __builtin_amdgcn_s_setprio(1);
       else __builtin_amdgcn_s_setprio(0);
       wait_vmem_all();                  // own copies of K(t+1), V(t) have landed
-      if (kPlace == kFinal && home_open && tid == 0) {
+      if (kPlace == kRecord && home_open && tid == 0) {
         // the ticket asked for one step ago
         s_next = ticket < home_size ? home_begin + int(ticket) : kHelp;
       }
@@ -414,15 +431,16 @@ void attn_pipe_kernel(AttnArgs) {
         locate(jk, kStage);
         issue(k_head, k_stage0 + kStage * kTileBytes);
       }
-      if (kPlace == kTicket && home_open && tid == 0) {
-        int at = home * kTicketStride;               // (in a vector register: for a uniform address the compiler
-        asm volatile("" : "+v"(at));                 // would add a use of the result right behind the atomic)
-        ticket = __hip_atomic_fetch_add(reload(args)->wq.tickets + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if constexpr (kPlace == kFinal) {
+      if (kPlace == kMid && kStage == 1 && ask_now) ask();
+      if constexpr (kPlace == kRecord) {
         // the next item's record arrives behind this step's work
         pos = home_open ? __builtin_amdgcn_readfirstlane(s_next) : kHelp;
         words = record_words(pos);
+      }
+      if constexpr (kPlace == kFinal && KS == 1) {
+        // all stages but that of V(t) are free and the last scores have been taken: the next item starts
+        if (pos >= 0 && read_record(pos, words, it)) start_item();
+        else it.n_sel = 0;
       }
 
       const char* kn = k_lds + (kStage ^ 1) * kTileBytes;
@@ -516,23 +534,18 @@ void attn_pipe_kernel(AttnArgs) {
     int b = 0;
     for (; b + 1 < n_pairs; ++b) {
       const int j2 = block_of(b + 2);
-      step(integral_constant<int, kMid>{}, even, sc_a, sc_b, j1, j0 == i || beyond(b), beyond(b));
-      step(integral_constant<int, kMid>{}, odd, sc_b, sc_a, j1, j1 == i || beyond(b + 1), beyond(b + 1));
+      step(integral_constant<int, kMid>{}, even, sc_a, sc_b, j1, j0 == i || beyond(b), beyond(b), false);
+      step(integral_constant<int, kMid>{}, odd, sc_b, sc_a, j1, j1 == i || beyond(b + 1), beyond(b + 1), b + 2 == n_pairs);
       j0 = j1;
       j1 = j2;
     }
-    // a workgroup that owes (nearly) as many merges as it can note stops taking items; the others carry on
-    // (there are far fewer split rows in a launch than the workgroups together can note)
-    const bool more = n_merge < kDeferredMerges - 1 && reload(args)->wq.items != nullptr;
-    home_open = more && home_open;
-    step(integral_constant<int, kTicket>{}, even, sc_a, sc_b, 0, j0 == i || beyond(b), beyond(b));
-    step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false);
+    step(integral_constant<int, kRecord>{}, even, sc_a, sc_b, 0, j0 == i || beyond(b), beyond(b), false);
+    step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false, false);
 
     // ---- the next item starts before this one's results are written
-    const Item cur = it;
     float l_tot = pair_sum(l_run);
-    __syncthreads();                                 // every wave is done with the stages
     if constexpr (KS > 1) {
+      __syncthreads();                               // every wave is done with the stages
       // The groups combine their partial results (the softmax of Eq. 1 over the union of their keys): group g
       // ends up with the dims 32 dt .. of the dt's that are its own.
       constexpr int kOwn = 4 / KS;
@@ -581,12 +594,17 @@ void attn_pipe_kernel(AttnArgs) {
       __syncthreads();                               // the stages are free again
     }
     home_open = pos != kHelp;
-    if (more && pos == kHelp) {
-      pos = help();
-      words = record_words(pos);
+    if (KS > 1 || (more && pos == kHelp)) {
+      if (KS == 1) __syncthreads();                  // every wave is done with the stages
+      if (more && pos == kHelp) {
+        pos = help();
+        words = record_words(pos);
+      }
+      have = more && pos >= 0 && read_record(pos, words, it);
+      if (have) start_item();
+    } else {
+      have = more && it.n_sel > 0;
     }
-    have = more && pos >= 0 && read_record(pos, words, it);
-    if (have) start_item();
 
     // ---- normalise and store: lane holds, for its query, dims 32dt + 8(r/4) + 4hi + (r%4)
     int q_in = wave * 32 + n;
