@@ -235,7 +235,10 @@ void attn_pipe_kernel(AttnArgs) {
   };
   // Place of an item from another die's queue, to all threads (-1: every queue is empty).
   auto help = [&]() {
-    if (tid == 0) s_next = help_item(reload(args)->wq.queue_begin, reload(args)->wq.tickets, home, &s_empty);
+    if (wave_all == 0) {
+      const int at = help_item(reload(args)->wq.queue_begin, reload(args)->wq.tickets, home, &s_empty);
+      if (lane == 0) s_next = at;
+    }
     __syncthreads();
     const int pos = __builtin_amdgcn_readfirstlane(s_next);
     __syncthreads();
@@ -249,7 +252,7 @@ void attn_pipe_kernel(AttnArgs) {
   if (args->wq.items == nullptr) {
     have = row_item(args, blockIdx.x, it);
   } else {
-    if (tid == 0) s_empty = 0;
+    if (tid < 64) s_empty = 0;                       // (wave 0's own)
     const int x = blockIdx.x % kXcds, begin = args->wq.queue_begin[x];
     int pos = begin + int(blockIdx.x / kXcds);
     if (pos >= args->wq.queue_begin[x + 1]) pos = help();

@@ -167,47 +167,42 @@ __device__ __forceinline__ void decode_row(const SeqMeta& m, int32_t row, int& s
   i = local - h * nb;
 }
 
-// The queue with the most items left, other than those in empty_mask (ties: the first one
-// from home on), or -1.  Counts are read with device-scope loads and may be a little old.
-__device__ __forceinline__ int fullest_queue(const int32_t* queue_begin, const uint32_t* tickets,
-                                                       int home, int empty_mask) {
-  int most = 0, pick = -1;
-  for (int d = 0; d < kXcds; ++d) {
-    const int x = (home + d) % kXcds;
-    if (empty_mask & 1 << x) continue;
-    const uint32_t size = uint32_t(queue_begin[x + 1] - queue_begin[x]);
-    const uint32_t taken = __hip_atomic_load(tickets + x * kTicketStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int left = taken < size ? int(size - taken) : 0;
-    if (left > most) {
-      most = left;
-      pick = x;
-    }
-  }
-  return pick;
-}
-
-// An item from another die's queue for a persistent workgroup whose own is empty (called by one
-// thread).  Every item comes from the queue that has the most items left at that moment.
-// Helpers so spread over the dies that still have work in proportion to what is left there,
-// and no queue is left for last with its heavy items still in it.  An old count only affects
-// which queue is tried, the ticket decides.  A queue whose ticket came back past its end is
-// never tried again (*empty_mask), so the loop ends after at most kXcds misses.  Returns the
-// item's place in the queues, or -1 when every queue is empty.
+// An item from another die's queue for a persistent workgroup whose own is empty (called by one whole
+// wave).  Every item comes from the queue that has the most items left at that moment (ties: the first
+// one from home on): helpers so spread over the dies that still have work in proportion to what is left
+// there, and no queue is left for last with its heavy items still in it.  Counts are read with device-scope
+// loads, a lane per queue, and may be a little old: that only affects which queue is tried, the ticket decides.
+// A queue whose ticket came back past its end is never tried again (*empty_mask), so the loop ends after at
+// most kXcds misses.  Returns the item's place in the queues, or -1 when every queue is empty.
+// (Now two memory round trips; with one thread going through the queues, load after load, it was ten: 48 sequences
+// x 28 heads, whose dies hold unequal work, 172 -> 165 us for the whole path, an 8K prompt 189 -> 187 us.  Asked
+// for behind the item's last steps they cost the tile loop registers, and 2% at 32K and 128K.)
 __device__ __attribute__((noinline)) int help_item(const int32_t* queue_begin, uint32_t* tickets, int home, int* empty_mask) {
-  int empty = *empty_mask, pos = -1;
+  static_assert(kXcds == 8, "the largest of eight lanes in three exchanges");
+  int empty = *empty_mask;
+  const int lane = threadIdx.x & 63, x = (home + lane) % kXcds;
+  const int begin = queue_begin[x], size = queue_begin[x + 1] - begin;
   for (;;) {
-    const int pick = fullest_queue(queue_begin, tickets, home, empty);
-    if (pick < 0) break;
-    const int begin = queue_begin[pick], end = queue_begin[pick + 1];
-    const uint32_t t = atomicAdd(tickets + pick * kTicketStride, 1u);
-    if (t < uint32_t(end - begin)) {
-      pos = begin + int(t);
-      break;
+    const uint32_t taken = __hip_atomic_load(tickets + x * kTicketStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int left = taken < uint32_t(size) && !(empty >> x & 1) ? size - int(taken) : 0;
+    // items left and, below them, the order from home on: the largest of lanes 0 .. 7
+    int best = left > 0 ? left << 3 | (kXcds - 1 - (lane & 7)) : 0;
+#pragma unroll
+    for (int d = 1; d < kXcds; d <<= 1) best = max(best, __shfl_xor(best, d));
+    best = __builtin_amdgcn_readfirstlane(best);
+    if (best == 0) break;
+    const int pick = kXcds - 1 - (best & 7);             // the lane of the queue
+    uint32_t t = 0;
+    if (lane == pick) t = atomicAdd(tickets + x * kTicketStride, 1u);
+    t = __builtin_amdgcn_readlane(t, pick);
+    if (t < uint32_t(__builtin_amdgcn_readlane(size, pick))) {
+      *empty_mask = empty;
+      return __builtin_amdgcn_readlane(begin, pick) + int(t);
     }
-    empty |= 1 << pick;
+    empty |= 1 << __builtin_amdgcn_readlane(x, pick);
   }
   *empty_mask = empty;
-  return pos;
+  return -1;
 }
 
 __device__ __forceinline__ int my_xcd() {
