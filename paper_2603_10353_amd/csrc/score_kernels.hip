@@ -71,9 +71,18 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
       for (int u = 0; u < U; ++u) add_bf16x8(acc, w[u]);
     }
-    for (; t < t1; t += kPoolWaves) {
-      const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + int64_t(t) * stride_t));
-      add_bf16x8(acc, w);
+    // What is left of a ragged block, in flight together likewise (loads past the end repeat the last token;
+    // one load after the other, a block of 127 tokens took 15 memory round trips: 48 ragged sequences 22.2 -> 19.5 us,
+    // the whole path of an 8231-token prompt 184.5 -> 182.7 us).
+    const int left = __builtin_amdgcn_readfirstlane((t1 - t + kPoolWaves - 1) / kPoolWaves);
+    if (left > 0) {
+      u32x4 w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + int64_t(min(t + u * kPoolWaves, t1 - 1)) * stride_t));
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (u < left) add_bf16x8(acc, w[u]);
     }
   }
 #pragma unroll

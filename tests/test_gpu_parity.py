@@ -371,3 +371,11 @@ def test_budgets_from_max_min_shifting():
     assert moves == mo and moves > 0 and budgets.min() >= 2 and budgets.sum() == 8 * hq
     wl = make_custom([128 * nb - 9], hq, 2, 128, budgets.tolist(), seed=93, name="shifted_budgets")
     full_parity(wl)
+
+
+@pytest.mark.parametrize("block, tails", [(128, [1, 3, 4, 5, 61, 63, 64, 65, 67, 127]), (64, [1, 4, 5, 60, 61, 63])])
+def test_pooling_of_ragged_blocks(block, tails):
+    # what is left of a block after whole rounds of loads: none to all of a round, for one wave or all four;
+    # sequences of one block and of two; scores of sequences of one block are a single product
+    wl = make_custom([t + block * (x % 2) for x, t in enumerate(tails)], 4, 2, block, [2] * 4, seed=block, name="ragged_%d" % block)
+    full_parity(wl)
