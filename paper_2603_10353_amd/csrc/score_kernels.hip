@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
 // anyway.  Six v_mfma_f32_32x32x16_bf16 do the work of eight v_mfma_f32_32x32x2_f32 in
 // 3/8 of the time.
 //
-// One workgroup = 128 query-block rows (32 per wave) of one (sequence, head) x a chunk of
+// One workgroup = 128 query-block rows (32 per wave; see kWaves) of one (sequence, head) x a chunk of
 // key-block rows, streamed in tiles of 32 through a double-buffered LDS stage; three
 // workgroups share a compute unit and hide each other's copy latency.  The Q planes of a
 // wave's rows stay in registers as MFMA B-operands; a K tile is 3 planes x 32 rows of 256
@@ -133,19 +133,23 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
 // output tile and four runs of four consecutive j: 16-byte stores.  Two accumulators take
 // the six products in turn (no MFMA waits for the one before it) and are added at the end;
 // the order of additions is fixed.
-constexpr int kScoreTile = 128;                       // query-block rows per workgroup
+// A launch whose sequences all have at most 32 blocks (kWaves = 1) takes workgroups of one wave, one K tile and one
+// LDS stage: of four waves three would have no row, and half as many workgroups would fit a compute unit.
+// (Whole path, 48 short sequences x 28 heads 159.0 -> 153.3 us, one prompt of 777 tokens 34.7 -> 34.5 us.)
 constexpr int kScoreJ = 32;                           // key-block rows per LDS stage
 constexpr int kPlanes = 3;
 constexpr int kScoreStageBytes = kPlanes * kScoreJ * kRowBytes;   // 24 KB
 // chunks (of `chunk` key-block rows) that hold some j <= i for the rows of tile row tr
-__host__ __device__ constexpr int score_chunks_of_row(int tr, int chunk) {
-  return (tr * kScoreTile + kScoreTile - 1) / chunk + 1;
+__host__ __device__ constexpr int score_chunks_of_row(int tr, int chunk, int tile) {
+  return (tr * tile + tile - 1) / chunk + 1;
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void score_kernel(
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void score_kernel(
     SeqMeta meta, const uint16_t* __restrict__ q_planes, const uint16_t* __restrict__ k_planes,
     float* __restrict__ scores, int total_blocks, int chunk, float scale) {
-  __shared__ __attribute__((aligned(1024))) char k_lds[2][kScoreStageBytes];
+  constexpr int kScoreTile = 32 * kWaves;               // query-block rows per workgroup
+  __shared__ __attribute__((aligned(1024))) char k_lds[kWaves == 1 ? 1 : 2][kScoreStageBytes];
   const int sh = blockIdx.z;
   const int s = sh / meta.n_q_heads, h = sh - s * meta.n_q_heads;
   const int nb = meta.blk_begin[s + 1] - meta.blk_begin[s];
@@ -154,7 +158,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   // so every die gets the same share of live work (a square grid would hand die x the whole
   // chunk column x, most of which lies above the diagonal for large x).
   int tr = 0, rest = int(blockIdx.x);
-  while (rest >= score_chunks_of_row(tr, chunk)) rest -= score_chunks_of_row(tr++, chunk);
+  while (rest >= score_chunks_of_row(tr, chunk, kScoreTile)) rest -= score_chunks_of_row(tr++, chunk, kScoreTile);
   const int ti = tr * kScoreTile, tj = rest * chunk;
   if (ti >= nb) return;                             // shorter sequence of a varlen batch
   const int tid = threadIdx.x;
@@ -168,19 +172,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int64_t k_plane = int64_t(meta.n_kv_heads) * total_blocks * kHeadDim;
   const char* k_rows = reinterpret_cast<const char*>(k_planes + (int64_t(g) * total_blocks + meta.blk_begin[s]) * kHeadDim);
 
-  // copies: round rd of a tile fills LDS rows 16rd .. 16rd+15 = plane rd/2, tile rows 16(rd&1)..;
-  // this lane's row inside the tile and its slot are the same in every round of one parity
-  const int cp_jl = 4 * wave + (lane >> 4);
+  // copies: a round fills 4 kWaves consecutive tile rows of one plane; a lane's row is its own in each
+  constexpr int kRoundRows = 4 * kWaves;
+  const int cp_row = 4 * wave + (lane >> 4);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_offset_of(&k_lds[0][0]) + 4 * wave * kRowBytes);
   auto issue_tile = [&](int jt, int stage) __attribute__((always_inline)) {
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int jl = 16 * half + cp_jl;
-      const int j = min(tj + kScoreJ * jt + jl, nb - 1);          // rows past the end repeat the last one (never stored)
+    for (int rd = 0; rd < kScoreJ / kRoundRows; ++rd) {
+      const int jl = kRoundRows * rd + cp_row;
+      // Rows past the end: repeat the last one, or leave what is there (a column j of the scores depends on
+      // row j alone, and these are never stored).
+      if (kWaves == 1 && tj + kScoreJ * jt + kRoundRows * rd >= nb) break;
+      const int j = min(tj + kScoreJ * jt + jl, nb - 1);
       const uint32_t off = uint32_t(j) * kRowBytes + (((lane & 15) ^ swz(jl)) << 4);
 #pragma unroll
       for (int pl = 0; pl < kPlanes; ++pl)
-        copy_g2l_16(k_rows + pl * k_plane * 2, off, lds0 + stage * kScoreStageBytes + (2 * pl + half) * 16 * kRowBytes);
+        copy_g2l_16(k_rows + pl * k_plane * 2, off, lds0 + stage * kScoreStageBytes + (pl * kScoreJ + kRoundRows * rd) * kRowBytes);
     }
   };
   issue_tile(0, 0);
@@ -300,16 +307,22 @@ int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, floa
   // Key-block rows per workgroup: the shortest chunk with which the whole launch is resident at
   // once (three workgroups per compute unit); more, shorter workgroups would run in rounds,
   // fewer, longer ones would leave compute units idle.
-  const int tiles = (g.max_nb + kScoreTile - 1) / kScoreTile;
+  const bool small = g.max_nb <= 32;
+  const int tile = small ? 32 : 128, tiles = (g.max_nb + tile - 1) / tile;
   const int64_t resident = int64_t(n_compute_units) * 3;
-  int chunk = 64, n_pairs = 0;
+  int chunk = small ? 32 : 64, n_pairs = 0;
   for (;; chunk *= 2) {
     n_pairs = 0;
-    for (int tr = 0; tr < tiles; ++tr) n_pairs += score_chunks_of_row(tr, chunk);
-    if (int64_t(n_pairs) * m.n_seq * m.n_q_heads <= resident || chunk >= tiles * kScoreTile) break;
+    for (int tr = 0; tr < tiles; ++tr) n_pairs += score_chunks_of_row(tr, chunk, tile);
+    if (int64_t(n_pairs) * m.n_seq * m.n_q_heads <= resident || chunk >= tiles * tile) break;
   }
-  hipLaunchKernelGGL(score_kernel, dim3(n_pairs, 1, m.n_seq * m.n_q_heads), dim3(256), 0, stream, m,
-                     q_planes, k_planes, scores, int(g.total_blocks), chunk, g.scale);
+  const dim3 grid(n_pairs, 1, m.n_seq * m.n_q_heads);
+  if (small)
+    hipLaunchKernelGGL((score_kernel<1>), grid, dim3(64), 0, stream, m, q_planes, k_planes, scores, int(g.total_blocks),
+                       chunk, g.scale);
+  else
+    hipLaunchKernelGGL((score_kernel<4>), grid, dim3(256), 0, stream, m, q_planes, k_planes, scores, int(g.total_blocks),
+                       chunk, g.scale);
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;
 }

@@ -379,3 +379,9 @@ def test_pooling_of_ragged_blocks(block, tails):
     # sequences of one block and of two; scores of sequences of one block are a single product
     wl = make_custom([t + block * (x % 2) for x, t in enumerate(tails)], 4, 2, block, [2] * 4, seed=block, name="ragged_%d" % block)
     full_parity(wl)
+
+
+@pytest.mark.parametrize("n_blocks", [3, 32, 33])
+def test_scores_where_one_wave_scores_a_sequence(n_blocks):
+    # sequences of at most 32 blocks are scored by workgroups of one wave, if the launch has no longer one
+    full_parity(make_custom([64 * n_blocks - 9, 64, 70], 4, 2, 64, [5] * 4, seed=n_blocks, name="score_%d" % n_blocks))
