@@ -48,8 +48,7 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
   uint16_t* dst = is_q ? q_planes : k_planes;
   const int64_t plane = int64_t(n_heads) * total_blocks * kHeadDim;
 
-  int s = 0;
-  while (s + 1 < meta.n_seq && gblk >= meta.blk_begin[s + 1]) ++s;
+  const int s = sequence_of(meta, gblk, 1);
   const int t0 = meta.tok_begin[s] + (gblk - meta.blk_begin[s]) * meta.block;
   const int t1 = min(meta.tok_begin[s + 1], t0 + meta.block);
   const int cnt = t1 - t0;

@@ -157,10 +157,20 @@ __device__ __forceinline__ int kv_head_of(const SeqMeta& m, int h) {
   return m.kv_map ? int(m.kv_of[h >> 2] >> (8 * (h & 3)) & 0xff) : h / (m.n_q_heads / m.n_kv_heads);
 }
 
+// The sequence of block `at` (per_block 1) or row `at` (per_block: the query heads), the same in all lanes of the
+// wave, all of them active: how many sequences end at or before it, a lane per sequence.  (A loop over the sequences
+// is a chain of up to 63 scalar loads in front of everything a workgroup
+// does: the path over 48 sequences took 160.4 us with it in the pooling and selection kernels, 155.4 without.)
+__device__ __forceinline__ int sequence_of(const SeqMeta& m, int32_t at, int per_block) {
+  static_assert(SHPLB_MAX_SEQ <= 64, "a lane per sequence");
+  if (m.n_seq == 1) return 0;
+  const int lane = threadIdx.x & 63;
+  return __builtin_popcountll(__ballot(lane < m.n_seq - 1 && at >= m.blk_begin[min(lane + 1, m.n_seq)] * per_block));
+}
+
 // Row -> (sequence, head, query block).  Rows of one sequence are contiguous.
 __device__ __forceinline__ void decode_row(const SeqMeta& m, int32_t row, int& s, int& h, int& i, int& nb) {
-  s = 0;
-  while (s + 1 < m.n_seq && row >= m.blk_begin[s + 1] * m.n_q_heads) ++s;
+  s = sequence_of(m, row, m.n_q_heads);
   const int local = row - m.blk_begin[s] * m.n_q_heads;
   nb = m.blk_begin[s + 1] - m.blk_begin[s];
   h = local / nb;
