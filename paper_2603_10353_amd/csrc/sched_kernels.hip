@@ -7,7 +7,7 @@
 // free.  MI355X has eight dies (XCDs), each with its own L2, so there is one sorted queue
 // per die: all rows that stream one KV head of one sequence share a home die, whose L2 then
 // sees that K/V once.  A workgroup drains its die's queue first and then helps whichever die
-// has the most items left (see next_item()), which keeps the greedy's balance when the dies'
+// has the most items left (see help_item()), which keeps the greedy's balance when the dies'
 // queues hold very different amounts of work.
 //
 // One launch of eight workgroups; workgroup x builds the queue of die x with a counting sort
