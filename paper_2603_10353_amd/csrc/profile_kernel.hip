@@ -40,6 +40,7 @@ struct QueryRun {
   int cp_row, k_rd0;
   uint32_t k_stage0;
   int64_t row_bytes;
+  uint32_t widest;                                  // largest distance of a sampled tile's keys, see issue_tile()
   const char* k_head;
   const char* k_lds;                                // two stages of kStageBytes
   bf16x8 qf[8];                                     // B operand of S^T = K Q^T: dims 16ks + 8hi.. of the lane's query
@@ -66,6 +67,7 @@ struct QueryRun {
     hi = lane >> 5;
     n_tiles = (i + 1) * (kQueries / kTile);
     row_bytes = st.kv_t * 2;
+    widest = uint32_t(fminf(float(1ull << 32) * (0.999f * kOne / kTile) / float(row_bytes), 0x1p23f));
     k_head = reinterpret_cast<const char*>(k + int64_t(kv_head_of(meta, h)) * st.kv_h);
     k_lds = lds;
     cp_row = 4 * wave + (lane >> 4);
@@ -84,7 +86,11 @@ struct QueryRun {
 
   // Copy a tile into LDS stage `buf`: keys kTile x .. of the row's, or of those that are left when only every
   // (stride / kOne)-th is taken.  Rows past the end of the sequence re-read its last key; they are masked.
+  // Offsets within a tile are 32 bits wide: the sampled keys of a tile move closer together where K's rows are so
+  // far apart that the tile would reach over 4 GiB (`widest`; at 128K tokens, rows of more than 130 KB).  Keys
+  // next to each other always fit: rows are less than 2^25 bytes apart, and `widest` is at least kOne then.
   __device__ __forceinline__ void issue_tile(int x, uint32_t stride, int buf) const {
+    const uint32_t step = stride == kOne ? kOne : min(stride, widest);
     const int first = int(uint32_t(kTile * x) * stride / kOne);
     const int key_base = min(seq_begin + first, seq_end - 1);
     const int last = seq_end - 1 - key_base;
@@ -92,7 +98,7 @@ struct QueryRun {
 #pragma unroll
     for (int rd = 0; rd < kRounds; ++rd) {
       const int r = rd * kRoundRows + cp_row;
-      const int key = int(__umul24(r, stride) / kOne);
+      const int key = int(__umul24(r, step) / kOne);
       const uint32_t off = uint32_t(min(key, last)) * uint32_t(row_bytes) + (((lane & 15) ^ swz(r)) << 4);
       copy_g2l_16(k_tile, off, __builtin_amdgcn_readfirstlane(k_stage0 + buf * kStageBytes + rd * kRoundRows * kRowBytes));
     }

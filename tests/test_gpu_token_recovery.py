@@ -89,6 +89,27 @@ def test_search_on_unfavourable_scores(shape, T):
     np.testing.assert_allclose(got, want, rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
 
 
+def test_sampled_keys_of_rows_far_apart():
+    # 128K tokens whose K rows lie 256 KB apart: the first sample takes every 512th key, 64 of them span 8 GiB.
+    # What lies between the rows is not K: were it read for K, a score would be infinite.
+    from harness import to_dev_bf16
+    T, stride = 131072, 131080
+    wl = make_custom([T], 2, 1, 128, [2, 2], seed=17, name="token_recovery_wide_rows")
+    q = to_dev_bf16(wl.q)
+    room = torch.zeros((T, stride), dtype=torch.bfloat16, device="cuda:0")
+    room[:, 128::128] = float("inf")
+    room[:, :128] = to_dev_bf16(wl.k)[:, 0]
+    p = S.Problem(wl.cu_seqlens, 2, 1, 128, kv_stride_t=stride, kv_stride_h=128)
+    budgets = [2000]
+    print("case", wl.name, "kv_stride_t", stride, "budgets", budgets, flush=True)
+    out = torch.full((1, 2, T), float("nan"), dtype=torch.float32, device="cuda:0")
+    S.shplb_token_recovery(p, q, room, budgets, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    _, want = _run(wl, budgets)
+    np.testing.assert_array_equal(out.cpu().numpy()[0, :, :2000], 1.0)
+    np.testing.assert_allclose(out.cpu().numpy(), want, rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
+
+
 def test_is_deterministic():
     wl = make_workload(1, seqlens=[3000])
     run, a = _run(wl, [256])
