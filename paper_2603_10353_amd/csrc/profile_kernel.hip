@@ -343,11 +343,13 @@ struct TokenBudgets {
 // again, and the kernel is bound by the number of sweeps.  Per query it needs two, and a little sampling:
 //
 //   1. a few tiles, evenly spread, give the range of the query's scores, then a histogram of a few more tiles
-//      over that range gives an interval that should hold the k-th largest score;
+//      over that range gives an interval that should hold the k-th largest score (a guess only: the sampled
+//      keys of the last tiles may be ones the query does not see; scores that are no numbers are left out);
 //   2. a sweep counts the scores in kBins bins over the interval, the outermost ones open: the bin that holds
 //      the k-th largest is known, and how many scores lie above it.  With more keys in the bin than there
 //      is room for, or with the k-th largest in an open bin, the sweep is done again over that bin or over
-//      what lies beyond.  A bin no wider than the resolution of a score (ties) needs no more division;
+//      what lies beyond.  A bin no wider than the resolution of a score (ties) needs no more division, nor does
+//      the lower open bin once it lies so far below the largest score that its weights are zero (-inf among them);
 //   3. the last sweep takes the exponentials: their sum, the sum of those above the bin, and the scores in
 //      the bin to a list.  The list gives the few weights that are missing.
 //
@@ -371,7 +373,11 @@ constexpr int kRangeTiles = 256 / QueryRun::kTile, kSampleTiles = 2048 / QueryRu
 // Tiles of a row that is searched over its whole range at once: sampling costs such rows as much as the sweep it
 // would save (384 and 768 keys alike; with 1536, 1391 tokens x 28 heads, three budgets, take 365 instead of 262 us)
 constexpr int kSmallRow = 768 / QueryRun::kTile;
-constexpr int kSearchRounds = 64;                  // never reached: a round divides the interval by kInner
+constexpr float kFar = 0x1p126f;                   // intervals end here, so that their widths are numbers
+constexpr float kNoWeight = 160.0f;                // 2^-160 is zero: so far below the largest, in log2 units of weight
+// Sweeps of a search at most.  One that divides the interval leaves 1/42 of it or less, one beyond it reaches 32 times as
+// far: some ten at most between the far end of an interval and ties.  Still open then (k-th scores beyond kFar): NaN.
+constexpr int kSearchRounds = 64, kUnknown = -1;
 
 template <int M>
 __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, Strides st,
@@ -424,16 +430,20 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   // least useful width of a bin around scores lo .. hi: half the distance of neighbouring floats, or what
   // changes a weight by 2^-26 of itself
   auto finest = [&](float lo, float hi) {
-    return fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 0x1p-26f / scale_log2);
+    const float least = fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 0x1p-26f / scale_log2);
+    return __builtin_amdgcn_fmed3f(least, 0x1p-120f, 0x1p119f);
   };
+  auto finite = [](float s) { return __builtin_amdgcn_classf(s, 0x1f8); };   // neither an infinity nor a NaN
   float bin_lo, bin_w, map_a, map_b;                          // interval's begin, width of a bin, x = fma(score, map_a, map_b)
   bool ties;                                                  // bins hold one score each (as far as a weight can tell)
   auto spread = [&](float lo, float hi) {
+    lo = __builtin_amdgcn_fmed3f(lo, -kFar, kFar);
+    hi = __builtin_amdgcn_fmed3f(hi, -kFar, kFar);
     const float least = finest(lo, hi);
     bin_lo = lo;
     bin_w = fmaxf((hi - lo) * (1.0f / kInner), least);
     ties = bin_w <= least;
-    map_a = fminf(fmaxf(1.0f / bin_w, 1e-30f), 1e30f);
+    map_a = 1.0f / bin_w;
     map_b = (kWhole + kFirst) - map_a * lo;
   };
   auto bin_begin = [&](int u) { return bin_lo + (float(u - kFirst) - 0.5f) * bin_w; };
@@ -467,15 +477,18 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
 
   // ---- 1. where to look
   float lo = INFINITY, hi = -INFINITY;
-  row.sweep(0, n_range, stride, false, [&](int, QueryRun::Scores& sc) {
+  row.sweep(0, n_range, stride, n_sample == 0, [&](int, QueryRun::Scores& sc) {
 #pragma unroll
     for (int r = 0; r < 16 * MT; ++r) {
-      hi = fmaxf(hi, sc[r / 16][r % 16]);
-      lo = fminf(lo, sc[r / 16][r % 16]);
+      const float s = sc[r / 16][r % 16];
+      const bool counts = finite(s);
+      hi = fmaxf(hi, counts ? s : -INFINITY);
+      lo = fminf(lo, counts ? s : INFINITY);
     }
   });
   hi = pair_max(hi);
   lo = -pair_max(-lo);
+  if (lo > hi) lo = hi = 0.0f;
   float from[M], to[M];
 #pragma unroll
   for (int b = 0; b < M; ++b) {
@@ -490,6 +503,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     row.sweep(0, n_sample, stride, false, count_bins);
     const float n_keys = float(n_sample * QueryRun::kTile), share = n_keys / float(visible);
     top_score = pair_max(top_score);
+    const float sample_top = finite(top_score) ? top_score : hi + kInner * bin_w;
 #pragma unroll
     for (int b = 0; b < M; ++b) {
       // the rank in the sample is off by its standard deviation; four of them
@@ -497,7 +511,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
       const float off = 4.0f * __builtin_sqrtf(fmaxf(rank * (1.0f - rank / n_keys), 0.0f)) + 4.0f;
       int bin, above, inside;
       find(max(1, int(rank - off)), bin, above, inside);
-      to[b] = bin < kBins - 1 && rank > off ? bin_begin(bin + 1) : top_score;
+      to[b] = bin < kBins - 1 && rank > off ? bin_begin(bin + 1) : sample_top;
       find(min(n_sample * QueryRun::kTile, int(rank + off)), bin, above, inside);
       from[b] = bin > 0 ? bin_begin(bin) : bin_begin(0) - kInner * bin_w;
     }
@@ -549,8 +563,12 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
         find(want, bin, above, inside);
         // beyond the interval: most often just beyond
         const float reach = (tries == 0 ? 2.0f : 32.0f) * kInner * bin_w;
-        if (bin == 0) {
-          spread(bin_begin(1) - reach, bin_begin(1) + bin_w);
+        const float nothing = fmaxf(top_score - kNoWeight / scale_log2, -kFar);   // no weight from here down
+        if (!finite(top_score)) {
+          open = false;                                       // the weights are no numbers, nor will the result be one
+        } else if (bin == 0) {
+          if (bin_begin(1) + bin_w <= nothing) open = false;  // all keys that weigh anything are among the k largest
+          else spread(fmaxf(bin_begin(1) - reach, nothing), bin_begin(1) + bin_w);
         } else if (bin == kBins - 1) {
           spread(bin_begin(kBins - 1) - bin_w, tries == 0 ? fminf(bin_begin(kBins - 1) + reach, top_score) : top_score);
         } else if (inside <= room || ties) {
@@ -573,7 +591,8 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
       }
       return __builtin_bit_cast(float, low ^ ((low >> 31) & 0x7fffffff));
     };
-    const float least_in = search ? least_score(kWhole + float(bin)) : INFINITY;
+    const bool listing = search && bin > 0;                   // (none of the lower open bin's weigh anything)
+    const float least_in = listing ? least_score(kWhole + float(bin)) : INFINITY;
     const float least_above = search ? least_score(kWhole + float(bin + 1)) : INFINITY;
     const bool tie = inside > room;
     const int entries = tie ? 1 : inside;
@@ -582,12 +601,12 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
       if (x == b) {
         list_from[x] = least_in;
         above_from[x] = least_above;
-        rest[x] = want - above;
-        listed[x] = search ? entries : 0;
+        rest[x] = open ? kUnknown : want - above;
+        listed[x] = listing ? entries : 0;
         list_at[x] = used;
         tied[x] = tie;
       }
-    if (search) used += entries;
+    if (listing) used += entries;
   }
 
   // ---- 3. weights
@@ -681,6 +700,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
       r += float(rest[b] - more) * w;
     }
     r /= total;
+    if (rest[b] == kUnknown) r = __uint_as_float(0x7fc00000u);
     if (visible <= budgets.k[b]) r = 1.0f;
     store(b, r);
   }

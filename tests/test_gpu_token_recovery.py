@@ -110,6 +110,34 @@ def test_sampled_keys_of_rows_far_apart():
     np.testing.assert_allclose(out.cpu().numpy(), want, rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
 
 
+@pytest.mark.parametrize("what", ["one_of_each", "later_nan", "most_without_weight", "far_below"])
+@pytest.mark.parametrize("T", [700, 2600])
+def test_infinite_scores(what, T):
+    # Infinities in K: a key that a query does not see must not change its result, a score of -inf weighs nothing.
+    # Every query whose reference is a number, rows that are sampled first (2600 tokens) and rows that are not.
+    rng = np.random.default_rng(T)
+    wl = make_custom([T], 2, 1, 128, [2, 2], seed=6, name="token_recovery_" + what)
+    q, k = rng.standard_normal((T, 2, 128)).astype(np.float32), rng.standard_normal((T, 1, 128)).astype(np.float32)
+    q[:, :, 9] = 0.5 + np.abs(q[:, :, 9])
+    if what == "one_of_each":
+        k[T // 2, 0, 3], k[T // 2 + 40, 0, 7], k[T // 3, 0, 9] = np.inf, -np.inf, -np.inf
+    elif what == "later_nan":
+        k[T - 70, 0, 3] = np.nan
+    elif what == "most_without_weight":
+        k[rng.permutation(T)[:2 * T // 3], 0, 9] = -np.inf       # more keys wanted than weigh anything
+    else:
+        # the same with finite scores, of at most 9000: fp32 rounds them by 5e-4, a weight by 5e-4 / sqrt(128) = 4e-5
+        k[rng.permutation(T)[:2 * T // 3], 0, 9] = -3000
+    wl.q, wl.k = bf16_bits_from_f32(q), bf16_bits_from_f32(k)
+    budgets = [1, 40, T // 2, T - 1]
+    _, got = _run(wl, budgets)
+    with np.errstate(invalid="ignore"):
+        want = orc.token_recovery(wl.q, wl.k, wl.cu_seqlens, budgets)
+    number = ~np.isnan(want)
+    assert number.mean() > 0.4
+    np.testing.assert_allclose(got[number], want[number], rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
+
+
 def test_is_deterministic():
     wl = make_workload(1, seqlens=[3000])
     run, a = _run(wl, [256])
