@@ -15,6 +15,8 @@
 // block size, in one or a few sweeps over their keys; the scores are recomputed in every sweep (the
 // triangle of scores does not fit anywhere).  The longest are launched first, so that the tail of
 // the launch is short.
+#include <cfloat>
+
 #include "attn_common.h"
 
 namespace shplb {
@@ -240,7 +242,8 @@ __global__ __launch_bounds__(256, 2) void mass_kernel(SeqMeta meta, Strides st, 
   };
   row.sweep(0, n_tiles, QueryRun::kOne, true, [&](int x, QueryRun::Scores& sc) {
     const int j = x / kTiles;
-    if (x == 0) ref = largest(sc);                            // every query sees its sequence's first key
+    // every query sees its sequence's first key; a tile whose scores are all -inf weighs nothing against any reference
+    if (x == 0) ref = fmaxf(largest(sc), -FLT_MAX);
     float sum = tile_sum(sc);
     if (__any(!(sum <= kSumRange))) {
       const float raised = fmaxf(ref, largest(sc));

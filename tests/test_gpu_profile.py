@@ -128,3 +128,25 @@ def test_block_mass_scores_far_above_those_of_the_first_keys(block):
     wl.k = bf16_bits_from_f32(k)
     rows = sorted({h * nb + i for h in range(2) for i in (0, 36, 37, 38, 99, 100, 101, 127, 128, 129)})
     _profile(wl, rows=rows)
+
+
+@pytest.mark.parametrize("block", [64, 128])
+def test_block_mass_where_the_first_keys_weigh_nothing(block):
+    # scores of -inf for all of the first tile and more: the reference exponent has to come from later keys.
+    # (Query blocks of the first 70 tokens see no key with a weight: no numbers, in the oracle either.)
+    from harness import DevicePass
+    T = 5 * block + 9
+    wl = make_custom([T], 2, 1, block, [2, 2], seed=8, name="mass_first_keys_%d" % block)
+    rng = np.random.default_rng(8)
+    q, k = rng.standard_normal((T, 2, 128)).astype(np.float32), rng.standard_normal((T, 1, 128)).astype(np.float32)
+    q[:, :, 9] = 0.5 + np.abs(q[:, :, 9])
+    k[:70, 0, 9] = -np.inf
+    wl.q, wl.k = bf16_bits_from_f32(q), bf16_bits_from_f32(k)
+    run = DevicePass(wl)
+    run.mass_step()
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        want = orc.block_mass(wl.q, wl.k, wl.cu_seqlens, wl.block)[0]
+    got, number = run.mass_host()[0], ~np.isnan(want)
+    assert number[:, 2:].any(axis=2).all()
+    np.testing.assert_allclose(got[number], want[number], rtol=MASS_RTOL, atol=MASS_ATOL)
