@@ -328,7 +328,8 @@ void attn_pipe_kernel(AttnArgs) {
     // that the scalar-memory latency never sits in front of a copy
     const ConstInts sel = (ConstInts)uintptr_t(reload(args)->sel_idx + it.sel_begin);
     auto block_of = [&](int b) { return sel[min(KS > 1 ? b * KS + grp : b, it.n_sel - 1)]; };
-    // a group whose blocks ran out repeats the last one with every key masked
+    // a group whose blocks ran out repeats the last one with every key masked and leaves its values out
+    // (an infinite one, with a probability of zero, would be NaN)
     auto beyond = [&](int b) { return KS > 1 && b * KS + grp >= it.n_sel; };
     int j0 = it.first_block, j1 = KS > 1 ? block_of(1) : it.second_block;
 
@@ -412,12 +413,12 @@ void attn_pipe_kernel(AttnArgs) {
 
     // One step: tile t's softmax and PV from sc_cur, tile t+1's scores into sc_nxt.
     //   stage: t & 1.  jk: block of tile t+2 (kMid only).  mask: tile t+1 is (in) the diagonal block, or `all`
-    //   of its keys are to be masked.
+    //   of its keys are to be masked.  drop: tile t belongs to a repeated block.
     // kPlace: kMid inside the item; kRecord the last step but one, kFinal the last one.
     enum { kMid, kRecord, kFinal };
     const Item cur = it;                             // (the last step starts the next item)
     auto step = [&](auto place_c, auto stage_c, f32x16 (&sc_cur)[MT], f32x16 (&sc_nxt)[MT], int jk, bool mask, bool all,
-                    bool ask_now) {
+                    bool drop, bool ask_now) {
       constexpr int kPlace = decltype(place_c)::value, kStage = decltype(stage_c)::value;
       constexpr bool kHasNext = kPlace != kFinal;
       // Take turns with the other workgroup of this compute unit (see kTurnShift).
@@ -520,6 +521,7 @@ void attn_pipe_kernel(AttnArgs) {
       __builtin_amdgcn_sched_barrier(0);
 
       // ---- O^T += V(t)^T P(t)^T: its MFMAs back to back
+      if (KS > 1 && drop) return;
 #pragma unroll
       for (int gi = 0; gi < kPV; ++gi) {
         if (gi + kLook < kPV) vf[gi + kLook] = read_v(vc, gi + kLook);
@@ -537,13 +539,14 @@ void attn_pipe_kernel(AttnArgs) {
     int b = 0;
     for (; b + 1 < n_pairs; ++b) {
       const int j2 = block_of(b + 2);
-      step(integral_constant<int, kMid>{}, even, sc_a, sc_b, j1, j0 == i || beyond(b), beyond(b), false);
-      step(integral_constant<int, kMid>{}, odd, sc_b, sc_a, j1, j1 == i || beyond(b + 1), beyond(b + 1), b + 2 == n_pairs);
+      step(integral_constant<int, kMid>{}, even, sc_a, sc_b, j1, j0 == i || beyond(b), beyond(b), beyond(b), false);
+      step(integral_constant<int, kMid>{}, odd, sc_b, sc_a, j1, j1 == i || beyond(b + 1), beyond(b + 1), beyond(b),
+           b + 2 == n_pairs);
       j0 = j1;
       j1 = j2;
     }
-    step(integral_constant<int, kRecord>{}, even, sc_a, sc_b, 0, j0 == i || beyond(b), beyond(b), false);
-    step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false, false);
+    step(integral_constant<int, kRecord>{}, even, sc_a, sc_b, 0, j0 == i || beyond(b), beyond(b), beyond(b), false);
+    step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false, beyond(b), false);
 
     // ---- the next item starts before this one's results are written
     float l_tot = pair_sum(l_run);

@@ -6,6 +6,7 @@ import pytest
 
 from workloads import make_custom
 
+from harness import DevicePass
 from test_gpu_parity import _split_against_whole_rows, full_parity
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +39,19 @@ def test_rows_shared_by_two_groups_of_waves(n_blocks, budgets):
     # even numbers, ragged tails; 520 rows go the other way.
     wl = make_custom([64 * n_blocks - 27], len(budgets), 1, 64, budgets, seed=500 + n_blocks, name="groups_%d" % n_blocks)
     full_parity(wl)
+
+
+@pytest.mark.parametrize("n_blocks", [1, 5, 6])
+def test_groups_of_waves_keep_infinite_values_apart(n_blocks):
+    # The last block's first token has an infinite value in one dim: every query of that block sees it, and no
+    # other dim or block may be touched by it.  A group of waves whose blocks ran out (rows of an odd number of
+    # blocks) must not multiply it by zero.
+    T = 64 * n_blocks
+    wl = make_custom([T], 2, 1, 64, [999, 999], seed=520 + n_blocks, name="infinite_value_%d" % n_blocks)
+    wl.v[T - 64, 0, 5], wl.v[T - 64, 0, 6] = 0x7f80, 0xff80            # bf16 infinities
+    print("case", wl.name, flush=True)
+    out = DevicePass(wl).run_all().out_host()
+    assert (out[T - 64:, :, 5] == np.inf).all() and (out[T - 64:, :, 6] == -np.inf).all()
+    rest = np.ones(out.shape, bool)
+    rest[T - 64:, :, 5:7] = False
+    assert np.isfinite(out[rest]).all()
