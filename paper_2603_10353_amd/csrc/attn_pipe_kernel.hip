@@ -68,6 +68,7 @@ struct AttnArgs {
   float* lse;
   shplb_wg_stats* stats;
   int32_t n_stats;
+  int32_t rows, rows_per_die, compute_units;   // how rows without queues are dealt, see row_item()
   float scale_log2;
   int64_t total_tokens;
   Strides st;
@@ -98,13 +99,30 @@ struct Item {
   int64_t sel_begin;
 };
 
-// The item of workgroup b in a launch that gives every row a workgroup of its own: die b % 8 (where the
-// dispatcher puts it) takes a run of consecutive rows, i.e. few K/V streams.  False: no row.
+// The item of workgroup b in a launch that gives every row a workgroup of its own.  False: no row.
+// The dispatcher puts workgroup b on die b % 8 and, one lap of all compute units after the other, beside workgroup
+// b - (compute units).
+// * No more rows than compute units: die x takes a run of consecutive rows (rows_per_die), i.e. few K/V streams.
+// * More: rows that lie next to each other (of one head, all long or all short) go to different compute units and
+//   dies, and every other lap runs backwards, so that the long end of a head mostly meets the short end of another.
+//   In runs, the long rows of a dense head shared few compute units.  The attention step for 4/2 heads x 16K with
+//   one dense head takes 257 us (in runs 335, with the ordering launch 266), for 2/1 x 32K 507 (782, 517), 8/2 x 8K
+//   131 (152, 140).  Of some 200 shapes of 256 to 1024 rows one is slower than with the ordering launch: two dense
+//   heads of five of 200 64-token blocks, whose long ends meet, 283 against 261.  Runs are the faster ones for up
+//   to one row per compute unit (2K x 8 heads, 64-token blocks: 25.2 against 26.5) and for equally short rows
+//   (32/8 heads x 2K at budgets of 2 to 4 blocks 21 against 23).
 __device__ __forceinline__ bool row_item(ArgsPtr a, int b, Item& it) {
-  const int n_seq = a->meta.n_seq, hq = a->meta.n_q_heads;
-  const int rows = a->meta.blk_begin[n_seq] * hq, per_die = (rows + kXcds - 1) / kXcds;
-  const int row = (b % kXcds) * per_die + b / kXcds;
-  if (b / kXcds >= per_die || row >= rows) return false;
+  const int n_seq = a->meta.n_seq, hq = a->meta.n_q_heads, rows = a->rows, per_die = a->rows_per_die;
+  int row = (b % kXcds) * per_die + b / kXcds;
+  bool any = b / kXcds < per_die && row < rows;
+  if (per_die == 0) {
+    int begin = 0, odd = 0;                          // first row of the lap
+    for (; begin + a->compute_units <= b; begin += a->compute_units) odd ^= 1;
+    const int place = b - begin, n = min(a->compute_units, rows - begin);
+    row = begin + (odd ? n - 1 - place : place);
+    any = place < n;
+  }
+  if (!any) return false;
   // sequence: how many of them end at or before the row (one lane per sequence)
   const int lane = threadIdx.x & 63;
   const int s = __builtin_popcountll(__ballot(lane < n_seq && row >= a->meta.blk_begin[min(lane, n_seq - 1) + 1] * hq));
@@ -721,7 +739,7 @@ void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
 
 AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capacity) {
   AttentionPlan plan;
-  const int cus = n_wg / (g.meta.block == 64 ? 4 : 2);
+  const int cus = plan.compute_units = n_wg / (g.meta.block == 64 ? 4 : 2);
   // A launch of few 64-token rows leaves half of every compute unit's SIMDs without a wave (a row is two
   // waves), and its length is that of the chain of tiles of the longest row: two groups of waves per row
   // halve that chain.  256 rows of up to 16 blocks 24.6 -> 18.1 us, 512 rows 28.2 -> 21.6 us, 64 rows of up to
@@ -748,6 +766,9 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.lse = lse;
   args.stats = stats;
   args.n_stats = n_wg;
+  args.rows = int32_t(g.rows);
+  args.rows_per_die = g.rows <= plan.compute_units ? int32_t((g.rows + kXcds - 1) / kXcds) : 0;
+  args.compute_units = plan.compute_units;
   args.scale_log2 = g.scale * 1.4426950408889634f;
   args.total_tokens = g.total_tokens;
   args.st = g.st;

@@ -145,6 +145,7 @@ struct SplitBuffers {
 struct AttentionPlan {
   int32_t key_groups;   // groups of waves of a workgroup that share a row
   int32_t grid;         // workgroups
+  int32_t compute_units;
   bool ordered;         // items come from queues; else every row has a workgroup
 };
 AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capacity);

@@ -55,3 +55,22 @@ def test_groups_of_waves_keep_infinite_values_apart(n_blocks):
     rest = np.ones(out.shape, bool)
     rest[T - 64:, :, 5:7] = False
     assert np.isfinite(out[rest]).all()
+
+
+@pytest.mark.parametrize("heads, block, n_blocks, budgets", [
+    ((8, 2), 128, 64, [64, 2, 2, 2, 2, 26, 2, 2]), ((8, 2), 128, 62, [62, 62, 2, 2, 2, 2, 2, 2]),
+    ((4, 2), 128, 128, [128, 4, 4, 4]), ((2, 1), 64, 256, [256, 8]), ((6, 1), 64, 170, [170, 170, 2, 2, 2, 2])])
+def test_few_long_rows_are_spread_over_the_compute_units(heads, block, n_blocks, budgets):
+    # Launches of one to four rows per compute unit, without queues: a dense head or two, and no compute unit may be
+    # given much more than the longest row (the least possible).
+    hq, hkv = heads
+    wl = make_custom([block * n_blocks - 5], hq, hkv, block, budgets, seed=540 + n_blocks, name="spread_%d" % n_blocks)
+    run = DevicePass(wl).run_all()
+    st = run.stats_host()
+    assert run.rows <= run.n_wg and st["n_items"].sum() == run.rows and st["cost_blocks"].sum() == run.sel_ptr_host[-1]
+    load = {}
+    for r in st[st["n_items"] > 0]:
+        cu = (int(r["xcc_id"]), int(r["cu_id"]))
+        load[cu] = load.get(cu, 0) + int(r["cost_blocks"])
+    print("case", wl.name, "rows", run.rows, "compute units", len(load), "heaviest", max(load.values()), flush=True)
+    assert max(load.values()) <= 1.3 * n_blocks
