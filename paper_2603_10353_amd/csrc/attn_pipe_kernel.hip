@@ -671,12 +671,13 @@ void attn_pipe_kernel(AttnArgs) {
       if (a->lse != nullptr && hi == 0 && grp == 0 && q_in < n_valid)
         a->lse[int64_t(cur.head) * a->total_tokens + q0 + q_in] = (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
       uint16_t* dst = a->out + int64_t(q0 + min(q_in, n_valid - 1)) * a->st.q_t + int64_t(cur.head) * a->st.q_h + 8 * hi;
+      constexpr int kRuns = 2, kStores = 4 * kRuns;    // 16-byte stores of a lane, of all four dim tiles
       auto store_rows = [&](bool valid) {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
           if (own(dt))
 #pragma unroll
-            for (int rp = 0; rp < 2; ++rp) {
+            for (int rp = 0; rp < kRuns; ++rp) {
               const int ra = 8 * rp, rb = 8 * rp + 4;      // first accumulator of the even and of the odd run
               uint32_t e0 = pack_bf16(acc_o[dt][ra] * inv, acc_o[dt][ra + 1] * inv);
               uint32_t e1 = pack_bf16(acc_o[dt][ra + 2] * inv, acc_o[dt][ra + 3] * inv);
@@ -687,11 +688,16 @@ void attn_pipe_kernel(AttnArgs) {
               if (valid) *reinterpret_cast<u32x4*>(dst + 32 * dt + 16 * rp) = u32x4{e0, e1, o0, o1};
             }
       };
-      // The next item's copies and Q loads were issued before these stores and memory operations of a wave
-      // complete in order: with at most the stores outstanding the copies have landed.
+      // The next item's copies and Q loads were issued before these stores, and the vector memory operations of
+      // a wave are reported complete in the order they were issued, loads and stores alike (LLVM's AMDGPU usage
+      // guide, memory model of gfx6 to gfx9 and of gfx942; flat accesses to LDS are the exception, and none is under
+      // way here): with at most the stores outstanding the copies have landed.  For that the stores must stay in
+      // front of the wait.
       if (KS == 1 && wave * 32 + 32 <= n_valid) {
         store_rows(true);
-        wait_vmem_but(std::integral_constant<int, 8>{});
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        wait_vmem_but(std::integral_constant<int, kStores>{});
       } else {
         store_rows(q_in < n_valid);
         wait_vmem_all();

@@ -247,8 +247,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 
   };
 
   // A finished tile is written out one iteration later, behind the barrier: the wait at
-  // the top of an iteration covers every memory operation of the wave (a wave's loads and
-  // stores need not complete in order, so a count would not do), and stores issued just
+  // the top of an iteration covers every memory operation of the wave (how many stores a lane
+  // issued depends on its row, so there is no count to wait for), and stores issued just
   // before it would make each iteration pay their full latency.
   f32x16 pend;
   int pend_j0 = -1;
