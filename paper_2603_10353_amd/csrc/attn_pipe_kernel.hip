@@ -275,6 +275,10 @@ void attn_pipe_kernel(AttnArgs) {
     int pos = begin + int(blockIdx.x / kXcds);
     if (pos >= args->wq.queue_begin[x + 1]) pos = help();
     have = pos >= 0 && read_record(pos, record_words(pos), it);
+    while (!have && pos >= 0) {                      // rows without a block (at the end of their queues)
+      pos = help();
+      have = pos >= 0 && read_record(pos, record_words(pos), it);
+    }
     home_open = true;
     home_begin = __builtin_amdgcn_readfirstlane(args->wq.queue_begin[home]);
     home_size = uint32_t(__builtin_amdgcn_readfirstlane(args->wq.queue_begin[home + 1]) - home_begin);
@@ -618,13 +622,14 @@ void attn_pipe_kernel(AttnArgs) {
       __syncthreads();                               // the stages are free again
     }
     home_open = pos != kHelp;
-    if (KS > 1 || (more && pos == kHelp)) {
+    if (KS > 1 || (more && it.n_sel <= 0)) {
       if (KS == 1) __syncthreads();                  // every wave is done with the stages
-      if (more && pos == kHelp) {
+      have = KS > 1 && pos >= 0 && read_record(pos, words, it);
+      while (more && !have) {                        // (again after a row without a block)
         pos = help();
-        words = record_words(pos);
+        if (pos < 0) break;
+        have = read_record(pos, record_words(pos), it);
       }
-      have = more && pos >= 0 && read_record(pos, words, it);
       if (have) start_item();
     } else {
       have = more && it.n_sel > 0;

@@ -3,9 +3,12 @@ K/V streams than dies (a stream is spread over several dies), and pieces of spli
 Every row must be dealt exactly once and the attention output match the oracle."""
 import numpy as np
 import pytest
+import torch
 
+from oracle import shplb_oracle as orc
 from workloads import make_custom
 
+from checks import compare_output
 from harness import DevicePass
 from test_gpu_parity import _split_against_whole_rows, full_parity
 
@@ -74,3 +77,25 @@ def test_few_long_rows_are_spread_over_the_compute_units(heads, block, n_blocks,
         load[cu] = load.get(cu, 0) + int(r["cost_blocks"])
     print("case", wl.name, "rows", run.rows, "compute units", len(load), "heaviest", max(load.values()), flush=True)
     assert max(load.values()) <= 1.3 * n_blocks
+
+
+def test_rows_without_a_block_do_not_end_a_workgroup():
+    # Seven of eight heads select one block for one row and nothing for the others: their output stays as it
+    # is, and the workgroups that are dealt such a row go on and help with the eighth head's.
+    nb, block, window = 256, 128, 40
+    wl = make_custom([block * nb], 8, 8, block, [2] * 8, seed=90, name="empty_rows")
+    run = DevicePass(wl)
+    lists = [list(range(max(0, i - window + 1), i + 1)) if h == 3 else [0] if i == 0 else [] for h in range(8) for i in range(nb)]
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    idx = np.concatenate([np.asarray(x, np.int32) for x in lists])
+    print("case", wl.name, flush=True)
+    run.attn_step(torch.from_numpy(ptr).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"))
+    torch.cuda.synchronize()
+    st = run.stats_host()
+    assert st["n_items"].sum() == nb + 7 and st["cost_blocks"].sum() == len(idx)
+    assert (st["n_items"] > 0).sum() >= 160                            # not the 64 of one die alone and seven more
+    rows = [r for r in range(8 * nb) if len(lists[r]) and (r % nb < 3 or r % 37 == 0)]
+    out_o, lse_o = orc.sparse_attention(wl.q, wl.k, wl.v, wl.cu_seqlens, block, ptr, idx, None, rows)
+    compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
+    out = run.out.view(nb, block, 8, 128)
+    assert not out[1:, :, [0, 1, 2, 4, 5, 6, 7]].any()
