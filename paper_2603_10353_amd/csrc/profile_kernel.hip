@@ -432,8 +432,9 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   };
   // least useful width of a bin around scores lo .. hi: half the distance of neighbouring floats, or what
   // changes a weight by 2^-26 of itself
+  const float unit = 1.0f / scale_log2;                       // scores that a weight halves over
   auto finest = [&](float lo, float hi) {
-    const float least = fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 0x1p-26f / scale_log2);
+    const float least = fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 0x1p-26f * unit);
     return __builtin_amdgcn_fmed3f(least, 0x1p-120f, 0x1p119f);
   };
   auto finite = [](float s) { return __builtin_amdgcn_classf(s, 0x1f8); };   // neither an infinity nor a NaN
@@ -481,13 +482,25 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   // ---- 1. where to look
   float lo = INFINITY, hi = -INFINITY;
   row.sweep(0, n_range, stride, n_sample == 0, [&](int, QueryRun::Scores& sc) {
+    float top = sc[0][0], low = top;
 #pragma unroll
-    for (int r = 0; r < 16 * MT; ++r) {
-      const float s = sc[r / 16][r % 16];
-      const bool counts = finite(s);
-      hi = fmaxf(hi, counts ? s : -INFINITY);
-      lo = fminf(lo, counts ? s : INFINITY);
+    for (int r = 1; r < 16 * MT; ++r) {
+      top = fmaxf(top, sc[r / 16][r % 16]);
+      low = fminf(low, sc[r / 16][r % 16]);
     }
+    if (__any(!finite(top) || !finite(low))) {                // (masked keys among them)
+      top = -INFINITY;
+      low = INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16 * MT; ++r) {
+        const float s = sc[r / 16][r % 16];
+        const bool counts = finite(s);
+        top = fmaxf(top, counts ? s : -INFINITY);
+        low = fminf(low, counts ? s : INFINITY);
+      }
+    }
+    hi = fmaxf(hi, top);
+    lo = fminf(lo, low);
   });
   hi = pair_max(hi);
   lo = -pair_max(-lo);
@@ -566,7 +579,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
         find(want, bin, above, inside);
         // beyond the interval: most often just beyond
         const float reach = (tries == 0 ? 2.0f : 32.0f) * kInner * bin_w;
-        const float nothing = fmaxf(top_score - kNoWeight / scale_log2, -kFar);   // no weight from here down
+        const float nothing = fmaxf(top_score - kNoWeight * unit, -kFar);   // no weight from here down
         if (!finite(top_score)) {
           open = false;                                       // the weights are no numbers, nor will the result be one
         } else if (bin == 0) {
