@@ -118,10 +118,9 @@ def test_config4_varlen_batch_quarter_scale():
 
 def test_config4_varlen_batch_full():
     # 8K + 24K + 64K + 128K tokens in one launch: 57 344 rows of four sequences go through the
-    # five-launch ordering (two counting sorts with multi-sequence row decoding) into one
-    # persistent attention launch.  Scores and selections on every row; attention on sampled
-    # rows that include the costliest and the last row of every sequence; then every output row
-    # through the constant-value check.
+    # ordering kernel into one persistent attention launch.  Scores and selections on every row;
+    # attention on sampled rows that include the costliest and the last row of every sequence; then
+    # every output row through the constant-value check.
     run, imb = _run_case(make_workload(4), 48, seed=5)
     assert imb < 0.05
     _constant_value_pass(run)
@@ -140,9 +139,9 @@ def test_block64_32k_layer():
 
 
 def test_three_sequences_above_the_single_workgroup_ordering():
-    # 17 024 rows (> 16 384, where the single-workgroup ordering ends) from three ragged sequences
-    # of a 64/16-head layer: the five-launch ordering with multi-sequence decoding at a size where
-    # the sample can be dense (1 row in 70) and the oracle still finishes in seconds.
+    # 17 024 rows from three ragged sequences of a 64/16-head layer: a multiple of what the ordering kernel's
+    # threads hold at once, at a size where the sample can be dense (1 row in 70) and the oracle still
+    # finishes in seconds.
     from workloads import make_custom
     rng = np.random.default_rng(123)
     budgets = rng.choice([2, 3, 5, 9, 17, 40, 999], size=3 * 64)

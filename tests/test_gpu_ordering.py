@@ -1,5 +1,7 @@
-"""The ordering kernel where its cases change: more (sequence, head) pairs than one batch holds, fewer
-K/V streams than dies (a stream is spread over several dies), and pieces of split rows in both layouts.
+"""How the rows of an attention launch are dealt to its workgroups, where the cases change.  The ordering kernel:
+more (sequence, head) pairs than one batch holds, fewer K/V streams than dies (a stream is spread over several
+dies), rows without a block, and pieces of split rows in both layouts.  Launches of at most two 64-token or 128-token
+rows per compute unit (four for 64-token rows of more than two) have no queues: runs of rows, or laps.
 Every row must be dealt exactly once and the attention output match the oracle."""
 import numpy as np
 import pytest
@@ -17,6 +19,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_seq, heads", [(64, (40, 8)), (1, (6, 1)), (1, (6, 3)), (1, (10, 5)), (2, (4, 2)), (7, (3, 1)), (9, (3, 1))])
 def test_every_row_is_dealt_once(n_seq, heads):
+    # the first shape through the ordering kernel (2800 rows and more), the others without queues: up to 140 rows
+    # in runs, 315 and 393 in laps
     hq, hkv = heads
     rng = np.random.default_rng(100 * n_seq + hq)
     top = 90 if n_seq == 64 else 64 * 23
@@ -26,6 +30,30 @@ def test_every_row_is_dealt_once(n_seq, heads):
     run = full_parity(wl)
     st = run.stats_host()
     assert st["n_items"].sum() == run.rows and st["cost_blocks"].sum() == run.sel_ptr_host[-1]
+
+
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("seqlens, heads", [
+    ([230], (6, 1)), ([181], (6, 3)), ([109], (10, 5)), ([70, 67], (8, 4)), ([60, 17, 3, 41, 22, 30, 9], (6, 1)),
+    ([30, 44, 7, 21, 50, 13, 36, 5, 19], (5, 1)), ([131], (8, 2)), ([40, 33, 67], (8, 2)), ([1, 260], (4, 4))])
+def test_every_row_is_dealt_once_from_queues(block, seqlens, heads):
+    # more rows than workgroups: 1, 3, 5, 4 x 2, 7, 9, 2, 6 and 8 K/V streams on eight dies, lengths that leave every
+    # remainder over the dies of a stream, sequences of unequal length; short budgets keep the oracle quick
+    hq, hkv = heads
+    rng = np.random.default_rng(sum(seqlens) + hq + block)
+    lens = [block * nb - int(rng.integers(0, block)) for nb in seqlens]
+    budgets = rng.choice([2, 3, 5, 11], size=len(lens) * hq).tolist()
+    wl = make_custom(lens, hq, hkv, block, budgets, seed=430 + len(lens), name="queues_%d_%d_%d" % (len(lens), hq, hkv))
+    run = DevicePass(wl).run_all()
+    assert run.rows > run.n_wg                       # (and so more than the launch has workgroups, of either kind)
+    rows = sorted({0, run.rows - 1} | set(rng.integers(0, run.rows, size=120).tolist()))
+    print("case", wl.name, "block", block, "rows", run.rows, "workgroups", run.n_wg, flush=True)
+    out_o, lse_o = orc.sparse_attention(wl.q, wl.k, wl.v, wl.cu_seqlens, block, run.sel_ptr_host, run.sel_idx_host(), None, rows)
+    compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
+    st = run.stats_host()
+    assert st["n_items"].sum() == run.rows and st["cost_blocks"].sum() == run.sel_ptr_host[-1]
+    # every row, by its denominators: those of whole causal rows are never zero, and the buffer was
+    assert (run.lse != 0).all()
 
 
 @pytest.mark.parametrize("heads", [(2, 1), (8, 8)])

@@ -232,7 +232,7 @@ def test_caller_supplied_selection_sink_and_window(block):
 
 def test_whole_path_in_a_hip_graph():
     # The three entry points captured into one HIP graph (kernel launches only, no memset nodes: the
-    # ordering kernels clear their own counters) and replayed several times with eager work
+    # ordering kernel clears its own counters) and replayed several times with eager work
     # and synchronisations in between; every replay must reproduce the eager result bit for bit.
     wl = make_workload(1, seqlens=[128 * 37 + 5])
     run = _gpu()(wl).run_all()                       # eager pass: reference, and warms up every lazy init

@@ -36,12 +36,15 @@ def _both_ways(wl):
 
 
 def test_static_scratch_matches_workspace_twice_second_smaller():
-    # first: 20 480 rows of two sequences (five-launch ordering); second: 288 rows (single-workgroup
-    # ordering) with block 64, on whatever the first call left in the array
+    # first: 20 480 rows of two sequences; second: 1072 rows with block 64, whose shorter queues lie on those
+    # that the first call left in the array; third: 288 rows, so few that the launch has no queues
     rng = np.random.default_rng(7)
     big = make_custom([128 * 400 + 9, 128 * 239 + 100], 32, 8, 128, rng.choice([2, 3, 6, 11, 30, 999], size=64),
                       seed=301, name="static_big")
     _both_ways(big)
+    fewer = make_custom([64 * 130 + 7, 64 * 3], 8, 4, 64, [2, 4, 999, 7, 3, 5, 9, 2] * 2, seed=303, name="static_fewer")
+    run = _both_ways(fewer)
+    assert run.rows == 1072 and run.rows > run.n_wg            # more rows than workgroups: from queues
     small = make_custom([64 * 35 + 7, 64], 8, 4, 64, [2, 4, 999, 7, 3, 5, 9, 2], seed=302, name="static_small")
     _both_ways(small)
     # and the first size again after the small one
