@@ -24,7 +24,10 @@
  *   - Device work is enqueued on `stream` (a hipStream_t passed as void*, NULL =
  *     the default stream) and is asynchronous; outputs are bit-identical from run
  *     to run (each work item owns its output rows; scheduling order never changes
- *     results).
+ *     results).  With 64-token blocks the order in which an attention row's sums are
+ *     taken depends on the size of the call: up to two rows per compute unit of the
+ *     device (512 rows), two groups of waves share a row and add up at the end, so a
+ *     sequence alone and inside a larger call agree up to rounding.
  *   - Tensors are token-major: Q is [T, n_q_heads, head_dim] bf16 with element
  *     strides (q_stride_t, q_stride_h, 1); K and V are [T, n_kv_heads, head_dim]
  *     bf16 with strides (kv_stride_t, kv_stride_h, 1).  T = cu_seqlens[n_seq].
@@ -78,7 +81,8 @@ typedef struct {
   const int32_t* kv_head_of;     /* host [n_q_heads], or NULL: see below */
 } shplb_problem;
 
-/* Per-workgroup record written by shplb_sparse_attn_prefill when asked for. */
+/* Per-workgroup record written by shplb_sparse_attn_prefill when asked for (all zeros where the
+ * launch had fewer workgroups than shplb_sched_num_workgroups()). */
 typedef struct {
   uint32_t xcc_id;        /* accelerator die the workgroup ran on */
   uint32_t cu_id;         /* (shader engine << 8) | compute unit inside the die */
@@ -150,7 +154,8 @@ SHPLB_API int32_t shplb_select_topk_per_head(const shplb_problem* p, const float
  * ordered by descending selected-block count and handed to persistent
  * workgroups through one queue per accelerator die with an atomic ticket each:
  * the greedy rule of Section 3.3 (largest first, to whichever worker is free
- * first) applied to compute units.
+ * first) applied to compute units.  A launch of no more rows than workgroups gives
+ * every row a workgroup of its own and has no queues.
  *   sel_ptr/sel_idx: device CSR; every row's list must be ascending, within
  *   [0, i], and contain i (lists written by shplb_select_topk_per_head are).
  *   out: device bf16 [T, n_q_heads, head_dim], strides as Q.
@@ -242,7 +247,8 @@ SHPLB_API int32_t shplb_recovery_curves(const shplb_problem* p, const float* mas
  * found by counting the scores in the bins of an interval that holds it, ties at the
  * k-th place counted at that weight), fp32 softmax statistics, bf16 MFMA products; a
  * dense pass of one sweep over the causal triangle and one more per budget (more where
- * scores crowd): an offline tool.
+ * scores crowd): an offline tool.  A score of -inf weighs nothing; a query that sees a
+ * score of +inf or NaN, or none above -inf, and more keys than the budget gets NaN.
  *   q, k: device bf16.  budgets: host [n_budgets], tokens, each >= 1;
  *   n_budgets: 1..SHPLB_MAX_TOKEN_BUDGETS.
  *   recovery_out: device fp32 [n_budgets][n_q_heads][T], T = cu_seqlens[n_seq].

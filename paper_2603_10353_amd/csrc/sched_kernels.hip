@@ -24,6 +24,9 @@
 // last combines them (count_piece() and merge_row() in attn_common.h).  Slots and counter
 // entries are handed out in the same arbitrary order; what is computed does not depend on it.
 //
+// Launches without splitting that have no more rows than workgroups skip all this: see row_item() in
+// attn_pipe_kernel.hip.
+//
 // What bounds it: a chain of dependent memory round trips (geometry, row pointer, first
 // selected blocks, record) on eight compute units.  A thread works out one (sequence, head)
 // pair, a prefix sum over the pairs lies in LDS, and threads then find their rows in it by
@@ -298,7 +301,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
         if (row[u] < 0) continue;
         const int h = base + pair[u] - seq[u] * hq;
         ItemRec rec;
-        rec.row = row[u];
+        rec.unused = 0;
         rec.n_sel = n;
         rec.sel_begin = sel_begin[u];
         rec.slot = rec.first_slot = rec.split_index = -1;

@@ -83,9 +83,9 @@ int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, c
                               int32_t n_budgets, float* recovery, hipStream_t stream);
 // One work item of an attention launch: a row, or one piece of a row that was split along
 // its selected key blocks (positions [first, first + n_sel) of the row's selection).  It carries
-// everything a workgroup needs to start: sixteen words, one scalar load.
+// everything a workgroup needs to start: sixteen words, one vector load of a word per lane (read_record()).
 struct alignas(64) ItemRec {
-  int32_t row;
+  int32_t unused;
   int32_t n_sel;        // selected key blocks this item covers
   int64_t sel_begin;    // index of its first one in sel_idx
   int32_t slot;         // partial-result slot it writes, or -1: the item is the whole row and writes the output
