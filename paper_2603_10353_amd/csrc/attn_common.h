@@ -101,21 +101,19 @@ __device__ __forceinline__ void slot_store(float* p, float a, float b) {
   const uint64_t w = uint64_t(__float_as_uint(a)) | uint64_t(__float_as_uint(b)) << 32;
   __hip_atomic_store(reinterpret_cast<uint64_t*>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void slot_load(const float* p, float& a, float& b) {
-  const uint64_t w = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  a = __uint_as_float(uint32_t(w));
-  b = __uint_as_float(uint32_t(w >> 32));
+// 16-byte device-scope load.  There is no 16-byte atomic load to ask the compiler for; a buffer load with the
+// device-scope bit (sc1) is the same access, as a builtin, so that the compiler knows what is in flight.
+typedef __amdgpu_buffer_rsrc_t SlotBuffer;
+__device__ __forceinline__ SlotBuffer slot_buffer(const float* begin, int64_t floats) {
+  const uint64_t x = reinterpret_cast<uint64_t>(begin);               // the same in all lanes: said explicitly
+  const uint64_t at = uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(x)))) |
+                      uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(x >> 32)))) << 32;
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(at), 0, __builtin_amdgcn_readfirstlane(int(floats * 4)),
+                                           0x00020000);
 }
-// 16-byte device-scope load.  Issued as assembly (there is no 16-byte atomic load to ask the compiler
-// for); the data is not valid before slot_wait() has been called on it.
-__device__ __forceinline__ f32x4 slot_load16_issue(const float* p) {
-  f32x4 v;
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-// Wait for all outstanding loads; the values pass through so that no use can be scheduled above the wait.
-__device__ __forceinline__ void slot_wait(f32x4& a, f32x4& b, f32x4& c, f32x4& d) {
-  asm volatile("s_waitcnt vmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : : "memory");
+__device__ __forceinline__ f32x4 slot_load16(SlotBuffer slots, int at) {
+  constexpr int kSc1 = 1 << 4;
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slots, at * 4, 0, kSc1));
 }
 __device__ __forceinline__ void slot_store1(float* p, float a) {
   __hip_atomic_store(reinterpret_cast<uint32_t*>(p), __float_as_uint(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -194,17 +192,16 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
   // chunk e = ((wave * 4 + dt) * 4 + rq) * 64 + lane is dims 32 dt + 8 rq + 4 (lane / 32) .. +3 of query
   // 32 wave + lane % 32.  A thread owns chunks threadIdx.x + THREADS * u; a wave reads 1 KB runs.
   constexpr int kChunks = BQ * (kHeadDim / 4) / THREADS;
-  static_assert(kChunks % 4 == 0, "chunks are awaited four at a time");
   f32x4 acc[kChunks];
+  const SlotBuffer slots = slot_buffer(part_o, pieces * kSlotFloatsO);
 #pragma unroll
   for (int u = 0; u < kChunks; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   for (int c = 0; c < pieces; ++c) {
     f32x4 o[kChunks];
 #pragma unroll
     for (int u = 0; u < kChunks; ++u)
-      o[u] = slot_load16_issue(part_o + c * kSlotFloatsO + 4 * (threadIdx.x + THREADS * u));
-#pragma unroll
-    for (int u = 0; u < kChunks; u += 4) slot_wait(o[u], o[u + 1], o[u + 2], o[u + 3]);
+      o[u] = slot_load16(slots, c * int(kSlotFloatsO) + 4 * (int(threadIdx.x) + THREADS * u));
+    __builtin_amdgcn_sched_barrier(0);              // all of them in flight together
 #pragma unroll
     for (int u = 0; u < kChunks; ++u) {
       const int e = threadIdx.x + THREADS * u;
