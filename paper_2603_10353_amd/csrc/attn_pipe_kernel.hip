@@ -108,9 +108,9 @@ struct Item {
 //   In runs, the long rows of a dense head shared few compute units.  The attention step for 4/2 heads x 16K with
 //   one dense head takes 257 us (in runs 335, with the ordering launch 266), for 2/1 x 32K 507 (782, 517), 8/2 x 8K
 //   131 (152, 140).  Of some 200 shapes of 256 to 1024 rows one is slower than with the ordering launch: dense heads
-//   among five of 200 64-token blocks, whose long ends meet (two 283 against 261, three 286 against 270).  Runs are the faster ones for up
-//   to one row per compute unit (2K x 8 heads, 64-token blocks: 25.2 against 26.5) and for equally short rows
-//   (32/8 heads x 2K at budgets of 2 to 4 blocks 21 against 23).
+//   among five of 200 64-token blocks, whose long ends meet (two 283 against 261, three 286 against 270).  Runs
+//   are the faster ones for up to one row per compute unit (2K x 8 heads, 64-token blocks: 25.2 against 26.5) and
+//   for equally short rows (32/8 heads x 2K at budgets of 2 to 4 blocks 21 against 23).
 __device__ __forceinline__ bool row_item(ArgsPtr a, int b, Item& it) {
   const int n_seq = a->meta.n_seq, hq = a->meta.n_q_heads, rows = a->rows, per_die = a->rows_per_die;
   int row = (b % kXcds) * per_die + b / kXcds;
