@@ -23,14 +23,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// Chunk swizzle of row r (only r mod 16 matters): a bijection on the 16 chunk slots.
-// The two low row bits move a chunk by 64 bytes, bit 2 by 32 bytes, bit 3 by 16 bytes.
-// A transpose read of V serves 32 lanes per cycle: four consecutive key rows, 64 bytes
-// of each; with this they fall on the four different 64-byte quarters of the 64 banks
-// (SQ_LDS_BANK_CONFLICT reads zero; with rows only 32 bytes apart every such read took
-// twice as long).  Sixteen consecutive K rows read by the lanes of one operand fetch
-// cover all sixteen slots under any bijection.
-__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1); }
+// Chunk swizzle of row r (only r mod 16 matters): a bijection on the 16 chunk slots, such that (slots are 16 bytes,
+// a row is all 64 banks)
+// * a transpose read of V, which serves 32 lanes a cycle, here eight consecutive key rows and two chunks of each, and
+// * an operand read of 16 K rows x 4 chunks, which serves lanes 0-3, 12-15, 20-23, 24-27 in one cycle (rows 0-3 and
+//   12-15 of one chunk, 4-11 of the next), 4-7, 8-11, 16-19, 28-31 in another, and the upper half likewise,
+// both fall on different slots: the two low row bits move a chunk by 64 bytes, the upper two by 0, 32, 48, 16.
+// (With the upper two moving it by 0, 32, 16, 48 the K reads took 8 cycles instead of 4.)
+__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((((r >> 2) ^ (r >> 3)) & 1) << 1) | ((r >> 3) & 1); }
 
 // LDS transpose read: inside every group of 16 lanes, lane L receives element L%4 of
 // the four 8-byte pieces addressed by lanes L/4, L/4+4, L/4+8, L/4+12.
@@ -75,9 +75,15 @@ __device__ __forceinline__ void pair_values(float x, float& lower, float& upper)
   lower = a;
   upper = b;
 }
-// The raw exchange: afterwards the upper half of a holds what the lower half of b held and vice versa.
-__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+// For rows of 16 lanes: the odd rows of a trade places with the even rows of b.
+__device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void row_values(float x, float& even, float& odd) {
+  float a = x, b = x;
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+  even = a;
+  odd = b;
 }
 __device__ __forceinline__ float pair_max(float x) {
   float a, b;
@@ -87,6 +93,18 @@ __device__ __forceinline__ float pair_max(float x) {
 __device__ __forceinline__ float pair_sum(float x) {
   float a, b;
   pair_values(x, a, b);
+  return a + b;
+}
+
+// Over the four lanes n, 16 + n, 32 + n, 48 + n.
+__device__ __forceinline__ float quad_max(float x) {
+  float a, b;
+  row_values(pair_max(x), a, b);
+  return fmaxf(a, b);
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  float a, b;
+  row_values(pair_sum(x), a, b);
   return a + b;
 }
 
@@ -189,8 +207,8 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
   }
   __syncthreads();
   // pass 2: the slots hold O in the order the attention kernels keep it in registers (slot_chunk()):
-  // chunk e = ((wave * 4 + dt) * 4 + rq) * 64 + lane is dims 32 dt + 8 rq + 4 (lane / 32) .. +3 of query
-  // 32 wave + lane % 32.  A thread owns chunks threadIdx.x + THREADS * u; a wave reads 1 KB runs.
+  // chunk e = ((wave * 2 + qg) * 8 + dt) * 64 + lane is dims 16 dt + 4 (lane / 16) .. +3 of query
+  // 32 wave + 16 qg + lane % 16.  A thread owns chunks threadIdx.x + THREADS * u; a wave reads 1 KB runs.
   constexpr int kChunks = BQ * (kHeadDim / 4) / THREADS;
   f32x4 acc[kChunks];
   const SlotBuffer slots = slot_buffer(part_o, pieces * kSlotFloatsO);
@@ -205,15 +223,15 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
 #pragma unroll
     for (int u = 0; u < kChunks; ++u) {
       const int e = threadIdx.x + THREADS * u;
-      const float w = lds_w[c * BQ + 32 * (e >> 10) + (e & 31)];
+      const float w = lds_w[c * BQ + 16 * (e >> 9) + (e & 15)];
       acc[u] += w * o[u];
     }
   }
 #pragma unroll
   for (int u = 0; u < kChunks; ++u) {
     const int e = threadIdx.x + THREADS * u;
-    const int q_in = 32 * (e >> 10) + (e & 31);
-    const int d = 32 * ((e >> 8) & 3) + 8 * ((e >> 6) & 3) + 4 * ((e >> 5) & 1);
+    const int q_in = 16 * (e >> 9) + (e & 15);
+    const int d = 16 * ((e >> 6) & 7) + 4 * ((e >> 4) & 3);
     if (q_in >= n_valid) continue;                  // padding of a ragged last block
     u32x2 w2;
     w2.x = pack_bf16(acc[u].x, acc[u].y);
@@ -222,10 +240,10 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
   }
 }
 
-// Where lane `lane` of wave `wave` keeps its four accumulator values rq of dim tile dt in a slot: the
+// Where lane `lane` of wave `wave` keeps its four accumulator values of query group qg and dim tile dt in a slot: the
 // 64 lanes of a wave write one run of 1 KB (full cache lines, which write-through stores need).
-__device__ __forceinline__ int slot_chunk(int wave, int dt, int rq, int lane) {
-  return 4 * ((((wave * 4 + dt) * 4 + rq) << 6) + lane);
+__device__ __forceinline__ int slot_chunk(int wave, int qg, int dt, int lane) {
+  return 4 * ((((wave * 2 + qg) * 8 + dt) << 6) + lane);
 }
 
 __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {

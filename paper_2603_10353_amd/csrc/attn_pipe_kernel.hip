@@ -4,9 +4,9 @@
 // Persistent workgroups draw items from cost-descending queues through atomic tickets; a launch of no
 // more rows than workgroups has no queues (wq.items is null): every row gets a workgroup.
 //
-// Tiling (wave64, v_mfma_f32_32x32x16_bf16), for blocks of BQ = 128 or 64 tokens:
-//   * a wave owns 32 query rows and keeps Q as MFMA B-operands in registers; a query block is
-//     BQ/32 waves.  Block 128: 4 waves, two workgroups per compute unit; block 64: 2 waves, four
+// Tiling (wave64, v_mfma_f32_16x16x32_bf16), for blocks of BQ = 128 or 64 tokens:
+//   * a wave owns 32 query rows, in two groups of 16, and keeps Q as MFMA B-operands in registers; a query
+//     block is BQ/32 waves.  Block 128: 4 waves, two workgroups per compute unit; block 64: 2 waves, four
 //     workgroups per compute unit.  Either way every SIMD holds two waves of different
 //     workgroups, each with 256 registers, and one wave's softmax VALU work overlaps the other's
 //     MFMAs;
@@ -15,25 +15,39 @@
 //     staging registers, no LDS store instructions).  Rows are 256 bytes, unpadded; the 16-byte
 //     chunk c of row r sits at chunk slot c ^ swz(r), which keeps both the K operand reads and
 //     the V transpose reads free of bank conflicts;
-//   * the first contraction is S^T = K Q^T (A = K from LDS by 16-byte reads), so a lane holds one
-//     query column: the softmax max/sum are in-lane plus one exchange with lane^32, and the
-//     probabilities feed the second contraction O^T += V^T P^T straight from registers (the key
-//     order inside a 16-key MFMA step is permuted identically on both operands, which a sum over
+//   * the first contraction is S^T = K Q^T (A = K from LDS by 16-byte reads, each operand for both query groups),
+//     so a lane holds one query column of each group: the softmax max/sum are in-lane plus two exchanges over the
+//     four lanes of a query, and the probabilities feed the second contraction O^T += V^T P^T straight from
+//     registers (the key order inside a 32-key MFMA step is permuted identically on both operands, which a sum over
 //     keys does not see); V^T operands come from the LDS transpose read (ds_read_b64_tr_b16);
 //   * the order of work inside a wave.  A step handles tile t's softmax and second contraction
 //     and tile t+1's first contraction:
 //
 //       step t:  barrier                      K(t+1), V(t) resident; stages of K(t), V(t-1) free
-//                copies K(t+2), V(t+1) start
-//                the MFMAs of S(t+1), back to back; mask S(t+1) if it is the diagonal block
+//                the first operands of K(t+1) are fetched, copies K(t+2), V(t+1) start
 //                exp / bf16 pack / row sum of the probabilities of tile t (one run of VALU work);
 //                if a row sum shows that the reference maximum was too low (rare): true
 //                maximum of the tile, rescale O and l, probabilities again
+//                the MFMAs of S(t+1), back to back; mask S(t+1) if it is the diagonal block
 //                the MFMAs of O += V(t)^T P(t)^T, back to back
 //
-//     so a wave alternates between blocks of MFMAs and a block of VALU work that depends
-//     on none of the MFMAs in flight, and the two waves of a SIMD (of different workgroups,
+//     so a wave alternates between a block of MFMAs, at wave priority 1, and a run of VALU work, at priority 0, that
+//     depends on none of the MFMAs in flight, and the two waves of a SIMD (of different workgroups,
 //     unsynchronised) mostly find the other unit free.
+//
+// Why 16x16x32: long launches run at the card's power limit, and of MFMAs alone on random operands that limit lets
+// through 2.07 PFLOP/s in this shape, 1.80 in 32x32x16 (twice the operand reads but half the accumulator
+// traffic per product).  By itself the change moved the bound from power (1.64 GHz, matrix pipe 70% busy) to the schedule
+// (2.0 GHz, 58%) and gained nothing; then
+//   * chunk slots free of conflicts for the new operand reads (see swz()): 128K +2%, 32K +1.3%;
+//   * the softmax in front of both contractions, not between them: the latency of the first K operands and the
+//     issue of the copies (64 bytes a cycle) pass behind it, and 32 fewer registers live in it: +4%;
+//   * the two groups' probabilities in turn, two partial sums each (the dot products form chains): +3%;
+//   * priority by phase instead of by turns of 41 us between the workgroups of a compute unit: +0.7%.
+// Together: 128K layer 30.7 -> 28.0 ms (1.32 PFLOP/s), 32K 1870 -> 1725 us, with 64-token blocks 2180 -> 1995 us, a
+// 64K share of 8 heads 1553 -> 1434 us, an 8K prompt 182 -> 171 us, 48 sequences 148 -> 144 us (whole path).  Now 1.85 GHz
+// and 70% at 128K.  Spreading the VALU work between the MFMAs of the same wave, in whatever part, costs 4 to 25%; copies
+// issued later in the step or between the exponentials 2 to 5%.
 //
 // Between items.  An item used to cost about 21 000 cycles beside its tiles (an atomic ticket that waited
 // for the output stores in front of it, the record, the first selected blocks, the first tile copies and
@@ -45,7 +59,7 @@
 // started one step later, between the last step and the output, these were 125 us, 1.81 ms and 0.7%.
 //
 // The two score buffers swap roles from step to step (the tile count is even, steps are
-// issued in pairs).  LDS operands are fetched kLook groups ahead of their use.  Fully
+// issued in pairs).  LDS operands are fetched kLook ahead of their use.  Fully
 // masked sub-tiles are computed like any other (their probabilities are exact zeros).
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
 //
@@ -68,7 +82,8 @@ struct AttnArgs {
   float* lse;
   shplb_wg_stats* stats;
   int32_t n_stats;
-  int32_t rows, rows_per_die, compute_units;   // how rows without queues are dealt, see row_item()
+  int32_t rows, rows_per_die, compute_units;   // how rows without queues are dealt, see row_place()
+  int32_t group;                               // query heads per KV head; 0: meta.kv_of names them
   float scale_log2;
   int64_t total_tokens;
   Strides st;
@@ -78,6 +93,7 @@ struct AttnArgs {
 };
 typedef const __attribute__((address_space(4))) AttnArgs* ArgsPtr;
 typedef const __attribute__((address_space(4))) int32_t* ConstInts;   // read by scalar loads
+typedef const __attribute__((address_space(4))) int64_t* ConstLongs;
 
 // The same pointer, but the compiler may not carry values loaded through it from before this point.
 __device__ __forceinline__ ArgsPtr reload(ArgsPtr a) {
@@ -99,7 +115,7 @@ struct Item {
   int64_t sel_begin;
 };
 
-// The item of workgroup b in a launch that gives every row a workgroup of its own.  False: no row.
+// The row of workgroup b in a launch that gives every row a workgroup of its own.  False: no row.
 // The dispatcher puts workgroup b on die b % 8 and, one lap of all compute units after the other, beside workgroup
 // b - (compute units).
 // * No more rows than compute units: die x takes a run of consecutive rows (rows_per_die), i.e. few K/V streams.
@@ -111,38 +127,48 @@ struct Item {
 //   among five of 200 64-token blocks, whose long ends meet (two 283 against 261, three 286 against 270).  Runs
 //   are the faster ones for up to one row per compute unit (2K x 8 heads, 64-token blocks: 25.2 against 26.5) and
 //   for equally short rows (32/8 heads x 2K at budgets of 2 to 4 blocks 21 against 23).
-__device__ __forceinline__ bool row_item(ArgsPtr a, int b, Item& it) {
-  const int n_seq = a->meta.n_seq, hq = a->meta.n_q_heads, rows = a->rows, per_die = a->rows_per_die;
+// What a single sequence needs of the arguments is loaded together, before the first use: each load that waits for
+// another one costs some 500 cycles here, at the start of the launch.
+__device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
+  const int n_seq = a->meta.n_seq, hq = a->meta.n_q_heads, rows = a->rows, per_die = a->rows_per_die, cus = a->compute_units;
+  const int group = a->group, nb0 = a->meta.blk_begin[1], t0 = a->meta.tok_begin[0], t1 = a->meta.tok_begin[1];
+  asm volatile("" ::"s"(n_seq), "s"(hq), "s"(rows), "s"(per_die), "s"(cus), "s"(group), "s"(nb0), "s"(t0), "s"(t1), "s"(a->q),
+               "s"(a->st.q_t));
   int row = (b % kXcds) * per_die + b / kXcds;
   bool any = b / kXcds < per_die && row < rows;
   if (per_die == 0) {
     int begin = 0, odd = 0;                          // first row of the lap
-    for (; begin + a->compute_units <= b; begin += a->compute_units) odd ^= 1;
-    const int place = b - begin, n = min(a->compute_units, rows - begin);
+    for (; begin + cus <= b; begin += cus) odd ^= 1;
+    const int place = b - begin, n = min(cus, rows - begin);
     row = begin + (odd ? n - 1 - place : place);
     any = place < n;
   }
   if (!any) return false;
-  // sequence: how many of them end at or before the row (one lane per sequence)
-  const int lane = threadIdx.x & 63;
-  const int s = __builtin_popcountll(__ballot(lane < n_seq && row >= a->meta.blk_begin[min(lane, n_seq - 1) + 1] * hq));
   auto scalar = [](int x) { return int(__builtin_amdgcn_readfirstlane(x)); };
-  const int b0 = a->meta.blk_begin[s], local = row - b0 * hq;
+  // x / y of small non-negative numbers (there are no more rows than workgroups here)
+  auto quotient = [&](int x, int y) {
+    const int q = scalar(int(float(x) * __builtin_amdgcn_rcpf(float(y)))), r = x - q * y;
+    return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
+  };
+  int s = 0, local = row;
+  it.n_blocks = nb0;
+  it.seq_begin = t0;
+  it.seq_end = t1;
+  if (n_seq > 1) {
+    // how many sequences end at or before the row (one lane per sequence)
+    const int lane = threadIdx.x & 63;
+    s = __builtin_popcountll(__ballot(lane < n_seq && row >= a->meta.blk_begin[min(lane, n_seq - 1) + 1] * hq));
+    const int b0 = scalar(a->meta.blk_begin[s]);
+    local = row - b0 * hq;
+    it.n_blocks = scalar(a->meta.blk_begin[s + 1]) - b0;
+    it.seq_begin = scalar(a->meta.tok_begin[s]);
+    it.seq_end = scalar(a->meta.tok_begin[s + 1]);
+  }
   it.pos = row;
-  it.n_blocks = scalar(a->meta.blk_begin[s + 1] - b0);
-  it.head = local / it.n_blocks;
+  it.head = quotient(local, it.n_blocks);
   it.q_block = local - it.head * it.n_blocks;
-  it.kv_head = scalar(a->meta.kv_map ? int(a->meta.kv_of[it.head >> 2] >> (8 * (it.head & 3)) & 0xff)
-                                     : it.head / (hq / a->meta.n_kv_heads));
-  it.seq_begin = scalar(a->meta.tok_begin[s]);
-  it.seq_end = scalar(a->meta.tok_begin[s + 1]);
+  it.kv_head = group > 0 ? quotient(it.head, group) : scalar(int(a->meta.kv_of[it.head >> 2] >> (8 * (it.head & 3)) & 0xff));
   it.slot = -1;
-  const int64_t first = a->sel_ptr[row];
-  it.sel_begin = int64_t(uint32_t(scalar(int(first)))) | int64_t(scalar(int(first >> 32))) << 32;
-  it.n_sel = scalar(int(a->sel_ptr[row + 1] - first));
-  if (it.n_sel <= 0) return false;
-  it.first_block = scalar(a->sel_idx[it.sel_begin]);
-  it.second_block = scalar(a->sel_idx[it.sel_begin + min(1, it.n_sel - 1)]);
   return true;
 }
 
@@ -154,14 +180,14 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each
   constexpr int kThreads = 64 * KS * kWaves;
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
-  constexpr int MT = KT / 32;                        // 32-key MFMA tiles of a tile's scores
+  constexpr int QG = 2, MT = KT / 16;                // 16-query and 16-key MFMA tiles of a tile's scores
   constexpr int kTileBytes = KT * kRowBytes;
   constexpr int kRoundRows = 4 * kWaves;             // rows one round of copies moves (4 per wave)
   constexpr int kRounds = KT / kRoundRows;
-  constexpr int kQK = 8 * MT;                        // MFMAs of a tile's first contraction, index MT*ks + mt
-  constexpr int kPV = 4 * (KT / 16);                 // ... of its second, index 4*gq + dt
-  constexpr int kLook = 8;                           // LDS operand fetches run this many groups ahead
-  constexpr float kSumLimit = 16.0f * MT * 256.0f;   // a lane's 16 MT probabilities of a tile can only sum to
+  constexpr int kQK = 4 * MT;                        // K operands of a tile's first contraction, index MT*ks + mt ...
+  constexpr int kPV = 8 * (KT / 32);                 // ... V operands of its second, index 8*gq + dt: QG MFMAs each
+  constexpr int kLook = KS > 1 ? 4 : 8;              // LDS operand fetches run this many operands ahead (12: no change)
+  constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
 
@@ -176,47 +202,28 @@ void attn_pipe_kernel(AttnArgs) {
   const int lane = tid & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = KS > 1 ? wave_all / kWaves : 0, wave = KS > 1 ? wave_all % kWaves : wave_all;
-  const int n = lane & 31, hi = lane >> 5;
+  const int n = lane & 15, hi = lane >> 4;
   const int64_t row_bytes = args->st.kv_t * 2;
   const float scale_log2 = args->scale_log2;
 
   // ---- per-lane constants
   // copies: lane (r4 = lane>>4, slot = lane&15) of a wave fills, in round rd, LDS row
   // rd*kRoundRows + cp_row, slot `slot`, with the source chunk slot ^ swz(row).  Rounds of 8
-  // rows alternate bit 3 of the row, which flips the low bit of the swizzle: two per-lane
+  // rows alternate bit 3 of the row, which flips the two low bits of the swizzle: two per-lane
   // source offsets cover all rounds.
-  // K operand reads: lane (n, hi) reads row 32mt + n, chunk 2ks + hi.
-  // V transpose reads: lane = 16*grp + 4e + a supplies the piece (key 16gq + 8half + 4hi + e,
-  // dims 32dt + 16(grp&1) + 4a ..) and receives keys 4hi+0..3 (+8half, +16gq) of dim 32dt + n.
+  // K operand reads: lane (n, hi) reads row 16mt + n, chunk 4ks + hi.
+  // V transpose reads: lane = 16*hi + 4e + a supplies the piece (key 32gq + 16half + 4hi + e, dims 16dt + 4a ..)
+  // and receives keys 4hi+0..3 (+16half, +32gq) of dim 16dt + n.
   const int cp_row = 4 * wave + (lane >> 4);
   const uint32_t cp_off0 = uint32_t(cp_row) * uint32_t(row_bytes) + (((lane & 15) ^ swz(cp_row)) << 4);
-  const uint32_t cp_off1 = uint32_t(cp_row) * uint32_t(row_bytes) + (((lane & 15) ^ swz(cp_row) ^ 1) << 4);
+  const uint32_t cp_off1 = uint32_t(cp_row) * uint32_t(row_bytes) + (((lane & 15) ^ swz(cp_row) ^ 3) << 4);
   const int k_rd0 = n * kRowBytes + ((hi ^ swz(n)) << 4);
-  const int tr_e = (lane >> 2) & 3, tr_a = lane & 3, tr_mh = (lane >> 4) & 1;
-  int v_rd0[2];
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int r = 8 * half + 4 * hi + tr_e;
-    v_rd0[half] = r * kRowBytes + (((2 * tr_mh + (tr_a >> 1)) ^ swz(r)) << 4) + 8 * (tr_a & 1);
-  }
+  const int tr_row = 4 * hi + ((lane >> 2) & 3), tr_a = lane & 3;
+  const int v_rd0 = tr_row * kRowBytes + (((tr_a >> 1) ^ swz(tr_row)) << 4) + 8 * (tr_a & 1);
   const char* const k_lds = lds + grp * 4 * kTileBytes;
   const char* const v_lds = k_lds + 2 * kTileBytes;
   const uint32_t k_stage0 = __builtin_amdgcn_readfirstlane(lds_offset_of(lds) + grp * 4 * kTileBytes + 4 * wave * kRowBytes);
   const uint32_t v_stage0 = k_stage0 + 2 * kTileBytes;
-
-  // The two workgroups of a compute unit compete for every SIMD's issue slots, and left alone
-  // one of them wins most of the time: workgroups were measured to get through 30-40% more or
-  // fewer key blocks than the average in the same time.  The sum is what counts in the middle
-  // of a launch, but near its end the slow workgroup of a pair holds its last item far longer
-  // than planned and the launch waits for it.  So the pair takes turns: wave priority 1 for
-  // one and 0 for the other, swapped every 2^kTurnShift ticks of the constant 100 MHz clock
-  // (41 us), the first half of the grid against the second half (the dispatcher fills every
-  // compute unit once before it places second workgroups; if it ever does not, two workgroups
-  // merely swap in step and nothing is lost).  Progress per workgroup then stays within 6-7%
-  // of the average and the idle tail of short launches shrinks (64K share of 8 heads: 6% of
-  // the launch to 2-3%).
-  constexpr int kTurnShift = 12;
-  const uint32_t second_wg = blockIdx.x >= gridDim.x / 2;
 
   uint32_t my_items = 0, my_cost = 0;
   uint64_t t_first = 0, t_last = 0;
@@ -268,7 +275,7 @@ void attn_pipe_kernel(AttnArgs) {
   Item it;
   bool have;
   if (args->wq.items == nullptr) {
-    have = row_item(args, blockIdx.x, it);
+    have = row_place(args, blockIdx.x, it);
   } else {
     if (tid < 64) s_empty = 0;                       // (wave 0's own)
     const int x = blockIdx.x % kXcds, begin = args->wq.queue_begin[x];
@@ -285,7 +292,7 @@ void attn_pipe_kernel(AttnArgs) {
   }
 
   const char *k_head = nullptr, *v_head = nullptr;
-  bf16x8 qf[8];
+  bf16x8 qf[QG][4];
   int64_t next_off = 0;                  // byte offset (from k_head, v_head) of the tile whose K copies were issued last ...
   int next_last = 0;                     // ... and the row in it that holds the sequence's last token (or a larger number)
 
@@ -299,11 +306,12 @@ void attn_pipe_kernel(AttnArgs) {
     next_off = int64_t(key_base) * row_bytes;
   };
   // Copy the K or V rows of the located tile into an LDS stage.
-  auto issue = [&](const char* head, uint32_t dst) {
+  auto issue_part = [&](const char* head, uint32_t dst, int part) {
     const char* tile = uniform(head + next_off);
     if (next_last >= KT - 1) {
 #pragma unroll
       for (int rd = 0; rd < kRounds; ++rd) {
+        if (part == 1 && rd >= kRounds / 2 || part == 2 && rd < kRounds / 2) continue;
         const bool odd8 = ((rd * kRoundRows) >> 3) & 1;       // round starts at an odd multiple of 8 rows
         copy_g2l_16(tile + int64_t(rd * kRoundRows) * row_bytes, odd8 ? cp_off1 : cp_off0,
                     dst + rd * kRoundRows * kRowBytes);
@@ -311,33 +319,76 @@ void attn_pipe_kernel(AttnArgs) {
     } else {                                     // ragged: rows past the end re-read the last valid key (masked)
 #pragma unroll
       for (int rd = 0; rd < kRounds; ++rd) {
+        if (part == 1 && rd >= kRounds / 2 || part == 2 && rd < kRounds / 2) continue;
         const int r = rd * kRoundRows + cp_row;
         const uint32_t off = uint32_t(min(r, next_last)) * uint32_t(row_bytes) + (((lane & 15) ^ swz(r)) << 4);
         copy_g2l_16(tile, off, dst + rd * kRoundRows * kRowBytes);
       }
     }
   };
+  auto issue = [&](const char* head, uint32_t dst) { issue_part(head, dst, 0); };
   // Everything an item can start before its turn: its first tile copies and its Q fragments (B operand of
-  // S^T = K Q^T, lane (n, hi) holds dims 16ks+8hi.. of its query).  The stages must be free.
-  auto start_item = [&]() {
+  // S^T = K Q^T, lane (n, hi) holds dims 32ks+8hi.. of queries n and 16 + n).  The stages must be free.
+  auto load_queries = [&](ArgsPtr a) {
+    const uint16_t* src[QG];
+#pragma unroll
+    for (int qg = 0; qg < QG; ++qg) {
+      const int tok = min(it.seq_begin + it.q_block * BQ + wave * 32 + 16 * qg + n, it.seq_end - 1);
+      src[qg] = a->q + int64_t(tok) * a->st.q_t + int64_t(it.head) * a->st.q_h + 8 * hi;
+    }
+#pragma unroll
+    for (int qg = 0; qg < QG; ++qg)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) qf[qg][ks] = *reinterpret_cast<const bf16x8*>(src[qg] + 32 * ks);
+  };
+  auto start_item = [&](auto copies_c, auto queries_c) {
+    constexpr bool kCopies = decltype(copies_c)::value, kQueries = decltype(queries_c)::value;
     ArgsPtr a = reload(args);
     k_head = reinterpret_cast<const char*>(a->k + int64_t(it.kv_head) * a->st.kv_h);
     v_head = reinterpret_cast<const char*>(a->v + int64_t(it.kv_head) * a->st.kv_h);
-    int j0 = it.first_block;
-    if (KS > 1 && grp == 1) j0 = it.second_block;
-    it.first_block = j0;
-    const int tok = min(it.seq_begin + it.q_block * BQ + wave * 32 + n, it.seq_end - 1);
-    const uint16_t* src = a->q + int64_t(tok) * a->st.q_t + int64_t(it.head) * a->st.q_h + 8 * hi;
-    locate(j0, 0);
-    issue(k_head, k_stage0);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
-    issue(v_head, v_stage0);
-    locate(j0, 1);
-    issue(k_head, k_stage0 + kTileBytes);
+    if (kCopies) {
+      locate(it.first_block, 0);
+      issue(k_head, k_stage0);
+    }
+    if (kQueries) load_queries(a);
+    if (kCopies) {
+      issue(v_head, v_stage0);
+      locate(it.first_block, 1);
+      issue(k_head, k_stage0 + kTileBytes);
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
-  if (have) start_item();
+  const std::true_type yes{};
+  const std::false_type no{};
+  // the group's own first block
+  auto own_first = [&]() {
+    if (KS > 1 && grp == 1) it.first_block = it.second_block;
+  };
+  if (have && args->wq.items != nullptr) {
+    own_first();
+    start_item(yes, yes);
+  } else if (have) {
+    // A row without a record: which blocks it has selected is two dependent loads away.  Block 0, the sink, is
+    // nearly always the first of them: its copies start meanwhile, and are done again if it is not.
+    const ConstLongs ptr = (ConstLongs)uintptr_t(args->sel_ptr + it.pos);
+    const int64_t begin = ptr[0], end = ptr[1];
+    it.first_block = 0;
+    if (KS == 1 || grp == 0) start_item(yes, yes);
+    else start_item(no, yes);
+    it.sel_begin = begin;
+    it.n_sel = int(end - begin);
+    have = it.n_sel > 0;
+    if (have) {
+      const ConstInts sel = (ConstInts)uintptr_t(args->sel_idx + begin);
+      it.first_block = sel[0];
+      it.second_block = sel[min(1, it.n_sel - 1)];
+      own_first();
+      if (it.first_block != 0 || (KS > 1 && grp == 1)) {
+        wait_vmem_all();                             // (of the copies that went to the same stages)
+        start_item(yes, no);
+      }
+    }
+  }
   wait_vmem_all();
 
   while (have) {
@@ -355,47 +406,54 @@ void attn_pipe_kernel(AttnArgs) {
     auto beyond = [&](int b) { return KS > 1 && b * KS + grp >= it.n_sel; };
     int j0 = it.first_block, j1 = KS > 1 ? block_of(1) : it.second_block;
 
-    f32x16 acc_o[4];
-    float m_ref, l_run = 0.0f;
+    typedef f32x4 Scores[QG][MT];
+    f32x4 acc_o[QG][8];
+    float m_ref[QG], l_run[QG];
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int qg = 0; qg < QG; ++qg) {
+      l_run[qg] = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc_o[dt][r] = 0.0f;
+      for (int dt = 0; dt < 8; ++dt) acc_o[qg][dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
 
-    auto mask_scores = [&](f32x16 (&sc)[MT], int half, bool all) {   // diagonal block: keys above the query
-      // key position minus query position, up to the part that depends on the register: taken
-      // through an opaque move so that the 32 comparisons are made here, on the rare diagonal
-      // tile, instead of being hoisted out of the item loop into 64 scalar registers of masks
-      int d = all ? BQ : KT * half + 4 * hi - (wave * 32 + n);
-      asm volatile("" : "+v"(d));
+    auto clear_scores = [&](Scores& sc) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int qg = 0; qg < QG; ++qg)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (d + (32 * mt + 8 * (r >> 2) + (r & 3)) > 0) sc[mt][r] = -INFINITY;
+        for (int mt = 0; mt < MT; ++mt) sc[qg][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     };
-    auto read_k = [&](const char* kt, int gi) {       // operand of QK group gi = MT*ks + mt
-      const int ks = gi / MT, mt = gi % MT;
-      return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ (ks << 5)) + mt * 32 * kRowBytes);
-    };
-    // in-lane maximum of a tile's scores
-    auto tile_max = [&](f32x16 (&sc)[MT]) {
-      float mx;
-      if constexpr (MT == 2) {
-        mx = fmaxf(sc[0][0], sc[1][0]);
+    auto mask_scores = [&](Scores& sc, int half, bool all) {         // diagonal block: keys above the query
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(sc[0][r], sc[1][r]));
-      } else {
-        mx = sc[0][0];
+      for (int qg = 0; qg < QG; ++qg) {
+        // key position minus query position, up to the part that depends on the register: taken
+        // through an opaque move so that the comparisons are made here, on the rare diagonal
+        // tile, instead of being hoisted out of the item loop into 64 scalar registers of masks
+        int d = all ? BQ : KT * half + 4 * hi - (wave * 32 + 16 * qg + n);
+        asm volatile("" : "+v"(d));
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[0][r]);
+        for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (d + (16 * mt + r) > 0) sc[qg][mt][r] = -INFINITY;
+          asm volatile("" : "+v"(sc[qg][mt]));         // (four masks at a time, not all of them in scalar registers)
+        }
       }
+    };
+    auto read_k = [&](const char* kt, int gi) {       // operand gi = MT*ks + mt of the first contraction
+      const int ks = gi / MT, mt = gi % MT;
+      return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ (ks << 6)) + mt * 16 * kRowBytes);
+    };
+    // in-lane maximum of a tile's scores of a query
+    auto tile_max = [&](const Scores& sc, int qg) {
+      float mx = sc[qg][0][0];
+#pragma unroll
+      for (int x = 1; x < 4 * MT; ++x) mx = fmaxf(mx, sc[qg][x >> 2][x & 3]);
       return mx;
     };
-    auto read_v = [&](const char* vt, int gi) {       // operand of PV group gi = 4*gq + dt
-      const int gq = gi >> 2, dt = gi & 3;
-      const s16x4 lo = lds_read_tr16(vt + (v_rd0[0] ^ (dt << 6)) + gq * 16 * kRowBytes);
-      const s16x4 up = lds_read_tr16(vt + (v_rd0[1] ^ (dt << 6)) + gq * 16 * kRowBytes);
+    auto read_v = [&](const char* vt, int gi) {       // operand gi = 8*gq + dt of the second
+      const int gq = gi >> 3, dt = gi & 7;
+      const char* at = vt + (v_rd0 ^ (dt << 5)) + gq * 32 * kRowBytes;
+      const s16x4 lo = lds_read_tr16(at), up = lds_read_tr16(at + 16 * kRowBytes);
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
     };
 
@@ -416,21 +474,21 @@ void attn_pipe_kernel(AttnArgs) {
     if (n_pairs == 1) ask();
 
     // ---- S(0).  (The item's copies have landed in this wave: see the end of the loop.)
-    f32x16 sc_a[MT], sc_b[MT];
+    Scores sc_a, sc_b;
     __syncthreads();
     {
       bf16x8 kf[kQK];
 #pragma unroll
       for (int gi = 0; gi < kQK; ++gi) kf[gi] = read_k(k_lds, gi);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sc_a[mt][r] = 0.0f;
+      clear_scores(sc_a);
 #pragma unroll
       for (int gi = 0; gi < kQK; ++gi)
-        sc_a[gi % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[gi], qf[gi / MT], sc_a[gi % MT], 0, 0, 0);
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg)
+          sc_a[qg][gi % MT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi], qf[qg][gi / MT], sc_a[qg][gi % MT], 0, 0, 0);
       if (j0 == i || beyond(0)) mask_scores(sc_a, 0, beyond(0));
-      m_ref = pair_max(tile_max(sc_a)) * scale_log2;
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg) m_ref[qg] = quad_max(tile_max(sc_a, qg)) * scale_log2;
     }
 
     // One step: tile t's softmax and PV from sc_cur, tile t+1's scores into sc_nxt.
@@ -439,24 +497,17 @@ void attn_pipe_kernel(AttnArgs) {
     // kPlace: kMid inside the item; kRecord the last step but one, kFinal the last one.
     enum { kMid, kRecord, kFinal };
     const Item cur = it;                             // (the last step starts the next item)
-    auto step = [&](auto place_c, auto stage_c, f32x16 (&sc_cur)[MT], f32x16 (&sc_nxt)[MT], int jk, bool mask, bool all,
+    auto step = [&](auto place_c, auto stage_c, Scores& sc_cur, Scores& sc_nxt, int jk, bool mask, bool all,
                     bool drop, bool ask_now) {
       constexpr int kPlace = decltype(place_c)::value, kStage = decltype(stage_c)::value;
       constexpr bool kHasNext = kPlace != kFinal;
-      // Take turns with the other workgroup of this compute unit (see kTurnShift).
-      if (((uint32_t(wall_clock64()) >> kTurnShift) & 1) ^ second_wg) __builtin_amdgcn_s_setprio(1);
-      else __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_s_setprio(0);
       wait_vmem_all();                  // own copies of K(t+1), V(t) have landed
       if (kPlace == kRecord && home_open && tid == 0) {
         // the ticket asked for one step ago
         s_next = ticket < home_size ? home_begin + int(ticket) : kHelp;
       }
       __syncthreads();                  // everyone's have; stages of K(t) and V(t-1) are free
-      if constexpr (kHasNext) issue(v_head, v_stage0 + (kStage ^ 1) * kTileBytes);
-      if constexpr (kPlace == kMid) {
-        locate(jk, kStage);
-        issue(k_head, k_stage0 + kStage * kTileBytes);
-      }
       if (kPlace == kMid && kStage == 1 && ask_now) ask();
       if constexpr (kPlace == kRecord) {
         // the next item's record arrives behind this step's work
@@ -465,27 +516,17 @@ void attn_pipe_kernel(AttnArgs) {
       }
       if constexpr (kPlace == kFinal && KS == 1) {
         // all stages but that of V(t) are free and the last scores have been taken: the next item starts
-        if (pos >= 0 && read_record(pos, words, it)) start_item();
+        if (pos >= 0 && read_record(pos, words, it)) start_item(yes, yes);
         else it.n_sel = 0;
       }
 
       const char* kn = k_lds + (kStage ^ 1) * kTileBytes;
       const char* vc = v_lds + kStage * kTileBytes;
-      float m_use = m_ref == -INFINITY ? 0.0f : m_ref;
 
       bf16x8 kf[kQK], vf[kPV];
-      uint32_t pk[MT][8];
-      float rs0 = 0.0f, rs1 = 0.0f;
-      if (kHasNext) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sc_nxt[mt][r] = 0.0f;
-      }
+      if (kHasNext) clear_scores(sc_nxt);
 
-      // ---- S(t+1): its MFMAs back to back (the operands of the second contraction are
-      // fetched behind the last K operands)
-      static_assert(kLook <= kQK && kLook <= kPV, "operand lookahead longer than a contraction");
+      // ---- the first LDS operands, and the copies of this step
       if (kHasNext) {
 #pragma unroll
         for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(kn, gi);
@@ -494,63 +535,85 @@ void attn_pipe_kernel(AttnArgs) {
         for (int gi = 0; gi < kLook; ++gi) vf[gi] = read_v(vc, gi);
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (kHasNext) {
-#pragma unroll
-        for (int gi = 0; gi < kQK; ++gi) {
-          if (gi + kLook < kQK) kf[gi + kLook] = read_k(kn, gi + kLook);
-          else vf[gi + kLook - kQK] = read_v(vc, gi + kLook - kQK);
-          sc_nxt[gi % MT] =
-              __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[gi], qf[gi / MT], sc_nxt[gi % MT], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (mask) mask_scores(sc_nxt, kStage ^ 1, all);
+      if constexpr (kHasNext) issue(v_head, v_stage0 + (kStage ^ 1) * kTileBytes);
+      if constexpr (kPlace == kMid) {
+        locate(jk, kStage);
+        issue(k_head, k_stage0 + kStage * kTileBytes);
       }
+      __builtin_amdgcn_sched_barrier(0);
 
-      // ---- probabilities of tile t, in one run of VALU work: the S(t+1) MFMAs of this wave
-      // are still in flight and the other wave of the SIMD is usually inside an MFMA block.
-      // (Spread between the MFMAs above, the same instructions make the kernel 2-4% slower.)
+      // ---- probabilities of tile t, in one run of VALU work: the first K operands arrive behind it, and the other
+      // wave of the SIMD is usually inside an MFMA block.
+      uint32_t pk[QG][MT][2];
+      float rs[QG];
       auto probabilities = [&]() {
-        m_use = m_ref == -INFINITY ? 0.0f : m_ref;
-        rs0 = rs1 = 0.0f;
+        float sum[QG][2];
 #pragma unroll
-        for (int u = 0; u < 8 * MT; ++u) {
-          const int mt = u >> 3, r = 2 * (u & 7);
-          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc_cur[mt][r], scale_log2, -m_use));
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc_cur[mt][r + 1], scale_log2, -m_use));
-          pk[mt][u & 7] = pack_bf16(p0, p1);
-          // row sum of the rounded probabilities (what the second contraction multiplies with)
-          if (u & 1) rs1 = dot2_ones(pk[mt][u & 7], rs1);
-          else rs0 = dot2_ones(pk[mt][u & 7], rs0);
+        for (int qg = 0; qg < QG; ++qg) sum[qg][0] = sum[qg][1] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4 * MT; ++u) {            // two probabilities of a query group, the groups in turn
+          const int qg = u % QG, mt = u / (2 * QG), c = u / QG % 2;
+          const float m_use = m_ref[qg] == -INFINITY ? 0.0f : m_ref[qg];
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc_cur[qg][mt][2 * c], scale_log2, -m_use));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc_cur[qg][mt][2 * c + 1], scale_log2, -m_use));
+          pk[qg][mt][c] = pack_bf16(p0, p1);
+          // row sums of the rounded probabilities (what the second contraction multiplies with)
+          sum[qg][c] = dot2_ones(pk[qg][mt][c], sum[qg][c]);
         }
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg) rs[qg] = sum[qg][0] + sum[qg][1];
       };
       probabilities();
       // The reference m_ref was fixed by earlier tiles.  It is too low for this tile exactly
       // when a probability came out large, and then the tile's row sum is large: no maximum
       // over the scores is needed to notice.  In that (rare) case take the tile's true
       // maximum, raise the reference, rescale O and l, and redo the tile's probabilities.
-      if (__any(!(rs0 + rs1 <= kSumLimit))) {
-        const float m_new = fmaxf(m_ref, pair_max(tile_max(sc_cur)) * scale_log2);
-        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_ref - m_new);
-        m_ref = m_new;
-        l_run *= alpha;
+      if (__any(!(rs[0] <= kSumLimit) || !(rs[1] <= kSumLimit))) {
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+        for (int qg = 0; qg < QG; ++qg) {
+          const float m_new = fmaxf(m_ref[qg], quad_max(tile_max(sc_cur, qg)) * scale_log2);
+          const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_ref[qg] - m_new);
+          m_ref[qg] = m_new;
+          l_run[qg] *= alpha;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc_o[dt][r] *= alpha;
+          for (int dt = 0; dt < 8; ++dt) acc_o[qg][dt] *= alpha;
+        }
         probabilities();
       }
-      l_run += rs0 + rs1;
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg) l_run[qg] += rs[qg];
       __builtin_amdgcn_sched_barrier(0);
+
+      // ---- S(t+1): its MFMAs back to back (the operands of the second contraction are
+      // fetched behind the last K operands)
+      __builtin_amdgcn_s_setprio(1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (kHasNext) {
+#pragma unroll
+        for (int gi = 0; gi < kQK; ++gi) {
+          if (gi + kLook < kQK) kf[gi + kLook] = read_k(kn, gi + kLook);
+          if (gi + kLook >= kQK) vf[gi + kLook - kQK] = read_v(vc, gi + kLook - kQK);
+#pragma unroll
+          for (int qg = 0; qg < QG; ++qg)
+            sc_nxt[qg][gi % MT] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi], qf[qg][gi / MT], sc_nxt[qg][gi % MT], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (mask) mask_scores(sc_nxt, kStage ^ 1, all);
+      }
 
       // ---- O^T += V(t)^T P(t)^T: its MFMAs back to back
       if (KS > 1 && drop) return;
 #pragma unroll
       for (int gi = 0; gi < kPV; ++gi) {
         if (gi + kLook < kPV) vf[gi + kLook] = read_v(vc, gi + kLook);
-        const int gq = gi >> 2, dt = gi & 3;
-        const u32x4 w = {pk[gq >> 1][4 * (gq & 1)], pk[gq >> 1][4 * (gq & 1) + 1],
-                         pk[gq >> 1][4 * (gq & 1) + 2], pk[gq >> 1][4 * (gq & 1) + 3]};
-        acc_o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[gi], __builtin_bit_cast(bf16x8, w), acc_o[dt], 0, 0, 0);
+        const int gq = gi >> 3, dt = gi & 7;
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg) {
+          const u32x4 w = {pk[qg][2 * gq][0], pk[qg][2 * gq][1], pk[qg][2 * gq + 1][0], pk[qg][2 * gq + 1][1]};
+          acc_o[qg][dt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[gi], __builtin_bit_cast(bf16x8, w), acc_o[qg][dt], 0, 0, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -571,54 +634,52 @@ void attn_pipe_kernel(AttnArgs) {
     step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false, beyond(b), false);
 
     // ---- the next item starts before this one's results are written
-    float l_tot = pair_sum(l_run);
+    float l_tot[QG];
+#pragma unroll
+    for (int qg = 0; qg < QG; ++qg) l_tot[qg] = quad_sum(l_run[qg]);
+    auto own = [&](int dt) { return KS == 1 || dt / (8 / KS) == grp; };   // dim tiles a group ends up with
     if constexpr (KS > 1) {
       __syncthreads();                               // every wave is done with the stages
       // The groups combine their partial results (the softmax of Eq. 1 over the union of their keys): group g
-      // ends up with the dims 32 dt .. of the dt's that are its own.
-      constexpr int kOwn = 4 / KS;
+      // ends up with the dims 16 dt .. of the dt's that are its own.
       f32x4* xo = reinterpret_cast<f32x4*>(lds);
-      auto chunk = [&](int g, int dt, int rq) { return ((((g * 4 + dt) * 4 + rq) * kWaves + wave) << 6) + lane; };
-      if (hi == 0) {
-        s_ml[grp * 2 * BQ + wave * 32 + n] = m_ref;
-        s_ml[grp * 2 * BQ + BQ + wave * 32 + n] = l_tot;
-      }
+      auto chunk = [&](int g, int qg, int dt) { return ((((g * QG + qg) * 8 + dt) * kWaves + wave) << 6) + lane; };
+      float* const ml = s_ml + wave * 32 + n;        // + 2 BQ group + 16 qg (+ BQ: denominators)
+      constexpr int kOwn = 8 / KS;
+      auto combine = [&](auto own_c) {               // (the group as a constant: no branch per dim tile)
+        constexpr int kGroup = decltype(own_c)::value, kOther = KS - 1 - kGroup;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-        if (dt / kOwn != grp)
+        for (int qg = 0; qg < QG; ++qg) {
+          if (hi == 0) {
+            ml[kGroup * 2 * BQ + 16 * qg] = m_ref[qg];
+            ml[kGroup * 2 * BQ + BQ + 16 * qg] = l_tot[qg];
+          }
 #pragma unroll
-          for (int rq = 0; rq < 4; ++rq)
-            xo[chunk(grp, dt, rq)] = f32x4{acc_o[dt][4 * rq], acc_o[dt][4 * rq + 1], acc_o[dt][4 * rq + 2], acc_o[dt][4 * rq + 3]};
-      __syncthreads();
-      float m_g[KS], m_all = -INFINITY, w_own = 0.0f;
-#pragma unroll
-      for (int g = 0; g < KS; ++g) {
-        m_g[g] = s_ml[g * 2 * BQ + wave * 32 + n];
-        m_all = fmaxf(m_all, m_g[g]);
-      }
-      l_tot = 0.0f;
-#pragma unroll
-      for (int g = 0; g < KS; ++g) {
-        m_g[g] = m_g[g] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_g[g] - m_all);     // now the group's weight
-        l_tot += m_g[g] * s_ml[g * 2 * BQ + BQ + wave * 32 + n];
-        if (g == grp) w_own = m_g[g];
-      }
-      m_ref = m_all;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-        if (dt / kOwn == grp) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc_o[dt][r] *= w_own;
-#pragma unroll
-          for (int g = 0; g < KS; ++g)
-            if (g != grp)
-#pragma unroll
-              for (int rq = 0; rq < 4; ++rq) {
-                const f32x4 o = xo[chunk(g, dt, rq)];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc_o[dt][4 * rq + c] += m_g[g] * o[c];
-              }
+          for (int x = 0; x < kOwn; ++x) xo[chunk(kGroup, qg, kOther * kOwn + x)] = acc_o[qg][kOther * kOwn + x];
         }
+        __syncthreads();
+        f32x4 other[QG][kOwn];
+        float m_other[QG], l_other[QG];
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg) {
+          m_other[qg] = ml[kOther * 2 * BQ + 16 * qg];
+          l_other[qg] = ml[kOther * 2 * BQ + BQ + 16 * qg];
+#pragma unroll
+          for (int x = 0; x < kOwn; ++x) other[qg][x] = xo[chunk(kOther, qg, kGroup * kOwn + x)];
+        }
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg) {
+          const float m_all = fmaxf(m_ref[qg], m_other[qg]);
+          const float w = m_ref[qg] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_ref[qg] - m_all);
+          const float w_other = m_other[qg] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_other[qg] - m_all);
+          l_tot[qg] = kGroup == 0 ? w * l_tot[qg] + w_other * l_other[qg] : w_other * l_other[qg] + w * l_tot[qg];
+          m_ref[qg] = m_all;
+#pragma unroll
+          for (int x = 0; x < kOwn; ++x) acc_o[qg][kGroup * kOwn + x] = w * acc_o[qg][kGroup * kOwn + x] + w_other * other[qg][x];
+        }
+      };
+      if (grp == 0) combine(std::integral_constant<int, 0>{});
+      else combine(std::integral_constant<int, KS - 1>{});
       __syncthreads();                               // the stages are free again
     }
     home_open = pos != kHelp;
@@ -630,33 +691,36 @@ void attn_pipe_kernel(AttnArgs) {
         if (pos < 0) break;
         have = read_record(pos, record_words(pos), it);
       }
-      if (have) start_item();
+      if (have) {
+        own_first();
+        start_item(yes, yes);
+      }
     } else {
       have = more && it.n_sel > 0;
     }
 
-    // ---- normalise and store: lane holds, for its query, dims 32dt + 8(r/4) + 4hi + (r%4)
-    int q_in = wave * 32 + n;
+    // ---- normalise and store: lane holds, for its queries, dims 16dt + 4hi + r
+    int q_in = wave * 32 + n;                        // + 16 qg
     asm volatile("" : "+v"(q_in));                   // output addresses are made here, not carried through the loop
     ArgsPtr a = reload(args);
     const int q0 = cur.seq_begin + cur.q_block * BQ;
-    auto own = [&](int dt) { return KS == 1 || dt / (4 / KS) == grp; };
     if (cur.slot >= 0) {
       // a piece of a split row: O and l as they stand (relative to 2^m_ref), for merge_row()
       float* part = a->sb.part_o + int64_t(cur.slot) * kSlotFloatsO;
+      float* ml = a->sb.part_ml + int64_t(cur.slot) * kSlotFloatsML;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-        if (own(dt))
+      for (int qg = 0; qg < QG; ++qg) {
 #pragma unroll
-          for (int rq = 0; rq < 4; ++rq) {
-            float* dst = part + slot_chunk(wave, dt, rq, lane);
-            slot_store(dst, acc_o[dt][4 * rq], acc_o[dt][4 * rq + 1]);
-            slot_store(dst + 2, acc_o[dt][4 * rq + 2], acc_o[dt][4 * rq + 3]);
+        for (int dt = 0; dt < 8; ++dt)
+          if (own(dt)) {
+            float* dst = part + slot_chunk(wave, qg, dt, lane);
+            slot_store(dst, acc_o[qg][dt][0], acc_o[qg][dt][1]);
+            slot_store(dst + 2, acc_o[qg][dt][2], acc_o[qg][dt][3]);
           }
-      if (hi == 0 && grp == 0) {
-        float* ml = a->sb.part_ml + int64_t(cur.slot) * kSlotFloatsML;
-        slot_store1(ml + q_in, m_ref);
-        slot_store1(ml + 128 + q_in, l_tot);
+        if (hi == 0 && grp == 0) {
+          slot_store1(ml + q_in + 16 * qg, m_ref[qg]);
+          slot_store1(ml + 128 + q_in + 16 * qg, l_tot[qg]);
+        }
       }
       // count the piece; if it completes its row, note the row for the merge after the loop
       const ItemRec* rec = a->wq.items + cur.pos;
@@ -667,31 +731,33 @@ void attn_pipe_kernel(AttnArgs) {
       }
       wait_vmem_all();
     } else {
-      // The two lanes of a query hold alternating runs of four dims (8 bytes as bf16).  They trade
-      // runs so that each ends up with eight consecutive dims: the lower lane takes both halves of
-      // the even runs, the upper lane of the odd ones, and a row goes out in 16-byte stores, two
-      // lanes per 32 bytes, instead of 8-byte stores scattered over 64 rows.
-      const float inv = 1.0f / l_tot;
+      // The four lanes of a query hold runs of four dims (8 bytes as bf16) of every dim tile.  Neighbours trade
+      // runs of two tiles so that each ends up with eight consecutive dims of one of them, and a row goes out in
+      // 16-byte stores, four lanes per 64 bytes.
       const int n_valid = cur.seq_end - q0;
-      if (a->lse != nullptr && hi == 0 && grp == 0 && q_in < n_valid)
-        a->lse[int64_t(cur.head) * a->total_tokens + q0 + q_in] = (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
-      uint16_t* dst = a->out + int64_t(q0 + min(q_in, n_valid - 1)) * a->st.q_t + int64_t(cur.head) * a->st.q_h + 8 * hi;
-      constexpr int kRuns = 2, kStores = 4 * kRuns;    // 16-byte stores of a lane, of all four dim tiles
-      auto store_rows = [&](bool valid) {
+      constexpr int kPairs = 4, kStores = QG * kPairs;   // pairs of dim tiles; 16-byte stores of a lane
+      auto store_rows = [&](bool all) {
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-          if (own(dt))
+        for (int qg = 0; qg < QG; ++qg) {
+          const int q_at = q_in + 16 * qg;
+          const bool valid = all || q_at < n_valid;
+          const float inv = 1.0f / l_tot[qg];
+          if (a->lse != nullptr && hi == 0 && grp == 0 && valid)
+            a->lse[int64_t(cur.head) * a->total_tokens + q0 + q_at] =
+                (m_ref[qg] + __builtin_amdgcn_logf(l_tot[qg])) * 0.6931471805599453f;
+          uint16_t* dst = a->out + int64_t(q0 + min(q_at, n_valid - 1)) * a->st.q_t + int64_t(cur.head) * a->st.q_h +
+                          16 * (hi & 1) + 8 * (hi >> 1);
 #pragma unroll
-            for (int rp = 0; rp < kRuns; ++rp) {
-              const int ra = 8 * rp, rb = 8 * rp + 4;      // first accumulator of the even and of the odd run
-              uint32_t e0 = pack_bf16(acc_o[dt][ra] * inv, acc_o[dt][ra + 1] * inv);
-              uint32_t e1 = pack_bf16(acc_o[dt][ra + 2] * inv, acc_o[dt][ra + 3] * inv);
-              uint32_t o0 = pack_bf16(acc_o[dt][rb] * inv, acc_o[dt][rb + 1] * inv);
-              uint32_t o1 = pack_bf16(acc_o[dt][rb + 2] * inv, acc_o[dt][rb + 3] * inv);
-              swap_halves(e0, o0);                         // lower lane: even run of both; upper lane: odd run of both
-              swap_halves(e1, o1);
-              if (valid) *reinterpret_cast<u32x4*>(dst + 32 * dt + 16 * rp) = u32x4{e0, e1, o0, o1};
+          for (int p = 0; p < kPairs; ++p)
+            if (own(2 * p)) {
+              const f32x4 &x = acc_o[qg][2 * p], &y = acc_o[qg][2 * p + 1];
+              uint32_t e0 = pack_bf16(x[0] * inv, x[1] * inv), e1 = pack_bf16(x[2] * inv, x[3] * inv);
+              uint32_t o0 = pack_bf16(y[0] * inv, y[1] * inv), o1 = pack_bf16(y[2] * inv, y[3] * inv);
+              swap_rows(e0, o0);                         // lanes of even hi: both runs of the even tile; of odd hi: of the odd one
+              swap_rows(e1, o1);
+              if (valid) *reinterpret_cast<u32x4*>(dst + 32 * p) = u32x4{e0, e1, o0, o1};
             }
+        }
       };
       // The next item's copies and Q loads were issued before these stores, and the vector memory operations of
       // a wave are reported complete in the order they were issued, loads and stores alike (LLVM's AMDGPU usage
@@ -704,12 +770,14 @@ void attn_pipe_kernel(AttnArgs) {
         asm volatile("" ::: "memory");
         wait_vmem_but(std::integral_constant<int, kStores>{});
       } else {
-        store_rows(q_in < n_valid);
+        store_rows(false);
         wait_vmem_all();
       }
     }
     // (said to the compiler too, which would else wait for the stores in front of the first use)
-    asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7]));
+#pragma unroll
+    for (int qg = 0; qg < QG; ++qg)
+      asm volatile("" : "+v"(qf[qg][0]), "+v"(qf[qg][1]), "+v"(qf[qg][2]), "+v"(qf[qg][3]));
     t_last = wall_clock64();
   }
 
@@ -780,6 +848,7 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.rows = int32_t(g.rows);
   args.rows_per_die = g.rows <= plan.compute_units ? int32_t((g.rows + kXcds - 1) / kXcds) : 0;
   args.compute_units = plan.compute_units;
+  args.group = g.meta.kv_map ? 0 : g.meta.n_q_heads / g.meta.n_kv_heads;
   args.scale_log2 = g.scale * 1.4426950408889634f;
   args.total_tokens = g.total_tokens;
   args.st = g.st;

@@ -132,3 +132,23 @@ def test_rows_without_a_block_do_not_end_a_workgroup():
     compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
     out = run.out.view(nb, block, 8, 128)
     assert not out[1:, :, [0, 1, 2, 4, 5, 6, 7]].any()
+
+
+@pytest.mark.parametrize("block, nb", [(64, 9), (128, 5), (128, 9)])
+def test_selections_that_do_not_begin_with_the_sink(block, nb):
+    # Rows without queues start on block 0 before they know their selection: windows, single blocks (with two groups
+    # of waves one has nothing), no block at all, and rows that do begin with it, one and two sequences.
+    for lens in ([block * nb - 17], [block * nb - 17, block * 3 + 1]):
+        wl = make_custom(lens, 4, 2, block, [2] * (4 * len(lens)), seed=100 + nb, name="no_sink_%d_%d" % (block, nb))
+        run = DevicePass(wl)
+        pick = [lambda i: list(range(max(0, i - 2), i + 1)), lambda i: [i], lambda i: [] if i % 3 == 1 else [i // 2, i] if i else [0],
+                lambda i: list(range(0, i + 1))]
+        lists = [pick[h](i) for n in lens for h in range(4) for i in range(-(-n // block))]
+        ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+        idx = np.concatenate([np.asarray(x, np.int32) for x in lists])
+        print("case", wl.name, len(lens), flush=True)
+        run.attn_step(torch.from_numpy(ptr).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"))
+        torch.cuda.synchronize()
+        rows = [r for r in range(len(lists)) if len(lists[r])]
+        out_o, lse_o = orc.sparse_attention(wl.q, wl.k, wl.v, wl.cu_seqlens, block, ptr, idx, None, rows)
+        compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
