@@ -64,7 +64,8 @@
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
 //
 // KS = 2: two groups of waves share a row, each with every other selected block, and combine their
-// results in LDS (launches of few 64-token rows, see plan_attention()).
+// results in LDS (launches of few rows, see plan_attention()).  Where the groups share SIMDs (kPingPong) they are kept
+// half a step apart by a second barrier: one group's MFMAs run against the other's softmax and copies.
 #include <type_traits>
 
 #include "attn_common.h"
@@ -189,6 +190,7 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kLook = KS > 1 ? 4 : 8;              // LDS operand fetches run this many operands ahead (12: no change)
   constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
+  constexpr bool kPingPong = KS * kWaves > 4;        // the groups share SIMDs
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
 
   // stages of group g: K tiles at (4g + 0, 1) * kTileBytes, V tiles at (4g + 2, 3) * kTileBytes
@@ -475,6 +477,7 @@ void attn_pipe_kernel(AttnArgs) {
 
     // ---- S(0).  (The item's copies have landed in this wave: see the end of the loop.)
     Scores sc_a, sc_b;
+    if (kPingPong && grp == 1) __builtin_amdgcn_s_barrier();   // half a step behind group 0, which waits at the end
     __syncthreads();
     {
       bf16x8 kf[kQK];
@@ -586,6 +589,10 @@ void attn_pipe_kernel(AttnArgs) {
 
       // ---- S(t+1): its MFMAs back to back (the operands of the second contraction are
       // fetched behind the last K operands)
+      if constexpr (kPingPong) {
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
       __builtin_amdgcn_s_setprio(1);
       __builtin_amdgcn_sched_barrier(0);
       if (kHasNext) {
@@ -639,6 +646,7 @@ void attn_pipe_kernel(AttnArgs) {
     for (int qg = 0; qg < QG; ++qg) l_tot[qg] = quad_sum(l_run[qg]);
     auto own = [&](int dt) { return KS == 1 || dt / (8 / KS) == grp; };   // dim tiles a group ends up with
     if constexpr (KS > 1) {
+      if (kPingPong && grp == 0) __builtin_amdgcn_s_barrier();
       __syncthreads();                               // every wave is done with the stages
       // The groups combine their partial results (the softmax of Eq. 1 over the union of their keys): group g
       // ends up with the dims 16 dt .. of the dt's that are its own.
@@ -823,8 +831,14 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // waves), and its length is that of the chain of tiles of the longest row: two groups of waves per row
   // halve that chain.  256 rows of up to 16 blocks 24.6 -> 18.1 us, 512 rows 28.2 -> 21.6 us, 64 rows of up to
   // 8 blocks 14.8 -> 11.8 us; at 1024 rows, where the chip is full without them, 54 -> 57 and 38 -> 51 us.
-  // 128-token rows fill the SIMDs by themselves: 224 rows 19.5 -> 20.6 us, 512 rows 41 -> 48 us.
-  plan.key_groups = g.meta.block == 64 && g.rows <= 2 * cus ? 2 : 1;
+  // A 128-token row fills the SIMDs by itself, but with no more rows than compute units every SIMD has one wave and
+  // its MFMAs and softmax wait for each other: two groups half a step apart (kPingPong; in step 224 rows took 38 us
+  // where one group takes 33).  Whole path: 256 rows of 32 blocks at 20 to 100% 75.6 -> 66.7 us, two heads of four dense
+  // over 8000 tokens 148 -> 118, 256 rows of 16 blocks 50.4 -> 44.9, of 8 34.0 -> 33.5, 224 of 7 32.2 -> 31.5; 160 of 5
+  // 27.0 -> 27.8 and 64 of 2 24.0 -> 24.5, for the groups combine at some 1.5 us: from 7 blocks on.  (Of 16 blocks with
+  // two or three selected 28.5 -> 30.4: the selection is not known here.)  512 rows: two rows a compute unit fill it, 41 -> 48.
+  plan.key_groups = g.meta.block == 64 ? (g.rows <= 2 * cus ? 2 : 1)
+                                       : (g.rows <= cus && g.max_nb >= 7 && slot_capacity == 0 ? 2 : 1);
   plan.grid = n_wg / plan.key_groups;
   // No more rows than workgroups and none to be cut: there is nothing to order, every row gets a workgroup
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).
@@ -856,7 +870,8 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.sb = sb;
   args.meta = g.meta;
   if (g.meta.block == 128) {
-    launch_one<128, 1>(args, plan.grid, stream);
+    if (plan.key_groups == 2) launch_one<128, 2>(args, plan.grid, stream);
+    else launch_one<128, 1>(args, plan.grid, stream);
   } else {
     if (plan.key_groups == 2) launch_one<64, 2>(args, plan.grid, stream);
     else launch_one<64, 1>(args, plan.grid, stream);

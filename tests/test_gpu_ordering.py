@@ -152,3 +152,18 @@ def test_selections_that_do_not_begin_with_the_sink(block, nb):
         rows = [r for r in range(len(lists)) if len(lists[r])]
         out_o, lse_o = orc.sparse_attention(wl.q, wl.k, wl.v, wl.cu_seqlens, block, ptr, idx, None, rows)
         compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
+
+
+@pytest.mark.parametrize("n_blocks, budgets", [(6, [2, 3, 6, 5]), (7, [2, 3, 7, 5]), (32, [2, 3, 4, 5, 32, 7, 31, 20]), (33, [2, 3, 4, 5, 33, 7, 31, 20])])
+def test_128_token_rows_shared_by_two_groups_of_waves(n_blocks, budgets):
+    # From 7 blocks on, rows of launches of up to one per compute unit (256) are shared by two groups of waves half a step
+    # apart: first and last sizes of both rules, rows of one block, odd and even numbers, a ragged tail; and an infinite
+    # value that every query of the last block sees, of a row of an odd number of blocks too.
+    T = 128 * n_blocks - 45
+    wl = make_custom([T], len(budgets), 1, 128, budgets, seed=560 + n_blocks, name="groups_128_%d" % n_blocks)
+    full_parity(wl)
+    last = 128 * (n_blocks - 1)
+    wl.v[last, 0, 5], wl.v[last, 0, 6] = 0x7f80, 0xff80                # bf16 infinities
+    out = DevicePass(wl).run_all().out_host()
+    assert (out[last:, :, 5] == np.inf).all() and (out[last:, :, 6] == -np.inf).all()
+    assert np.isfinite(np.delete(out[last:], [5, 6], axis=2)).all() and np.isfinite(out[:last]).all()
