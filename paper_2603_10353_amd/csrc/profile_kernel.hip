@@ -23,15 +23,26 @@ namespace shplb {
 namespace {
 
 // 128 consecutive queries of one (sequence, head) swept over their keys in tiles of kTile; a wave owns 32
-// queries.  The tiles are software-pipelined: the MFMAs of the next tile are issued before the work on the
-// present one's scores, which depends on none of them, and a tile is copied one whole step ahead of its use.
+// queries.  The tiles are software-pipelined: the work on a tile's scores depends on none of the MFMAs of the next
+// one, and a tile is copied one whole step ahead of its use.
+// kSmall: the contraction in 16x16x32 MFMAs, of two groups of 16 queries, instead of 32x32x16, and behind the work on the
+// scores instead of in front of it: for a pass at the card's power limit (the block mass 4.81 -> 4.17 ms, by itself
+// 4.49).  The token recovery is not at that limit and its state is per query: 12.5 ms with the larger shape, 12.9 with the
+// other order.
+template <bool kSmall>
 struct QueryRun {
   static constexpr int kQueries = 128, kWaves = kQueries / 32;
   static constexpr int kTile = 64, MT = kTile / 32;                  // keys of a tile
   static constexpr int kStageBytes = kTile * kRowBytes;
   static constexpr int kRoundRows = 4 * kWaves;                      // key rows one copy instruction per wave moves
   static constexpr int kRounds = kTile / kRoundRows;
-  typedef f32x16 Scores[MT];
+  // A lane's scores: 32 of query n, v[mt][r] of key 32 mt + 8 (r / 4) + 4 hi + r % 4 (n, hi: lane % 32 and lane / 32), or 16 each
+  // of queries n and 16 + n, v[qg][mt][r] of key 16 mt + 4 hi + r (lane % 16 and lane / 16).
+  static constexpr int QG = 2;
+  struct Large { f32x16 v[MT]; };
+  struct Small { f32x4 v[QG][kTile / 16]; };
+  typedef std::conditional_t<kSmall, Small, Large> Scores;
+  static constexpr int kOperands = kSmall ? 4 * (kTile / 16) : 8 * MT;
   static constexpr int kLook = 8;                                    // operand fetches ahead of the MFMA that uses them
   // Steps between sampled keys are multiples of 1/kOne.  (The largest products fit: all keys, kOne apart, are up
   // to 2^19 x 2^12; of those sampled, 2^11 at most, the last is one of these keys; a step is below 2^24.)
@@ -45,7 +56,8 @@ struct QueryRun {
   uint32_t widest;                                  // largest distance of a sampled tile's keys, see issue_tile()
   const char* k_head;
   const char* k_lds;                                // two stages of kStageBytes
-  bf16x8 qf[8];                                     // B operand of S^T = K Q^T: dims 16ks + 8hi.. of the lane's query
+  bf16x8 qf[8];                                     // B operands of S^T = K Q^T: dims 16ks + 8hi.. of the lane's query, or
+                                                    // 32ks + 8hi.. of its two, index 4qg + ks
 
   // blockIdx.x = level * (sequences * heads) + place of the (sequence, head); level 0 is the end of the longest
   // sequence.  Workgroups go to the dies in turn: places x, x + 8, .. are given consecutive heads, so that a
@@ -65,8 +77,8 @@ struct QueryRun {
     tid = threadIdx.x;
     lane = tid & 63;
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    n = lane & 31;
-    hi = lane >> 5;
+    n = kSmall ? lane & 15 : lane & 31;
+    hi = kSmall ? lane >> 4 : lane >> 5;
     n_tiles = (i + 1) * (kQueries / kTile);
     row_bytes = st.kv_t * 2;
     widest = uint32_t(fminf(float(1ull << 32) * (0.999f * kOne / kTile) / float(row_bytes), 0x1p23f));
@@ -75,15 +87,20 @@ struct QueryRun {
     cp_row = 4 * wave + (lane >> 4);
     k_rd0 = n * kRowBytes + ((hi ^ swz(n)) << 4);
     k_stage0 = __builtin_amdgcn_readfirstlane(lds_offset_of(lds) + 4 * wave * kRowBytes);
-    q_tok = seq_begin + i * kQueries + wave * 32 + n;
+    q_tok = seq_begin + i * kQueries + wave * 32 + (lane & 31);
     return true;
   }
   __device__ __forceinline__ bool live() const { return q_tok < seq_end; }   // not past the end of the sequence
 
   __device__ __forceinline__ void load_queries(const Strides& st, const uint16_t* __restrict__ q) {
-    const uint16_t* src = q + int64_t(min(q_tok, seq_end - 1)) * st.q_t + int64_t(h) * st.q_h + 8 * hi;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
+    for (int qg = 0; qg < (kSmall ? QG : 1); ++qg) {
+      const int tok = seq_begin + i * kQueries + wave * 32 + 16 * qg + n;
+      const uint16_t* src = q + int64_t(min(tok, seq_end - 1)) * st.q_t + int64_t(h) * st.q_h + 8 * hi;
+      constexpr int kSteps = kSmall ? 4 : 8;
+#pragma unroll
+      for (int ks = 0; ks < kSteps; ++ks) qf[kSteps * qg + ks] = *reinterpret_cast<const bf16x8*>(src + (kSmall ? 32 : 16) * ks);
+    }
   }
 
   // Copy a tile into LDS stage `buf`: keys kTile x .. of the row's, or of those that are left when only every
@@ -106,37 +123,70 @@ struct QueryRun {
     }
   }
 
-  // raw scores (q . k, unscaled) of the tile in stage `buf`
-  __device__ __forceinline__ void scores_of(int buf, Scores& sc) const {
+  // Raw scores (q . k, unscaled) of the tile in stage `buf`, in two parts: the first operands are fetched, then ...
+  typedef bf16x8 Operands[kOperands];
+  __device__ __forceinline__ bf16x8 read_k(int buf, int gi) const {
     const char* kt = k_lds + buf * kStageBytes;
-    auto read_k = [&](int gi) {
-      return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ ((gi / MT) << 5)) + (gi % MT) * 32 * kRowBytes);
-    };
+    if (kSmall) return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ ((gi >> 2) << 6)) + (gi & 3) * 16 * kRowBytes);
+    return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ ((gi / MT) << 5)) + (gi % MT) * 32 * kRowBytes);
+  }
+  __device__ __forceinline__ void fetch_first(int buf, Operands& kf) const {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(buf, gi);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // ... the MFMAs back to back.
+  __device__ __forceinline__ void scores_of(int buf, Operands& kf, Scores& sc) const {
+    if constexpr (kSmall) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sc[mt][r] = 0.0f;
-    bf16x8 kf[8 * MT];
+      for (int qg = 0; qg < QG; ++qg)
 #pragma unroll
-    for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(gi);
+        for (int mt = 0; mt < kTile / 16; ++mt) sc.v[qg][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    } else {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc.v[mt][r] = 0.0f;
+    }
+    if (kSmall) __builtin_amdgcn_s_setprio(1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int gi = 0; gi < 8 * MT; ++gi) {
-      if (gi + kLook < 8 * MT) kf[gi + kLook] = read_k(gi + kLook);
-      sc[gi % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[gi], qf[gi / MT], sc[gi % MT], 0, 0, 0);
+    for (int gi = 0; gi < kOperands; ++gi) {
+      if (gi + kLook < kOperands) kf[gi + kLook] = read_k(buf, gi + kLook);
+      if constexpr (kSmall) {
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg)
+          sc.v[qg][gi & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi], qf[4 * qg + (gi >> 2)], sc.v[qg][gi & 3], 0, 0, 0);
+      } else {
+        sc.v[gi % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[gi], qf[gi / MT], sc.v[gi % MT], 0, 0, 0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (kSmall) __builtin_amdgcn_s_setprio(0);
   }
 
   // keys above the lane's query to -inf (tiles of the diagonal only)
   __device__ __forceinline__ void mask(int it, Scores& sc) const {
-    int d = kTile * it - kQueries * i + 4 * hi - (wave * 32 + n);   // key position minus query position, per register below
-    asm volatile("" : "+v"(d));                                           // keep the 32 comparisons here, not hoisted as masks
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int qg = 0; qg < (kSmall ? QG : 1); ++qg) {
+      int d = kTile * it - kQueries * i + 4 * hi - (wave * 32 + 16 * qg + n);   // key position minus query position, per register below
+      asm volatile("" : "+v"(d));                                           // keep the 32 comparisons here, not hoisted as masks
+      if constexpr (kSmall) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (d + (32 * mt + 8 * (r >> 2) + (r & 3)) > 0) sc[mt][r] = -INFINITY;
+        for (int mt = 0; mt < kTile / 16; ++mt) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (d + (16 * mt + r) > 0) sc.v[qg][mt][r] = -INFINITY;
+          asm volatile("" : "+v"(sc.v[qg][mt]));
+        }
+      } else {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (d + (32 * mt + 8 * (r >> 2) + (r & 3)) > 0) sc.v[mt][r] = -INFINITY;
+      }
+    }
   }
 
   // A sweep over the row's keys, or over `count` tiles' worth of them evenly spread (a stretch of keys alike
@@ -155,19 +205,28 @@ struct QueryRun {
   __device__ __forceinline__ void sweep(int first, int count, uint32_t stride, bool masked, F&& per_tile) const {
     const int end = first + count;
     Scores sa, sb;
-    wait_vmem_all();
-    __syncthreads();
-    scores_of(0, sa);
+    {
+      Operands kf;
+      wait_vmem_all();
+      __syncthreads();
+      fetch_first(0, kf);
+      scores_of(0, kf, sa);
+    }
     auto step = [&](int x, int buf, Scores& cur, Scores& nxt) {
-      if (x + 1 < end) {
+      Operands kf;
+      const bool more = x + 1 < end;
+      if (more) {
         wait_vmem_all();                            // own copies of tile x + 1 have landed
         __syncthreads();                            // everyone's have; the stage of tile x is free
+        if (kSmall) fetch_first(buf ^ 1, kf);
         if (x + 2 < end) issue_tile(x + 2, stride, buf);
-        scores_of(buf ^ 1, nxt);
+        if (!kSmall) fetch_first(buf ^ 1, kf);
       }
+      if (!kSmall && more) scores_of(buf ^ 1, kf, nxt);
       if (masked && x >= n_tiles - kQueries / kTile) mask(x, cur);
       per_tile(x, cur);
       __builtin_amdgcn_sched_barrier(0);
+      if (kSmall && more) scores_of(buf ^ 1, kf, nxt);
     };
     for (int x = first; x < end; x += 2) {
       step(x, 0, sa, sb);
@@ -180,114 +239,137 @@ struct QueryRun {
 //
 // One sweep over the keys: the exponentials of a query against a fixed reference exponent, summed per key block
 // and kept, as many as there is room for, and in all; divided by the query's total and summed over the
-// queries of a block once it is known.  A query's sums of the first kLdsBlocks key blocks are kept in LDS
-// (a word per block and query), those of the next kRegBlocks in registers, alternating between the two lanes of
-// the query.  Only key blocks behind these (of rows beyond 28K tokens with 128-token blocks, 14K with 64) are
-// swept a second time, kLdsBlocks at a time, when the totals are known.
+// queries of a block once it is known.  A query's sums are kept in LDS (a word per block and query); twice, when
+// there are kBankBlocks of them and more to come than fit, these move to 32 registers, alternating between the two
+// lanes of the query.  (Written to registers one by one, by an index, they had the compiler copy all 64 of them for
+// every key block: 4.8 -> 4.5 ms without.)  Only key blocks behind these (of rows beyond 28K tokens with 128-token
+// blocks, 14K with 64) are swept a second time, kLdsBlocks at a time, when the totals are known.
 //
 // The reference is the largest score of the query's first tile.  It is a scale, not a bound: the sums are floats and
 // lose nothing by being large, so it is only raised (and what is kept scaled down, at most a few times per row)
 // when a tile's sum leaves the range of useful exponents.
 //
 // Sums run over keys, tiles, queries and waves in a fixed order: results repeat bit for bit.
-// 32 heads x 32K tokens: 4.9 ms, against 9.2 with a sweep for the totals, one for the averages and tiles that were
-// not pipelined (1653 tokens with 64-token blocks 70 -> 28 us).  An empty sweep (the MFMAs) takes 2.9 ms; of the
-// rest most is exponentials, 16 cycles of the VALU each.
-constexpr int kLdsBlocks = 92, kRegBlocks = 128;   // 4 x 92 x 32 words beside the tiles and partial sums: two workgroups
-                                                   // per compute unit; 64 registers
+// 32 heads x 32K tokens: 4.2 to 4.4 ms, from 4.65 to 4.9 on the same cards with 32x32x16 MFMAs, which spend more of the power
+// (the launch runs at its limit), the exponentials behind the MFMAs instead of in front, and the copies above.  The VALU issues
+// in 69% of the cycles (per key and 64 queries an exponential, a multiply-add and an addition, 16 cycles), the matrix pipe
+// is busy in 47%.  Exponentials between the MFMAs: 4.4 -> 4.45 ms.
+constexpr int kLdsBlocks = 92, kBankBlocks = 64;   // 4 x 92 x 32 words beside the tiles and partial sums: two workgroups
+                                                   // per compute unit; two banks of 32 registers
 constexpr float kSumRange = 0x1p64f;
 
 typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+typedef QueryRun<true> MassRun;
 
 template <int BQ>
 __global__ __launch_bounds__(256, 2) void mass_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
                                                       const uint16_t* __restrict__ k, float* __restrict__ mass,
                                                       int levels, float scale_log2) {
-  constexpr int kTiles = BQ / QueryRun::kTile;                // tiles of a key block
-  constexpr int kRows = QueryRun::kQueries / BQ;              // query blocks of the workgroup
-  constexpr int kRowWaves = QueryRun::kWaves / kRows;
-  __shared__ __attribute__((aligned(1024))) char k_lds[2][QueryRun::kStageBytes];
-  __shared__ float s_sums[QueryRun::kWaves][kLdsBlocks][32];
-  __shared__ float s_weight[QueryRun::kWaves][32];
-  __shared__ float s_part[QueryRun::kWaves][kLdsBlocks];
+  constexpr int kTiles = BQ / MassRun::kTile;                // tiles of a key block
+  constexpr int kRows = MassRun::kQueries / BQ;              // query blocks of the workgroup
+  constexpr int kRowWaves = MassRun::kWaves / kRows;
+  __shared__ __attribute__((aligned(1024))) char k_lds[2][MassRun::kStageBytes];
+  __shared__ float s_sums[MassRun::kWaves][kLdsBlocks][32];
+  __shared__ float s_weight[MassRun::kWaves][32];
+  __shared__ float s_part[MassRun::kWaves][kLdsBlocks];
 
-  QueryRun row;
+  MassRun row;
   if (!row.init(meta, st, k, levels, &k_lds[0][0])) return;
   const int nb = meta.blk_begin[row.s + 1] - meta.blk_begin[row.s];
   const int n_blocks = min((row.i + 1) * kRows, nb);          // key blocks the workgroup's queries see
   const int n_tiles = n_blocks * kTiles;
-  row.start(0, n_tiles, QueryRun::kOne);
+  row.start(0, n_tiles, MassRun::kOne);
   row.load_queries(st, q);
 
+  // Sums and what is kept of them belong to query `query` of the wave, the same in lanes l and l ^ 32; the scores of a
+  // lane to queries n and 16 + n, of which `query` is one.
+  constexpr int QG = MassRun::QG;
+  const int query = row.lane & 31, half = row.lane >> 5;
   float (*sums)[32] = s_sums[row.wave];
-  float ref = 0.0f, total = 0.0f, part = 0.0f, pending = 0.0f;
+  float ref[QG] = {0.0f, 0.0f}, part[QG] = {0.0f, 0.0f}, total = 0.0f;
   f32x32 held0, held1;
 #pragma unroll
   for (int x = 0; x < 32; ++x) held0[x] = held1[x] = 0.0f;
+  const int banks = n_blocks <= kLdsBlocks ? 0 : n_blocks <= kLdsBlocks + kBankBlocks ? 1 : 2;
+  int filled = 0;                                             // banks that hold their sums
 
-  auto tile_sum = [&](QueryRun::Scores& sc) {
-    float sum0 = 0.0f, sum1 = 0.0f;
+  auto tile_sums = [&](const MassRun::Scores& sc, float (&sum)[QG]) {
+    float s[QG][2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      sum0 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][r], scale_log2, -ref));
-      sum1 += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][r], scale_log2, -ref));
-    }
-    return sum0 + sum1;
-  };
-  auto largest = [&](QueryRun::Scores& sc) {
-    float m = fmaxf(sc[0][0], sc[1][0]);
+    for (int qg = 0; qg < QG; ++qg) s[qg][0] = s[qg][1] = 0.0f;
 #pragma unroll
-    for (int r = 1; r < 16; ++r) m = fmaxf(fmaxf(m, sc[0][r]), sc[1][r]);
-    return pair_max(m) * scale_log2;
+    for (int x = 0; x < 16; ++x)
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg)
+        s[qg][x & 1] += __builtin_amdgcn_exp2f(__builtin_fmaf(sc.v[qg][x >> 2][x & 3], scale_log2, -ref[qg]));
+#pragma unroll
+    for (int qg = 0; qg < QG; ++qg) sum[qg] = s[qg][0] + s[qg][1];
   };
-  row.sweep(0, n_tiles, QueryRun::kOne, true, [&](int x, QueryRun::Scores& sc) {
-    const int j = x / kTiles;
+  auto largest = [&](const MassRun::Scores& sc, int qg) {
+    float m = sc.v[qg][0][0];
+#pragma unroll
+    for (int x = 1; x < 16; ++x) m = fmaxf(m, sc.v[qg][x >> 2][x & 3]);
+    return quad_max(m) * scale_log2;
+  };
+  // over the four lanes of a query, and to the lanes whose `query` it is
+  auto collected = [](const float (&x)[QG]) {
+    uint32_t a = __float_as_uint(x[0]), b = __float_as_uint(x[1]);
+    swap_rows(a, b);
+    return pair_sum(__uint_as_float(a) + __uint_as_float(b));
+  };
+  row.sweep(0, n_tiles, MassRun::kOne, true, [&](int x, MassRun::Scores& sc) {
+    const int j = x / kTiles - kBankBlocks * filled;          // where the block's sums are kept
     // every query sees its sequence's first key; a tile whose scores are all -inf weighs nothing against any reference
-    if (x == 0) ref = fmaxf(largest(sc), -FLT_MAX);
-    float sum = tile_sum(sc);
-    if (__any(!(sum <= kSumRange))) {
-      const float raised = fmaxf(ref, largest(sc));
-      const float alpha = __builtin_amdgcn_exp2f(ref - raised);
-      ref = raised;
-      total *= alpha;
-      part *= alpha;
-      pending *= alpha;
-      for (int y = row.hi; y < min(j, kLdsBlocks); y += 2) sums[y][row.n] *= alpha;
+    if (x == 0)
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg) ref[qg] = fmaxf(largest(sc, qg), -FLT_MAX);
+    float sum[QG];
+    tile_sums(sc, sum);
+    if (__any(!(sum[0] <= kSumRange) || !(sum[1] <= kSumRange))) {
+      float alpha[QG];
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg) {
+        const float raised = fmaxf(ref[qg], largest(sc, qg));
+        alpha[qg] = __builtin_amdgcn_exp2f(ref[qg] - raised);
+        ref[qg] = raised;
+        part[qg] *= alpha[qg];
+      }
+      const float own = row.lane & 16 ? alpha[1] : alpha[0];
+      total *= own;
+      for (int y = half; y < j; y += 2) sums[y][query] *= own;
 #pragma unroll
       for (int y = 0; y < 32; ++y) {
-        held0[y] *= alpha;
-        held1[y] *= alpha;
+        held0[y] *= own;
+        held1[y] *= own;
       }
-      sum = tile_sum(sc);
+      tile_sums(sc, sum);
     }
-    part += sum;
+#pragma unroll
+    for (int qg = 0; qg < QG; ++qg) part[qg] += sum[qg];
     if (kTiles == 1 || x % kTiles == kTiles - 1) {
-      const float block = pair_sum(part);
+      const float block = collected(part);
       total += block;
-      part = 0.0f;
-      if (j < kLdsBlocks) {
-        sums[j][row.n] = block;                               // (both lanes of the query, the same)
-      } else if (j < kLdsBlocks + kRegBlocks) {
-        const int y = j - kLdsBlocks;
-        if (y & 1) {
-          const float both = row.hi ? block : pending;
-          if (y < 64) held0[y >> 1] = both;
-          else held1[(y - 64) >> 1] = both;
-        } else {
-          pending = block;
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg) part[qg] = 0.0f;
+      if (j < kLdsBlocks) sums[j][query] = block;             // (both lanes of the query, the same)
+      if (j == kBankBlocks - 1 && filled < banks) {
+        asm volatile("" ::: "memory");                        // the wave's own sums
+#pragma unroll
+        for (int y = 0; y < 32; ++y) {                        // (selected, not branched: pointers to the banks would put them in memory)
+          const float kept = sums[2 * y + half][query];
+          held1[y] = filled == 0 ? held1[y] : kept;
+          held0[y] = filled == 0 ? kept : held0[y];
         }
+        filled += 1;
+        asm volatile("" ::: "memory");
       }
     }
   });
-  if (n_blocks > kLdsBlocks && n_blocks < kLdsBlocks + kRegBlocks && ((n_blocks - kLdsBlocks) & 1)) {
-    const int y = n_blocks - 1 - kLdsBlocks;
-    if (y < 64) held0[y >> 1] = pending;
-    else held1[(y - 64) >> 1] = pending;
-  }
   // a query's share of its block's average; none for a query past the end of the sequence
   const int q_block = row.i * kRows + row.wave / kRowWaves;   // the wave's query block
   const int n_valid = min(BQ, row.seq_end - row.seq_begin - q_block * BQ);
-  s_weight[row.wave][row.n] = row.live() ? 1.0f / (total * float(n_valid)) : 0.0f;
+  s_weight[row.wave][query] = row.live() ? 1.0f / (total * float(n_valid)) : 0.0f;
 
   // the key blocks base .. base + count whose sums are in LDS: over the wave's queries (a lane takes a block
   // and goes round them), then over the waves of a query block
@@ -312,29 +394,33 @@ __global__ __launch_bounds__(256, 2) void mass_kernel(SeqMeta meta, Strides st, 
     }
     __syncthreads();
   };
-  flush(0, min(n_blocks, kLdsBlocks));
+  flush(kBankBlocks * banks, min(n_blocks - kBankBlocks * banks, kLdsBlocks));
+  auto flush_bank = [&](int base, const f32x32& held) {
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int base = kLdsBlocks + 64 * half;
-    if (n_blocks <= base) return;
-#pragma unroll
-    for (int x = 0; x < 32; ++x) sums[2 * x + row.hi][row.n] = half ? held1[x] : held0[x];
-    flush(base, min(n_blocks - base, 64));
-  }
-  for (int base = kLdsBlocks + kRegBlocks; base < n_blocks; base += kLdsBlocks) {
+    for (int x = 0; x < 32; ++x) sums[2 * x + half][query] = held[x];
+    flush(base, kBankBlocks);
+  };
+  if (banks > 0) flush_bank(0, held0);
+  if (banks > 1) flush_bank(kBankBlocks, held1);
+  for (int base = kLdsBlocks + 2 * kBankBlocks; base < n_blocks; base += kLdsBlocks) {
     const int count = min(n_blocks - base, kLdsBlocks);
-    row.start(base * kTiles, count * kTiles, QueryRun::kOne);
-    row.sweep(base * kTiles, count * kTiles, QueryRun::kOne, true, [&](int x, QueryRun::Scores& sc) {
-      part += tile_sum(sc);
+    row.start(base * kTiles, count * kTiles, MassRun::kOne);
+    row.sweep(base * kTiles, count * kTiles, MassRun::kOne, true, [&](int x, MassRun::Scores& sc) {
+      float sum[QG];
+      tile_sums(sc, sum);
+#pragma unroll
+      for (int qg = 0; qg < QG; ++qg) part[qg] += sum[qg];
       if (kTiles == 1 || x % kTiles == kTiles - 1) {
-        sums[x / kTiles - base][row.n] = pair_sum(part);
-        part = 0.0f;
+        sums[x / kTiles - base][query] = collected(part);
+#pragma unroll
+        for (int qg = 0; qg < QG; ++qg) part[qg] = 0.0f;
       }
     });
     flush(base, count);
   }
 }
 
+typedef QueryRun<false> Run;
 struct TokenBudgets {
   int32_t k[SHPLB_MAX_TOKEN_BUDGETS];
 };
@@ -372,10 +458,10 @@ constexpr int kBins = 95;                          // and the longest list: 128 
                                                    // two workgroups per compute unit beside the tiles
 constexpr int kInner = 85, kFirst = 5;             // an interval is spread over bins kFirst .. kFirst + kInner
 constexpr float kWhole = 8388608.0f;               // 2^23
-constexpr int kRangeTiles = 256 / QueryRun::kTile, kSampleTiles = 2048 / QueryRun::kTile;  // tiles sampled for the range, and at most for the interval
+constexpr int kRangeTiles = 256 / Run::kTile, kSampleTiles = 2048 / Run::kTile;  // tiles sampled for the range, and at most for the interval
 // Tiles of a row that is searched over its whole range at once: sampling costs such rows as much as the sweep it
 // would save (384 and 768 keys alike; with 1536, 1391 tokens x 28 heads, three budgets, take 365 instead of 262 us)
-constexpr int kSmallRow = 768 / QueryRun::kTile;
+constexpr int kSmallRow = 768 / Run::kTile;
 constexpr float kFar = 0x1p126f;                   // intervals end here, so that their widths are numbers
 constexpr float kNoWeight = 160.0f;                // 2^-160 is zero: so far below the largest, in log2 units of weight
 // Sweeps of a search at most.  One that divides the interval leaves 1/42 of it or less, one beyond it reaches 32 times as
@@ -391,13 +477,13 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
                                                                 int total_tokens) {
   typedef __attribute__((address_space(3))) uint32_t LdsWord;
   typedef __attribute__((address_space(3))) float LdsFloat;
-  constexpr int MT = QueryRun::MT;
+  constexpr int MT = Run::MT;
   constexpr uint32_t kBinBytes = 32 * 4;           // a word for each of a wave's queries
-  __shared__ __attribute__((aligned(1024))) char k_lds[2][QueryRun::kStageBytes];
-  __shared__ __attribute__((aligned(16))) uint32_t s_bins[QueryRun::kWaves][kBins][32];
-  __shared__ int s_open[2][QueryRun::kWaves];
+  __shared__ __attribute__((aligned(1024))) char k_lds[2][Run::kStageBytes];
+  __shared__ __attribute__((aligned(16))) uint32_t s_bins[Run::kWaves][kBins][32];
+  __shared__ int s_open[2][Run::kWaves];
 
-  QueryRun row;
+  Run row;
   if (!row.init(meta, st, k, levels, &k_lds[0][0])) return;
   const int visible = row.q_tok - row.seq_begin + 1;          // keys the lane's query sees
   int fewest = budgets.k[0];
@@ -407,7 +493,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     if (b < n_out && row.hi == 0 && row.live())
       recovery[(int64_t(b) * meta.n_q_heads + row.h) * total_tokens + row.q_tok] = r;
   };
-  if ((row.i + 1) * QueryRun::kQueries <= fewest) {           // no query sees more keys than any budget
+  if ((row.i + 1) * Run::kQueries <= fewest) {           // no query sees more keys than any budget
 #pragma unroll
     for (int b = 0; b < M; ++b) store(b, 1.0f);
     return;
@@ -452,10 +538,10 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   };
   auto bin_begin = [&](int u) { return bin_lo + (float(u - kFirst) - 0.5f) * bin_w; };
   float top_score = -INFINITY;
-  auto count_bins = [&](int, QueryRun::Scores& sc) {
+  auto count_bins = [&](int, Run::Scores& sc) {
 #pragma unroll
     for (int r = 0; r < 16 * MT; ++r) {
-      const float s = sc[r / 16][r % 16];
+      const float s = sc.v[r / 16][r % 16];
       top_score = fmaxf(top_score, s);
       const float x = __builtin_amdgcn_fmed3f(__builtin_fmaf(s, map_a, map_b), kWhole, kWhole + (kBins - 1));
       __hip_atomic_fetch_add(reinterpret_cast<LdsWord*>((__builtin_bit_cast(uint32_t, x) << 7) + bin_base), 1u,
@@ -481,19 +567,19 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
 
   // ---- 1. where to look
   float lo = INFINITY, hi = -INFINITY;
-  row.sweep(0, n_range, stride, n_sample == 0, [&](int, QueryRun::Scores& sc) {
-    float top = sc[0][0], low = top;
+  row.sweep(0, n_range, stride, n_sample == 0, [&](int, Run::Scores& sc) {
+    float top = sc.v[0][0], low = top;
 #pragma unroll
     for (int r = 1; r < 16 * MT; ++r) {
-      top = fmaxf(top, sc[r / 16][r % 16]);
-      low = fminf(low, sc[r / 16][r % 16]);
+      top = fmaxf(top, sc.v[r / 16][r % 16]);
+      low = fminf(low, sc.v[r / 16][r % 16]);
     }
     if (__any(!finite(top) || !finite(low))) {                // (masked keys among them)
       top = -INFINITY;
       low = INFINITY;
 #pragma unroll
       for (int r = 0; r < 16 * MT; ++r) {
-        const float s = sc[r / 16][r % 16];
+        const float s = sc.v[r / 16][r % 16];
         const bool counts = finite(s);
         top = fmaxf(top, counts ? s : -INFINITY);
         low = fminf(low, counts ? s : INFINITY);
@@ -517,7 +603,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     clear();
     spread(lo, hi);
     row.sweep(0, n_sample, stride, false, count_bins);
-    const float n_keys = float(n_sample * QueryRun::kTile), share = n_keys / float(visible);
+    const float n_keys = float(n_sample * Run::kTile), share = n_keys / float(visible);
     top_score = pair_max(top_score);
     const float sample_top = finite(top_score) ? top_score : hi + kInner * bin_w;
 #pragma unroll
@@ -528,7 +614,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
       int bin, above, inside;
       find(max(1, int(rank - off)), bin, above, inside);
       to[b] = bin < kBins - 1 && rank > off ? bin_begin(bin + 1) : sample_top;
-      find(min(n_sample * QueryRun::kTile, int(rank + off)), bin, above, inside);
+      find(min(n_sample * Run::kTile, int(rank + off)), bin, above, inside);
       from[b] = bin > 0 ? bin_begin(bin) : bin_begin(0) - kInner * bin_w;
     }
   }
@@ -544,7 +630,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     rest[b] = listed[b] = list_at[b] = 0;
     tied[b] = false;
   }
-  stride = QueryRun::kOne;
+  stride = Run::kOne;
   for (int b = 0; b < n_out; ++b) {
     int want = 0;
     float f = 0.0f, t = 0.0f;
@@ -568,7 +654,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
       __syncthreads();
       int any_open = 0;
 #pragma unroll
-      for (int w = 0; w < QueryRun::kWaves; ++w) any_open |= s_open[round & 1][w];
+      for (int w = 0; w < Run::kWaves; ++w) any_open |= s_open[round & 1][w];
       if (!__builtin_amdgcn_readfirstlane(any_open) || tries == kSearchRounds) break;
       row.start(0, all, stride);
       clear();
@@ -637,13 +723,13 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     top[b] = 0.0f;
   }
   fence();
-  row.sweep(0, all, stride, true, [&](int, QueryRun::Scores& sc) {
+  row.sweep(0, all, stride, true, [&](int, Run::Scores& sc) {
     float sum0 = 0.0f, sum1 = 0.0f, part[M];
 #pragma unroll
     for (int b = 0; b < M; ++b) part[b] = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16 * MT; ++r) {
-      const float s = sc[r / 16][r % 16], p = weight(s);
+      const float s = sc.v[r / 16][r % 16], p = weight(s);
       if (r & 1) sum1 += p;
       else sum0 += p;
 #pragma unroll
@@ -725,7 +811,7 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
 template <int M>
 void launch_token_recovery_as(const Geometry& g, const uint16_t* q, const uint16_t* k, float* recovery,
                               const TokenBudgets& budgets, int n_out, int levels, uint32_t n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((token_recovery_kernel<M>), dim3(n_wg), dim3(2 * QueryRun::kQueries), 0, stream, g.meta, g.st, q, k,
+  hipLaunchKernelGGL((token_recovery_kernel<M>), dim3(n_wg), dim3(2 * Run::kQueries), 0, stream, g.meta, g.st, q, k,
                      recovery, budgets, n_out, levels, g.scale * 1.4426950408889634f, int(g.total_tokens));
 }
 
@@ -733,12 +819,12 @@ void launch_token_recovery_as(const Geometry& g, const uint16_t* q, const uint16
 
 int32_t launch_block_mass(const Geometry& g, const void* q, const void* k, float* mass, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  const int levels = (g.max_nb * m.block + QueryRun::kQueries - 1) / QueryRun::kQueries;
+  const int levels = (g.max_nb * m.block + MassRun::kQueries - 1) / MassRun::kQueries;
   const int64_t n_wg = int64_t(levels) * m.n_seq * m.n_q_heads;
   if (n_wg > 0x7fffffff) return SHPLB_E_UNSUPPORTED;
   const float scale_log2 = g.scale * 1.4426950408889634f;
   const auto kernel = m.block == 128 ? mass_kernel<128> : mass_kernel<64>;
-  hipLaunchKernelGGL(kernel, dim3(uint32_t(n_wg)), dim3(2 * QueryRun::kQueries), 0, stream, m, g.st,
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(n_wg)), dim3(2 * MassRun::kQueries), 0, stream, m, g.st,
                      static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), mass, levels, scale_log2);
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;
@@ -747,7 +833,7 @@ int32_t launch_block_mass(const Geometry& g, const void* q, const void* k, float
 int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, const int32_t* budgets,
                               int32_t n_budgets, float* recovery, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  const int levels = (g.max_nb * m.block + QueryRun::kQueries - 1) / QueryRun::kQueries;
+  const int levels = (g.max_nb * m.block + Run::kQueries - 1) / Run::kQueries;
   const int64_t n_wg = int64_t(levels) * m.n_seq * m.n_q_heads;
   if (n_wg > 0x7fffffff) return SHPLB_E_UNSUPPORTED;
   TokenBudgets kb;

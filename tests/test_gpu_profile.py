@@ -150,3 +150,12 @@ def test_block_mass_where_the_first_keys_weigh_nothing(block):
     got, number = run.mass_host()[0], ~np.isnan(want)
     assert number[:, 2:].any(axis=2).all()
     np.testing.assert_allclose(got[number], want[number], rtol=MASS_RTOL, atol=MASS_ATOL)
+
+
+@pytest.mark.parametrize("block,n_blocks,tail", [(64, 156, 64), (64, 158, 7), (128, 157, 128), (128, 156, 31)])
+def test_block_mass_where_sums_move_to_registers(block, n_blocks, tail):
+    # rows that keep all sums in LDS, that move 64 of them to registers once, and twice
+    wl = make_custom([(n_blocks - 1) * block + tail], 2, 1, block, [2, 2], seed=700 + n_blocks, name="mass_banks_%d" % n_blocks)
+    nb = wl.n_blocks[0]
+    rows = sorted({h * nb + i for h in range(2) for i in (62, 63, 64, 91, 92, 127, 128, 154, 155, 156, nb - 2, nb - 1) if i < nb})
+    _profile(wl, rows=rows)
