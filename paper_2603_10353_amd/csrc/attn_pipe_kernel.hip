@@ -837,8 +837,9 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // over 8000 tokens 148 -> 118, 256 rows of 16 blocks 50.4 -> 44.9, of 8 34.0 -> 33.5, 224 of 7 32.2 -> 31.5; 160 of 5
   // 27.0 -> 27.8 and 64 of 2 24.0 -> 24.5, for the groups combine at some 1.5 us: from 7 blocks on.  (Of 16 blocks with
   // two or three selected 28.5 -> 30.4: the selection is not known here.)  512 rows: two rows a compute unit fill it, 41 -> 48.
-  plan.key_groups = g.meta.block == 64 ? (g.rows <= 2 * cus ? 2 : 1)
-                                       : (g.rows <= cus && g.max_nb >= 7 && slot_capacity == 0 ? 2 : 1);
+  // Rows that may be cut go the same way: an uncut row has the same result in either entry point (pieces take the
+  // advantage: 4/1 heads x 8000 with a dense one 99 -> 104 us, 2/1 x 16384 171 -> 176, 8/2 x 4096 59.4 -> 57.5, 16/4 x 2048 60.5 -> 56.8).
+  plan.key_groups = g.meta.block == 64 ? (g.rows <= 2 * cus ? 2 : 1) : (g.rows <= cus && g.max_nb >= 7 ? 2 : 1);
   plan.grid = n_wg / plan.key_groups;
   // No more rows than workgroups and none to be cut: there is nothing to order, every row gets a workgroup
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).

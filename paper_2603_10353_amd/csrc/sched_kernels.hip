@@ -24,7 +24,7 @@
 // last combines them (count_piece() and merge_row() in attn_common.h).  Slots and counter
 // entries are handed out in the same arbitrary order; what is computed does not depend on it.
 //
-// Launches without splitting that have no more rows than workgroups skip all this: see row_item() in
+// Launches without splitting that have no more rows than workgroups skip all this: see row_place() in
 // attn_pipe_kernel.hip.
 //
 // What bounds it: a chain of dependent memory round trips (geometry, row pointer, first
