@@ -337,7 +337,8 @@ __global__ __launch_bounds__(256, 2) void mass_kernel(SeqMeta meta, Strides st, 
       }
       const float own = row.lane & 16 ? alpha[1] : alpha[0];
       total *= own;
-      for (int y = half; y < j; y += 2) sums[y][query] *= own;
+      // (blocks behind the kept ones keep counting j: they are not in LDS, and are swept again against the final reference)
+      for (int y = half; y < min(j, kLdsBlocks); y += 2) sums[y][query] *= own;
 #pragma unroll
       for (int y = 0; y < 32; ++y) {
         held0[y] *= own;

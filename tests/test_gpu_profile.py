@@ -159,3 +159,58 @@ def test_block_mass_where_sums_move_to_registers(block, n_blocks, tail):
     nb = wl.n_blocks[0]
     rows = sorted({h * nb + i for h in range(2) for i in (62, 63, 64, 91, 92, 127, 128, 154, 155, 156, nb - 2, nb - 1) if i < nb})
     _profile(wl, rows=rows)
+
+
+# Key blocks 0 .. 219 of a long row are kept (64 each in two banks of registers, 92 in LDS), those behind them swept again.
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("raises_at, wave", [(50, 0), (100, 1), (130, 2), (219, 0), (225, 0), (250, 3), (310, 1)])
+def test_block_mass_reference_raised_in_long_rows(block, raises_at, wave):
+    # Only the queries of one of the four waves of a workgroup see the raise: a token 46 nats above the first tile's
+    # scores (2^66), where tokens of 43 nats (2^62) among the kept sums of every kind, and behind them, do not raise the
+    # reference and have some 4% of the weight each.  The other waves' queries give all of these no weight, and their
+    # sums may not follow.  Scores of up to 46 nats: fp32 rounding of 2^-24 of that, well inside MASS_RTOL.
+    nb = 320
+    T = nb * block - 3
+    rng = np.random.default_rng(block + raises_at)
+    wl = make_custom([T], 2, 1, block, [2, 2], seed=9, name="mass_raised_b%d_at%d_wave%d" % (block, raises_at, wave))
+    q, k = rng.standard_normal((T, 2, 128)).astype(np.float32), rng.standard_normal((T, 1, 128)).astype(np.float32)
+    q[:, :, 9] = np.where(np.arange(T) // 32 % 4 == wave, 4.0, -4.0)[:, None]
+    k[:64] *= 0.05
+    k[:, :, 9] = 0.0
+    for b, height in [(x, 121.5) for x in (37, 101, 129, 200, 240)] + [(raises_at, 130.0)]:
+        k[b * block + 7] = 0.0
+        k[b * block + 7, :, 9] = height
+    wl.q, wl.k = bf16_bits_from_f32(q), bf16_bits_from_f32(k)
+    rows = sorted({h * nb + i for h in range(2) for i in (raises_at - 1, raises_at, raises_at + 1, 221, 230, nb - 2, nb - 1)})
+    _profile(wl, rows=rows)
+
+
+@pytest.mark.parametrize("head", [0, 1])
+def test_block_mass_infinite_score_leaves_other_queries_alone(head):
+    # One infinite key at block 240: the queries of every other block of one head, which share a workgroup with those of the
+    # block behind them, have a score of +inf there and no numbers; the others' score is -inf.
+    from harness import DevicePass
+    block, nb = 64, 256
+    T = nb * block
+    wl = make_custom([T], 2, 1, block, [2, 2], seed=10, name="mass_infinite_key_%d" % head)
+    rng = np.random.default_rng(10 + head)
+    q, k = rng.standard_normal((T, 2, 128)).astype(np.float32), rng.standard_normal((T, 1, 128)).astype(np.float32)
+    q[:, :, 9] = -1.0
+    q[np.arange(T) // block % 2 == 0, head, 9] = 1.0
+    k[:, 0, 9] = 0.0
+    k[240 * block, 0, 9] = np.inf
+    wl.q, wl.k = bf16_bits_from_f32(q), bf16_bits_from_f32(k)
+    print("case", wl.name, flush=True)
+    run = DevicePass(wl)
+    run.mass_step()
+    torch.cuda.synchronize()
+    got = run.mass_host()[0]
+    tri = np.tri(nb, dtype=bool)
+    sums = np.where(tri, got, 0.0).sum(axis=2)
+    lost = np.zeros((2, nb), bool)
+    lost[head, 240::2] = True
+    np.testing.assert_allclose(sums[~lost], 1.0, rtol=0, atol=2e-5)
+    rows = sorted({h * nb + i for h in range(2) for i in (240, 241, 243, 249, nb - 2, nb - 1) if not lost[h, i]})
+    want = orc.block_mass(wl.q, wl.k, wl.cu_seqlens, block, rows=rows)[0]
+    number = ~np.isnan(want)
+    np.testing.assert_allclose(got[number], want[number], rtol=MASS_RTOL, atol=MASS_ATOL)
