@@ -24,11 +24,11 @@
  *   - Device work is enqueued on `stream` (a hipStream_t passed as void*, NULL =
  *     the default stream) and is asynchronous; outputs are bit-identical from run
  *     to run (each work item owns its output rows; scheduling order never changes
- *     results).  The order in which an attention row's sums are taken depends on the size
- *     of the call: where rows are few (64-token blocks: up to two per compute unit of the
- *     device, 512; 128-token blocks: up to one, 256, and a sequence of 7 blocks or more), two
- *     groups of waves share a row and add up at the end, so a sequence alone and inside a
- *     larger call agree up to rounding.
+ *     results).  With 64-token blocks the order in which an attention row's sums are
+ *     taken depends on the size of the call: up to two rows per compute unit of the
+ *     device (512 rows), two groups of waves share a row and add up at the end, so a
+ *     sequence alone and inside a larger call agree up to rounding.  With 128-token
+ *     blocks its output and denominators are the same, bit for bit.
  *   - Tensors are token-major: Q is [T, n_q_heads, head_dim] bf16 with element
  *     strides (q_stride_t, q_stride_h, 1); K and V are [T, n_kv_heads, head_dim]
  *     bf16 with strides (kv_stride_t, kv_stride_h, 1).  T = cu_seqlens[n_seq].

@@ -169,8 +169,8 @@ __device__ __forceinline__ bool count_piece(const SplitBuffers& sb, int pieces, 
 
 // Combine the pieces of one row into the output.  Two passes, so that few dependent memory round
 // trips remain: first one thread per query turns the pieces' (m_c, l_c) into weights
-// w_c / sum w_c l_c in LDS, then every thread accumulates its 16 output chunks piece by piece, the 16
-// loads of a piece in flight together.  Kept out of line and called when nothing of the attention
+// w_c / sum w_c l_c in LDS, then every thread accumulates its output chunks (16, or 8) piece by piece,
+// the loads of a piece in flight together.  Kept out of line and called when nothing of the attention
 // loop is live any more: inside that loop it cost the loop its register allocation (59 spilled
 // registers against 4).
 //   out_row: output of the row's first query (head applied); lse_row: likewise, or null;
@@ -207,8 +207,8 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
   }
   __syncthreads();
   // pass 2: the slots hold O in the order the attention kernels keep it in registers (slot_chunk()):
-  // chunk e = ((wave * 2 + qg) * 8 + dt) * 64 + lane is dims 16 dt + 4 (lane / 16) .. +3 of query
-  // 32 wave + 16 qg + lane % 16.  A thread owns chunks threadIdx.x + THREADS * u; a wave reads 1 KB runs.
+  // chunk e = (queries * 8 + dt) * 64 + lane is dims 16 dt + 4 (lane / 16) .. +3 of query
+  // 16 queries + lane % 16.  A thread owns chunks threadIdx.x + THREADS * u; a wave reads 1 KB runs.
   constexpr int kChunks = BQ * (kHeadDim / 4) / THREADS;
   f32x4 acc[kChunks];
   const SlotBuffer slots = slot_buffer(part_o, pieces * kSlotFloatsO);
@@ -240,10 +240,10 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
   }
 }
 
-// Where lane `lane` of wave `wave` keeps its four accumulator values of query group qg and dim tile dt in a slot: the
+// Where lane `lane` of a wave keeps its four accumulator values of dim tile dt of a row's queries 16 queries .. +15 in a slot: the
 // 64 lanes of a wave write one run of 1 KB (full cache lines, which write-through stores need).
-__device__ __forceinline__ int slot_chunk(int wave, int qg, int dt, int lane) {
-  return 4 * ((((wave * 2 + qg) * 8 + dt) << 6) + lane);
+__device__ __forceinline__ int slot_chunk(int queries, int dt, int lane) {
+  return 4 * (((queries * 8 + dt) << 6) + lane);
 }
 
 __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {

@@ -64,8 +64,14 @@
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
 //
 // KS = 2: two groups of waves share a row, each with every other selected block, and combine their
-// results in LDS (launches of few rows, see plan_attention()).  Where the groups share SIMDs (kPingPong) they are kept
-// half a step apart by a second barrier: one group's MFMAs run against the other's softmax and copies.
+// results in LDS (launches of few 64-token rows, see plan_attention()).
+//
+// QS = 2: two groups of four waves share a 128-token row's queries, 16 a wave (launches of no more rows than compute units).
+// Both work on the same tiles, group 1 half a step behind, kept there by a second barrier in the middle of a step: one
+// group's MFMAs run against the other's softmax.  Group 1 issues the copies, at the start of its step t like above: that is
+// the middle of group 0's, when both are done with K(t) and V(t-1).  What it waits for at the start of its next step
+// is K(t+2) and V(t+1), which group 0 first reads behind that same barrier, in the second half of its step t+1.  Nothing a
+// query's sums are made of or their order depends on QS.
 #include <type_traits>
 
 #include "attn_common.h"
@@ -174,23 +180,25 @@ __device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
 }
 
 // BQ: tokens per block.  KS: groups of BQ/32 waves that share a row, each with every KS-th selected block.
-template <int BQ, int KS>
-__global__ __launch_bounds__(64 * KS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int BQ, int KS, int QS>
+__global__ __launch_bounds__(64 * KS * QS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
   static_assert(KS == 1 || KS == 2, "an item's record names its first two blocks");
-  constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each
-  constexpr int kThreads = 64 * KS * kWaves;
+  static_assert(QS == 1 || (QS == 2 && KS == 1), "a row is shared by keys or by queries");
+  constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each, or 16
+  constexpr int kThreads = 64 * KS * QS * kWaves;
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
-  constexpr int QG = 2, MT = KT / 16;                // 16-query and 16-key MFMA tiles of a tile's scores
+  constexpr int QG = 2 / QS, MT = KT / 16;                // 16-query and 16-key MFMA tiles of a tile's scores
   constexpr int kTileBytes = KT * kRowBytes;
   constexpr int kRoundRows = 4 * kWaves;             // rows one round of copies moves (4 per wave)
   constexpr int kRounds = KT / kRoundRows;
   constexpr int kQK = 4 * MT;                        // K operands of a tile's first contraction, index MT*ks + mt ...
   constexpr int kPV = 8 * (KT / 32);                 // ... V operands of its second, index 8*gq + dt: QG MFMAs each
-  constexpr int kLook = KS > 1 ? 4 : 8;              // LDS operand fetches run this many operands ahead (12: no change)
+  constexpr int kLook = KS * QS > 1 ? 4 : 8;         // LDS operand fetches run this many operands ahead (8: 12 no change.  Of
+                                                     // rows shared by two groups 1/1 heads x 20000 take 266 us with 4, 281 with
+                                                     // 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8)
   constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
-  constexpr bool kPingPong = KS * kWaves > 4;        // the groups share SIMDs
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
 
   // stages of group g: K tiles at (4g + 0, 1) * kTileBytes, V tiles at (4g + 2, 3) * kTileBytes
@@ -203,7 +211,9 @@ void attn_pipe_kernel(AttnArgs) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = KS > 1 ? wave_all / kWaves : 0, wave = KS > 1 ? wave_all % kWaves : wave_all;
+  const int team = KS * QS > 1 ? wave_all / kWaves : 0, wave = KS * QS > 1 ? wave_all % kWaves : wave_all;
+  const int grp = KS > 1 ? team : 0, q_grp = QS > 1 ? team : 0;         // group of waves, by keys or by queries
+  const int q_wave = 16 * QG * (q_grp * kWaves + wave);                 // the wave's first query
   const int n = lane & 15, hi = lane >> 4;
   const int64_t row_bytes = args->st.kv_t * 2;
   const float scale_log2 = args->scale_log2;
@@ -335,7 +345,7 @@ void attn_pipe_kernel(AttnArgs) {
     const uint16_t* src[QG];
 #pragma unroll
     for (int qg = 0; qg < QG; ++qg) {
-      const int tok = min(it.seq_begin + it.q_block * BQ + wave * 32 + 16 * qg + n, it.seq_end - 1);
+      const int tok = min(it.seq_begin + it.q_block * BQ + q_wave + 16 * qg + n, it.seq_end - 1);
       src[qg] = a->q + int64_t(tok) * a->st.q_t + int64_t(it.head) * a->st.q_h + 8 * hi;
     }
 #pragma unroll
@@ -343,25 +353,26 @@ void attn_pipe_kernel(AttnArgs) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) qf[qg][ks] = *reinterpret_cast<const bf16x8*>(src[qg] + 32 * ks);
   };
+  const std::true_type yes{};
+  const std::false_type no{};
+  const bool copies = QS == 1 || q_grp == 1;         // of query groups the later one copies, for both (see the header)
   auto start_item = [&](auto copies_c, auto queries_c) {
     constexpr bool kCopies = decltype(copies_c)::value, kQueries = decltype(queries_c)::value;
     ArgsPtr a = reload(args);
     k_head = reinterpret_cast<const char*>(a->k + int64_t(it.kv_head) * a->st.kv_h);
     v_head = reinterpret_cast<const char*>(a->v + int64_t(it.kv_head) * a->st.kv_h);
-    if (kCopies) {
+    if (kCopies && copies) {
       locate(it.first_block, 0);
       issue(k_head, k_stage0);
     }
     if (kQueries) load_queries(a);
-    if (kCopies) {
+    if (kCopies && copies) {
       issue(v_head, v_stage0);
       locate(it.first_block, 1);
       issue(k_head, k_stage0 + kTileBytes);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  const std::true_type yes{};
-  const std::false_type no{};
   // the group's own first block
   auto own_first = [&]() {
     if (KS > 1 && grp == 1) it.first_block = it.second_block;
@@ -430,7 +441,7 @@ void attn_pipe_kernel(AttnArgs) {
         // key position minus query position, up to the part that depends on the register: taken
         // through an opaque move so that the comparisons are made here, on the rare diagonal
         // tile, instead of being hoisted out of the item loop into 64 scalar registers of masks
-        int d = all ? BQ : KT * half + 4 * hi - (wave * 32 + 16 * qg + n);
+        int d = all ? BQ : KT * half + 4 * hi - (q_wave + 16 * qg + n);
         asm volatile("" : "+v"(d));
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -477,7 +488,7 @@ void attn_pipe_kernel(AttnArgs) {
 
     // ---- S(0).  (The item's copies have landed in this wave: see the end of the loop.)
     Scores sc_a, sc_b;
-    if (kPingPong && grp == 1) __builtin_amdgcn_s_barrier();   // half a step behind group 0, which waits at the end
+    if (QS > 1 && q_grp == 1) __builtin_amdgcn_s_barrier();   // half a step behind group 0, which waits at the end
     __syncthreads();
     {
       bf16x8 kf[kQK];
@@ -530,18 +541,23 @@ void attn_pipe_kernel(AttnArgs) {
       if (kHasNext) clear_scores(sc_nxt);
 
       // ---- the first LDS operands, and the copies of this step
-      if (kHasNext) {
+      auto fetch_first = [&]() {
+        if (kHasNext) {
 #pragma unroll
-        for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(kn, gi);
-      } else {
+          for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(kn, gi);
+        } else {
 #pragma unroll
-        for (int gi = 0; gi < kLook; ++gi) vf[gi] = read_v(vc, gi);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (kHasNext) issue(v_head, v_stage0 + (kStage ^ 1) * kTileBytes);
-      if constexpr (kPlace == kMid) {
-        locate(jk, kStage);
-        issue(k_head, k_stage0 + kStage * kTileBytes);
+          for (int gi = 0; gi < kLook; ++gi) vf[gi] = read_v(vc, gi);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      if constexpr (QS == 1) fetch_first();
+      if (kHasNext && copies) {
+        issue(v_head, v_stage0 + (kStage ^ 1) * kTileBytes);
+        if constexpr (kPlace == kMid) {
+          locate(jk, kStage);
+          issue(k_head, k_stage0 + kStage * kTileBytes);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
 
@@ -554,7 +570,7 @@ void attn_pipe_kernel(AttnArgs) {
 #pragma unroll
         for (int qg = 0; qg < QG; ++qg) sum[qg][0] = sum[qg][1] = 0.0f;
 #pragma unroll
-        for (int u = 0; u < 4 * MT; ++u) {            // two probabilities of a query group, the groups in turn
+        for (int u = 0; u < 2 * QG * MT; ++u) {       // two probabilities of a query group, the groups in turn
           const int qg = u % QG, mt = u / (2 * QG), c = u / QG % 2;
           const float m_use = m_ref[qg] == -INFINITY ? 0.0f : m_ref[qg];
           const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc_cur[qg][mt][2 * c], scale_log2, -m_use));
@@ -570,11 +586,14 @@ void attn_pipe_kernel(AttnArgs) {
       // The reference m_ref was fixed by earlier tiles.  It is too low for this tile exactly
       // when a probability came out large, and then the tile's row sum is large: no maximum
       // over the scores is needed to notice.  In that (rare) case take the tile's true
-      // maximum, raise the reference, rescale O and l, and redo the tile's probabilities.
-      if (__any(!(rs[0] <= kSumLimit) || !(rs[1] <= kSumLimit))) {
+      // maximum, raise the reference, rescale O and l, and redo the tile's probabilities.  (For 16 queries at a time,
+      // so that what a row comes to does not depend on how many a wave has.)
+      auto too_low = [&](int qg) { return !(rs[qg] <= kSumLimit); };
+      if (__any(too_low(0) || too_low(QG - 1))) {
 #pragma unroll
         for (int qg = 0; qg < QG; ++qg) {
-          const float m_new = fmaxf(m_ref[qg], quad_max(tile_max(sc_cur, qg)) * scale_log2);
+          const float m_tile = quad_max(tile_max(sc_cur, qg)) * scale_log2;
+          const float m_new = QG == 1 || __any(too_low(qg)) ? fmaxf(m_ref[qg], m_tile) : m_ref[qg];
           const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_ref[qg] - m_new);
           m_ref[qg] = m_new;
           l_run[qg] *= alpha;
@@ -589,9 +608,13 @@ void attn_pipe_kernel(AttnArgs) {
 
       // ---- S(t+1): its MFMAs back to back (the operands of the second contraction are
       // fetched behind the last K operands)
-      if constexpr (kPingPong) {
+      if constexpr (QS > 1) {
+        // (group 1 has waited for the copies of K(t+1) and V(t) in front of the barrier that is group 0's this one)
+        asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
+        fetch_first();
       }
       __builtin_amdgcn_s_setprio(1);
       __builtin_amdgcn_sched_barrier(0);
@@ -644,9 +667,9 @@ void attn_pipe_kernel(AttnArgs) {
     float l_tot[QG];
 #pragma unroll
     for (int qg = 0; qg < QG; ++qg) l_tot[qg] = quad_sum(l_run[qg]);
+    if (QS > 1 && q_grp == 0) __builtin_amdgcn_s_barrier();
     auto own = [&](int dt) { return KS == 1 || dt / (8 / KS) == grp; };   // dim tiles a group ends up with
     if constexpr (KS > 1) {
-      if (kPingPong && grp == 0) __builtin_amdgcn_s_barrier();
       __syncthreads();                               // every wave is done with the stages
       // The groups combine their partial results (the softmax of Eq. 1 over the union of their keys): group g
       // ends up with the dims 16 dt .. of the dt's that are its own.
@@ -708,7 +731,7 @@ void attn_pipe_kernel(AttnArgs) {
     }
 
     // ---- normalise and store: lane holds, for its queries, dims 16dt + 4hi + r
-    int q_in = wave * 32 + n;                        // + 16 qg
+    int q_in = q_wave + n;                           // + 16 qg
     asm volatile("" : "+v"(q_in));                   // output addresses are made here, not carried through the loop
     ArgsPtr a = reload(args);
     const int q0 = cur.seq_begin + cur.q_block * BQ;
@@ -721,7 +744,7 @@ void attn_pipe_kernel(AttnArgs) {
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt)
           if (own(dt)) {
-            float* dst = part + slot_chunk(wave, qg, dt, lane);
+            float* dst = part + slot_chunk(q_wave / 16 + qg, dt, lane);
             slot_store(dst, acc_o[qg][dt][0], acc_o[qg][dt][1]);
             slot_store(dst + 2, acc_o[qg][dt][2], acc_o[qg][dt][3]);
           }
@@ -772,7 +795,7 @@ void attn_pipe_kernel(AttnArgs) {
       // guide, memory model of gfx6 to gfx9 and of gfx942; flat accesses to LDS are the exception, and none is under
       // way here): with at most the stores outstanding the copies have landed.  For that the stores must stay in
       // front of the wait.
-      if (KS == 1 && wave * 32 + 32 <= n_valid) {
+      if (KS == 1 && q_wave + 16 * QG <= n_valid) {
         store_rows(true);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -817,9 +840,9 @@ void attn_pipe_kernel(AttnArgs) {
   }
 }
 
-template <int BQ, int KS>
+template <int BQ, int KS, int QS>
 void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_pipe_kernel<BQ, KS>), dim3(n_wg), dim3(64 * KS * BQ / 32), 0, stream, args);
+  hipLaunchKernelGGL((attn_pipe_kernel<BQ, KS, QS>), dim3(n_wg), dim3(64 * KS * QS * BQ / 32), 0, stream, args);
 }
 
 }  // namespace
@@ -831,16 +854,16 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // waves), and its length is that of the chain of tiles of the longest row: two groups of waves per row
   // halve that chain.  256 rows of up to 16 blocks 24.6 -> 18.1 us, 512 rows 28.2 -> 21.6 us, 64 rows of up to
   // 8 blocks 14.8 -> 11.8 us; at 1024 rows, where the chip is full without them, 54 -> 57 and 38 -> 51 us.
-  // A 128-token row fills the SIMDs by itself, but with no more rows than compute units every SIMD has one wave and
-  // its MFMAs and softmax wait for each other: two groups half a step apart (kPingPong; in step 224 rows took 38 us
-  // where one group takes 33).  Whole path: 256 rows of 32 blocks at 20 to 100% 75.6 -> 66.7 us, two heads of four dense
-  // over 8000 tokens 148 -> 118, 256 rows of 16 blocks 50.4 -> 44.9, of 8 34.0 -> 33.5, 224 of 7 32.2 -> 31.5; 160 of 5
-  // 27.0 -> 27.8 and 64 of 2 24.0 -> 24.5, for the groups combine at some 1.5 us: from 7 blocks on.  (Of 16 blocks with
-  // two or three selected 28.5 -> 30.4: the selection is not known here.)  512 rows: two rows a compute unit fill it, 41 -> 48.
-  // Rows that may be cut go the same way: an uncut row has the same result in either entry point (pieces take the
-  // advantage: 4/1 heads x 8000 with a dense one 99 -> 104 us, 2/1 x 16384 171 -> 176, 8/2 x 4096 59.4 -> 57.5, 16/4 x 2048 60.5 -> 56.8).
-  plan.key_groups = g.meta.block == 64 ? (g.rows <= 2 * cus ? 2 : 1) : (g.rows <= cus && g.max_nb >= 7 ? 2 : 1);
-  plan.grid = n_wg / plan.key_groups;
+  // A 128-token row fills the SIMDs by itself, but with no more rows than compute units every SIMD has one wave and its
+  // MFMAs and softmax wait for each other: two groups of waves share it, 64 queries each and half a step apart.  Not by
+  // its keys: a query's sums are taken in the order of the other launches, bit for bit, and short rows combine nothing.
+  // Whole path, one group against two: 32/8 heads x 777 tokens 32.0 -> 28.4 us, with two blocks a row 22.0 -> 21.1, 8/2 x
+  // 4096 at 20 to 100% 68.7 -> 57.4, 16/4 x 2048 with two or three blocks a row 27.2 -> 25.8, 4/1 x 8000 with a dense one
+  // 155 -> 125, 1/1 x 20000 dense 347 -> 266 (by keys 31.0, 23.2, 58.4, 29.3, 120 and 251), in pieces 4/1 x 8000 82.0 -> 74.1,
+  // 2/1 x 16384 151 -> 141, 16/4 x 2048 63.9 -> 56.0.  512 rows are two rows a compute unit, which fill it.
+  plan.key_groups = g.meta.block == 64 && g.rows <= 2 * cus ? 2 : 1;
+  plan.query_groups = g.meta.block == 128 && g.rows <= cus ? 2 : 1;
+  plan.grid = n_wg / (plan.key_groups * plan.query_groups);
   // No more rows than workgroups and none to be cut: there is nothing to order, every row gets a workgroup
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).
   plan.ordered = slot_capacity > 0 || g.rows > plan.grid - plan.grid % kXcds;
@@ -871,11 +894,11 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.sb = sb;
   args.meta = g.meta;
   if (g.meta.block == 128) {
-    if (plan.key_groups == 2) launch_one<128, 2>(args, plan.grid, stream);
-    else launch_one<128, 1>(args, plan.grid, stream);
+    if (plan.query_groups == 2) launch_one<128, 1, 2>(args, plan.grid, stream);
+    else launch_one<128, 1, 1>(args, plan.grid, stream);
   } else {
-    if (plan.key_groups == 2) launch_one<64, 2>(args, plan.grid, stream);
-    else launch_one<64, 1>(args, plan.grid, stream);
+    if (plan.key_groups == 2) launch_one<64, 2, 1>(args, plan.grid, stream);
+    else launch_one<64, 1, 1>(args, plan.grid, stream);
   }
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;

@@ -156,9 +156,9 @@ def test_selections_that_do_not_begin_with_the_sink(block, nb):
 
 @pytest.mark.parametrize("n_blocks, budgets", [(6, [2, 3, 6, 5]), (7, [2, 3, 7, 5]), (32, [2, 3, 4, 5, 32, 7, 31, 20]), (33, [2, 3, 4, 5, 33, 7, 31, 20])])
 def test_128_token_rows_shared_by_two_groups_of_waves(n_blocks, budgets):
-    # From 7 blocks on, rows of launches of up to one per compute unit (256) are shared by two groups of waves half a step
-    # apart: first and last sizes of both rules, rows of one block, odd and even numbers, a ragged tail; and an infinite
-    # value that every query of the last block sees, of a row of an odd number of blocks too.
+    # Rows of launches of up to one per compute unit (256) are shared by two groups of waves half a step apart: few rows,
+    # the last size of the rule and the first of the other, rows of one block, odd and even numbers, a ragged tail; and an
+    # infinite value that every query of the last block sees, of a row of an odd number of blocks too.
     T = 128 * n_blocks - 45
     wl = make_custom([T], len(budgets), 1, 128, budgets, seed=560 + n_blocks, name="groups_128_%d" % n_blocks)
     full_parity(wl)
@@ -167,3 +167,31 @@ def test_128_token_rows_shared_by_two_groups_of_waves(n_blocks, budgets):
     out = DevicePass(wl).run_all().out_host()
     assert (out[last:, :, 5] == np.inf).all() and (out[last:, :, 6] == -np.inf).all()
     assert np.isfinite(np.delete(out[last:], [5, 6], axis=2)).all() and np.isfinite(out[:last]).all()
+
+
+@pytest.mark.parametrize("n_blocks, tail, heads, times", [(1, 37, (8, 2), 64), (2, 128, (4, 2), 64), (7, 9, (32, 8), 2), (7, 9, (32, 8), 3),
+                                                         (33, 64, (4, 1), 3), (64, 1, (4, 4), 3)])
+def test_a_128_token_sequence_alone_and_in_a_larger_call(n_blocks, tail, heads, times):
+    # The same bits in a launch of up to 256 rows, whose rows two groups of waves share, in one of up to 512 and in one with
+    # queues; odd and even numbers of blocks, ragged tails.  Half of the queries of every 32 meet scores far above the earlier ones
+    # (a later key's component 9), in one of two heads: references are raised for 16 queries at a time.
+    hq, hkv = heads
+    T = 128 * (n_blocks - 1) + tail
+    budgets = np.random.default_rng(n_blocks).integers(2, n_blocks + 2, hq).tolist()
+    one = make_custom([T], hq, hkv, 128, budgets, seed=600 + n_blocks, name="alone_%d" % n_blocks)
+    sign = np.where(np.arange(T) % 32 < 16, 0x4000, 0xc000).astype(np.uint16)                  # 2 and -2
+    one.q[:, ::2, 9] = sign[:, None]
+    for j in range(1, n_blocks):
+        one.k[128 * j, :, 9] = 0x4270 + 8 * j                                                  # from 60 on: 10.6 nats and more
+    many = make_custom([T] * times, hq, hkv, 128, budgets, seed=1, name="together_%d" % n_blocks)
+    for name in ("q", "k", "v"):
+        setattr(many, name, np.tile(getattr(one, name), (times, 1, 1)))
+    a, b = DevicePass(one).run_all(), DevicePass(many).run_all()
+    print("case", one.name, "rows", a.rows, b.rows, flush=True)
+    assert a.rows <= 256 < b.rows
+    out_o, lse_o = orc.sparse_attention(one.q, one.k, one.v, one.cu_seqlens, 128, a.sel_ptr_host, a.sel_idx_host(), None, None)
+    compare_output(a.out_host(), out_o, a.lse_host(), lse_o)
+    for x in range(times):
+        at = slice(x * T, (x + 1) * T)
+        assert torch.equal(a.sel_idx, b.sel_idx[x * len(a.sel_idx):(x + 1) * len(a.sel_idx)])
+        assert torch.equal(a.out.view(torch.int16), b.out[at].view(torch.int16)) and torch.equal(a.lse, b.lse[:, at])

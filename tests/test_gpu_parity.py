@@ -148,6 +148,12 @@ def test_long_rows_split_along_keys_and_merged(split_slots):
     _split_against_whole_rows(wl, split_slots, 3 if split_slots == 1024 else 1)
 
 
+def test_long_rows_of_a_full_launch_split_and_merged():
+    # 328 rows, more than one per compute unit: pieces by the 128-token kernel that has a row to itself
+    wl = make_custom([128 * 40 + 37], 8, 2, 128, [999, 3, 23, 2, 999, 18, 40, 7], seed=63, name="split_full")
+    _split_against_whole_rows(wl, 2048, 3)
+
+
 def test_split_rows_block_64_many_pieces():
     # 64-token blocks (the non-pipelined kernel): rows of up to 141 blocks are cut into up to five
     # pieces of at least 32 blocks; GQA, ragged tail, a second sequence of one block
