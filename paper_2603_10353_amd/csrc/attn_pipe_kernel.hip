@@ -64,7 +64,9 @@
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
 //
 // KS = 2: two groups of waves share a row, each with every other selected block, and combine their
-// results in LDS (launches of few 64-token rows, see plan_attention()).
+// results in LDS (launches of few 64-token rows, see plan_attention()).  There the MFMAs of S(t+1) stay in front of the
+// softmax: with up to one row per compute unit a SIMD has one wave, and its last MFMAs then run behind its own exponentials
+// (2/1 heads x 8000 with a dense one 112 -> 108.6 us, 256 dense rows of up to 64 blocks 66.5 -> 64.8, 512 73.3 -> 72.3).
 //
 // QS = 2: two groups of four waves share a 128-token row's queries, 16 a wave (launches of no more rows than compute units).
 // Both work on the same tiles, group 1 half a step behind, kept there by a second barrier in the middle of a step: one
@@ -197,6 +199,7 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kLook = KS * QS > 1 ? 4 : 8;         // LDS operand fetches run this many operands ahead (8: 12 no change.  Of
                                                      // rows shared by two groups 1/1 heads x 20000 take 266 us with 4, 281 with
                                                      // 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8)
+  constexpr bool kScoresFirst = KS > 1;              // S(t+1) in front of the softmax (see the header)
   constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
@@ -561,6 +564,24 @@ void attn_pipe_kernel(AttnArgs) {
       }
       __builtin_amdgcn_sched_barrier(0);
 
+      // S(t+1): its MFMAs back to back (the operands of the second contraction are fetched behind the last K operands)
+      auto next_scores = [&]() {
+        if (kHasNext) {
+#pragma unroll
+          for (int gi = 0; gi < kQK; ++gi) {
+            if (gi + kLook < kQK) kf[gi + kLook] = read_k(kn, gi + kLook);
+            if (gi + kLook >= kQK) vf[gi + kLook - kQK] = read_v(vc, gi + kLook - kQK);
+#pragma unroll
+            for (int qg = 0; qg < QG; ++qg)
+              sc_nxt[qg][gi % MT] =
+                  __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi], qf[qg][gi / MT], sc_nxt[qg][gi % MT], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (mask) mask_scores(sc_nxt, kStage ^ 1, all);
+        }
+      };
+      if (kScoresFirst) next_scores();
+
       // ---- probabilities of tile t, in one run of VALU work: the first K operands arrive behind it, and the other
       // wave of the SIMD is usually inside an MFMA block.
       uint32_t pk[QG][MT][2];
@@ -606,8 +627,7 @@ void attn_pipe_kernel(AttnArgs) {
       for (int qg = 0; qg < QG; ++qg) l_run[qg] += rs[qg];
       __builtin_amdgcn_sched_barrier(0);
 
-      // ---- S(t+1): its MFMAs back to back (the operands of the second contraction are
-      // fetched behind the last K operands)
+      // ---- S(t+1)
       if constexpr (QS > 1) {
         // (group 1 has waited for the copies of K(t+1) and V(t) in front of the barrier that is group 0's this one)
         asm volatile("" ::: "memory");
@@ -618,19 +638,7 @@ void attn_pipe_kernel(AttnArgs) {
       }
       __builtin_amdgcn_s_setprio(1);
       __builtin_amdgcn_sched_barrier(0);
-      if (kHasNext) {
-#pragma unroll
-        for (int gi = 0; gi < kQK; ++gi) {
-          if (gi + kLook < kQK) kf[gi + kLook] = read_k(kn, gi + kLook);
-          if (gi + kLook >= kQK) vf[gi + kLook - kQK] = read_v(vc, gi + kLook - kQK);
-#pragma unroll
-          for (int qg = 0; qg < QG; ++qg)
-            sc_nxt[qg][gi % MT] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi], qf[qg][gi / MT], sc_nxt[qg][gi % MT], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (mask) mask_scores(sc_nxt, kStage ^ 1, all);
-      }
+      if (!kScoresFirst) next_scores();
 
       // ---- O^T += V(t)^T P(t)^T: its MFMAs back to back
       if (KS > 1 && drop) return;
