@@ -23,12 +23,13 @@ namespace shplb {
 namespace {
 
 // 128 consecutive queries of one (sequence, head) swept over their keys in tiles of kTile; a wave owns 32
-// queries.  The tiles are software-pipelined: the work on a tile's scores depends on none of the MFMAs of the next
-// one, and a tile is copied one whole step ahead of its use.
-// kSmall: the contraction in 16x16x32 MFMAs, of two groups of 16 queries, instead of 32x32x16, and behind the work on the
-// scores instead of in front of it: for a pass at the card's power limit (the block mass 4.81 -> 4.17 ms, by itself
-// 4.49).  The token recovery is not at that limit and its state is per query: 12.5 ms with the larger shape, 12.9 with the
-// other order.
+// queries.  The tiles are software-pipelined: the MFMAs of the next tile are issued before the work on the
+// present one's scores, which depends on none of them, and a tile is copied one whole step ahead of its use.
+// kSmall: the contraction in 16x16x32 MFMAs, of two groups of 16 queries, instead of 32x32x16: for a pass at the card's
+// power limit (the block mass of 32 heads x 32K tokens 4.60 -> 3.99 ms, with the kept sums below).  The token recovery is not at
+// that limit and its state is per query.  With the MFMAs behind the work on the scores the mass takes 4.18 ms, and launches of
+// one workgroup per compute unit or fewer, whose SIMDs have one wave, are slower than with 32x32x16: 8/2 heads x 4000 tokens
+// 51.5 us for 49.7, now 48.8; 8/2 x 1000 18.0 for 17.4, now 17.3.  The recovery takes 12.9 ms that way, for 12.5.
 template <bool kSmall>
 struct QueryRun {
   static constexpr int kQueries = 128, kWaves = kQueries / 32;
@@ -123,20 +124,13 @@ struct QueryRun {
     }
   }
 
-  // Raw scores (q . k, unscaled) of the tile in stage `buf`, in two parts: the first operands are fetched, then ...
-  typedef bf16x8 Operands[kOperands];
   __device__ __forceinline__ bf16x8 read_k(int buf, int gi) const {
     const char* kt = k_lds + buf * kStageBytes;
     if (kSmall) return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ ((gi >> 2) << 6)) + (gi & 3) * 16 * kRowBytes);
     return *reinterpret_cast<const bf16x8*>(kt + (k_rd0 ^ ((gi / MT) << 5)) + (gi % MT) * 32 * kRowBytes);
   }
-  __device__ __forceinline__ void fetch_first(int buf, Operands& kf) const {
-#pragma unroll
-    for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(buf, gi);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // ... the MFMAs back to back.
-  __device__ __forceinline__ void scores_of(int buf, Operands& kf, Scores& sc) const {
+  // raw scores (q . k, unscaled) of the tile in stage `buf`
+  __device__ __forceinline__ void scores_of(int buf, Scores& sc) const {
     if constexpr (kSmall) {
 #pragma unroll
       for (int qg = 0; qg < QG; ++qg)
@@ -148,7 +142,9 @@ struct QueryRun {
 #pragma unroll
         for (int r = 0; r < 16; ++r) sc.v[mt][r] = 0.0f;
     }
-    if (kSmall) __builtin_amdgcn_s_setprio(1);
+    bf16x8 kf[kOperands];
+#pragma unroll
+    for (int gi = 0; gi < kLook; ++gi) kf[gi] = read_k(buf, gi);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int gi = 0; gi < kOperands; ++gi) {
@@ -162,7 +158,6 @@ struct QueryRun {
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (kSmall) __builtin_amdgcn_s_setprio(0);
   }
 
   // keys above the lane's query to -inf (tiles of the diagonal only)
@@ -205,28 +200,19 @@ struct QueryRun {
   __device__ __forceinline__ void sweep(int first, int count, uint32_t stride, bool masked, F&& per_tile) const {
     const int end = first + count;
     Scores sa, sb;
-    {
-      Operands kf;
-      wait_vmem_all();
-      __syncthreads();
-      fetch_first(0, kf);
-      scores_of(0, kf, sa);
-    }
+    wait_vmem_all();
+    __syncthreads();
+    scores_of(0, sa);
     auto step = [&](int x, int buf, Scores& cur, Scores& nxt) {
-      Operands kf;
-      const bool more = x + 1 < end;
-      if (more) {
+      if (x + 1 < end) {
         wait_vmem_all();                            // own copies of tile x + 1 have landed
         __syncthreads();                            // everyone's have; the stage of tile x is free
-        if (kSmall) fetch_first(buf ^ 1, kf);
         if (x + 2 < end) issue_tile(x + 2, stride, buf);
-        if (!kSmall) fetch_first(buf ^ 1, kf);
+        scores_of(buf ^ 1, nxt);
       }
-      if (!kSmall && more) scores_of(buf ^ 1, kf, nxt);
       if (masked && x >= n_tiles - kQueries / kTile) mask(x, cur);
       per_tile(x, cur);
       __builtin_amdgcn_sched_barrier(0);
-      if (kSmall && more) scores_of(buf ^ 1, kf, nxt);
     };
     for (int x = first; x < end; x += 2) {
       step(x, 0, sa, sb);
@@ -250,10 +236,9 @@ struct QueryRun {
 // when a tile's sum leaves the range of useful exponents.
 //
 // Sums run over keys, tiles, queries and waves in a fixed order: results repeat bit for bit.
-// 32 heads x 32K tokens: 4.2 to 4.4 ms, from 4.65 to 4.9 on the same cards with 32x32x16 MFMAs, which spend more of the power
-// (the launch runs at its limit), the exponentials behind the MFMAs instead of in front, and the copies above.  The VALU issues
-// in 69% of the cycles (per key and 64 queries an exponential, a multiply-add and an addition, 16 cycles), the matrix pipe
-// is busy in 47%.  Exponentials between the MFMAs: 4.4 -> 4.45 ms.
+// 32 heads x 32K tokens: 4.0 ms, from 4.6 on the same card with 32x32x16 MFMAs, which spend more of the power (the launch
+// runs at its limit, at 2.1 GHz), and the copies above.  The VALU issues in 76% of the cycles (per key and 64 queries an
+// exponential, a multiply-add and an addition, 16 cycles), the matrix pipe is busy in 51%.
 constexpr int kLdsBlocks = 92, kBankBlocks = 64;   // 4 x 92 x 32 words beside the tiles and partial sums: two workgroups
                                                    // per compute unit; two banks of 32 registers
 constexpr float kSumRange = 0x1p64f;
