@@ -321,12 +321,11 @@ void attn_pipe_kernel(AttnArgs) {
     next_off = int64_t(key_base) * row_bytes;
   };
   // Copy the K or V rows of the located tile into an LDS stage.
-  auto issue_part = [&](const char* head, uint32_t dst, int part) {
+  auto issue = [&](const char* head, uint32_t dst) {
     const char* tile = uniform(head + next_off);
     if (next_last >= KT - 1) {
 #pragma unroll
       for (int rd = 0; rd < kRounds; ++rd) {
-        if (part == 1 && rd >= kRounds / 2 || part == 2 && rd < kRounds / 2) continue;
         const bool odd8 = ((rd * kRoundRows) >> 3) & 1;       // round starts at an odd multiple of 8 rows
         copy_g2l_16(tile + int64_t(rd * kRoundRows) * row_bytes, odd8 ? cp_off1 : cp_off0,
                     dst + rd * kRoundRows * kRowBytes);
@@ -334,14 +333,12 @@ void attn_pipe_kernel(AttnArgs) {
     } else {                                     // ragged: rows past the end re-read the last valid key (masked)
 #pragma unroll
       for (int rd = 0; rd < kRounds; ++rd) {
-        if (part == 1 && rd >= kRounds / 2 || part == 2 && rd < kRounds / 2) continue;
         const int r = rd * kRoundRows + cp_row;
         const uint32_t off = uint32_t(min(r, next_last)) * uint32_t(row_bytes) + (((lane & 15) ^ swz(r)) << 4);
         copy_g2l_16(tile, off, dst + rd * kRoundRows * kRowBytes);
       }
     }
   };
-  auto issue = [&](const char* head, uint32_t dst) { issue_part(head, dst, 0); };
   // Everything an item can start before its turn: its first tile copies and its Q fragments (B operand of
   // S^T = K Q^T, lane (n, hi) holds dims 32ks+8hi.. of queries n and 16 + n).  The stages must be free.
   auto load_queries = [&](ArgsPtr a) {
