@@ -63,7 +63,7 @@
 // masked sub-tiles are computed like any other (their probabilities are exact zeros).
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
 //
-// KS = 2: two groups of waves share a row, each with every other selected block, and combine their
+// KS = 2: two groups of waves share a 64-token row, each with every other selected block, and combine their
 // results in LDS (launches of few 64-token rows, see plan_attention()).  There the MFMAs of S(t+1) stay in front of the
 // softmax: with up to one row per compute unit a SIMD has one wave, and its last MFMAs then run behind its own exponentials
 // (2/1 heads x 8000 with a dense one 112 -> 108.6 us, 256 dense rows of up to 64 blocks 66.5 -> 64.8, 512 73.3 -> 72.3).
@@ -182,13 +182,13 @@ __device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
 }
 
 // BQ: tokens per block.  KS: groups of BQ/32 waves that share a row, each with every KS-th selected block.
-template <int BQ, int KS, int QS>
-__global__ __launch_bounds__(64 * KS * QS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int BQ, int GROUPS>
+__global__ __launch_bounds__(64 * GROUPS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
-  static_assert(KS == 1 || KS == 2, "an item's record names its first two blocks");
-  static_assert(QS == 1 || (QS == 2 && KS == 1), "a row is shared by keys or by queries");
+  static_assert(GROUPS == 1 || GROUPS == 2, "an item's record names its first two blocks");
+  constexpr int KS = BQ == 64 ? GROUPS : 1, QS = BQ == 128 ? GROUPS : 1;   // groups that share a row, by keys and by queries
   constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each, or 16
-  constexpr int kThreads = 64 * KS * QS * kWaves;
+  constexpr int kThreads = 64 * GROUPS * kWaves;
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
   constexpr int QG = 2 / QS, MT = KT / 16;                // 16-query and 16-key MFMA tiles of a tile's scores
   constexpr int kTileBytes = KT * kRowBytes;
@@ -196,7 +196,7 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kRounds = KT / kRoundRows;
   constexpr int kQK = 4 * MT;                        // K operands of a tile's first contraction, index MT*ks + mt ...
   constexpr int kPV = 8 * (KT / 32);                 // ... V operands of its second, index 8*gq + dt: QG MFMAs each
-  constexpr int kLook = KS * QS > 1 ? 4 : 8;         // LDS operand fetches run this many operands ahead (8: 12 no change.  Of
+  constexpr int kLook = GROUPS > 1 ? 4 : 8;          // LDS operand fetches run this many operands ahead (8: 12 no change.  Of
                                                      // rows shared by two groups 1/1 heads x 20000 take 266 us with 4, 281 with
                                                      // 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8)
   constexpr bool kScoresFirst = KS > 1;              // S(t+1) in front of the softmax (see the header)
@@ -214,7 +214,7 @@ void attn_pipe_kernel(AttnArgs) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int team = KS * QS > 1 ? wave_all / kWaves : 0, wave = KS * QS > 1 ? wave_all % kWaves : wave_all;
+  const int team = GROUPS > 1 ? wave_all / kWaves : 0, wave = GROUPS > 1 ? wave_all % kWaves : wave_all;
   const int grp = KS > 1 ? team : 0, q_grp = QS > 1 ? team : 0;         // group of waves, by keys or by queries
   const int q_wave = 16 * QG * (q_grp * kWaves + wave);                 // the wave's first query
   const int n = lane & 15, hi = lane >> 4;
@@ -845,9 +845,9 @@ void attn_pipe_kernel(AttnArgs) {
   }
 }
 
-template <int BQ, int KS, int QS>
+template <int BQ, int GROUPS>
 void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_pipe_kernel<BQ, KS, QS>), dim3(n_wg), dim3(64 * KS * QS * BQ / 32), 0, stream, args);
+  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS>), dim3(n_wg), dim3(64 * GROUPS * BQ / 32), 0, stream, args);
 }
 
 }  // namespace
@@ -866,9 +866,8 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // 4096 at 20 to 100% 68.7 -> 57.4, 16/4 x 2048 with two or three blocks a row 27.2 -> 25.8, 4/1 x 8000 with a dense one
   // 155 -> 125, 1/1 x 20000 dense 347 -> 266 (by keys 31.0, 23.2, 58.4, 29.3, 120 and 251), in pieces 4/1 x 8000 82.0 -> 74.1,
   // 2/1 x 16384 151 -> 141, 16/4 x 2048 63.9 -> 56.0.  512 rows are two rows a compute unit, which fill it.
-  plan.key_groups = g.meta.block == 64 && g.rows <= 2 * cus ? 2 : 1;
-  plan.query_groups = g.meta.block == 128 && g.rows <= cus ? 2 : 1;
-  plan.grid = n_wg / (plan.key_groups * plan.query_groups);
+  plan.groups = g.rows <= (g.meta.block == 64 ? 2 * cus : cus) ? 2 : 1;
+  plan.grid = n_wg / plan.groups;
   // No more rows than workgroups and none to be cut: there is nothing to order, every row gets a workgroup
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).
   plan.ordered = slot_capacity > 0 || g.rows > plan.grid - plan.grid % kXcds;
@@ -899,11 +898,11 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.sb = sb;
   args.meta = g.meta;
   if (g.meta.block == 128) {
-    if (plan.query_groups == 2) launch_one<128, 1, 2>(args, plan.grid, stream);
-    else launch_one<128, 1, 1>(args, plan.grid, stream);
+    if (plan.groups == 2) launch_one<128, 2>(args, plan.grid, stream);
+    else launch_one<128, 1>(args, plan.grid, stream);
   } else {
-    if (plan.key_groups == 2) launch_one<64, 2, 1>(args, plan.grid, stream);
-    else launch_one<64, 1, 1>(args, plan.grid, stream);
+    if (plan.groups == 2) launch_one<64, 2>(args, plan.grid, stream);
+    else launch_one<64, 1>(args, plan.grid, stream);
   }
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;

@@ -143,8 +143,7 @@ struct SplitBuffers {
 
 // How an attention launch is laid out.
 struct AttentionPlan {
-  int32_t key_groups;   // groups of waves of a workgroup that share a row, by its keys ...
-  int32_t query_groups; // ... and by its queries
+  int32_t groups;       // groups of waves of a workgroup that share a row: of 64 tokens by its keys, of 128 by its queries
   int32_t grid;         // workgroups
   int32_t compute_units;
   bool ordered;         // items come from queues; else every row has a workgroup
