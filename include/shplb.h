@@ -306,7 +306,7 @@ SHPLB_API int32_t shplb_shift_budgets(const double* recovery, int32_t n_heads, i
 /* ---- diagnostic ------------------------------------------------------------ */
 
 /* Rate of the bf16 matrix pipe as this chip sustains it: launches n_workgroups
- * workgroups of eight waves that issue 8 * iters v_mfma_f32_32x32x16_bf16 each on
+ * workgroups of eight waves that issue 16 * iters v_mfma_f32_16x16x32_bf16 each on
  * register operands and nothing else.  random_operands != 0: operands with random
  * signs and mantissas and magnitudes around one (what attention multiplies);
  * 0: one small constant.  The caller times the launch (FLOP = n_workgroups * 8 *

@@ -36,8 +36,8 @@
 //     unsynchronised) mostly find the other unit free.
 //
 // Why 16x16x32: long launches run at the card's power limit, and of MFMAs alone on random operands that limit lets
-// through 2.07 PFLOP/s in this shape, 1.80 in 32x32x16 (twice the operand reads but half the accumulator
-// traffic per product).  By itself the change moved the bound from power (1.64 GHz, matrix pipe 70% busy) to the schedule
+// through 1.87 PFLOP/s in this shape (the loop of probe_kernels.hip), 1.67 in 32x32x16 (twice the operand reads but half the
+// accumulator traffic per product).  By itself the change moved the bound from power (1.64 GHz, matrix pipe 70% busy) to the schedule
 // (2.0 GHz, 58%) and gained nothing; then
 //   * chunk slots free of conflicts for the new operand reads (see swz()): 128K +2%, 32K +1.3%;
 //   * the softmax in front of both contractions, not between them: the latency of the first K operands and the

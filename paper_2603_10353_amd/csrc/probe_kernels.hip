@@ -1,6 +1,8 @@
 // What the matrix pipe sustains on this chip, measured: a loop of nothing but
-// v_mfma_f32_32x32x16_bf16 on register operands, eight waves per compute unit, no memory
-// traffic.  With operands that look like the attention kernel's (random signs and mantissas,
+// v_mfma_f32_16x16x32_bf16 (the attention kernel's shape) on register operands, eight waves per
+// workgroup, no memory traffic, which sets of operands meet known when it is compiled (chosen in the loop, they were
+// copied by some eight instructions per MFMA, and random ones reached 1.51 PFLOP/s in 32x32x16; this loop reaches 1.67 in
+// that shape, 1.87 in this one, at 1.68 and 1.87 GHz, and 2.47 with one constant in either).  With operands that look like the attention kernel's (random signs and mantissas,
 // magnitudes around one) the chip holds a much lower clock than with constant operands, and
 // that rate, not the nominal peak, is what a bf16 attention kernel can approach.  Used by the
 // benchmark to put the measured ceiling next to its roofline figure.
@@ -11,12 +13,10 @@ namespace {
 
 template <int RANDOM>
 __global__ __launch_bounds__(512) void mfma_rate_kernel(float* sink, uint64_t* clocks, int iters, uint32_t seed) {
-  f32x16 acc[4];
+  f32x4 acc[16];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
-  // eight operand sets per lane, cycled so that consecutive MFMAs never see the same pair
+  for (int j = 0; j < 16; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // eight operand sets per lane, cycled so that both operands of consecutive MFMAs differ
   u32x4 av[8], bv[8];
   uint32_t x = seed ^ (threadIdx.x * 2654435761u) ^ (blockIdx.x * 40503u);
   auto bf16_bits = [](uint32_t r) {       // random sign, exponent 2^-2 .. 2^1, random mantissa; or one small constant
@@ -36,16 +36,14 @@ __global__ __launch_bounds__(512) void mfma_rate_kernel(float* sink, uint64_t* c
   const uint64_t c0 = __builtin_readcyclecounter(), w0 = wall_clock64();
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-      acc[s & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[s]),
-                                                           __builtin_bit_cast(bf16x8, bv[(s + it) & 7]), acc[s & 3], 0, 0, 0);
+    for (int m = 0; m < 16; ++m)
+      acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[m & 7]),
+                                                       __builtin_bit_cast(bf16x8, bv[(3 * m + (m >> 3)) & 7]), acc[m], 0, 0, 0);
   }
   const uint64_t c1 = __builtin_readcyclecounter(), w1 = wall_clock64();
   float total = 0.0f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) total += acc[j][r];
+  for (int j = 0; j < 16; ++j) total += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
   sink[blockIdx.x * blockDim.x + threadIdx.x] = total;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     clocks[0] = c1 - c0;                  // shader clock cycles of the loop
