@@ -45,8 +45,8 @@
 //   * the two groups' probabilities in turn, two partial sums each (the dot products form chains): +3%;
 //   * priority by phase instead of by turns of 41 us between the workgroups of a compute unit: +0.7%.
 // Together: 128K layer 30.7 -> 28.0 ms (1.32 PFLOP/s), 32K 1870 -> 1725 us, with 64-token blocks 2180 -> 1995 us, a
-// 64K share of 8 heads 1553 -> 1434 us, an 8K prompt 182 -> 171 us, 48 sequences 148 -> 144 us (whole path).  Now 1.85 GHz
-// and 70% at 128K.  Spreading the VALU work between the MFMAs of the same wave, in whatever part, costs 4 to 25%; copies
+// 64K share of 8 heads 1553 -> 1434 us, an 8K prompt 182 -> 171 us, 48 sequences 148 -> 144 us (whole path).  Now 1.78 GHz
+// and 72% at 128K.  Spreading the VALU work between the MFMAs of the same wave, in whatever part, costs 4 to 25%; copies
 // issued later in the step or between the exponentials 2 to 5%.
 //
 // Between items.  An item used to cost about 21 000 cycles beside its tiles (an atomic ticket that waited
@@ -64,9 +64,13 @@
 // With 64-token blocks a tile feeds half as many MFMAs per copy, barrier and item as with 128.
 //
 // KS = 2: two groups of waves share a 64-token row, each with every other selected block, and combine their
-// results in LDS (launches of few 64-token rows, see plan_attention()).  There the MFMAs of S(t+1) stay in front of the
-// softmax: with up to one row per compute unit a SIMD has one wave, and its last MFMAs then run behind its own exponentials
-// (2/1 heads x 8000 with a dense one 112 -> 108.6 us, 256 dense rows of up to 64 blocks 66.5 -> 64.8, 512 73.3 -> 72.3).
+// results in LDS (launches of few 64-token rows, see plan_attention()).
+//
+// SCORES_FIRST: the MFMAs of S(t+1) in front of the softmax, all at one priority, for 64-token rows shared by two groups and
+// dealt without queues: with up to one row per compute unit a SIMD has one wave, and its last MFMAs then run behind its own
+// exponentials (2/1 heads x 8000 with a dense one 112.1 -> 108.6 us, 256 dense rows of up to 64 blocks 66.1 -> 64.0, with two
+// rows 512 dense ones 73.0 -> 72.1, 512 at 5 to 50% 39.2 -> 38.6).  Pieces from queues, where 512 dense rows take 88.6 us with
+// the softmax in front, take 99.9 that way (2/1 x 8000 72.4 -> 71.8, 256 dense rows 65.7 -> 67.2).
 //
 // QS = 2: two groups of four waves share a 128-token row's queries, 16 a wave (launches of no more rows than compute units).
 // Both work on the same tiles, group 1 half a step behind, kept there by a second barrier in the middle of a step: one
@@ -182,7 +186,7 @@ __device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
 }
 
 // BQ: tokens per block.  KS: groups of BQ/32 waves that share a row, each with every KS-th selected block.
-template <int BQ, int GROUPS>
+template <int BQ, int GROUPS, bool SCORES_FIRST>
 __global__ __launch_bounds__(64 * GROUPS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
   static_assert(GROUPS == 1 || GROUPS == 2, "an item's record names its first two blocks");
@@ -199,7 +203,6 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kLook = GROUPS > 1 ? 4 : 8;          // LDS operand fetches run this many operands ahead (8: 12 no change.  Of
                                                      // rows shared by two groups 1/1 heads x 20000 take 266 us with 4, 281 with
                                                      // 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8)
-  constexpr bool kScoresFirst = KS > 1;              // S(t+1) in front of the softmax (see the header)
   constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
@@ -515,7 +518,7 @@ void attn_pipe_kernel(AttnArgs) {
                     bool drop, bool ask_now) {
       constexpr int kPlace = decltype(place_c)::value, kStage = decltype(stage_c)::value;
       constexpr bool kHasNext = kPlace != kFinal;
-      __builtin_amdgcn_s_setprio(0);
+      if (!SCORES_FIRST) __builtin_amdgcn_s_setprio(0);
       wait_vmem_all();                  // own copies of K(t+1), V(t) have landed
       if (kPlace == kRecord && home_open && tid == 0) {
         // the ticket asked for one step ago
@@ -577,7 +580,7 @@ void attn_pipe_kernel(AttnArgs) {
           if (mask) mask_scores(sc_nxt, kStage ^ 1, all);
         }
       };
-      if (kScoresFirst) next_scores();
+      if (SCORES_FIRST) next_scores();
 
       // ---- probabilities of tile t, in one run of VALU work: the first K operands arrive behind it, and the other
       // wave of the SIMD is usually inside an MFMA block.
@@ -633,9 +636,9 @@ void attn_pipe_kernel(AttnArgs) {
         __builtin_amdgcn_sched_barrier(0);
         fetch_first();
       }
-      __builtin_amdgcn_s_setprio(1);
+      if (!SCORES_FIRST) __builtin_amdgcn_s_setprio(1);
       __builtin_amdgcn_sched_barrier(0);
-      if (!kScoresFirst) next_scores();
+      if (!SCORES_FIRST) next_scores();
 
       // ---- O^T += V(t)^T P(t)^T: its MFMAs back to back
       if (KS > 1 && drop) return;
@@ -845,9 +848,9 @@ void attn_pipe_kernel(AttnArgs) {
   }
 }
 
-template <int BQ, int GROUPS>
+template <int BQ, int GROUPS, bool SCORES_FIRST = false>
 void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS>), dim3(n_wg), dim3(64 * GROUPS * BQ / 32), 0, stream, args);
+  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS, SCORES_FIRST>), dim3(n_wg), dim3(64 * GROUPS * BQ / 32), 0, stream, args);
 }
 
 }  // namespace
@@ -901,7 +904,8 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
     if (plan.groups == 2) launch_one<128, 2>(args, plan.grid, stream);
     else launch_one<128, 1>(args, plan.grid, stream);
   } else {
-    if (plan.groups == 2) launch_one<64, 2>(args, plan.grid, stream);
+    if (plan.groups == 2 && wq.items == nullptr) launch_one<64, 2, true>(args, plan.grid, stream);
+    else if (plan.groups == 2) launch_one<64, 2>(args, plan.grid, stream);
     else launch_one<64, 1>(args, plan.grid, stream);
   }
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
