@@ -352,7 +352,7 @@ def main():
         run32 = Pass(S, torch, wl32)
         # the card idles while the host draws this layer's inputs, and a 2 ms step does not bring the clock
         # back by itself: at least 50 untimed steps (0.1 s) first, so that the timed ones run at the clock a
-        # stream of such layers sees (measured on one box: 2.017 ms after 3 untimed steps, 1.956 after 20,
+        # stream of such layers sees (measured on one card: 2.017 ms after 3 untimed steps, 1.956 after 20,
         # 1.936 after 60)
         m32 = run32.measure(args.steps, max(args.warmup, 50))
         result["warmup_32k"] = max(args.warmup, 50)

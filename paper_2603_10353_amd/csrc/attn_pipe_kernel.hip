@@ -45,7 +45,7 @@
 //   * the two groups' probabilities in turn, two partial sums each (the dot products form chains): +3%;
 //   * priority by phase instead of by turns of 41 us between the workgroups of a compute unit: +0.7%.
 // Together: 128K layer 30.7 -> 28.0 ms (1.32 PFLOP/s), 32K 1870 -> 1725 us, with 64-token blocks 2180 -> 1995 us, a
-// 64K share of 8 heads 1553 -> 1434 us, an 8K prompt 182 -> 171 us, 48 sequences 148 -> 144 us (whole path).  Now 1.78 GHz
+// 64K share of 8 heads 1553 -> 1434 us, an 8K prompt 182 -> 171 us, 48 sequences 148 -> 144 us (whole path).  Now 1.79 GHz
 // and 72% at 128K.  Spreading the VALU work between the MFMAs of the same wave, in whatever part, costs 4 to 25%; copies
 // issued later in the step or between the exponentials 2 to 5%.
 //
