@@ -28,7 +28,7 @@
  *     taken depends on the size of the call: up to two rows per compute unit of the
  *     device (512 rows), two groups of waves share a row and add up at the end, so a
  *     sequence alone and inside a larger call agree up to rounding.  With 128-token
- *     blocks its output and denominators are the same, bit for bit.
+ *     blocks they are the same, bit for bit (of rows that are not cut into pieces, below).
  *   - Tensors are token-major: Q is [T, n_q_heads, head_dim] bf16 with element
  *     strides (q_stride_t, q_stride_h, 1); K and V are [T, n_kv_heads, head_dim]
  *     bf16 with strides (kv_stride_t, kv_stride_h, 1).  T = cu_seqlens[n_seq].

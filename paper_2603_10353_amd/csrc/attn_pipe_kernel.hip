@@ -185,7 +185,7 @@ __device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
   return true;
 }
 
-// BQ: tokens per block.  KS: groups of BQ/32 waves that share a row, each with every KS-th selected block.
+// BQ: tokens per block.  GROUPS: groups of BQ/32 waves that share a row, see KS, QS and SCORES_FIRST in the header.
 template <int BQ, int GROUPS, bool SCORES_FIRST>
 __global__ __launch_bounds__(64 * GROUPS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
@@ -194,15 +194,15 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each, or 16
   constexpr int kThreads = 64 * GROUPS * kWaves;
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
-  constexpr int QG = 2 / QS, MT = KT / 16;                // 16-query and 16-key MFMA tiles of a tile's scores
+  constexpr int QG = 2 / QS, MT = KT / 16;           // 16-query and 16-key MFMA tiles of a tile's scores
   constexpr int kTileBytes = KT * kRowBytes;
   constexpr int kRoundRows = 4 * kWaves;             // rows one round of copies moves (4 per wave)
   constexpr int kRounds = KT / kRoundRows;
   constexpr int kQK = 4 * MT;                        // K operands of a tile's first contraction, index MT*ks + mt ...
   constexpr int kPV = 8 * (KT / 32);                 // ... V operands of its second, index 8*gq + dt: QG MFMAs each
-  constexpr int kLook = GROUPS > 1 ? 4 : 8;          // LDS operand fetches run this many operands ahead (8: 12 no change.  Of
-                                                     // rows shared by two groups 1/1 heads x 20000 take 266 us with 4, 281 with
-                                                     // 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8)
+  // LDS operand fetches run this many operands ahead.  (A row to a workgroup: 12 no change.  Shared by two groups: 1/1 heads
+  // x 20000 take 266 us with 4, 281 with 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8.)
+  constexpr int kLook = GROUPS > 1 ? 4 : 8;
   constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
