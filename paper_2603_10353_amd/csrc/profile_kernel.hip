@@ -437,11 +437,11 @@ struct TokenBudgets {
 // The list takes the counters' place; the two lanes of a query fill it from its two ends.
 // Sums are per tile first, then over tiles, always in the same order: results repeat bit for bit.
 //
-// 32 heads x 32K tokens, k = 4096: 12.7 ms, against 131 ms with the threshold found bit by bit in 27 to 29
-// sweeps; three budgets at 9.7K tokens 7.5 -> 1.7 ms.  Of the 12.7 ms an empty sweep (the MFMAs) takes 2.9, the
-// counting 2.6, the exponentials and sums 1.9 and looking for the bin's scores 1.9: the VALU is busy 60% of the
-// time and the matrix pipe 29%, two waves per SIMD not being enough to hide either behind the other.  Three
-// (tiles of 32 keys, 74 bins) were slower, 16.4 ms.
+// 32 heads x 32K tokens, k = 4096: 11.5 to 12.0 ms on several cards, against 131 ms with the threshold found bit by bit in 27
+// to 29 sweeps; three budgets at 4000 tokens x 16 heads 520 us.  The two sweeps and the samples would take 6.8 ms without any
+// work on the scores, which is what their MFMAs take at the card's power limit (1.32 PFLOP/s, at 1.5 GHz; the whole kernel
+// runs at 2.1 GHz).  Three waves per SIMD (tiles of 32 keys, 74 bins) were slower, 16.4 ms; so were workgroups of eight waves
+// that share a tile, 2.5%, also with half of the waves doing their MFMAs behind the work on the scores, 6%.
 constexpr int kBins = 95;                          // and the longest list: 128 queries x 95 words leave room for
                                                    // two workgroups per compute unit beside the tiles
 constexpr int kInner = 85, kFirst = 5;             // an interval is spread over bins kFirst .. kFirst + kInner
@@ -527,13 +527,26 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   auto bin_begin = [&](int u) { return bin_lo + (float(u - kFirst) - 0.5f) * bin_w; };
   float top_score = -INFINITY;
   auto count_bins = [&](int, Run::Scores& sc) {
+    // Addresses of four scores, then their atomics: score after score, every atomic waited for three dependent operations in
+    // one register (32K x 32 heads 12.0 -> 11.7 ms; two or eight at a time take as long, within 0.5%, at 32K and up to 3% more
+    // at 1500 tokens).
+    constexpr int G = 4;
 #pragma unroll
-    for (int r = 0; r < 16 * MT; ++r) {
-      const float s = sc.v[r / 16][r % 16];
-      top_score = fmaxf(top_score, s);
-      const float x = __builtin_amdgcn_fmed3f(__builtin_fmaf(s, map_a, map_b), kWhole, kWhole + (kBins - 1));
-      __hip_atomic_fetch_add(reinterpret_cast<LdsWord*>((__builtin_bit_cast(uint32_t, x) << 7) + bin_base), 1u,
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int g = 0; g < 16 * MT; g += G) {
+      uint32_t at[G];
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        const float s = sc.v[(g + r) / 16][(g + r) % 16];
+        const float x = __builtin_amdgcn_fmed3f(__builtin_fmaf(s, map_a, map_b), kWhole, kWhole + (kBins - 1));
+        at[r] = (__builtin_bit_cast(uint32_t, x) << 7) + bin_base;
+        top_score = fmaxf(top_score, s);
+      }
+#pragma unroll
+      for (int r = 0; r < G; ++r) asm volatile("" : "+v"(at[r]));   // all four, before the first atomic
+      asm volatile("" : "+v"(top_score));
+#pragma unroll
+      for (int r = 0; r < G; ++r)
+        __hip_atomic_fetch_add(reinterpret_cast<LdsWord*>(at[r]), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   };
   // the bin that holds the rank-th largest score: how many scores lie above it and in it
@@ -711,25 +724,48 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
     top[b] = 0.0f;
   }
   fence();
+  // Sums and masks of a group of scores first, without a branch; then the scores of the group that go to a list, which few
+  // do: a scalar test and a branch each.  (With the branch behind every score's own comparison a score waited for its
+  // exponential, two comparisons and four scalar operations before the next one began; 32K x 32 heads, one budget: 12.4 ->
+  // 11.9 ms, 6001 tokens x 28 heads, two: 903 -> 818 us.  Groups of 8 over all budgets take up to 2% more, of 32 spill scalar
+  // registers and are as slow as none.)
+  constexpr int G = 16 / M;
   row.sweep(0, all, stride, true, [&](int, Run::Scores& sc) {
     float sum0 = 0.0f, sum1 = 0.0f, part[M];
 #pragma unroll
     for (int b = 0; b < M; ++b) part[b] = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16 * MT; ++r) {
-      const float s = sc.v[r / 16][r % 16], p = weight(s);
-      if (r & 1) sum1 += p;
-      else sum0 += p;
+    for (int g = 0; g < 16 * MT; g += G) {
+      auto score = [&](int r) { return sc.v[(g + r) / 16][(g + r) % 16]; };
+      uint64_t in[M][G];                                      // lanes whose score goes to the list
+      float p[G];
 #pragma unroll
-      for (int b = 0; b < M; ++b) {
-        const bool over = s >= above_from[b];
-        part[b] += over ? p : 0.0f;
-        asm volatile("" : "+v"(part[b]));                     // here, and not all comparisons first: their masks fit no registers
-        if (s >= list_from[b] && !over) {
-          if (put[b] - column < kBins * kBinBytes) *reinterpret_cast<LdsFloat*>(put[b]) = s;
-          if (!tied[b]) put[b] += row.hi == 0 ? kBinBytes : 0u - kBinBytes;
+      for (int r = 0; r < G; ++r) p[r] = weight(score(r));
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        if (r & 1) sum1 += p[r];
+        else sum0 += p[r];
+#pragma unroll
+        for (int b = 0; b < M; ++b) {
+          const bool over = score(r) >= above_from[b];
+          part[b] += over ? p[r] : 0.0f;
+          in[b][r] = __builtin_amdgcn_ballot_w64(score(r) >= list_from[b]) & ~__builtin_amdgcn_ballot_w64(over);
         }
       }
+      asm volatile("" : "+v"(sum0), "+v"(sum1));              // here, not behind the branches
+#pragma unroll
+      for (int b = 0; b < M; ++b) asm volatile("" : "+v"(part[b]));
+#pragma unroll
+      for (int r = 0; r < G; ++r)
+#pragma unroll
+        for (int b = 0; b < M; ++b)
+          if (in[b][r] != 0) {
+            if (__builtin_amdgcn_inverse_ballot_w64(in[b][r])) {
+              // (a place outside the query's words is none of a list's: held inside, without a branch, 11.9 -> 11.6 ms)
+              *reinterpret_cast<LdsFloat*>(column + min(put[b] - column, (kBins - 1) * kBinBytes)) = score(r);
+              if (!tied[b]) put[b] += row.hi == 0 ? kBinBytes : 0u - kBinBytes;
+            }
+          }
     }
     sum += sum0 + sum1;
 #pragma unroll
