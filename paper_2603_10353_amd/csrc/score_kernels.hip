@@ -290,11 +290,133 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 
   if (pend_j0 >= 0) store_tile(pend, pend_j0);
 }
 
+// Both steps in one launch, for few rows of short sequences: a workgroup pools the one query block of its row (sequence, head,
+// query block) and, again, all key blocks in front of it, and multiplies them.
+//
+// Two launches of some 5 us each, of which most is starting, waiting for the first loads and ending, become one.  What that
+// costs is key blocks read by every row behind them, from the die's L2 (rows of a KV head share a die): at 64 bytes a cycle
+// and compute unit some 0.25 us per block of 128 tokens, see the rule in launch_pool_scores().  A wave pools a block at a
+// time, each of its rows of 16 lanes every fourth token, a lane 8 dims: sums, means, planes and products are those of the two
+// kernels above, bit for bit.  All 32 columns of the product are the one query block; its 24 dependent MFMAs, on a wave for each
+// accumulator, take 0.4 us.
+// Whole path: 32/8 heads x 777 tokens 29.6 -> 26.6 us, x 300 tokens 21.2 -> 17.8, 4/2 x 60 20.3 -> 17.7, 28/4 x (513, 129)
+// 25.8 -> 22.8, eight sequences of 250 x 32/8 31.3 -> 27.0.  Workgroups of 16 waves do as well, but only one fits a
+// compute unit (the last of these 29.6); 32 loads in flight per lane change nothing.
+constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
+constexpr int kRowTokens = 1024;                      // of the longest sequence
+
+template <int BQ>
+__global__ __launch_bounds__(kRowThreads) void row_score_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
+                                                                const uint16_t* __restrict__ k, float* __restrict__ scores,
+                                                                int rows, float scale) {
+  static_assert(kRowTokens / BQ <= kScoreJ, "one tile of key blocks");
+  __shared__ __attribute__((aligned(1024))) char k_lds[kScoreStageBytes];
+  __shared__ __attribute__((aligned(16))) char q_lds[kPlanes][kRowBytes];
+  __shared__ float s_sum[2][kScoreJ];
+  const int per_die = (rows + kXcds - 1) / kXcds;      // workgroup b is on die b % 8: a run of rows per die
+  const int row = int(blockIdx.x) % kXcds * per_die + int(blockIdx.x) / kXcds;
+  if (row >= rows) return;
+  int s, h, i, nb;
+  decode_row(meta, row, s, h, i, nb);
+  const int g = kv_head_of(meta, h);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = lane >> 4, chunk = lane & 15;        // tokens part, part + 4, ..; dims 8 chunk ..
+  const int seq_begin = meta.tok_begin[s], seq_end = meta.tok_begin[s + 1];
+
+  for (int b = wave; b < i + 2; b += kRowWaves) {        // the query block, then key blocks 0 .. i
+    const bool is_q = b == 0;
+    const int j = is_q ? i : b - 1;
+    const int t0 = seq_begin + j * BQ, t1 = min(seq_end, t0 + BQ);
+    const int64_t stride = is_q ? st.q_t : st.kv_t;
+    const uint16_t* src = (is_q ? q + h * st.q_h : k + g * st.kv_h) + 8 * chunk;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    constexpr int U = 16;                                // loads in flight per lane
+#pragma unroll
+    for (int first = 0; first < BQ / 4; first += U) {
+      u32x4 w[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        w[u] = *reinterpret_cast<const u32x4*>(src + int64_t(min(t0 + part + 4 * (first + u), t1 - 1)) * stride);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool there = t0 + part + 4 * (first + u) < t1;     // (zero changes no sum: none is -0)
+        add_bf16x8(acc, u32x4{there ? w[u][0] : 0u, there ? w[u][1] : 0u, there ? w[u][2] : 0u, there ? w[u][3] : 0u});
+      }
+    }
+    // the four parts in order, in all lanes; then plane `part` of the mean goes to LDS
+    const float count = float(t1 - t0);
+    uint16_t plane[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      float lower, upper, p0, p1, p2, p3;
+      pair_values(acc[c], lower, upper);
+      row_values(lower, p0, p1);
+      row_values(upper, p2, p3);
+      float v = (((p0 + p1) + p2) + p3) / count;
+      const __bf16 b0 = (__bf16)v;
+      v -= float(b0);
+      const __bf16 b1 = (__bf16)v;
+      v -= float(b1);
+      const __bf16 b2 = (__bf16)v;
+      plane[c] = __builtin_bit_cast(uint16_t, part == 0 ? b0 : part == 1 ? b1 : b2);
+    }
+    if (part < kPlanes) {
+      char* at = is_q ? q_lds[part] + 16 * chunk : k_lds + (part * kScoreJ + j) * kRowBytes + ((chunk ^ swz(j)) << 4);
+      *reinterpret_cast<u32x4*>(at) = u32x4{plane[0] | uint32_t(plane[1]) << 16, plane[2] | uint32_t(plane[3]) << 16,
+                                            plane[4] | uint32_t(plane[5]) << 16, plane[6] | uint32_t(plane[7]) << 16};
+    }
+  }
+  __syncthreads();
+  if (wave < 2) {                                        // the two accumulators of score_kernel, a wave each
+    const int n = lane & 31, hi = lane >> 5;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    auto q_at = [&](int pl, int ks) { return *reinterpret_cast<const bf16x8*>(q_lds[pl] + 32 * ks + 16 * hi); };
+    auto k_at = [&](int pl, int ks) {
+      return *reinterpret_cast<const bf16x8*>(k_lds + (pl * kScoreJ + n) * kRowBytes + ((2 * ks + hi ^ swz(n)) << 4));
+    };
+    // wave 0: q1 k1 + q2 k1 + q1 k3, wave 1: q1 k2 + q2 k2 + q3 k1
+    bf16x8 kf[8][2], qf[8][3];
+    const int k_first = wave, k_last = wave == 0 ? 2 : 0;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      kf[ks][0] = k_at(k_first, ks);
+      kf[ks][1] = k_at(k_last, ks);
+      qf[ks][0] = q_at(0, ks);
+      qf[ks][1] = q_at(1, ks);
+      qf[ks][2] = q_at(wave == 0 ? 0 : 2, ks);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][0], qf[ks][0], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][0], qf[ks][1], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][1], qf[ks][2], acc, 0, 0, 0);
+    }
+    if (n == 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_sum[wave][8 * (r >> 2) + 4 * hi + (r & 3)] = acc[r];
+  }
+  __syncthreads();
+  if (tid <= i) scores[meta.score_off[s] + (int64_t(h) * nb + i) * nb + tid] = (s_sum[0][tid] + s_sum[1][tid]) * scale;
+}
+
 }  // namespace
 
 int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, float* scores,
                            uint16_t* q_planes, uint16_t* k_planes, int n_compute_units, hipStream_t stream) {
   const SeqMeta& m = g.meta;
+  // One launch for both steps up to one row per compute unit and 1024 tokens, or two rows and 512: what a compute unit reads
+  // is what it costs.  At 2048 tokens x 16/4 heads both ways take 43 us, with 64-token blocks one launch takes 33.3 us for
+  // 8/8 heads, two 31.0; with two rows, at 900 tokens and 64-token blocks 34.8 and 33.5, at 2 x 1000 40.8 and 41.1.
+  const int64_t longest = int64_t(g.max_nb) * m.block;
+  if ((g.rows <= n_compute_units && longest <= kRowTokens) || (g.rows <= 2 * n_compute_units && 2 * longest <= kRowTokens)) {
+    const int per_die = int((g.rows + kXcds - 1) / kXcds);
+    const auto kernel = m.block == 128 ? row_score_kernel<128> : row_score_kernel<64>;
+    hipLaunchKernelGGL(kernel, dim3(per_die * kXcds), dim3(kRowThreads), 0, stream, m, g.st, static_cast<const uint16_t*>(q),
+                       static_cast<const uint16_t*>(k), scores, int(g.rows), g.scale);
+    return hipGetLastError() == hipSuccess ? SHPLB_OK : SHPLB_E_HIP;
+  }
   const int q_chunks = (m.n_q_heads * kHeadDim + kPoolElems - 1) / kPoolElems;
   const int k_chunks = (m.n_kv_heads * kHeadDim + kPoolElems - 1) / kPoolElems;
   const int64_t n_wg = g.total_blocks * (q_chunks + k_chunks);

@@ -391,3 +391,32 @@ def test_pooling_of_ragged_blocks(block, tails):
 def test_scores_where_one_wave_scores_a_sequence(n_blocks):
     # sequences of at most 32 blocks are scored by workgroups of one wave, if the launch has no longer one
     full_parity(make_custom([64 * n_blocks - 9, 64, 70], 4, 2, 64, [5] * 4, seed=n_blocks, name="score_%d" % n_blocks))
+
+
+@pytest.mark.parametrize("block, heads, lens", [
+    (128, (4, 2), [1, 3, 4, 5, 61, 63, 64, 65, 67, 127, 128, 129, 255, 1024]),
+    (64, (5, 5), [1, 5, 60, 63, 64, 65, 1023]),
+    (128, (32, 8), [1021]),                              # one row per compute unit of an MI355X
+    (64, (32, 8), [512, 449]),                           # two
+])
+def test_scores_of_few_short_rows(block, heads, lens):
+    # few rows of short sequences are pooled and scored in one launch, beside a longer sequence in two: the same bits,
+    # also from the columns of a fused QKV buffer; and nothing is written above the diagonal
+    import paper_2603_10353_amd as S
+    from harness import to_dev_bf16
+    hq, hkv = heads
+    wl = make_custom([*lens, 1100], hq, hkv, block, [2] * (hq * (len(lens) + 1)), seed=block + hq, name="few_rows")
+    full_parity(wl)
+    ref = _gpu()(wl)
+    ref.scores_step()
+    n = sum(lens)
+    packed = torch.empty((n, hq + hkv, wl.head_dim), dtype=torch.bfloat16, device="cuda:0")
+    packed[:, :hq] = to_dev_bf16(wl.q)[:n]
+    packed[:, hq:] = to_dev_bf16(wl.k)[:n]
+    st = dict(q_stride_t=packed.stride(0), q_stride_h=wl.head_dim, kv_stride_t=packed.stride(0), kv_stride_h=wl.head_dim)
+    p = S.Problem(wl.cu_seqlens[:-1], hq, hkv, block, wl.head_dim, **st)
+    scores = torch.full((int(S.shplb_score_layout(p)[-1]),), float("nan"), dtype=torch.float32, device="cuda:0")
+    ws = torch.empty(S.shplb_workspace_bytes(p), dtype=torch.uint8, device="cuda:0")
+    S.shplb_block_scores(p, packed[:, :hq], packed[:, hq:], scores, ws, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(scores.view(torch.int32), ref.scores[:scores.numel()].view(torch.int32))
