@@ -301,14 +301,16 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 
 // accumulator, take 0.4 us.
 // Whole path: 32/8 heads x 777 tokens 29.6 -> 26.6 us, x 300 tokens 21.2 -> 17.8, 4/2 x 60 20.3 -> 17.7, 28/4 x (513, 129)
 // 25.8 -> 22.8, eight sequences of 250 x 32/8 31.3 -> 27.0.  Workgroups of 16 waves do as well, but only one fits a
-// compute unit (the last of these 29.6); 32 loads in flight per lane change nothing.
-constexpr int kRowThreads = 512, kRowWaves = kRowThreads / 64;
+// compute unit (the last of these 29.6); they are the faster ones where eight waves take two turns at 64-token blocks (8/2
+// heads x 800 tokens, 64-token blocks: 26.3 us in two launches, 25.5 with eight waves, 24.7 with 16).  32 loads in
+// flight per lane change nothing.
 constexpr int kRowTokens = 1024;                      // of the longest sequence
 
-template <int BQ>
-__global__ __launch_bounds__(kRowThreads) void row_score_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
-                                                                const uint16_t* __restrict__ k, float* __restrict__ scores,
-                                                                int rows, float scale) {
+template <int BQ, int kThreads>
+__global__ __launch_bounds__(kThreads) void row_score_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
+                                                             const uint16_t* __restrict__ k, float* __restrict__ scores,
+                                                             int rows, float scale) {
+  constexpr int kWaves = kThreads / 64;
   static_assert(kRowTokens / BQ <= kScoreJ, "one tile of key blocks");
   __shared__ __attribute__((aligned(1024))) char k_lds[kScoreStageBytes];
   __shared__ __attribute__((aligned(16))) char q_lds[kPlanes][kRowBytes];
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(kRowThreads) void row_score_kernel(SeqMeta meta, St
   const int part = lane >> 4, chunk = lane & 15;        // tokens part, part + 4, ..; dims 8 chunk ..
   const int seq_begin = meta.tok_begin[s], seq_end = meta.tok_begin[s + 1];
 
-  for (int b = wave; b < i + 2; b += kRowWaves) {        // the query block, then key blocks 0 .. i
+  for (int b = wave; b < i + 2; b += kWaves) {        // the query block, then key blocks 0 .. i
     const bool is_q = b == 0;
     const int j = is_q ? i : b - 1;
     const int t0 = seq_begin + j * BQ, t1 = min(seq_end, t0 + BQ);
@@ -412,8 +414,9 @@ int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, floa
   const int64_t longest = int64_t(g.max_nb) * m.block;
   if ((g.rows <= n_compute_units && longest <= kRowTokens) || (g.rows <= 2 * n_compute_units && 2 * longest <= kRowTokens)) {
     const int per_die = int((g.rows + kXcds - 1) / kXcds);
-    const auto kernel = m.block == 128 ? row_score_kernel<128> : row_score_kernel<64>;
-    hipLaunchKernelGGL(kernel, dim3(per_die * kXcds), dim3(kRowThreads), 0, stream, m, g.st, static_cast<const uint16_t*>(q),
+    const bool wide = m.block == 64 && 2 * longest > kRowTokens;
+    const auto kernel = m.block == 128 ? row_score_kernel<128, 512> : wide ? row_score_kernel<64, 1024> : row_score_kernel<64, 512>;
+    hipLaunchKernelGGL(kernel, dim3(per_die * kXcds), dim3(wide ? 1024 : 512), 0, stream, m, g.st, static_cast<const uint16_t*>(q),
                        static_cast<const uint16_t*>(k), scores, int(g.rows), g.scale);
     return hipGetLastError() == hipSuccess ? SHPLB_OK : SHPLB_E_HIP;
   }
