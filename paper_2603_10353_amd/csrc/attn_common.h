@@ -75,6 +75,10 @@ __device__ __forceinline__ void pair_values(float x, float& lower, float& upper)
   lower = a;
   upper = b;
 }
+// The upper half of a trades places with the lower half of b.
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
 // For rows of 16 lanes: the odd rows of a trade places with the even rows of b.
 __device__ __forceinline__ void swap_rows(uint32_t& a, uint32_t& b) {
   asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));

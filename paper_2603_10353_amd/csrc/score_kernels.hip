@@ -294,24 +294,25 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 
 // query block) and, again, all key blocks in front of it, and multiplies them.
 //
 // Two launches of some 5 us each, of which most is starting, waiting for the first loads and ending, become one.  What that
-// costs is key blocks read by every row behind them, from the die's L2 (rows of a KV head share a die): at 64 bytes a cycle
-// and compute unit some 0.25 us per block of 128 tokens, see the rule in launch_pool_scores().  A wave pools a block at a
-// time, each of its rows of 16 lanes every fourth token, a lane 8 dims: sums, means, planes and products are those of the two
-// kernels above, bit for bit.  All 32 columns of the product are the one query block; its 24 dependent MFMAs, on a wave for each
-// accumulator, take 0.4 us.
-// Whole path: 32/8 heads x 777 tokens 29.6 -> 26.6 us, x 300 tokens 21.2 -> 17.8, 4/2 x 60 20.3 -> 17.7, 28/4 x (513, 129)
-// 25.8 -> 22.8, eight sequences of 250 x 32/8 31.3 -> 27.0.  Workgroups of 16 waves do as well, but only one fits a
-// compute unit (the last of these 29.6); they are the faster ones where eight waves take two turns at 64-token blocks (8/2
-// heads x 800 tokens, 64-token blocks: 26.3 us in two launches, 25.5 with eight waves, 24.7 with 16).  32 loads in
-// flight per lane change nothing.
-constexpr int kRowTokens = 1024;                      // of the longest sequence
+// costs is key blocks read and added up by every row behind them: some 0.2 us per block of 128 tokens, from the die's L2 (rows
+// of a KV head share a die), see the rule in launch_pool_scores().  A wave pools a block at a time, each of its rows of 16 lanes
+// every fourth token, a lane 8 dims: sums, means, planes and products are those of the two kernels above, bit for bit.
+// What a wave does per block is mostly VALU work, so full blocks have a loop without a test per token, at addresses from scalar
+// registers, and the parts trade dims before their sums meet (each part working out all 8 dims' planes, and tests for all
+// tokens, 777 tokens took 26.6 us and 8/2 x 1000 at 64-token blocks 21.3, now 25.8 and 19.3).  All 32 columns of the
+// product are the one query block; its 24 dependent MFMAs, on a wave for each accumulator, take 0.4 us.
+// Whole path: 32/8 heads x 777 tokens 29.4 -> 25.8 us, x 300 tokens 21.2 -> 17.8, 4/2 x 60 20.4 -> 17.7, 28/4 x (513, 129)
+// 26.4 -> 21.8, eight sequences of 250 x 32/8 31.4 -> 26.5.  Workgroups of 16 waves, of which one fits a compute unit, are
+// the faster ones only where eight waves take two turns and more at 64-token blocks (16/4 heads x 1000: 25.8 for 26.2 us).
+// 32 loads in flight per lane change nothing.
+constexpr int kRowTokens = 2048;                      // of the longest sequence
+static_assert(kRowTokens / 64 <= kScoreJ, "one tile of key blocks");
 
 template <int BQ, int kThreads>
 __global__ __launch_bounds__(kThreads) void row_score_kernel(SeqMeta meta, Strides st, const uint16_t* __restrict__ q,
                                                              const uint16_t* __restrict__ k, float* __restrict__ scores,
                                                              int rows, float scale) {
   constexpr int kWaves = kThreads / 64;
-  static_assert(kRowTokens / BQ <= kScoreJ, "one tile of key blocks");
   __shared__ __attribute__((aligned(1024))) char k_lds[kScoreStageBytes];
   __shared__ __attribute__((aligned(16))) char q_lds[kPlanes][kRowBytes];
   __shared__ float s_sum[2][kScoreJ];
@@ -328,44 +329,66 @@ __global__ __launch_bounds__(kThreads) void row_score_kernel(SeqMeta meta, Strid
   for (int b = wave; b < i + 2; b += kWaves) {        // the query block, then key blocks 0 .. i
     const bool is_q = b == 0;
     const int j = is_q ? i : b - 1;
-    const int t0 = seq_begin + j * BQ, t1 = min(seq_end, t0 + BQ);
+    const int t0 = seq_begin + j * BQ, count = min(seq_end - t0, BQ);
     const int64_t stride = is_q ? st.q_t : st.kv_t;
-    const uint16_t* src = (is_q ? q + h * st.q_h : k + g * st.kv_h) + 8 * chunk;
+    const char* src = reinterpret_cast<const char*>((is_q ? q + h * st.q_h : k + g * st.kv_h) + t0 * stride);
+    const uint32_t step = uint32_t(stride) * 2;          // (strides are below 2^24: 127 tokens fit 32 bits)
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     constexpr int U = 16;                                // loads in flight per lane
+    if (count == BQ) {
+      const uint32_t off = uint32_t(part) * step + 16 * chunk;
 #pragma unroll
-    for (int first = 0; first < BQ / 4; first += U) {
-      u32x4 w[U];
+      for (int first = 0; first < BQ / 4; first += U) {
+        u32x4 w[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        w[u] = *reinterpret_cast<const u32x4*>(src + int64_t(min(t0 + part + 4 * (first + u), t1 - 1)) * stride);
+        for (int u = 0; u < U; ++u) w[u] = *reinterpret_cast<const u32x4*>(src + int64_t(4 * (first + u)) * step + off);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool there = t0 + part + 4 * (first + u) < t1;     // (zero changes no sum: none is -0)
-        add_bf16x8(acc, u32x4{there ? w[u][0] : 0u, there ? w[u][1] : 0u, there ? w[u][2] : 0u, there ? w[u][3] : 0u});
+        for (int u = 0; u < U; ++u) add_bf16x8(acc, w[u]);
+      }
+    } else {
+      for (int first = 0; first < BQ / 4; first += U) {
+        u32x4 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          w[u] = *reinterpret_cast<const u32x4*>(src + uint32_t(min(part + 4 * (first + u), count - 1)) * step + 16 * chunk);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool there = part + 4 * (first + u) < count;     // (zero changes no sum: none is -0)
+          add_bf16x8(acc, u32x4{there ? w[u][0] : 0u, there ? w[u][1] : 0u, there ? w[u][2] : 0u, there ? w[u][3] : 0u});
+        }
       }
     }
-    // the four parts in order, in all lanes; then plane `part` of the mean goes to LDS
-    const float count = float(t1 - t0);
-    uint16_t plane[8];
+    // Parts trade dims until each has two of the eight, 2 part and 2 part + 1, from all four; their sum, in order, is the
+    // pool's.  The mean goes to LDS as three planes.
+    float of_part[2][4];
+    {
+      uint32_t a[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      float lower, upper, p0, p1, p2, p3;
-      pair_values(acc[c], lower, upper);
-      row_values(lower, p0, p1);
-      row_values(upper, p2, p3);
-      float v = (((p0 + p1) + p2) + p3) / count;
-      const __bf16 b0 = (__bf16)v;
-      v -= float(b0);
-      const __bf16 b1 = (__bf16)v;
-      v -= float(b1);
-      const __bf16 b2 = (__bf16)v;
-      plane[c] = __builtin_bit_cast(uint16_t, part == 0 ? b0 : part == 1 ? b1 : b2);
+      for (int c = 0; c < 8; ++c) a[c] = __float_as_uint(acc[c]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) swap_halves(a[c], a[c + 4]);   // parts 0, 1 now hold dims 0 .. 3, of parts p and p + 2
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        swap_rows(a[c], a[c + 2]);                               // even parts: dims 0, 1 of these, of parts 0 and 1 ..
+        swap_rows(a[c + 4], a[c + 6]);                           // .. and of 2 and 3
+        of_part[c][0] = __uint_as_float(a[c]);
+        of_part[c][1] = __uint_as_float(a[c + 2]);
+        of_part[c][2] = __uint_as_float(a[c + 4]);
+        of_part[c][3] = __uint_as_float(a[c + 6]);
+      }
     }
-    if (part < kPlanes) {
-      char* at = is_q ? q_lds[part] + 16 * chunk : k_lds + (part * kScoreJ + j) * kRowBytes + ((chunk ^ swz(j)) << 4);
-      *reinterpret_cast<u32x4*>(at) = u32x4{plane[0] | uint32_t(plane[1]) << 16, plane[2] | uint32_t(plane[3]) << 16,
-                                            plane[4] | uint32_t(plane[5]) << 16, plane[6] | uint32_t(plane[7]) << 16};
+    float mean[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      mean[c] = (((of_part[c][0] + of_part[c][1]) + of_part[c][2]) + of_part[c][3]) / float(count);
+#pragma unroll
+    for (int pl = 0; pl < kPlanes; ++pl) {
+      char* at = is_q ? q_lds[pl] + 16 * chunk : k_lds + (pl * kScoreJ + j) * kRowBytes + ((chunk ^ swz(j)) << 4);
+      const __bf16 b0 = (__bf16)mean[0], b1 = (__bf16)mean[1];
+      *reinterpret_cast<uint32_t*>(at + 4 * part) =
+          uint32_t(__builtin_bit_cast(uint16_t, b0)) | uint32_t(__builtin_bit_cast(uint16_t, b1)) << 16;
+      mean[0] -= float(b0);
+      mean[1] -= float(b1);
     }
   }
   __syncthreads();
@@ -408,13 +431,14 @@ __global__ __launch_bounds__(kThreads) void row_score_kernel(SeqMeta meta, Strid
 int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, float* scores,
                            uint16_t* q_planes, uint16_t* k_planes, int n_compute_units, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  // One launch for both steps up to one row per compute unit and 1024 tokens, or two rows and 512: what a compute unit reads
-  // is what it costs.  At 2048 tokens x 16/4 heads both ways take 43 us, with 64-token blocks one launch takes 33.3 us for
-  // 8/8 heads, two 31.0; with two rows, at 900 tokens and 64-token blocks 34.8 and 33.5, at 2 x 1000 40.8 and 41.1.
   const int64_t longest = int64_t(g.max_nb) * m.block;
-  if ((g.rows <= n_compute_units && longest <= kRowTokens) || (g.rows <= 2 * n_compute_units && 2 * longest <= kRowTokens)) {
+  // One launch for both steps up to sequences of 2048 tokens, and as many rows as one of such a sequence per compute unit
+  // reads as much as: reading is what it costs.  In two launches and in one: 8/8 heads x 2048, 64-token blocks 30.5 and 29.0 us,
+  // 16/4 x 2047 44.1 and 41.5, 40/8 x 1024 39.7 and 37.3, 16 sequences of 250 x 32/8 56.8 and 52.8, 40 of 100 x 28/4 55.9 and
+  // 52.2.  Beyond: 4/2 x 4096 61.5 and 63.7, 32/8 x 2000 (two rows a compute unit) 55.9 and 58.1.
+  if (longest <= kRowTokens && g.rows * longest <= int64_t(kRowTokens) * n_compute_units) {
     const int per_die = int((g.rows + kXcds - 1) / kXcds);
-    const bool wide = m.block == 64 && 2 * longest > kRowTokens;
+    const bool wide = m.block == 64 && longest > 512 && g.rows <= n_compute_units;
     const auto kernel = m.block == 128 ? row_score_kernel<128, 512> : wide ? row_score_kernel<64, 1024> : row_score_kernel<64, 512>;
     hipLaunchKernelGGL(kernel, dim3(per_die * kXcds), dim3(wide ? 1024 : 512), 0, stream, m, g.st, static_cast<const uint16_t*>(q),
                        static_cast<const uint16_t*>(k), scores, int(g.rows), g.scale);

@@ -396,8 +396,9 @@ def test_scores_where_one_wave_scores_a_sequence(n_blocks):
 @pytest.mark.parametrize("block, heads, lens", [
     (128, (4, 2), [1, 3, 4, 5, 61, 63, 64, 65, 67, 127, 128, 129, 255, 1024]),
     (64, (5, 5), [1, 5, 60, 63, 64, 65, 1023]),
-    (128, (32, 8), [1021]),                              # one row per compute unit of an MI355X
-    (64, (32, 8), [512, 449]),                           # two
+    (128, (16, 4), [2047]),                              # one row per compute unit of an MI355X, of the longest there are
+    (64, (8, 8), [2048]),
+    (128, (28, 4), [129, 513, 385, 511]),                # more, of shorter ones
 ])
 def test_scores_of_few_short_rows(block, heads, lens):
     # few rows of short sequences are pooled and scored in one launch, beside a longer sequence in two: the same bits,
@@ -405,7 +406,7 @@ def test_scores_of_few_short_rows(block, heads, lens):
     import paper_2603_10353_amd as S
     from harness import to_dev_bf16
     hq, hkv = heads
-    wl = make_custom([*lens, 1100], hq, hkv, block, [2] * (hq * (len(lens) + 1)), seed=block + hq, name="few_rows")
+    wl = make_custom([*lens, 2100], hq, hkv, block, [2] * (hq * (len(lens) + 1)), seed=block + hq, name="few_rows")
     full_parity(wl)
     ref = _gpu()(wl)
     ref.scores_step()
