@@ -419,7 +419,8 @@ struct TokenBudgets {
 // on rows of half the length, after which one of the pair counts while the other sums, for most of the launch (the rows get shorter
 // slowly).  12345 tokens x 32 heads, four budgets: 6.92 -> 6.60 ms; 6001 x 28, two: 832 -> 814 us; 16K x 32, one: 3.04 -> 3.01 ms;
 // 32K, at the card's power limit, 0.3 to 1%.  A third or two thirds of the length: less, at 6001 tokens slower than none.
-// Launches of fewer than three laps, or whose rows of half the length are part of the first, keep their order.
+// Launches of fewer than five laps, or whose rows of half the length are part of the first, keep their order: with 3.5 laps
+// (3576 tokens x 32, three budgets) 568 -> 582 us, with 5.1 (6001 x 28) as above.
 struct Laps {
   int32_t lap, half;                                 // workgroups of a lap, the first row of half the longest's length
   __device__ __forceinline__ int index_of(int b) const {
@@ -884,7 +885,7 @@ int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, c
   const int32_t resident = persistent_workgroups();            // two laps
   if (resident < 0) return SHPLB_E_HIP;
   Laps laps{resident / 2, levels / 2 * m.n_seq * m.n_q_heads};
-  if (laps.half < laps.lap || int64_t(laps.half) + laps.lap > n_wg || n_wg < 3 * int64_t(laps.lap)) laps.lap = 0x7fffffff;
+  if (laps.half < laps.lap || int64_t(laps.half) + laps.lap > n_wg || n_wg < 5 * int64_t(laps.lap)) laps.lap = 0x7fffffff;
   if (n_budgets <= 1) launch_token_recovery_as<1>(g, qp, kp, recovery, kb, n_budgets, levels, laps, wg, stream);
   else if (n_budgets <= 2) launch_token_recovery_as<2>(g, qp, kp, recovery, kb, n_budgets, levels, laps, wg, stream);
   else if (n_budgets <= 4) launch_token_recovery_as<4>(g, qp, kp, recovery, kb, n_budgets, levels, laps, wg, stream);
