@@ -64,7 +64,7 @@ struct QueryRun {
   // sequence.  Workgroups go to the dies in turn: places x, x + 8, .. are given consecutive heads, so that a
   // die works on few K streams (32 heads, 8 KV heads: on one).  False: this sequence is shorter.
   __device__ __forceinline__ bool init(const SeqMeta& meta, const Strides& st, const uint16_t* __restrict__ k,
-                                       int levels, const char* lds, int index) {
+                                       int levels, const char* lds, uint32_t index) {
     const int per_level = meta.n_seq * meta.n_q_heads;
     const int level = index / per_level, place = index - level * per_level;
     const int die = place % kXcds;
@@ -422,8 +422,8 @@ struct TokenBudgets {
 // Launches of fewer than five laps, or whose rows of half the length are part of the first, keep their order: with 3.5 laps
 // (3576 tokens x 32, three budgets) 568 -> 582 us, with 5.1 (6001 x 28) as above.
 struct Laps {
-  int32_t lap, half;                                 // workgroups of a lap, the first row of half the longest's length
-  __device__ __forceinline__ int index_of(int b) const {
+  uint32_t lap, half;                                // workgroups of a lap, the first row of half the longest's length
+  __device__ __forceinline__ uint32_t index_of(uint32_t b) const {
     if (b < lap) return b;
     if (b - lap < lap) return half + b - lap;
     return b - lap < half ? b - lap : b;             // those before the second lap's rows, then those behind them
@@ -884,7 +884,7 @@ int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, c
   const uint32_t wg = uint32_t(n_wg);
   const int32_t resident = persistent_workgroups();            // two laps
   if (resident < 0) return SHPLB_E_HIP;
-  Laps laps{resident / 2, levels / 2 * m.n_seq * m.n_q_heads};
+  Laps laps{uint32_t(resident / 2), uint32_t(levels / 2) * m.n_seq * m.n_q_heads};
   if (laps.half < laps.lap || int64_t(laps.half) + laps.lap > n_wg || n_wg < 5 * int64_t(laps.lap)) laps.lap = 0x7fffffff;
   if (n_budgets <= 1) launch_token_recovery_as<1>(g, qp, kp, recovery, kb, n_budgets, levels, laps, wg, stream);
   else if (n_budgets <= 2) launch_token_recovery_as<2>(g, qp, kp, recovery, kb, n_budgets, levels, laps, wg, stream);
