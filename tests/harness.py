@@ -46,6 +46,12 @@ class DevicePass:
     def scores_step(self):
         S.shplb_block_scores(self.p, self.q, self.k, self.scores, self.ws, torch.cuda.current_stream())
 
+    def pools_into_workspace(self):
+        """Takes the scores again; whether by way of block means in the workspace (two launches) or without (one)."""
+        self.ws.fill_(0xA5)
+        self.scores_step()
+        return bool((self.ws != 0xA5).any())
+
     def select_step(self, scores=None):
         S.shplb_select_topk_per_head(self.p, self.scores if scores is None else scores, self.wl.budgets,
                                      self.sel_ptr, self.sel_idx, torch.cuda.current_stream())

@@ -387,10 +387,18 @@ def test_pooling_of_ragged_blocks(block, tails):
     full_parity(wl)
 
 
-@pytest.mark.parametrize("n_blocks", [3, 32, 33])
-def test_scores_where_one_wave_scores_a_sequence(n_blocks):
-    # sequences of at most 32 blocks are scored by workgroups of one wave, if the launch has no longer one
-    full_parity(make_custom([64 * n_blocks - 9, 64, 70], 4, 2, 64, [5] * 4, seed=n_blocks, name="score_%d" % n_blocks))
+@pytest.mark.parametrize("block, heads, n_blocks, pooled", [
+    (64, (4, 2), 3, False), (64, (4, 2), 32, False),      # few short rows: pooled and scored in one launch
+    (64, (12, 2), 32, True), (64, (28, 4), 18, True),     # more rows than that takes; 32 blocks fill the wave's tile
+    (128, (4, 2), 18, True), (128, (4, 2), 31, True), (128, (4, 2), 32, True),    # longer sequences
+    (64, (4, 2), 33, True), (128, (4, 2), 33, True),      # four waves
+])
+def test_scores_where_one_wave_scores_a_sequence(block, heads, n_blocks, pooled):
+    # sequences of at most 32 blocks are scored by workgroups of one wave, if the launch has no longer one and is
+    # not small enough for one launch of pooling and scoring, which leaves the workspace alone
+    hq, hkv = heads
+    run = full_parity(make_custom([block * n_blocks - 9, 64, 70], hq, hkv, block, [5] * hq, seed=n_blocks, name="score_%d" % n_blocks))
+    assert run.pools_into_workspace() == pooled
 
 
 @pytest.mark.parametrize("block, heads, lens", [
