@@ -174,15 +174,16 @@ def test_split_leaves_short_rows_whole():
     assert torch.equal(run.out.view(torch.int16), o_plain.view(torch.int16)) and torch.equal(run.lse, l_plain)
 
 
+@pytest.mark.parametrize("last", [300, 2100])            # pooled and scored in one launch, and in two
 @pytest.mark.parametrize("block", [64, 128])
-def test_packed_qkv_strides(block):
+def test_packed_qkv_strides(block, last):
     # Q, K, V as column slices of one [T, Hq + 2 Hkv, 128] buffer (the output of a fused QKV
     # projection), O into a buffer with the strides of Q: only the addressing differs from the
     # contiguous case, so scores, selection, output and lse must come out bit-identical to it,
     # and the contiguous case is what the oracle checks.
     import paper_2603_10353_amd as S
     from harness import to_dev_bf16
-    wl = make_custom([128 * 9 + 77, 300], 6, 2, block, [5, 999, 3, 7, 2, 4] * 2, seed=71, name="packed")
+    wl = make_custom([128 * 9 + 77, last], 6, 2, block, [5, 999, 3, 7, 2, 4] * 2, seed=71, name="packed")
     ref = full_parity(wl)
     hq, hkv, d = wl.n_q_heads, wl.n_kv_heads, wl.head_dim
     width = hq + 2 * hkv
@@ -195,12 +196,13 @@ def test_packed_qkv_strides(block):
     out = out_buf[:, :hq]
     p = S.Problem(wl.cu_seqlens, hq, hkv, block, d, q_stride_t=width * d, q_stride_h=d,
                   kv_stride_t=width * d, kv_stride_h=d)
-    ws = torch.empty(S.shplb_workspace_bytes(p), dtype=torch.uint8, device="cuda:0")
+    ws = torch.full((S.shplb_workspace_bytes(p),), 0xA5, dtype=torch.uint8, device="cuda:0")
     scores = torch.full_like(ref.scores, float("nan"))
     sel_idx = torch.full_like(ref.sel_idx, -1)
     lse = torch.zeros_like(ref.lse)
     st = torch.cuda.current_stream()
     S.shplb_block_scores(p, q, k, scores, ws, st)
+    assert bool((ws != 0xA5).any()) == (last > 2048)    # block means in the workspace: two launches
     S.shplb_select_topk_per_head(p, scores, wl.budgets, ref.sel_ptr, sel_idx, st)
     S.shplb_sparse_attn_prefill(p, q, k, v, ref.sel_ptr, sel_idx, out, lse, None, ws, st)
     torch.cuda.synchronize()
@@ -266,17 +268,19 @@ def test_whole_path_in_a_hip_graph():
         assert torch.equal(run.lse, ref[3]), replay
 
 
+@pytest.mark.parametrize("beside", [[], [2100]])         # pooled and scored in one launch, and in two
 @pytest.mark.parametrize("block", [64, 128])
-def test_irregular_share_of_heads(block):
+def test_irregular_share_of_heads(block, beside):
     # A device's share under the head-to-device assignment: query heads 0, 3, 4, 5, 7, 9 of a 12/4-head
     # layer (groups of 3) read KV heads 0, 1, 1, 1, 2, 3 -- groups of 1, 3, 1 and 1 heads, which only an
-    # explicit map can express.  Two ragged sequences.
+    # explicit map can express.  Two ragged sequences, and a longer one.
     from workloads import take_heads
-    layer = make_custom([block * 9 + 31, block * 3 + 2], 12, 4, block, [2, 999, 5, 3, 7, 4, 999, 2, 6, 5, 3, 8] * 2,
-                        seed=97, name="layer12")
+    lens = [block * 9 + 31, block * 3 + 2, *beside]
+    layer = make_custom(lens, 12, 4, block, [2, 999, 5, 3, 7, 4, 999, 2, 6, 5, 3, 8] * len(lens), seed=97, name="layer12")
     share = take_heads(layer, [0, 3, 4, 5, 7, 9])
     assert share.kv_head_of.tolist() == [0, 1, 1, 1, 2, 3] and share.n_kv_heads == 4
     run = full_parity(share)
+    assert run.pools_into_workspace() == bool(beside)
     # the shared run must agree bit for bit with the same heads run with private K/V copies
     from workloads import one_kv_head_per_query_head
     ref = _gpu()(one_kv_head_per_query_head(share)).run_all()
@@ -379,12 +383,13 @@ def test_budgets_from_max_min_shifting():
     full_parity(wl)
 
 
+@pytest.mark.parametrize("beside", [[], [2100]])         # pooled and scored in one launch, and in two
 @pytest.mark.parametrize("block, tails", [(128, [1, 3, 4, 5, 61, 63, 64, 65, 67, 127]), (64, [1, 4, 5, 60, 61, 63])])
-def test_pooling_of_ragged_blocks(block, tails):
+def test_pooling_of_ragged_blocks(block, tails, beside):
     # what is left of a block after whole rounds of loads: none to all of a round, for one wave or all four;
     # sequences of one block and of two; scores of sequences of one block are a single product
-    wl = make_custom([t + block * (x % 2) for x, t in enumerate(tails)], 4, 2, block, [2] * 4, seed=block, name="ragged_%d" % block)
-    full_parity(wl)
+    wl = make_custom([t + block * (x % 2) for x, t in enumerate(tails)] + beside, 4, 2, block, [2] * 4, seed=block, name="ragged_%d" % block)
+    assert full_parity(wl).pools_into_workspace() == bool(beside)
 
 
 @pytest.mark.parametrize("block, heads, n_blocks, pooled", [
