@@ -412,6 +412,9 @@ def test_scores_where_one_wave_scores_a_sequence(block, heads, n_blocks, pooled)
     (128, (16, 4), [2047]),                              # one row per compute unit of an MI355X, of the longest there are
     (64, (8, 8), [2048]),
     (128, (28, 4), [129, 513, 385, 511]),                # more, of shorter ones
+    (64, (8, 2), [1, 65, 449, 512]),                     # 64-token blocks in workgroups of eight waves: short sequences ..
+    (64, (28, 4), [577, 321]),                           # .. and more rows than compute units
+    (64, (40, 8), [895]),                                # up to two blocks a wave
 ])
 def test_scores_of_few_short_rows(block, heads, lens):
     # few rows of short sequences are pooled and scored in one launch, beside a longer sequence in two: the same bits,
@@ -422,7 +425,7 @@ def test_scores_of_few_short_rows(block, heads, lens):
     wl = make_custom([*lens, 2100], hq, hkv, block, [2] * (hq * (len(lens) + 1)), seed=block + hq, name="few_rows")
     full_parity(wl)
     ref = _gpu()(wl)
-    ref.scores_step()
+    assert ref.pools_into_workspace()                    # two launches
     n = sum(lens)
     packed = torch.empty((n, hq + hkv, wl.head_dim), dtype=torch.bfloat16, device="cuda:0")
     packed[:, :hq] = to_dev_bf16(wl.q)[:n]
@@ -430,7 +433,8 @@ def test_scores_of_few_short_rows(block, heads, lens):
     st = dict(q_stride_t=packed.stride(0), q_stride_h=wl.head_dim, kv_stride_t=packed.stride(0), kv_stride_h=wl.head_dim)
     p = S.Problem(wl.cu_seqlens[:-1], hq, hkv, block, wl.head_dim, **st)
     scores = torch.full((int(S.shplb_score_layout(p)[-1]),), float("nan"), dtype=torch.float32, device="cuda:0")
-    ws = torch.empty(S.shplb_workspace_bytes(p), dtype=torch.uint8, device="cuda:0")
+    ws = torch.full((S.shplb_workspace_bytes(p),), 0xA5, dtype=torch.uint8, device="cuda:0")
     S.shplb_block_scores(p, packed[:, :hq], packed[:, hq:], scores, ws, torch.cuda.current_stream())
     torch.cuda.synchronize()
+    assert not bool((ws != 0xA5).any())                  # one
     assert torch.equal(scores.view(torch.int32), ref.scores[:scores.numel()].view(torch.int32))
