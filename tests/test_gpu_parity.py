@@ -288,9 +288,10 @@ def test_irregular_share_of_heads(block, beside):
     assert torch.equal(run.sel_idx, ref.sel_idx)
 
 
-def test_explicit_softmax_scale():
-    wl = make_custom([700], 2, 2, 64, [3, 6], seed=41, name="scale")
-    full_parity(wl, softmax_scale=0.05)
+@pytest.mark.parametrize("tokens", [700, 2100])           # pooled and scored in one launch, and in two
+def test_explicit_softmax_scale(tokens):
+    wl = make_custom([tokens], 2, 2, 64, [3, 6], seed=41, name="scale")
+    assert full_parity(wl, softmax_scale=0.05).pools_into_workspace() == (tokens > 2048)
 
 
 def test_select_kernel_bit_exact_on_given_scores():
