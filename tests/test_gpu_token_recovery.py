@@ -138,6 +138,29 @@ def test_infinite_scores(what, T):
     np.testing.assert_allclose(got[number], want[number], rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
 
 
+@pytest.mark.parametrize("budgets", [[200], [100, 400], [3, 150, 151, 1200], [1, 20, 90, 300, 700, 1300, 2000, 2800]])
+@pytest.mark.parametrize("seqlens, heads", [([3100, 1100], (28, 4)), ([900, 2, 2300, 130], (20, 4))])
+def test_rows_of_a_batch_taken_out_of_their_order(seqlens, heads, budgets):
+    # Enough workgroups for the second lap of compute units to start on rows of half the length, in batches of
+    # unequal sequences, most of whose first workgroups have no row: every query is written, and those around
+    # the rows of half the length, of the sequences' ends and some others agree with the oracle.
+    hq, hkv = heads
+    wl = make_custom(seqlens, hq, hkv, 128, [2] * hq, seed=sum(seqlens), name="token_recovery_laps")
+    levels = -(-max(seqlens) // 128)
+    per_level = len(seqlens) * hq
+    assert levels * per_level >= 5 * 256 and (levels // 2) * per_level >= 256     # (256 compute units)
+    _, got = _run(wl, budgets)
+    assert not np.isnan(got).any()
+    half = (levels - levels // 2) * 128                                           # behind the first row of half the length
+    rng = np.random.default_rng(len(budgets))
+    tokens = set(rng.integers(0, sum(seqlens), size=20).tolist())
+    for s, n in enumerate(seqlens):
+        tokens |= {int(wl.cu_seqlens[s]) + t for t in (0, half - 129, half - 128, half - 1, half, n - 1) if 0 <= t < n}
+    tokens = sorted(tokens)
+    want = orc.token_recovery(wl.q, wl.k, wl.cu_seqlens, budgets, tokens=tokens)
+    np.testing.assert_allclose(got[:, :, tokens], want[:, :, tokens], rtol=TOKEN_RECOVERY_RTOL, atol=TOKEN_RECOVERY_ATOL)
+
+
 def test_is_deterministic():
     wl = make_workload(1, seqlens=[3000])
     run, a = _run(wl, [256])
