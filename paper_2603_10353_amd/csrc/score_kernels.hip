@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
 // the order of additions is fixed.
 // A launch whose sequences all have at most 32 blocks (kWaves = 1) takes workgroups of one wave, one K tile and one
 // LDS stage: of four waves three would have no row, and half as many workgroups would fit a compute unit.
-// (Whole path, 48 short sequences x 28 heads 159.0 -> 153.3 us, one prompt of 777 tokens 34.7 -> 34.5 us.)
+// (Whole path, 48 short sequences x 28 heads 159.0 -> 153.3 us.)
 constexpr int kScoreJ = 32;                           // key-block rows per LDS stage
 constexpr int kPlanes = 3;
 constexpr int kScoreStageBytes = kPlanes * kScoreJ * kRowBytes;   // 24 KB
@@ -294,16 +294,19 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 
 // query block) and, again, all key blocks in front of it, and multiplies them.
 //
 // Two launches of some 5 us each, of which most is starting, waiting for the first loads and ending, become one.  What that
-// costs is key blocks read and added up by every row behind them: some 0.2 us per block of 128 tokens, from the die's L2 (rows
-// of a KV head share a die), see the rule in launch_pool_scores().  A wave pools a block at a time, each of its rows of 16 lanes
-// every fourth token, a lane 8 dims: sums, means, planes and products are those of the two kernels above, bit for bit.
+// costs is key blocks read and added up by every row behind them: some 0.2 us per block of 128 tokens, from the die's L2 (a die
+// takes a run of rows; those of a KV head are on one die or, where a run ends inside them, on two and more), see the rule in
+// launch_pool_scores().
+// A wave pools a block at a time, each of its rows of 16 lanes every fourth token, a lane 8 dims: sums, means, planes and
+// products are those of the two kernels above, bit for bit.
 // What a wave does per block is mostly VALU work, so full blocks have a loop without a test per token, at addresses from scalar
 // registers, and the parts trade dims before their sums meet (each part working out all 8 dims' planes, and tests for all
-// tokens, 777 tokens took 26.6 us and 8/2 x 1000 at 64-token blocks 21.3, now 25.8 and 19.3).  All 32 columns of the
+// tokens, 777 tokens took 26.6 us for 25.8 and 8/2 x 1000 at 64-token blocks 21.3 for 19.3).  All 32 columns of the
 // product are the one query block; its 24 dependent MFMAs, on a wave for each accumulator, take 0.4 us.
-// Whole path: 32/8 heads x 777 tokens 29.4 -> 25.8 us, x 300 tokens 21.2 -> 17.8, 4/2 x 60 20.4 -> 17.7, 28/4 x (513, 129)
-// 26.4 -> 21.8, eight sequences of 250 x 32/8 31.4 -> 26.5.  Workgroups of 16 waves, of which one fits a compute unit, are
-// the faster ones only where eight waves take two turns and more at 64-token blocks (16/4 heads x 1000: 25.8 for 26.2 us).
+// Whole path, passes back to back on one card: 32/8 heads x 777 tokens 29.4 -> 25.4 us, x 300 tokens 23.9 -> 19.9, 4/2 x 60
+// 23.7 -> 19.8, 28/4 x (513, 129) 26.5 -> 22.0, eight sequences of 250 x 32/8 31.3 -> 26.7.  Workgroups of 16 waves, of which
+// one fits a compute unit, are the faster ones only where eight waves take two turns and more at 64-token blocks (16/4 heads
+// x 1000: 25.9 for 26.3 us, 8/8 x 2048 29.1 for 29.9).
 // 32 loads in flight per lane change nothing.
 constexpr int kRowTokens = 2048;                      // of the longest sequence
 static_assert(kRowTokens / 64 <= kScoreJ, "one tile of key blocks");
@@ -433,9 +436,14 @@ int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, floa
   const SeqMeta& m = g.meta;
   const int64_t longest = int64_t(g.max_nb) * m.block;
   // One launch for both steps up to sequences of 2048 tokens, and as many rows as one of such a sequence per compute unit
-  // reads as much as: reading is what it costs.  In two launches and in one: 8/8 heads x 2048, 64-token blocks 30.5 and 29.0 us,
-  // 16/4 x 2047 44.1 and 41.5, 40/8 x 1024 39.7 and 37.3, 16 sequences of 250 x 32/8 56.8 and 52.8, 40 of 100 x 28/4 55.9 and
-  // 52.2.  Beyond: 4/2 x 4096 61.5 and 63.7, 32/8 x 2000 (two rows a compute unit) 55.9 and 58.1.
+  // reads as much as: reading is what it costs.  Whole path in two launches and in one: 8/8 heads x 2048, 64-token blocks 31.0
+  // and 29.1 us, 16/4 x 2047 43.7 and 41.2, 40/8 x 1024 39.6 and 37.2, 16 sequences of 250 x 32/8 57.3 and 53.5, 40 of 100 x
+  // 28/4 56.1 and 52.3.  Beyond: 4/2 x 4096 61.9 and 64.1, 32/8 x 2000 (two rows a compute unit) 56.0 and 58.2.  Over 100 shapes
+  // within the rule, 46 at three quarters of its limit and more, one launch takes 0.83 to 1.01 of the time of two, eagerly and in
+  // a graph.
+  // That is the path with selection and attention behind the scores.  The scores alone, taken again and again from the same
+  // tensors, which the caches then hold, are slower in one launch near the limit (16 sequences of 239 x 28/4 at 64-token
+  // blocks, seven rows a compute unit, 15.2 for 10.9 us; the whole path 62.7 for 64.4).
   if (longest <= kRowTokens && g.rows * longest <= int64_t(kRowTokens) * n_compute_units) {
     const int per_die = int((g.rows + kXcds - 1) / kXcds);
     const bool wide = m.block == 64 && longest > 512 && g.rows <= n_compute_units;
