@@ -26,10 +26,11 @@ namespace {
 // queries.  The tiles are software-pipelined: the MFMAs of the next tile are issued before the work on the
 // present one's scores, which depends on none of them, and a tile is copied one whole step ahead of its use.
 // kSmall: the contraction in 16x16x32 MFMAs, of two groups of 16 queries, instead of 32x32x16: for a pass at the card's
-// power limit (the block mass of 32 heads x 32K tokens 4.60 -> 3.99 ms, with the kept sums below).  The token recovery is not at
-// that limit and its state is per query.  With the MFMAs behind the work on the scores the mass takes 4.18 ms, and launches of
-// one workgroup per compute unit or fewer, whose SIMDs have one wave, are slower than with 32x32x16: 8/2 heads x 4000 tokens
-// 51.5 us for 49.7, now 48.8; 8/2 x 1000 18.0 for 17.4, now 17.3.  The recovery takes 12.9 ms that way, for 12.5.
+// power limit (the block mass of 32 heads x 32K tokens 4.60 -> 3.99 ms, with the kept sums below).  The token recovery, whose
+// state is per query, is near that limit too, but waits for LDS and for VALU issue: with small products 32 heads x 32K tokens
+// take 12.2 ms for 11.7 and 28 x 6001, two budgets, 925 us for 833.  With the MFMAs behind the work on the scores the mass takes
+// 4.18 ms, and launches of one workgroup per compute unit or fewer, whose SIMDs have one wave, are slower than with 32x32x16: 8/2
+// heads x 4000 tokens 51.5 us for 49.7, now 48.8; 8/2 x 1000 18.0 for 17.4, now 17.3.
 template <bool kSmall>
 struct QueryRun {
   static constexpr int kQueries = 128, kWaves = kQueries / 32;
@@ -421,6 +422,10 @@ struct TokenBudgets {
 // 32K, at the card's power limit, 0.3 to 1%.  A third or two thirds of the length: less, at 6001 tokens slower than none.
 // Launches of fewer than five laps, or whose rows of half the length are part of the first, keep their order: with 3.5 laps
 // (3576 tokens x 32, three budgets) 568 -> 582 us, with 5.1 (6001 x 28) as above.
+// In a batch the laps also count workgroups whose sequence is shorter, which return at once and leave less of the pairing
+// above.  19 batches of equal and unequal sequences, one to five budgets: 12000 and 11000 tokens x 28/4 heads, three budgets, 8.32 ->
+// 8.10 ms, 20000 and three of 1000 x 4/2 2.31 -> 2.24 ms, eight of 3000 x 8/2 310 -> 301 us; most within 1%, the least
+// favourable 2000 and thirty of 10 tokens x 8, 170.9 -> 172.4 us.
 struct Laps {
   uint32_t lap, half;                                // workgroups of a lap, the first row of half the longest's length
   __device__ __forceinline__ uint32_t index_of(uint32_t b) const {
@@ -456,8 +461,8 @@ struct Laps {
 //
 // 32 heads x 32K tokens, k = 4096: 11.5 to 12.0 ms on several cards, against 131 ms with the threshold found bit by bit in 27
 // to 29 sweeps; three budgets at 4000 tokens x 16 heads 520 us.  The two sweeps and the samples would take 6.8 ms without any
-// work on the scores, which is what their MFMAs take at the card's power limit (1.32 PFLOP/s, at 1.5 GHz; the whole kernel
-// runs at 2.1 GHz).  Three waves per SIMD (tiles of 32 keys, 74 bins) were slower, 16.4 ms; so were workgroups of eight waves
+// work on the scores, which is what their MFMAs, 2.05 passes of products, take at the card's power limit (1.32 PFLOP/s, at
+// 1.5 GHz; the whole kernel runs at 2.1 GHz).  Three waves per SIMD (tiles of 32 keys, 74 bins) were slower, 16.4 ms; so were workgroups of eight waves
 // that share a tile, 2.5%, also with half of the waves doing their MFMAs behind the work on the scores, 6%.
 constexpr int kBins = 95;                          // and the longest list: 128 queries x 95 words leave room for
                                                    // two workgroups per compute unit beside the tiles
@@ -744,8 +749,9 @@ __global__ __launch_bounds__(256, 2) void token_recovery_kernel(SeqMeta meta, St
   // Sums and masks of a group of scores first, without a branch; then the scores of the group that go to a list, which few
   // do: a scalar test and a branch each.  (With the branch behind every score's own comparison a score waited for its
   // exponential, two comparisons and four scalar operations before the next one began; 32K x 32 heads, one budget: 12.4 ->
-  // 11.9 ms, 6001 tokens x 28 heads, two: 903 -> 818 us.  Groups of 8 over all budgets take up to 2% more, of 32 spill scalar
-  // registers and are as slow as none.)
+  // 11.9 ms, 6001 tokens x 28 heads, two: 903 -> 818 us; eight: 3000 tokens x 8/2 heads 1185 -> 957 us, 8000 x 32/8 7.98 -> 6.84
+  // ms.  Groups of 8 over all budgets take up to 2% more.  The masks cost scalar registers: 5, 14, 38 and 90 of them are
+  // spilled with 1, 2, 4 and 8 budgets; with groups of 32 104 to 586 are, which is as slow as no groups.)
   constexpr int G = 16 / M;
   row.sweep(0, all, stride, true, [&](int, Run::Scores& sc) {
     float sum0 = 0.0f, sum1 = 0.0f, part[M];
