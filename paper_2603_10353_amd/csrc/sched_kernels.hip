@@ -10,7 +10,8 @@
 // has the most items left (see help_item()), which keeps the greedy's balance when the dies'
 // queues hold very different amounts of work.
 //
-// One launch of eight workgroups; workgroup x builds the queue of die x with a counting sort
+// Whole rows of up to 2048 (sequence, head) pairs find their places without a sort: see place_kernel.  The others
+// go through one launch of eight workgroups (order_kernel); workgroup x builds the queue of die x with a counting sort
 // whose histogram (one entry per possible cost) lies in LDS: count, scan, place.  It looks
 // only at the rows that live on its die; where its queue begins follows from the shapes
 // alone, so the workgroups need nothing from each other.  Rows of equal cost are placed in
@@ -27,14 +28,10 @@
 // Launches without splitting that have no more rows than workgroups skip all this: see row_place() in
 // attn_pipe_kernel.hip.
 //
-// What bounds it: a chain of dependent memory round trips (geometry, row pointer, first
+// What bounds order_kernel: a chain of dependent memory round trips (geometry, row pointer, first
 // selected blocks, record) on eight compute units.  A thread works out one (sequence, head)
 // pair, a prefix sum over the pairs lies in LDS, and threads then find their rows in it by
 // bisection: nothing loops over sequences and no lane is idle when sequences are short.
-// 8.1 us at 2080 rows (one 8K prompt, 32 heads), 9.2 us for 3668 rows in 48 sequences, 15.4 us at
-// 16384, 26 us at 32768.  Before, one workgroup sorted launches of up to 16384 rows and five dependent
-// launches the larger ones, decoding every row (a loop over the sequences and two integer divisions)
-// twice: 8.8, 41.8, 37.8 and 38 us.
 #include <type_traits>
 
 #include "shplb_internal.h"
@@ -230,13 +227,11 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
   // ---- count: items per cost on this die; items (and slots, split rows) of the dies before it
   int begin = 0, before = 0, slots = 0, splits = 0;   // without splitting every row is one item and the shapes say `begin`
   int n_rows = 0;
-  bool fetched = false;                              // all rows of the die are in the threads' registers
   for (int base = 0; base < n_pairs; base += kBatch) {
     if (base > 0) __syncthreads();
     n_rows = load_batch(base, split, begin);
-    fetched = !split && n_pairs <= kBatch && n_rows <= kInFlight * kOrderThreads;
     for (int r0 = tid; r0 - tid < n_rows; r0 += kInFlight * kOrderThreads) {
-      fetch(r0, n_rows, fetched);
+      fetch(r0, n_rows, false);
 #pragma unroll
       for (int u = 0; u < kInFlight; ++u) {
         if (!split) {
@@ -285,13 +280,11 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 
   // ---- place
   for (int base = 0; base < n_pairs; base += kBatch) {
-    if (split || n_pairs > kBatch) {                 // else the batch is still laid out
-      int unused = 0;
-      if (base > 0) __syncthreads();
-      n_rows = load_batch(base, false, unused);
-    }
+    int unused = 0;
+    if (base > 0) __syncthreads();
+    n_rows = load_batch(base, false, unused);
     for (int r0 = tid; r0 - tid < n_rows; r0 += kInFlight * kOrderThreads) {
-      if (!fetched) fetch(r0, n_rows, true);
+      fetch(r0, n_rows, true);
 #pragma unroll
       for (int u = 0; u < kInFlight; ++u) {
         const int n = n_sel[u], bin = min(n, n_bins - 1), pieces = split ? pieces_of(n, split_len) : 1;
@@ -338,10 +331,191 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
   }
 }
 
+// The queues of a launch of whole rows, without a sort: where a row goes follows from its own number of blocks and
+// from the budgets of the heads on its die, and every row works it out for itself.
+//
+// A row of query block i selects c = min(k, i + 1) blocks, k being what the last row of its (sequence, head) pair
+// selects.  So the rows with more than c blocks are counted pair by pair, nb - c of each pair with k > c, and so are those with
+// as many in front of it (pairs in order, then query blocks).  Keys are taken from k and i alone, never from a row's own entry in sel_ptr: the
+// places are then a permutation whatever sel_ptr holds (a caller may list other blocks than a budget's), only
+// the order is by cost just where rows are those of a budget.  The record holds what sel_ptr says.
+//
+// A workgroup takes 32 consecutive rows of a stream (the heads of one KV head of one sequence; with a caller's map of heads,
+// of one head), eight lanes each, which share the pairs of the die between them and write the record together.  An extra
+// workgroup at the end writes the queues' beginnings and tickets.
+// What bounds it is the chain arguments -> row pointer -> first blocks, with the pairs' budgets behind the
+// arguments at the same time; nothing is sorted, and it takes as many compute units as there are rows for.  Under
+// the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.6 us, 48 sequences x 28 heads 10.2 -> 6.5, 32K x 32
+// heads 12.0 -> 5.2, 128K 26 -> 5.7 (whole path: 8K 180.6 -> 175.1 us, the 48 sequences 145.4 -> 143.3).  With the pairs
+// listed one by one, a division each, instead of by streams the 48 sequences took 7.9.
+constexpr int kPlaceThreads = 256, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes;
+constexpr int kPlacePairs = 2048;         // pairs of a launch, each of which may be on the same die
+
+__global__ __launch_bounds__(kPlaceThreads) void place_kernel(
+    SeqMeta meta, const int64_t* __restrict__ sel_ptr, const int32_t* __restrict__ sel_idx,
+    ItemRec* __restrict__ items, int32_t* __restrict__ queue_begin, uint32_t* __restrict__ tickets, int item_capacity,
+    int grid) {
+  __shared__ int32_t s_blk[SHPLB_MAX_SEQ + 1], s_tok[SHPLB_MAX_SEQ + 1];
+  __shared__ uint32_t s_kv[SHPLB_MAX_MAPPED_HEADS / 4];
+  __shared__ uint32_t s_unit[kPlacePairs];   // units on this die: number of the first pair | blocks << 16 ...
+  __shared__ int32_t s_row[kPlacePairs];     // ... and first row
+  __shared__ uint32_t s_pair[kPlacePairs];   // their pairs: number | blocks << 16 ...
+  __shared__ int32_t s_k[kPlacePairs];       // ... and blocks of the last row
+  __shared__ int32_t s_count, s_before, s_total[kXcds];
+  static_assert(SHPLB_MAX_SEQ < kPlaceThreads && SHPLB_MAX_BLOCKS < 1 << 16 && kPlacePairs <= 1 << 16, "");
+  const int tid = threadIdx.x, lane = tid & 63;
+  // asked for together: the geometry, of which a lane-dependent index is read
+  const int my_blk = meta.blk_begin[min(tid, SHPLB_MAX_SEQ)], my_tok = meta.tok_begin[min(tid, SHPLB_MAX_SEQ)];
+  const uint32_t my_kv = meta.kv_of[min(tid, SHPLB_MAX_MAPPED_HEADS / 4 - 1)];
+  const int n_seq = meta.n_seq, hq = meta.n_q_heads, hkv = meta.n_kv_heads;
+  const bool map = meta.kv_map != 0;
+  auto scalar = [](int v) { return int(__builtin_amdgcn_readfirstlane(v)); };
+  // x / y of non-negative numbers below 2^24, quotients below 2^16
+  auto quotient = [](int x, int y) {
+    const int q = int(float(x) * __builtin_amdgcn_rcpf(float(y))), r = x - q * y;
+    return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
+  };
+  const int group = map ? 1 : scalar(quotient(hq, hkv));      // heads of a unit, whose K/V is one stream ...
+  const int units = map ? hq : hkv, n_units = n_seq * units;  // ... and how many units a sequence has, and all have
+  const int n_streams = n_seq * hkv;
+  const int mod = n_streams < kXcds ? scalar(quotient(kXcds, n_streams)) : 1;   // dies of a stream: 1, 2, 4 or 8
+  const int log_mod = 31 - __builtin_clz(mod);
+  if (tid <= SHPLB_MAX_SEQ) {
+    s_blk[tid] = my_blk;
+    s_tok[tid] = my_tok;
+  }
+  if (tid < SHPLB_MAX_MAPPED_HEADS / 4) s_kv[tid] = my_kv;
+  if (tid < kXcds) s_total[tid] = 0;
+  if (tid == 0) s_count = s_before = 0;
+  __syncthreads();
+  auto kv_head = [&](int h) { return map ? int(s_kv[h >> 2] >> (8 * (h & 3)) & 0xff) : quotient(h, group); };
+  struct Unit { int stream, nb, pair, row; };                 // (pair, row: its first)
+  auto unit_of = [&](int u) {
+    const int s = quotient(u, units), first = (u - s * units) * group, b0 = s_blk[s], nb = s_blk[s + 1] - b0;
+    return Unit{map ? s * hkv + kv_head(first) : u, nb, s * hq + first, b0 * hq + first * nb};
+  };
+
+  if (blockIdx.x == gridDim.x - 1) {                          // the queues' beginnings
+    for (int u = tid; u < n_units; u += kPlaceThreads) {
+      const Unit e = unit_of(u);
+      if (mod == 1) atomicAdd(&s_total[e.stream % kXcds], group * e.nb);
+      else
+        for (int r = 0; r < mod; ++r) atomicAdd(&s_total[e.stream * mod + r], group * ((e.nb + mod - 1 - r) >> log_mod));
+    }
+    __syncthreads();
+    if (tid <= kXcds) {
+      int begin = 0;
+      for (int x = 0; x < tid; ++x) begin += s_total[x];
+      queue_begin[tid] = begin;
+    }
+    if (tid < kXcds) tickets[tid * kTicketStride] = uint32_t(grid - tid + kXcds - 1) / kXcds;   // see order_kernel
+    return;
+  }
+
+  // ---- the workgroup's sequence, heads and rows
+  int s = 0, part = int(blockIdx.x);
+  if (n_seq > 1) {
+    const int at = min(lane, n_seq - 1), nb = s_blk[at + 1] - s_blk[at];
+    const int parts = lane < n_seq ? units * ((group * nb + kPlaceRows - 1) / kPlaceRows) : 0;
+    const int end = wave_scan(parts);
+    s = min(int(__builtin_popcountll(__ballot(lane < n_seq && part >= end))), n_seq - 1);
+    part -= s > 0 ? __builtin_amdgcn_readlane(end, s - 1) : 0;
+  }
+  const int b0 = scalar(s_blk[s]), nb = scalar(s_blk[s + 1]) - b0;
+  const int parts = (group * nb + kPlaceRows - 1) / kPlaceRows;
+  const int unit = scalar(quotient(part, parts));
+  const int at = (part - unit * parts) * kPlaceRows + tid / kPlaceLanes, e8 = tid % kPlaceLanes;
+  const bool live = at < group * nb;
+  const int head_in = live ? quotient(at, nb) : 0, i = live ? at - head_in * nb : 0;
+  const int h = unit * group + head_in, row = b0 * hq + h * nb + i, own_pair = s * hq + h;
+  const int64_t begin = sel_ptr[row], end = sel_ptr[row + 1];
+  const int kv = map ? scalar(kv_head(unit)) : unit, stream = s * hkv + kv;
+  const int res = i & (mod - 1);                              // the row's die is stream * mod + res, or stream % 8
+  // query blocks below v whose rows are on the row's die
+  auto below = [&](int v) { return (v + mod - 1 - res) >> log_mod; };
+
+  // ---- the units of the die, and the rows of the dies before it
+  int before = 0;
+  for (int u0 = 0; u0 < n_units; u0 += kPlaceThreads) {
+    const int u = u0 + tid;
+    bool own = false;
+    Unit e{0, 0, 0, 0};
+    if (u < n_units) {
+      e = unit_of(u);
+      own = mod == 1 ? e.stream % kXcds == stream % kXcds : e.stream == stream;
+      before += (mod == 1 ? e.stream % kXcds < stream % kXcds : e.stream < stream) ? group * e.nb : 0;
+    }
+    const uint64_t mask = __ballot(own);
+    int first = 0;
+    if (mask != 0) {
+      if (lane == 0) first = atomicAdd(&s_count, __builtin_popcountll(mask));
+      first = scalar(first);
+    }
+    if (own) {
+      const int x = first + int(__builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u)));
+      s_unit[x] = uint32_t(e.pair | e.nb << 16);
+      s_row[x] = e.row;
+    }
+  }
+  before = wave_scan(before);
+  if (lane == 63 && before != 0) atomicAdd(&s_before, before);
+  const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1)));
+  const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
+  __syncthreads();
+  const int n_own = s_count * group;
+  for (int x = tid; x < n_own; x += kPlaceThreads) {
+    const int u = quotient(x, group), head = x - u * group, rows = int(s_unit[u] >> 16);
+    const int end = s_row[u] + (head + 1) * rows;
+    s_pair[x] = s_unit[u] + head;
+    s_k[x] = int(min(max(sel_ptr[end] - sel_ptr[end - 1], int64_t(1)), int64_t(rows)));
+  }
+  __syncthreads();
+
+  // ---- the row's place
+  const int own_end = b0 * hq + (h + 1) * nb;
+  const int k = int(min(max(sel_ptr[own_end] - sel_ptr[own_end - 1], int64_t(1)), int64_t(nb)));
+  const int c = min(k, i + 1), below_c = below(c), at_c = below_c - below(c - 1);
+  int place = 0;
+  for (int x = e8; x < n_own; x += kPlaceLanes) {
+    const int p = int(s_pair[x] & 0xffff), rows = int(s_pair[x] >> 16), k_p = s_k[x], all = below(rows);
+    place += (rows >> log_mod) * res + min(rows & (mod - 1), res);      // on the stream's dies before this one
+    if (c < k_p) place += all - below_c;
+    if (p < own_pair) place += c < k_p ? at_c : c == k_p ? all - below_c + at_c : 0;
+    if (p == own_pair && c == k_p) place += below(i) - below(k_p - 1);
+  }
+  place += __shfl_xor(place, 1);
+  place += __shfl_xor(place, 2);
+  place += __shfl_xor(place, 4);
+  place += s_before;
+  if (!live || uint32_t(place) >= uint32_t(item_capacity)) return;      // (the latter never: keeps stores in bounds)
+  // a lane's two words of the record
+  int lo = 0, hi = n_sel;
+  if (e8 == 1) lo = int(uint32_t(begin)), hi = int(begin >> 32);
+  if (e8 == 2) lo = -1, hi = 1;                                         // slot, pieces
+  if (e8 == 3) lo = hi = -1;                                            // first_slot, split_index
+  if (e8 == 4) lo = s_tok[s], hi = s_tok[s + 1];
+  if (e8 == 5) lo = h, hi = kv;
+  if (e8 == 6) lo = i, hi = nb;
+  if (e8 == 7) lo = first_j, hi = second_j;
+  reinterpret_cast<int2*>(items + place)[e8] = int2{lo, hi};
+}
+
 }  // namespace
 
 int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* sel_idx, const WorkspaceLayout& w,
                      char* workspace, int32_t n_wg, int32_t grid, hipStream_t stream) {
+  const SeqMeta& m = g.meta;
+  if (w.slot_capacity == 0 && int64_t(m.n_seq) * m.n_q_heads <= kPlacePairs) {
+    const int units = m.kv_map ? m.n_q_heads : m.n_kv_heads, group = m.n_q_heads / units;
+    int64_t parts = 0;
+    for (int s = 0; s < m.n_seq; ++s)
+      parts += units * ((int64_t(group) * (m.blk_begin[s + 1] - m.blk_begin[s]) + kPlaceRows - 1) / kPlaceRows);
+    hipLaunchKernelGGL(place_kernel, dim3(uint32_t(parts + 1)), dim3(kPlaceThreads), 0, stream, m, sel_ptr, sel_idx,
+                       reinterpret_cast<ItemRec*>(workspace + w.items),
+                       reinterpret_cast<int32_t*>(workspace + w.queue_begin),
+                       reinterpret_cast<uint32_t*>(workspace + w.tickets), int(w.item_capacity), grid);
+    return hipGetLastError() == hipSuccess ? SHPLB_OK : SHPLB_E_HIP;
+  }
   hipLaunchKernelGGL(order_kernel, dim3(kXcds), dim3(kOrderThreads), 0, stream, g.meta, sel_ptr, sel_idx,
                      reinterpret_cast<ItemRec*>(workspace + w.items),
                      reinterpret_cast<int32_t*>(workspace + w.queue_begin),

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2603_10353_amd as S
 from oracle import shplb_oracle as orc
 from workloads import make_custom
 
@@ -19,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_seq, heads", [(64, (40, 8)), (1, (6, 1)), (1, (6, 3)), (1, (10, 5)), (2, (4, 2)), (7, (3, 1)), (9, (3, 1))])
 def test_every_row_is_dealt_once(n_seq, heads):
-    # the first shape through the ordering kernel (2800 rows and more), the others without queues: up to 140 rows
+    # the first shape through the sorting kernel (2560 pairs), the others without queues: up to 140 rows
     # in runs, 315 and 393 in laps
     hq, hkv = heads
     rng = np.random.default_rng(100 * n_seq + hq)
@@ -54,6 +55,67 @@ def test_every_row_is_dealt_once_from_queues(block, seqlens, heads):
     assert st["n_items"].sum() == run.rows and st["cost_blocks"].sum() == run.sel_ptr_host[-1]
     # every row, by its denominators: those of whole causal rows are never zero, and the buffer was
     assert (run.lse != 0).all()
+
+
+@pytest.mark.parametrize("block, seqlens, heads, kv_of", [
+    (128, [230], (6, 1), None), (128, [181], (6, 3), None), (64, [300], (10, 5), None), (128, [70, 67], (8, 4), None),
+    (128, [33, 1, 64], (28, 4), None), (64, [97, 31, 32], (16, 8), None), (64, [17] * 64, (32, 8), None),
+    (128, [90, 40], (8, 2), [0, 1, 1, 1, 1, 1, 1, 1]), (64, [131, 9], (24, 9), [x % 9 for x in range(24)])])
+def test_queues_hold_every_row_by_cost(block, seqlens, heads, kv_of):
+    # What the ordering kernel leaves in the workspace, where rows work their places out for themselves (up to 2048
+    # (sequence, head) pairs: the seventh shape): 1, 3, 5, 8, 12 .. 512 K/V streams on eight dies, heads of a stream and mapped ones, runs of 32 rows
+    # that end inside a head; for rows of a budget and for rows of any number of blocks, none among them.
+    hq, hkv = heads
+    rng = np.random.default_rng(len(seqlens) + hq + block)
+    lens = [block * nb - int(rng.integers(0, block)) for nb in seqlens]
+    n_seq, nbs = len(lens), np.array(seqlens)
+    budgets = rng.choice([2, 3, 5, 11, 999], size=n_seq * hq).astype(np.int32)
+    p = S.Problem(np.concatenate([[0], np.cumsum(lens)]), hq, hkv, block, 128, kv_head_of=kv_of)
+    ptr = S.shplb_sel_row_ptr(p, budgets)
+    kv_of = kv_of or [h // (hq // hkv) for h in range(hq)]
+    what = np.array([(s, h, i) for s in range(n_seq) for h in range(hq) for i in range(nbs[s])])
+    rows, n_streams = len(what), n_seq * hkv
+    stream = what[:, 0] * hkv + np.array(kv_of)[what[:, 1]]
+    spread = 8 // n_streams if n_streams < 8 else 1
+    die = stream % 8 if n_streams >= 8 else stream * spread + what[:, 2] % spread
+    odd = np.concatenate([[0], np.cumsum([int(rng.integers(0, i + 2)) for _, _, i in what])]).astype(np.int64)
+    total = int(p.cu[-1])
+    q = torch.zeros((total, hq, 128), dtype=torch.bfloat16, device="cuda:0")
+    kv = torch.zeros((total, hkv, 128), dtype=torch.bfloat16, device="cuda:0")
+    out = torch.zeros_like(q)
+    size = S.shplb_workspace_bytes(p)
+    for by_budget, sel in ((True, ptr), (False, odd)):
+        idx = np.concatenate([rng.permutation(i + 1)[:n] for (_, _, i), n in zip(what, np.diff(sel))]).astype(np.int32)
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        print("case", block, seqlens[:4], heads, "rows", rows, "by budget", by_budget, flush=True)
+        S.shplb_sparse_attn_prefill(p, q, kv, kv, torch.from_numpy(sel).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"), out, None,
+                                    None, ws, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert rows > S.shplb_sched_num_workgroups(p)             # (so there are queues)
+        left = ws.cpu().numpy()
+        # the workspace ends with the items, an unused piece of 256 bytes, where the queues begin, and eight tickets 64 bytes apart
+        at = size - 512 - 256 - 256 - -(-rows * 64 // 256) * 256
+        item = left[at:at + 64 * rows].view(np.int32).reshape(rows, 16)
+        begin = left[size - 768:size - 768 + 36].view(np.int32)
+        assert begin.tolist() == np.concatenate([[0], np.cumsum(np.bincount(die, minlength=8))]).tolist()
+        index = {tuple(w): r for r, w in enumerate(what)}
+        at_token = np.concatenate([[0], np.cumsum(lens)])
+        s_of = np.searchsorted(at_token, item[:, 8])
+        row = np.array([index[(int(s), int(x[10]), int(x[12]))] for s, x in zip(s_of, item)])
+        assert (np.sort(row) == np.arange(rows)).all()
+        assert (die[row] == np.repeat(np.arange(8), np.diff(begin))).all()
+        n = np.diff(sel)[row]
+        expect = np.zeros((rows, 16), np.int64)
+        expect[:, 1], expect[:, 2], expect[:, 4], expect[:, 5], expect[:, 6], expect[:, 7] = n, sel[row], -1, 1, -1, -1
+        expect[:, 8], expect[:, 9], expect[:, 10], expect[:, 11] = at_token[s_of], at_token[s_of + 1], what[row, 1], np.array(kv_of)[what[row, 1]]
+        expect[:, 12], expect[:, 13] = what[row, 2], nbs[s_of]
+        full = np.append(idx, 0)
+        expect[:, 14] = np.where(n > 0, full[sel[row]], 0)
+        expect[:, 15] = np.where(n > 0, full[sel[row] + np.minimum(1, np.maximum(n - 1, 0))], 0)
+        assert (item == expect).all()
+        if by_budget:
+            for x in range(8):
+                assert (np.diff(n[begin[x]:begin[x + 1]]) <= 0).all()
 
 
 @pytest.mark.parametrize("heads", [(2, 1), (8, 8)])
