@@ -118,6 +118,22 @@ def test_queues_hold_every_row_by_cost(block, seqlens, heads, kv_of):
                 assert (np.diff(n[begin[x]:begin[x + 1]]) <= 0).all()
 
 
+@pytest.mark.parametrize("block, n_blocks, heads", [(128, 16, (32, 8)), (128, 17, (32, 8)), (64, 32, (40, 8)), (64, 33, (40, 8)), (128, 3, (8, 2))])
+def test_rows_too_short_to_cut_through_the_splitting_entry_point(block, n_blocks, heads):
+    # Up to 16 blocks of 128 tokens or 32 of 64 no row is cut: no queue, or the same as without splitting; beyond, as many
+    # pieces as rows.  The same bits as from the entry point of whole rows (with 64-token rows shared by two groups of waves too).
+    hq, hkv = heads
+    wl = make_custom([block * n_blocks - 9], hq, hkv, block, [999] * (hq // 2) + [3] * (hq // 2), seed=700 + n_blocks, name="uncut_%d" % n_blocks)
+    run = DevicePass(wl).run_all()
+    out, lse = run.out.clone(), run.lse.clone()
+    run.out.zero_()
+    run.attn_split_step(64)
+    torch.cuda.synchronize()
+    st = run.stats_host()
+    assert st["n_items"].sum() == run.rows and st["cost_blocks"].sum() == run.sel_ptr_host[-1]
+    assert torch.equal(run.out.view(torch.int16), out.view(torch.int16)) and torch.equal(run.lse, lse)
+
+
 @pytest.mark.parametrize("heads", [(2, 1), (8, 8)])
 def test_pieces_of_split_rows(heads):
     hq, hkv = heads
