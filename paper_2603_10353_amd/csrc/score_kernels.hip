@@ -35,6 +35,10 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
     uint16_t* __restrict__ q_planes, uint16_t* __restrict__ k_planes, int q_chunks, int k_chunks,
     int total_blocks) {
   __shared__ float part[kPoolWaves][kPoolElems];
+  // what a single sequence needs of the arguments is loaded together, before the first use
+  asm volatile("" ::"s"(q_chunks), "s"(k_chunks), "s"(total_blocks), "s"(meta.n_seq), "s"(meta.n_q_heads), "s"(meta.n_kv_heads), "s"(meta.block),
+               "s"(meta.tok_begin[1]), "s"(q), "s"(k), "s"(q_planes), "s"(k_planes), "s"(st.q_t), "s"(st.q_h),
+               "s"(st.kv_t), "s"(st.kv_h));
   int bid = blockIdx.x;
   const bool is_q = bid < total_blocks * q_chunks;
   if (!is_q) bid -= total_blocks * q_chunks;
@@ -48,9 +52,16 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
   uint16_t* dst = is_q ? q_planes : k_planes;
   const int64_t plane = int64_t(n_heads) * total_blocks * kHeadDim;
 
-  const int s = sequence_of(meta, gblk, 1);
-  const int t0 = meta.tok_begin[s] + (gblk - meta.blk_begin[s]) * meta.block;
-  const int t1 = min(meta.tok_begin[s + 1], t0 + meta.block);
+  int t0 = gblk * meta.block, t1 = meta.tok_begin[1];
+  if (meta.n_seq > 1) {
+    // a lane per sequence: how many end at or before the block, and the rest from the lane of its own
+    const int lane = threadIdx.x & 63, blk_end = meta.blk_begin[lane + 1], tok = meta.tok_begin[lane], tok_end = meta.tok_begin[lane + 1];
+    const int s = __builtin_popcountll(__ballot(lane < meta.n_seq - 1 && gblk >= blk_end));
+    const int first = s > 0 ? __builtin_amdgcn_readlane(blk_end, s - 1) : 0;
+    t0 = __builtin_amdgcn_readlane(tok, s) + (gblk - first) * meta.block;
+    t1 = __builtin_amdgcn_readlane(tok_end, s);
+  }
+  t1 = min(t1, t0 + meta.block);
   const int cnt = t1 - t0;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -319,12 +330,16 @@ __global__ __launch_bounds__(kThreads) void row_score_kernel(SeqMeta meta, Strid
   __shared__ __attribute__((aligned(1024))) char k_lds[kScoreStageBytes];
   __shared__ __attribute__((aligned(16))) char q_lds[kPlanes][kRowBytes];
   __shared__ float s_sum[2][kScoreJ];
+  // what a single sequence needs of the arguments is loaded together, before the first use
+  asm volatile("" ::"s"(rows), "s"(meta.n_seq), "s"(meta.blk_begin[1]), "s"(meta.n_kv_heads),
+               "s"(meta.kv_map), "s"(q), "s"(k), "s"(scores), "s"(st.q_t), "s"(st.q_h), "s"(st.kv_t), "s"(st.kv_h));
   const int per_die = (rows + kXcds - 1) / kXcds;      // workgroup b is on die b % 8: a run of rows per die
   const int row = int(blockIdx.x) % kXcds * per_die + int(blockIdx.x) / kXcds;
   if (row >= rows) return;
   int s, h, i, nb;
-  decode_row(meta, row, s, h, i, nb);
-  const int g = kv_head_of(meta, h);
+  int64_t score_off;
+  decode_row(meta, row, s, h, i, nb, score_off);
+  const int g = meta.kv_map ? kv_head_of(meta, h) : small_quotient(h, small_quotient(meta.n_q_heads, meta.n_kv_heads));
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int part = lane >> 4, chunk = lane & 15;        // tokens part, part + 4, ..; dims 8 chunk ..
   const int seq_begin = meta.tok_begin[s], seq_end = meta.tok_begin[s + 1];
@@ -426,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void row_score_kernel(SeqMeta meta, Strid
       for (int r = 0; r < 16; ++r) s_sum[wave][8 * (r >> 2) + 4 * hi + (r & 3)] = acc[r];
   }
   __syncthreads();
-  if (tid <= i) scores[meta.score_off[s] + (int64_t(h) * nb + i) * nb + tid] = (s_sum[0][tid] + s_sum[1][tid]) * scale;
+  if (tid <= i) scores[score_off + (int64_t(h) * nb + i) * nb + tid] = (s_sum[0][tid] + s_sum[1][tid]) * scale;
 }
 
 }  // namespace

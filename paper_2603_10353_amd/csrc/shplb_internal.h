@@ -158,24 +158,33 @@ __device__ __forceinline__ int kv_head_of(const SeqMeta& m, int h) {
   return m.kv_map ? int(m.kv_of[h >> 2] >> (8 * (h & 3)) & 0xff) : h / (m.n_q_heads / m.n_kv_heads);
 }
 
-// The sequence of block `at` (per_block 1) or row `at` (per_block: the query heads), the same in all lanes of the
-// wave, all of them active: how many sequences end at or before it, a lane per sequence.  (A loop over the sequences
-// is a chain of up to 63 scalar loads in front of everything a workgroup
-// does: the path over 48 sequences took 160.4 us with it in the pooling and selection kernels, 155.4 without.)
-__device__ __forceinline__ int sequence_of(const SeqMeta& m, int32_t at, int per_block) {
-  static_assert(SHPLB_MAX_SEQ <= 64, "a lane per sequence");
-  if (m.n_seq == 1) return 0;
-  const int lane = threadIdx.x & 63;
-  return __builtin_popcountll(__ballot(lane < m.n_seq - 1 && at >= m.blk_begin[min(lane + 1, m.n_seq)] * per_block));
+// x / y, the same in all lanes, of non-negative numbers; quotients below 2^20 (the approximate one is then off by one at most).
+__device__ __forceinline__ int small_quotient(int x, int y) {
+  const int q = __builtin_amdgcn_readfirstlane(int(float(x) * __builtin_amdgcn_rcpf(float(y)))), r = x - q * y;
+  return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
-// Row -> (sequence, head, query block).  Rows of one sequence are contiguous.
-__device__ __forceinline__ void decode_row(const SeqMeta& m, int32_t row, int& s, int& h, int& i, int& nb) {
-  s = sequence_of(m, row, m.n_q_heads);
-  const int local = row - m.blk_begin[s] * m.n_q_heads;
-  nb = m.blk_begin[s + 1] - m.blk_begin[s];
-  h = local / nb;
-  i = local - h * nb;
+// Row -> (sequence, head, query block), blocks of the sequence and offset of its scores.  Rows of one sequence are
+// contiguous.  Of several sequences a lane looks at one (all 64 of them active); what is wanted of the row's comes from
+// that lane, not by another load.  (A load that waits for another one costs some 0.3 us at the start of a launch.  With the
+// geometry, the row's entry in sel_ptr and its scores asked for as early as they can be, here and in the kernels, the whole path takes 24.2
+// us for 25.3 at 777 tokens x 32/8 heads, 28.9 for 30.3 at 2048 x 8/8 with 64-token blocks, 139.2 for 140.5 for 48 sequences.)
+__device__ __forceinline__ void decode_row(const SeqMeta& m, int32_t row, int& s, int& h, int& i, int& nb, int64_t& score_off) {
+  static_assert(SHPLB_MAX_SEQ == 64, "a lane per sequence");
+  s = 0;
+  nb = m.blk_begin[1];
+  score_off = 0;
+  if (m.n_seq > 1) {
+    const int lane = threadIdx.x & 63, end = m.blk_begin[lane + 1];
+    const int64_t off = m.score_off[lane];
+    s = __builtin_popcountll(__ballot(lane < m.n_seq - 1 && row >= end * m.n_q_heads));
+    const int first = s > 0 ? __builtin_amdgcn_readlane(end, s - 1) : 0;
+    nb = __builtin_amdgcn_readlane(end, s) - first;
+    row -= first * m.n_q_heads;
+    score_off = int64_t(uint32_t(__builtin_amdgcn_readlane(int(off), s))) | int64_t(__builtin_amdgcn_readlane(int(off >> 32), s)) << 32;
+  }
+  h = small_quotient(row, nb);
+  i = row - h * nb;
 }
 
 // An item from another die's queue for a persistent workgroup whose own is empty (called by one whole
