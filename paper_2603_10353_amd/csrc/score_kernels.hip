@@ -143,38 +143,41 @@ __global__ __launch_bounds__(kPoolThreads) __attribute__((amdgpu_waves_per_eu(2,
 // output tile and four runs of four consecutive j: 16-byte stores.  Two accumulators take
 // the six products in turn (no MFMA waits for the one before it) and are added at the end;
 // the order of additions is fixed.
-// A launch whose sequences all have at most 32 blocks (kWaves = 1) takes workgroups of one wave, one K tile and one
-// LDS stage: of four waves three would have no row, and half as many workgroups would fit a compute unit.
-// (Whole path, 48 short sequences x 28 heads 159.0 -> 153.3 us.)
+// Launches of few rows (kWaves = 1, see the rule in launch_pool_scores()) take workgroups of one wave, one K tile and one
+// LDS stage: of sequences of up to 32 blocks three of four waves would have no row, and half as many workgroups would fit a
+// compute unit.  (Whole path, 48 short sequences x 28 heads 159.0 -> 153.3 us.)
 constexpr int kScoreJ = 32;                           // key-block rows per LDS stage
 constexpr int kPlanes = 3;
 constexpr int kScoreStageBytes = kPlanes * kScoreJ * kRowBytes;   // 24 KB
-// chunks (of `chunk` key-block rows) that hold some j <= i for the rows of tile row tr
-__host__ __device__ constexpr int score_chunks_of_row(int tr, int chunk, int tile) {
-  return (tr * tile + tile - 1) / chunk + 1;
+// chunks (of 2^log_chunk key-block rows) that hold some j <= i for the rows of tile row tr
+__host__ __device__ constexpr int score_chunks_of_row(int tr, int log_chunk, int tile) {
+  return ((tr * tile + tile - 1) >> log_chunk) + 1;
 }
 
 template <int kWaves>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void score_kernel(
     SeqMeta meta, const uint16_t* __restrict__ q_planes, const uint16_t* __restrict__ k_planes,
-    float* __restrict__ scores, int total_blocks, int chunk, float scale) {
+    float* __restrict__ scores, int total_blocks, int log_chunk, float scale) {
   constexpr int kScoreTile = 32 * kWaves;               // query-block rows per workgroup
   __shared__ __attribute__((aligned(1024))) char k_lds[kWaves == 1 ? 1 : 2][kScoreStageBytes];
+  // what needs no sequence is loaded together, before the first use
+  asm volatile("" ::"s"(meta.n_q_heads), "s"(meta.n_kv_heads), "s"(meta.kv_map), "s"(q_planes), "s"(k_planes), "s"(scores), "s"(total_blocks),
+               "s"(log_chunk), "s"(scale));
   const int sh = blockIdx.z;
-  const int s = sh / meta.n_q_heads, h = sh - s * meta.n_q_heads;
+  const int s = small_quotient(sh, meta.n_q_heads), h = sh - s * meta.n_q_heads;
   const int nb = meta.blk_begin[s + 1] - meta.blk_begin[s];
   // blockIdx.x enumerates (128-row tile of query blocks, chunk of key blocks) pairs of the
   // lower triangle, tile row by tile row.  Consecutive workgroup ids go to different XCDs,
   // so every die gets the same share of live work (a square grid would hand die x the whole
   // chunk column x, most of which lies above the diagonal for large x).
   int tr = 0, rest = int(blockIdx.x);
-  while (rest >= score_chunks_of_row(tr, chunk, kScoreTile)) rest -= score_chunks_of_row(tr++, chunk, kScoreTile);
-  const int ti = tr * kScoreTile, tj = rest * chunk;
+  while (rest >= score_chunks_of_row(tr, log_chunk, kScoreTile)) rest -= score_chunks_of_row(tr++, log_chunk, kScoreTile);
+  const int ti = tr * kScoreTile, chunk = 1 << log_chunk, tj = rest << log_chunk;
   if (ti >= nb) return;                             // shorter sequence of a varlen batch
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, hi = lane >> 5;
-  const int g = kv_head_of(meta, h);
+  const int g = meta.kv_map ? kv_head_of(meta, h) : small_quotient(h, small_quotient(meta.n_q_heads, meta.n_kv_heads));
   const int i_first = ti + 32 * wave;               // this wave's rows
   const int i_last = min(ti + kScoreTile, nb) - 1;  // last row of the workgroup
   if (tj > i_last) return;                          // chunk entirely right of a short sequence's last row (before any copy is issued)
@@ -478,22 +481,27 @@ int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, floa
   // Key-block rows per workgroup: the shortest chunk with which the whole launch is resident at
   // once (three workgroups per compute unit); more, shorter workgroups would run in rounds,
   // fewer, longer ones would leave compute units idle.
-  const bool small = g.max_nb <= 32;
+  const int64_t resident = int64_t(n_compute_units) * 3, n_sh = int64_t(m.n_seq) * m.n_q_heads;
+  // Workgroups of one wave, 32 rows and one K tile, while no more than three per compute unit come of it: with four waves such
+  // a launch has few workgroups, each of which goes through its tiles in turn.  Scoring call, four waves against one: 32/8 heads x
+  // 6000 18.3 -> 16.6 us, x 8231 23.1 -> 21.2, x 16384 37.1 -> 35.9, 8/2 x 20000 18.1 -> 15.5, 28/4 x 8000 with 64-token blocks 20.7 -> 18.7;
+  // 32/8 x 24000 (672 workgroups) 49.3 and 49.3, x 32768 (1152) 63.6 and 63.9, with 64-token blocks (4352) 72.1 and 75.4.
+  const int tiles32 = (g.max_nb + 31) / 32;
+  const bool small = tiles32 == 1 || int64_t(tiles32) * (tiles32 + 1) / 2 * n_sh <= resident;
   const int tile = small ? 32 : 128, tiles = (g.max_nb + tile - 1) / tile;
-  const int64_t resident = int64_t(n_compute_units) * 3;
-  int chunk = small ? 32 : 64, n_pairs = 0;
-  for (;; chunk *= 2) {
+  int log_chunk = small ? 5 : 6, n_pairs = 0;
+  for (;; ++log_chunk) {
     n_pairs = 0;
-    for (int tr = 0; tr < tiles; ++tr) n_pairs += score_chunks_of_row(tr, chunk, tile);
-    if (int64_t(n_pairs) * m.n_seq * m.n_q_heads <= resident || chunk >= tiles * tile) break;
+    for (int tr = 0; tr < tiles; ++tr) n_pairs += score_chunks_of_row(tr, log_chunk, tile);
+    if (small || n_pairs * n_sh <= resident || 1 << log_chunk >= tiles * tile) break;
   }
   const dim3 grid(n_pairs, 1, m.n_seq * m.n_q_heads);
   if (small)
     hipLaunchKernelGGL((score_kernel<1>), grid, dim3(64), 0, stream, m, q_planes, k_planes, scores, int(g.total_blocks),
-                       chunk, g.scale);
+                       log_chunk, g.scale);
   else
     hipLaunchKernelGGL((score_kernel<4>), grid, dim3(256), 0, stream, m, q_planes, k_planes, scores, int(g.total_blocks),
-                       chunk, g.scale);
+                       log_chunk, g.scale);
   if (hipGetLastError() != hipSuccess) return SHPLB_E_HIP;
   return SHPLB_OK;
 }

@@ -407,6 +407,29 @@ def test_scores_where_one_wave_scores_a_sequence(block, heads, n_blocks, pooled)
     assert run.pools_into_workspace() == pooled
 
 
+@pytest.mark.parametrize("block, n_blocks", [(64, 33), (64, 64), (128, 65), (64, 129)])
+def test_scores_by_one_wave_and_by_four(block, n_blocks):
+    # Launches of up to three workgroups per compute unit score 32 rows and 32 key blocks in one of one wave, larger ones
+    # (here: the same sequence among 63 of one block) 128 rows in four waves: the same bits, nothing above the diagonal.
+    T = block * n_blocks - 9
+    one = make_custom([T], 8, 2, block, [2] * 8, seed=800 + n_blocks, name="one_wave_%d" % n_blocks)
+    many = make_custom([T] + [7] * 63, 8, 2, block, [2] * 8, seed=1, name="four_waves_%d" % n_blocks)
+    many.q[:T], many.k[:T] = one.q, one.k
+    tiles = -(-n_blocks // 32)
+    assert tiles * (tiles + 1) // 2 * 8 <= 768 < tiles * (tiles + 1) // 2 * 512
+    a, b = _gpu()(one), _gpu()(many)
+    print("case", one.name, flush=True)
+    a.scores_step()
+    b.scores_step()
+    torch.cuda.synchronize()
+    sc_o, sc_g = orc.block_scores(one.q, one.k, one.cu_seqlens, block, None)[0], a.scores_host()[0]
+    low, up = np.tril_indices(n_blocks), np.triu_indices(n_blocks, 1)
+    for h in range(8):
+        np.testing.assert_allclose(sc_g[h][low], sc_o[h][low], rtol=1e-5, atol=SCORE_ATOL)
+        assert np.isnan(sc_g[h][up]).all()
+    assert torch.equal(a.scores.view(torch.int32), b.scores[:a.scores.numel()].view(torch.int32))
+
+
 @pytest.mark.parametrize("block, heads, lens", [
     (128, (4, 2), [1, 3, 4, 5, 61, 63, 64, 65, 67, 127, 128, 129, 255, 1024]),
     (64, (5, 5), [1, 5, 60, 63, 64, 65, 1023]),
