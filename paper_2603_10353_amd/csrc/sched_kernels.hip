@@ -10,7 +10,7 @@
 // has the most items left (see help_item()), which keeps the greedy's balance when the dies'
 // queues hold very different amounts of work.
 //
-// Whole rows of up to 2048 (sequence, head) pairs find their places without a sort: see place_kernel.  The others
+// Rows of up to 2048 (sequence, head) pairs find their places without a sort: see place_kernel.  Launches of more pairs
 // go through one launch of eight workgroups (order_kernel); workgroup x builds the queue of die x with a counting sort
 // whose histogram (one entry per possible cost) lies in LDS: count, scan, place.  It looks
 // only at the rows that live on its die; where its queue begins follows from the shapes
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
   }
 }
 
-// The queues of a launch of whole rows, without a sort: where a row goes follows from its own number of blocks and
+// The queues without a sort: where a row goes follows from its own number of blocks and
 // from the budgets of the heads on its die, and every row works it out for itself.
 //
 // A row of query block i selects c = min(k, i + 1) blocks, k being what the last row of its (sequence, head) pair
@@ -340,6 +340,12 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 // places are then a permutation whatever sel_ptr holds (a caller may list other blocks than a budget's), only
 // the order is by cost just where rows are those of a budget.  The record holds what sel_ptr says.
 //
+// Pieces (kPieces): a row of c blocks is cut into one piece more for every m with m len < c, so the items in front of a row are
+// the rows with more than max(c, m len) blocks, summed over m.  The length is split_length() of the budgets' cost, which is the selection's where
+// rows are those of a budget: never more pieces than slots.  Split rows are the first of their queues, so slots and counters are
+// numbered like items and rows, behind those of the dies before.  A row that is not its budget's is cut into as many pieces
+// as its place has room for, or as it has blocks.
+//
 // A workgroup takes 32 consecutive rows of a stream (the heads of one KV head of one sequence; with a caller's map of heads,
 // of one head), eight lanes each, which share the pairs of the die between them and write the record together.  An extra
 // workgroup at the end writes the queues' beginnings and tickets.
@@ -347,14 +353,16 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 // arguments at the same time; nothing is sorted, and it takes as many compute units as there are rows for.  Under
 // the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.6 us, 48 sequences x 28 heads 10.2 -> 6.5, 32K x 32
 // heads 12.0 -> 5.2, 128K 26 -> 5.7 (whole path: 8K 180.6 -> 175.1 us, the 48 sequences 145.4 -> 143.3).  With the pairs
-// listed one by one, a division each, instead of by streams the 48 sequences took 7.9.
+// listed one by one, a division each, instead of by streams the 48 sequences took 7.9.  In pieces, whole path: 16K x 32 heads
+// with four dense ones 546 -> 538 us, 3000 x 32 with a dense one 75.1 -> 70.0, 9000 x 28 with 64-token blocks 276 -> 268.
 constexpr int kPlaceThreads = 256, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes;
 constexpr int kPlacePairs = 2048;         // pairs of a launch, each of which may be on the same die
 
+template <bool kPieces>
 __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     SeqMeta meta, const int64_t* __restrict__ sel_ptr, const int32_t* __restrict__ sel_idx,
-    ItemRec* __restrict__ items, int32_t* __restrict__ queue_begin, uint32_t* __restrict__ tickets, int item_capacity,
-    int grid) {
+    ItemRec* __restrict__ items, int32_t* __restrict__ queue_begin, uint32_t* __restrict__ tickets, uint32_t* __restrict__ split_done,
+    int item_capacity, int slot_capacity, int n_wg, int grid) {
   __shared__ int32_t s_blk[SHPLB_MAX_SEQ + 1], s_tok[SHPLB_MAX_SEQ + 1];
   __shared__ uint32_t s_kv[SHPLB_MAX_MAPPED_HEADS / 4];
   __shared__ uint32_t s_unit[kPlacePairs];   // units on this die: number of the first pair | blocks << 16 ...
@@ -362,6 +370,12 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   __shared__ uint32_t s_pair[kPlacePairs];   // their pairs: number | blocks << 16 ...
   __shared__ int32_t s_k[kPlacePairs];       // ... and blocks of the last row
   __shared__ int32_t s_count, s_before, s_total[kXcds];
+  // pieces: of all pairs the blocks of the last row | blocks << 13 | die << 26 (0 the workgroup's, 1 before it, 2 behind it);
+  // all blocks selected; slots and split rows on the dies before
+  __shared__ uint32_t s_all[kPieces ? kPlacePairs : 1];
+  __shared__ unsigned long long s_cost;
+  __shared__ int32_t s_slots, s_splits;
+  static_assert(SHPLB_MAX_BLOCKS < 1 << 13, "");
   static_assert(SHPLB_MAX_SEQ < kPlaceThreads && SHPLB_MAX_BLOCKS < 1 << 16 && kPlacePairs <= 1 << 16, "");
   const int tid = threadIdx.x, lane = tid & 63;
   // asked for together: the geometry, of which a lane-dependent index is read
@@ -377,6 +391,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   };
   const int group = map ? 1 : scalar(quotient(hq, hkv));      // heads of a unit, whose K/V is one stream ...
   const int units = map ? hq : hkv, n_units = n_seq * units;  // ... and how many units a sequence has, and all have
+  const int n_pairs = n_seq * hq;
   const int n_streams = n_seq * hkv;
   const int mod = n_streams < kXcds ? scalar(quotient(kXcds, n_streams)) : 1;   // dies of a stream: 1, 2, 4 or 8
   const int log_mod = 31 - __builtin_clz(mod);
@@ -386,7 +401,10 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   }
   if (tid < SHPLB_MAX_MAPPED_HEADS / 4) s_kv[tid] = my_kv;
   if (tid < kXcds) s_total[tid] = 0;
-  if (tid == 0) s_count = s_before = 0;
+  if (tid == 0) {
+    s_count = s_before = s_slots = s_splits = 0;
+    s_cost = 0;
+  }
   __syncthreads();
   auto kv_head = [&](int h) { return map ? int(s_kv[h >> 2] >> (8 * (h & 3)) & 0xff) : quotient(h, group); };
   struct Unit { int stream, nb, pair, row; };                 // (pair, row: its first)
@@ -395,8 +413,41 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     return Unit{map ? s * hkv + kv_head(first) : u, nb, s * hq + first, b0 * hq + first * nb};
   };
 
+  // ---- pieces: what the pairs' last rows select, and the length that rows are cut at
+  int len = 1 << 30;
+  auto load_pairs = [&](int own_stream) {
+    unsigned long long cost = 0;
+    for (int p = tid; p < n_pairs; p += kPlaceThreads) {
+      const int s = quotient(p, hq), h = p - s * hq, b0 = s_blk[s], nb = s_blk[s + 1] - b0, end = b0 * hq + (h + 1) * nb;
+      const int k = int(min(max(sel_ptr[end] - sel_ptr[end - 1], int64_t(1)), int64_t(nb))), stream = s * hkv + kv_head(h);
+      const int a = mod == 1 ? stream % kXcds : stream, b = mod == 1 ? own_stream % kXcds : own_stream;
+      s_all[p] = uint32_t(k | nb << 13 | (a == b ? 0 : a < b ? 1 : 2) << 26);
+      cost += uint32_t(k) * uint32_t(nb) - uint32_t(k) * uint32_t(k - 1) / 2;
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) cost += __shfl_xor(cost, d);
+    if (lane == 0 && cost != 0) atomicAdd(&s_cost, cost);
+    __syncthreads();
+    len = int(min(split_length(int64_t(s_cost), slot_capacity, n_wg, meta.block), int64_t(1 << 30)));
+  };
+  // f(t) for t = 0, len, 2 len .. below k: a row of more than t blocks has a piece more than one of t
+  auto each_piece = [&](int k, auto&& f) {
+    int t = 0;
+    for (int m = 0; m < kSplitMaxPieces && t < k; ++m, t += len) f(t);
+  };
+
   if (blockIdx.x == gridDim.x - 1) {                          // the queues' beginnings
-    for (int u = tid; u < n_units; u += kPlaceThreads) {
+    if constexpr (kPieces) {
+      load_pairs(0);
+      for (int p = tid; p < n_pairs; p += kPlaceThreads) {
+        const int k = int(s_all[p] & 0x1fff), nb = int(s_all[p] >> 13 & 0x1fff), s = quotient(p, hq), stream = s * hkv + kv_head(p - s * hq);
+        for (int r = 0; r < mod; ++r) {
+          int n = 0;
+          each_piece(k, [&](int t) { n += ((nb + mod - 1 - r) >> log_mod) - ((t + mod - 1 - r) >> log_mod); });
+          atomicAdd(&s_total[mod == 1 ? stream % kXcds : stream * mod + r], n);
+        }
+      }
+    } else for (int u = tid; u < n_units; u += kPlaceThreads) {
       const Unit e = unit_of(u);
       if (mod == 1) atomicAdd(&s_total[e.stream % kXcds], group * e.nb);
       else
@@ -435,8 +486,8 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   auto below = [&](int v) { return (v + mod - 1 - res) >> log_mod; };
 
   // ---- the units of the die, and the rows of the dies before it
-  int before = 0;
-  for (int u0 = 0; u0 < n_units; u0 += kPlaceThreads) {
+  int before = 0, slots = 0, splits = 0;
+  for (int u0 = 0; !kPieces && u0 < n_units; u0 += kPlaceThreads) {
     const int u = u0 + tid;
     bool own = false;
     Unit e{0, 0, 0, 0};
@@ -457,13 +508,45 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
       s_row[x] = e.row;
     }
   }
+  if constexpr (kPieces) {
+    load_pairs(stream);
+    for (int p0 = 0; p0 < n_pairs; p0 += kPlaceThreads) {
+      const int p = p0 + tid;
+      const uint32_t e = p < n_pairs ? s_all[p] : 2u << 26;
+      const int k = int(e & 0x1fff), rows = int(e >> 13 & 0x1fff);
+      if (e >> 26 == 1) {
+        each_piece(k, [&](int t) {
+          before += rows - t;
+          slots += max(t, len) < k ? rows - max(t, len) : 0;
+        });
+        splits += len < k ? rows - len : 0;
+      }
+      const uint64_t mask = __ballot(e >> 26 == 0);
+      int first = 0;
+      if (mask != 0) {
+        if (lane == 0) first = atomicAdd(&s_count, __builtin_popcountll(mask));
+        first = scalar(first);
+      }
+      if (e >> 26 == 0) {
+        const int x = first + int(__builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u)));
+        s_pair[x] = uint32_t(p | rows << 16);
+        s_k[x] = k;
+      }
+    }
+    slots = wave_scan(slots);
+    splits = wave_scan(splits);
+    if (lane == 63 && splits != 0) {
+      atomicAdd(&s_slots, slots);
+      atomicAdd(&s_splits, splits);
+    }
+  }
   before = wave_scan(before);
   if (lane == 63 && before != 0) atomicAdd(&s_before, before);
   const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1)));
   const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
   __syncthreads();
-  const int n_own = s_count * group;
-  for (int x = tid; x < n_own; x += kPlaceThreads) {
+  const int n_own = kPieces ? s_count : s_count * group;
+  for (int x = tid; !kPieces && x < n_own; x += kPlaceThreads) {
     const int u = quotient(x, group), head = x - u * group, rows = int(s_unit[u] >> 16);
     const int end = s_row[u] + (head + 1) * rows;
     s_pair[x] = s_unit[u] + head;
@@ -475,19 +558,65 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   const int own_end = b0 * hq + (h + 1) * nb;
   const int k = int(min(max(sel_ptr[own_end] - sel_ptr[own_end - 1], int64_t(1)), int64_t(nb)));
   const int c = min(k, i + 1), below_c = below(c), at_c = below_c - below(c - 1);
-  int place = 0;
+  // rows of the same stream's dies before this one: those of the first v query blocks
+  auto earlier = [&](int v) { return (v >> log_mod) * res + min(v & (mod - 1), res); };
+  const int pieces = kPieces ? pieces_of(c, len) : 1;
+  int place = 0;                              // items in front of the row, on this die and those before
+  int slot = 0, entry = 0;                    // its first slot and its counter: split rows are the first of a queue
   for (int x = e8; x < n_own; x += kPlaceLanes) {
     const int p = int(s_pair[x] & 0xffff), rows = int(s_pair[x] >> 16), k_p = s_k[x], all = below(rows);
-    place += (rows >> log_mod) * res + min(rows & (mod - 1), res);      // on the stream's dies before this one
-    if (c < k_p) place += all - below_c;
-    if (p < own_pair) place += c < k_p ? at_c : c == k_p ? all - below_c + at_c : 0;
-    if (p == own_pair && c == k_p) place += below(i) - below(k_p - 1);
+    const int same = p < own_pair ? (c < k_p ? at_c : c == k_p ? all - below_c + at_c : 0) : p == own_pair && c == k_p ? below(i) - below(k_p - 1) : 0;
+    if constexpr (kPieces) {
+      each_piece(k_p, [&](int t) {
+        place += earlier(rows) - earlier(t);
+        if (max(t, len) < k_p) slot += earlier(rows) - earlier(max(t, len));
+        if (max(t, c) < k_p) {
+          place += all - below(max(t, c));
+          slot += all - below(max(t, c));
+        }
+      });
+      if (len < k_p) entry += earlier(rows) - earlier(len);
+      place += pieces * same;
+      slot += pieces * same;
+      entry += (c < k_p ? all - below_c : 0) + same;
+    } else {
+      place += earlier(rows) + (c < k_p ? all - below_c : 0) + same;
+    }
   }
-  place += __shfl_xor(place, 1);
-  place += __shfl_xor(place, 2);
-  place += __shfl_xor(place, 4);
-  place += s_before;
-  if (!live || uint32_t(place) >= uint32_t(item_capacity)) return;      // (the latter never: keeps stores in bounds)
+  auto of_row = [](int v) {
+    v += __shfl_xor(v, 1);
+    v += __shfl_xor(v, 2);
+    return v + __shfl_xor(v, 4);
+  };
+  place = of_row(place) + s_before;
+  if constexpr (kPieces) {
+    slot = of_row(slot) + s_slots;
+    entry = of_row(entry) + s_splits;
+  }
+  if (!live || uint32_t(place) + uint32_t(pieces) > uint32_t(item_capacity)) return;      // (the latter never: keeps stores in bounds)
+  if constexpr (kPieces) {
+    if (pieces > 1) {
+      // A row that is not its budget's may have fewer blocks than pieces are reserved for it: the others are items without a block.
+      const int real = min(pieces, n_sel);
+      if (slot + pieces > slot_capacity || entry >= slot_capacity / 2 + 1) return;        // likewise
+      if (e8 == 0) split_done[entry] = 0;
+      for (int x = 0; x < pieces; ++x) {
+        const int64_t from = x < real ? piece_begin(n_sel, real, x) : 0, to = x < real ? piece_begin(n_sel, real, x + 1) : 0;
+        const int n = int(to - from);
+        const int64_t at = begin + from;
+        int lo = 0, hi = n;
+        if (e8 == 1) lo = int(uint32_t(at)), hi = int(at >> 32);
+        if (e8 == 2) lo = real > 1 ? slot + x : -1, hi = max(real, 1);                    // slot, pieces
+        if (e8 == 3) lo = real > 1 ? slot : -1, hi = real > 1 ? entry : -1;               // first_slot, split_index
+        if (e8 == 4) lo = s_tok[s], hi = s_tok[s + 1];
+        if (e8 == 5) lo = h, hi = kv;
+        if (e8 == 6) lo = i, hi = nb;
+        if (e8 == 7 && n > 0) lo = sel_idx[at], hi = sel_idx[at + min(1, n - 1)];
+        reinterpret_cast<int2*>(items + place + x)[e8] = int2{lo, hi};
+      }
+      return;
+    }
+  }
   // a lane's two words of the record
   int lo = 0, hi = n_sel;
   if (e8 == 1) lo = int(uint32_t(begin)), hi = int(begin >> 32);
@@ -505,15 +634,15 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
 int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* sel_idx, const WorkspaceLayout& w,
                      char* workspace, int32_t n_wg, int32_t grid, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  if (w.slot_capacity == 0 && int64_t(m.n_seq) * m.n_q_heads <= kPlacePairs) {
+  if (int64_t(m.n_seq) * m.n_q_heads <= kPlacePairs) {
     const int units = m.kv_map ? m.n_q_heads : m.n_kv_heads, group = m.n_q_heads / units;
     int64_t parts = 0;
     for (int s = 0; s < m.n_seq; ++s)
       parts += units * ((int64_t(group) * (m.blk_begin[s + 1] - m.blk_begin[s]) + kPlaceRows - 1) / kPlaceRows);
-    hipLaunchKernelGGL(place_kernel, dim3(uint32_t(parts + 1)), dim3(kPlaceThreads), 0, stream, m, sel_ptr, sel_idx,
-                       reinterpret_cast<ItemRec*>(workspace + w.items),
-                       reinterpret_cast<int32_t*>(workspace + w.queue_begin),
-                       reinterpret_cast<uint32_t*>(workspace + w.tickets), int(w.item_capacity), grid);
+    hipLaunchKernelGGL(w.slot_capacity >= 2 ? place_kernel<true> : place_kernel<false>, dim3(uint32_t(parts + 1)), dim3(kPlaceThreads), 0,
+                       stream, m, sel_ptr, sel_idx, reinterpret_cast<ItemRec*>(workspace + w.items),
+                       reinterpret_cast<int32_t*>(workspace + w.queue_begin), reinterpret_cast<uint32_t*>(workspace + w.tickets),
+                       reinterpret_cast<uint32_t*>(workspace + w.split_done), int(w.item_capacity), int(w.slot_capacity), n_wg, grid);
     return hipGetLastError() == hipSuccess ? SHPLB_OK : SHPLB_E_HIP;
   }
   hipLaunchKernelGGL(order_kernel, dim3(kXcds), dim3(kOrderThreads), 0, stream, g.meta, sel_ptr, sel_idx,

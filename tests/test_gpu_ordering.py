@@ -118,6 +118,80 @@ def test_queues_hold_every_row_by_cost(block, seqlens, heads, kv_of):
                 assert (np.diff(n[begin[x]:begin[x + 1]]) <= 0).all()
 
 
+@pytest.mark.parametrize("block, seqlens, heads, kv_of, slots", [
+    (128, [230], (6, 1), None, 64), (128, [181], (6, 3), None, 2048), (64, [300], (10, 5), None, 512), (128, [70, 67], (8, 4), None, 2048),
+    (128, [33, 1, 64], (28, 4), None, 2048), (64, [97, 31, 32], (16, 8), None, 3), (128, [17] * 64, (32, 8), None, 4096),
+    (128, [90, 40], (8, 2), [0, 1, 1, 1, 1, 1, 1, 1], 2048), (64, [131, 9], (24, 9), [x % 9 for x in range(24)], 2048), (128, [40], (4, 4), None, 2048)])
+def test_queues_hold_every_piece_of_cut_rows(block, seqlens, heads, kv_of, slots):
+    # The same with pieces: every block of a row is in one of them, in order; slots and counters are a split row's own and within
+    # what the workspace holds; items lie by the cost of their rows.  For rows of a budget, cut at split_length(), and for rows
+    # of any number of blocks, where a row may have fewer blocks than pieces.
+    hq, hkv = heads
+    rng = np.random.default_rng(len(seqlens) + hq + block)
+    lens = [block * nb - int(rng.integers(0, block)) for nb in seqlens]
+    n_seq, nbs = len(lens), np.array(seqlens)
+    budgets = rng.choice([2, 3, 11, 999, 999], size=n_seq * hq).astype(np.int32)
+    p = S.Problem(np.concatenate([[0], np.cumsum(lens)]), hq, hkv, block, 128, kv_head_of=kv_of)
+    ptr = S.shplb_sel_row_ptr(p, budgets)
+    kv_of = kv_of or [h // (hq // hkv) for h in range(hq)]
+    what = np.array([(s, h, i) for s in range(n_seq) for h in range(hq) for i in range(nbs[s])])
+    rows, n_streams = len(what), n_seq * hkv
+    stream = what[:, 0] * hkv + np.array(kv_of)[what[:, 1]]
+    spread = 8 // n_streams if n_streams < 8 else 1
+    die = stream % 8 if n_streams >= 8 else stream * spread + what[:, 2] % spread
+    last = (what[:, 2] == nbs[what[:, 0]] - 1)
+    odd = np.concatenate([[0], np.cumsum([n if end else int(rng.integers(0, i + 2)) for n, end, (_, _, i) in zip(np.diff(ptr), last, what)])]).astype(np.int64)
+    total = int(p.cu[-1])
+    q = torch.zeros((total, hq, 128), dtype=torch.bfloat16, device="cuda:0")
+    kv = torch.zeros((total, hkv, 128), dtype=torch.bfloat16, device="cuda:0")
+    out = torch.zeros_like(q)
+    size = S.shplb_split_workspace_bytes(p, slots)
+    up = lambda x: -(-x // 256) * 256
+    n_wg = S.shplb_sched_num_workgroups(p)
+    few = rows <= n_wg // 2 if block == 128 else False
+    share_wg = n_wg // 2 if few else n_wg
+    cost = int(ptr[-1])
+    cut = max(32 * 64 // block, -(-2 * cost // slots), -(-cost // (share_wg * 2)))
+    wanted = np.minimum(-(-np.diff(ptr) // cut), 64)                  # pieces of a row of its budget
+    for by_budget, sel in ((True, ptr), (False, odd)):
+        idx = np.concatenate([np.sort(rng.permutation(i + 1)[:n]) for (_, _, i), n in zip(what, np.diff(sel))]).astype(np.int32)
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        print("case", block, seqlens[:4], heads, "rows", rows, "cut at", cut, "split rows", int((wanted > 1).sum()), "by budget", by_budget, flush=True)
+        S.shplb_sparse_attn_prefill_split(p, q, kv, kv, torch.from_numpy(sel).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"), out, None,
+                                          None, ws, slots, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        left = ws.cpu().numpy()
+        n_items = int(wanted.sum())
+        at = size - 512 - 256 - up(slots * 1024) - up(slots * 65536) - up((slots // 2 + 1) * 4) - up((rows + slots) * 64)
+        begin = left[size - 768:size - 768 + 36].view(np.int32)
+        assert begin.tolist() == np.concatenate([[0], np.cumsum(np.bincount(die, weights=wanted, minlength=8))]).astype(int).tolist()
+        item = left[at:at + 64 * n_items].view(np.int32).reshape(n_items, 16)
+        index = {tuple(w): r for r, w in enumerate(what)}
+        s_of = np.searchsorted(np.concatenate([[0], np.cumsum(lens)]), item[:, 8])
+        row = np.array([index[(int(s), int(x[10]), int(x[12]))] for s, x in zip(s_of, item)])
+        assert (np.bincount(row, minlength=rows) == wanted).all()
+        assert (die[row] == np.repeat(np.arange(8), np.diff(begin))).all()
+        n_of = np.diff(ptr)[row]
+        for x in range(8):
+            assert (np.diff(n_of[begin[x]:begin[x + 1]]) <= 0).all()  # (by the budgets' costs in either case)
+        used, counters = [], []
+        for r in range(rows):
+            mine = item[row == r] if wanted[r] > 1 else item[np.flatnonzero(row == r)]
+            pieces = mine[mine[:, 1] > 0]
+            assert int(pieces[:, 1].sum()) == sel[r + 1] - sel[r]
+            assert (pieces[:, 2] == sel[r] + np.concatenate([[0], np.cumsum(pieces[:, 1])])[:-1]).all()
+            assert (pieces[:, 14] == idx[pieces[:, 2]]).all() and (pieces[:, 15] == idx[pieces[:, 2] + np.minimum(1, pieces[:, 1] - 1)]).all()
+            if len(pieces) <= 1:
+                assert (pieces[:, 4] == -1).all() and (pieces[:, 5] == 1).all()
+                continue
+            assert (pieces[:, 5] == len(pieces)).all() and (pieces[:, 6] == pieces[0, 6]).all() and (pieces[:, 7] == pieces[0, 7]).all()
+            assert (pieces[:, 4] == pieces[0, 6] + np.arange(len(pieces))).all()
+            used += pieces[:, 4].tolist()
+            counters.append(int(pieces[0, 7]))
+        assert len(set(used)) == len(used) and len(set(counters)) == len(counters)
+        assert not used or (min(used) >= 0 and max(used) < slots and min(counters) >= 0 and max(counters) <= slots // 2)
+
+
 @pytest.mark.parametrize("block, n_blocks, heads", [(128, 16, (32, 8)), (128, 17, (32, 8)), (64, 32, (40, 8)), (64, 33, (40, 8)), (128, 3, (8, 2))])
 def test_rows_too_short_to_cut_through_the_splitting_entry_point(block, n_blocks, heads):
     # Up to 16 blocks of 128 tokens or 32 of 64 no row is cut: no queue, or the same as without splitting; beyond, as many
