@@ -39,11 +39,11 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const char* p) {
 }
 
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
-// Wait until at most N (< 16) of the wave's vector memory operations are outstanding.
+// Wait until at most N of the wave's vector memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmem_but(std::integral_constant<int, N>) {
-  static_assert(N >= 0 && N < 16, "the low four bits of the count");
-  __builtin_amdgcn_s_waitcnt(0x0f70 | N);
+  static_assert(N >= 0 && N < 64, "six bits, of which the upper two lie apart");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | (N >> 4) << 14);
 }
 
 // One wave copies 64 x 16 bytes from global memory (uniform base + per-lane byte

@@ -72,6 +72,14 @@
 // rows 512 dense ones 73.0 -> 72.1, 512 at 5 to 50% 39.2 -> 38.6).  Pieces from queues, where 512 dense rows take 88.6 us with
 // the softmax in front, take 99.9 that way (2/1 x 8000 72.4 -> 71.8, 256 dense rows 65.7 -> 67.2).
 //
+// COPIERS (KS = 2, up to one 64-token row per compute unit): a wave for each group does nothing but copy its tiles, into four stages, three
+// steps ahead.  With one wave per SIMD a step was a chain of its copies (64 bytes a cycle: some 450 of 1600 cycles), products and
+// exponentials, and tiles that come from further away than the die's L2 were waited for.  The two waves meet the others at every
+// barrier.  Whole path: 2048 x 8/8 heads, 2 to 16 blocks a row, 29.0 -> 26.7 us, 2000 x 8/2 with a dense head 39.3 -> 34.5, 500 x 32/8
+// 18.9 -> 17.9, 16000 x 1/1 dense 207 -> 154, two blocks a row 18.0 and 18.0.  With four such waves and two stages 27.1, 35.3,
+// 18.1, 209 and 18.8.  Two rows a compute unit have no LDS for it.  For 128-token rows (QS = 2 below), where reading the operands bounds
+// a step, it does not pay: 2 to 20% slower.
+//
 // QS = 2: two groups of four waves share a 128-token row's queries, 16 a wave (launches of no more rows than compute units).
 // Both work on the same tiles, group 1 half a step behind, kept there by a second barrier in the middle of a step: one
 // group's MFMAs run against the other's softmax.  Group 1 issues the copies, at the start of its step t like above: that is
@@ -185,14 +193,95 @@ __device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
   return true;
 }
 
-// BQ: tokens per block.  GROUPS: groups of BQ/32 waves that share a row, see KS, QS and SCORES_FIRST in the header.
-template <int BQ, int GROUPS, bool SCORES_FIRST>
-__global__ __launch_bounds__(64 * GROUPS * BQ / 32) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// The wave that copies the tiles of group `grp` of a row without a record (see COPIERS).  It meets the others at the barriers of
+// the kernel: one in front of S(0), one at the start of each step, three around the combination of the groups.
+template <int BQ, int KT, int kStages>
+__device__ __forceinline__ void copy_row(ArgsPtr args, const Item& it, int grp, int lane, uint32_t k_lds, uint32_t v_lds) {
+  static_assert(kStages == 4 && KT == 32, "counts of copies below");
+  constexpr int kTileBytes = KT * kRowBytes, kRounds = KT / 4;      // four rows a copy
+  const int64_t row_bytes = args->st.kv_t * 2;
+  const char* const k_head = reinterpret_cast<const char*>(args->k + int64_t(it.kv_head) * args->st.kv_h);
+  const char* const v_head = reinterpret_cast<const char*>(args->v + int64_t(it.kv_head) * args->st.kv_h);
+  const int r4 = lane >> 4;
+  uint32_t off[4];                                   // of a lane in rounds 0 .. 3 mod 4, without the round's first row
+#pragma unroll
+  for (int x = 0; x < 4; ++x) off[x] = uint32_t(r4) * uint32_t(row_bytes) + (((lane & 15) ^ swz(4 * x + r4)) << 4);
+  auto copy_tile = [&](const char* head, int j, int half, uint32_t dst) {
+    const int key_base = min(it.seq_begin + min(max(j, 0), it.n_blocks - 1) * BQ + KT * half, it.seq_end - 1);
+    const int last = it.seq_end - 1 - key_base;
+    const char* tile = uniform(head + int64_t(key_base) * row_bytes);
+    dst = __builtin_amdgcn_readfirstlane(dst);
+    if (last >= KT - 1) {
+#pragma unroll
+      for (int rd = 0; rd < kRounds; ++rd) copy_g2l_16(tile + int64_t(4 * rd) * row_bytes, off[rd & 3], dst + rd * 4 * kRowBytes);
+    } else {                                         // rows past the end re-read the last valid key (masked)
+#pragma unroll
+      for (int rd = 0; rd < kRounds; ++rd) {
+        const int r = 4 * rd + r4;
+        copy_g2l_16(tile, uint32_t(min(r, last)) * uint32_t(row_bytes) + (((lane & 15) ^ swz(r)) << 4), dst + rd * 4 * kRowBytes);
+      }
+    }
+  };
+  auto k_tile = [&](int j, int t) { copy_tile(k_head, j, t & 1, k_lds + (t & 3) * kTileBytes); };
+  auto v_tile = [&](int j, int t) { copy_tile(v_head, j, t & 1, v_lds + (t & 3) * kTileBytes); };
+  auto first_block = [&](int j) {
+    k_tile(j, 0);
+    v_tile(j, 0);
+    k_tile(j, 1);
+    v_tile(j, 1);
+  };
+  // (block 0, the sink, is nearly always a row's first: its copies start before the selection is known)
+  const ConstLongs ptr = (ConstLongs)uintptr_t(args->sel_ptr + it.pos);
+  const int64_t begin = ptr[0], end = ptr[1];
+  if (grp == 0) first_block(0);
+  const int n_sel = int(end - begin);
+  if (n_sel <= 0) {
+    wait_vmem_all();
+    return;
+  }
+  const ConstInts sel = (ConstInts)uintptr_t(args->sel_idx + begin);
+  auto block_of = [&](int b) { return sel[min(2 * b + grp, n_sel - 1)]; };
+  const int n_tiles = 2 * ((n_sel + 1) / 2);         // of either group
+  const int j0 = block_of(0);
+  int jv = block_of(1), jk = block_of(2);            // the blocks of V(t+3) and K(t+4)
+  if (grp == 1 || j0 != 0) {
+    wait_vmem_all();                                 // (of the copies that went to the same stages)
+    first_block(j0);
+  }
+  if (n_tiles > 2) {
+    k_tile(jv, 2);
+    v_tile(jv, 2);
+    k_tile(jv, 3);
+  }
+  // tile t + 1's K and tile t's V are wanted at the start of step t, K(0) before the first: what was issued after them may be under way
+  if (n_tiles > 2) wait_vmem_but(std::integral_constant<int, 6 * kRounds>{});
+  else wait_vmem_but(std::integral_constant<int, 3 * kRounds>{});
+  __syncthreads();
+  for (int t = 0; t < n_tiles; ++t) {
+    if (t + 3 < n_tiles) wait_vmem_but(std::integral_constant<int, 4 * kRounds>{});
+    else wait_vmem_all();
+    __syncthreads();
+    // the stages of K(t) and V(t-1) are free
+    if (t + 3 < n_tiles) v_tile(jv, t + 3);
+    if (t + 4 < n_tiles) k_tile(jk, t + 4);
+    jv = jk;
+    jk = block_of((t + 5) / 2);
+  }
+  __syncthreads();
+  __syncthreads();
+  __syncthreads();
+}
+
+// BQ: tokens per block.  GROUPS: groups of BQ/32 waves that share a row, see KS, QS, SCORES_FIRST and COPIERS in the header.
+template <int BQ, int GROUPS, bool SCORES_FIRST, bool COPIERS>
+__global__ __launch_bounds__(64 * (GROUPS * BQ / 32 + (COPIERS ? GROUPS : 0))) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
   static_assert(GROUPS == 1 || GROUPS == 2, "an item's record names its first two blocks");
   constexpr int KS = BQ == 64 ? GROUPS : 1, QS = BQ == 128 ? GROUPS : 1;   // groups that share a row, by keys and by queries
   constexpr int kWaves = BQ / 32;                    // waves of a group: 32 query rows each, or 16
-  constexpr int kThreads = 64 * GROUPS * kWaves;
+  static_assert(!COPIERS || (KS == 2 && SCORES_FIRST), "rows without queues, shared by their keys");
+  constexpr int kThreads = 64 * (GROUPS * kWaves + (COPIERS ? GROUPS : 0));
+  constexpr int kStages = COPIERS ? 4 : 2;           // of K and V tiles each: tile t is in stage t mod kStages
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
   constexpr int QG = 2 / QS, MT = KT / 16;           // 16-query and 16-key MFMA tiles of a tile's scores
   constexpr int kTileBytes = KT * kRowBytes;
@@ -207,8 +296,8 @@ void attn_pipe_kernel(AttnArgs) {
                                                      // more if one of them exceeds 2^8
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
 
-  // stages of group g: K tiles at (4g + 0, 1) * kTileBytes, V tiles at (4g + 2, 3) * kTileBytes
-  __shared__ __attribute__((aligned(1024))) char lds[KS * 4 * kTileBytes];
+  // stages of group g: K tiles from 2 kStages g * kTileBytes on, V tiles kStages behind them
+  __shared__ __attribute__((aligned(1024))) char lds[KS * 2 * kStages * kTileBytes];
   __shared__ float s_ml[KS > 1 ? KS * 2 * BQ : 1];   // groups' reference exponents and denominators
   __shared__ int32_t s_next, s_flag, s_empty;
   __shared__ int32_t s_merge[kDeferredMerges];       // items whose row this workgroup still has to combine
@@ -218,7 +307,8 @@ void attn_pipe_kernel(AttnArgs) {
   const int lane = tid & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int team = GROUPS > 1 ? wave_all / kWaves : 0, wave = GROUPS > 1 ? wave_all % kWaves : wave_all;
-  const int grp = KS > 1 ? team : 0, q_grp = QS > 1 ? team : 0;         // group of waves, by keys or by queries
+  const bool computes = !COPIERS || wave_all < GROUPS * kWaves;
+  const int grp = COPIERS && !computes ? wave_all - GROUPS * kWaves : KS > 1 ? team : 0, q_grp = QS > 1 ? team : 0;         // group of waves, by keys or by queries
   const int q_wave = 16 * QG * (q_grp * kWaves + wave);                 // the wave's first query
   const int n = lane & 15, hi = lane >> 4;
   const int64_t row_bytes = args->st.kv_t * 2;
@@ -238,8 +328,8 @@ void attn_pipe_kernel(AttnArgs) {
   const int k_rd0 = n * kRowBytes + ((hi ^ swz(n)) << 4);
   const int tr_row = 4 * hi + ((lane >> 2) & 3), tr_a = lane & 3;
   const int v_rd0 = tr_row * kRowBytes + (((tr_a >> 1) ^ swz(tr_row)) << 4) + 8 * (tr_a & 1);
-  const char* const k_lds = lds + grp * 4 * kTileBytes;
-  const char* const v_lds = k_lds + 2 * kTileBytes;
+  const char* const k_lds = lds + grp * 2 * kStages * kTileBytes;
+  const char* const v_lds = k_lds + kStages * kTileBytes;
   const uint32_t k_stage0 = __builtin_amdgcn_readfirstlane(lds_offset_of(lds) + grp * 4 * kTileBytes + 4 * wave * kRowBytes);
   const uint32_t v_stage0 = k_stage0 + 2 * kTileBytes;
 
@@ -309,6 +399,12 @@ void attn_pipe_kernel(AttnArgs) {
     home_size = uint32_t(__builtin_amdgcn_readfirstlane(args->wq.queue_begin[home + 1]) - home_begin);
   }
 
+  if constexpr (COPIERS) {
+    if (!computes) {
+      if (have) copy_row<BQ, KT, kStages>(args, it, grp, lane, lds_offset_of(k_lds), lds_offset_of(v_lds));
+      return;
+    }
+  }
   const char *k_head = nullptr, *v_head = nullptr;
   bf16x8 qf[QG][4];
   int64_t next_off = 0;                  // byte offset (from k_head, v_head) of the tile whose K copies were issued last ...
@@ -358,7 +454,7 @@ void attn_pipe_kernel(AttnArgs) {
   };
   const std::true_type yes{};
   const std::false_type no{};
-  const bool copies = QS == 1 || q_grp == 1;         // of query groups the later one copies, for both (see the header)
+  const bool copies = !COPIERS && (QS == 1 || q_grp == 1);   // of query groups the later one copies, for both (see the header)
   auto start_item = [&](auto copies_c, auto queries_c) {
     constexpr bool kCopies = decltype(copies_c)::value, kQueries = decltype(queries_c)::value;
     ArgsPtr a = reload(args);
@@ -389,7 +485,7 @@ void attn_pipe_kernel(AttnArgs) {
     const ConstLongs ptr = (ConstLongs)uintptr_t(args->sel_ptr + it.pos);
     const int64_t begin = ptr[0], end = ptr[1];
     it.first_block = 0;
-    if (KS == 1 || grp == 0) start_item(yes, yes);
+    if ((KS == 1 || grp == 0) && !COPIERS) start_item(yes, yes);
     else start_item(no, yes);
     it.sel_begin = begin;
     it.n_sel = int(end - begin);
@@ -399,7 +495,7 @@ void attn_pipe_kernel(AttnArgs) {
       it.first_block = sel[0];
       it.second_block = sel[min(1, it.n_sel - 1)];
       own_first();
-      if (it.first_block != 0 || (KS > 1 && grp == 1)) {
+      if (!COPIERS && (it.first_block != 0 || (KS > 1 && grp == 1))) {
         wait_vmem_all();                             // (of the copies that went to the same stages)
         start_item(yes, no);
       }
@@ -515,11 +611,11 @@ void attn_pipe_kernel(AttnArgs) {
     enum { kMid, kRecord, kFinal };
     const Item cur = it;                             // (the last step starts the next item)
     auto step = [&](auto place_c, auto stage_c, Scores& sc_cur, Scores& sc_nxt, int jk, bool mask, bool all,
-                    bool drop, bool ask_now) {
+                    bool drop, bool ask_now, int pair) {   // pair: t / 2
       constexpr int kPlace = decltype(place_c)::value, kStage = decltype(stage_c)::value;
       constexpr bool kHasNext = kPlace != kFinal;
       if (!SCORES_FIRST) __builtin_amdgcn_s_setprio(0);
-      wait_vmem_all();                  // own copies of K(t+1), V(t) have landed
+      if (!COPIERS) wait_vmem_all();    // own copies of K(t+1), V(t) have landed
       if (kPlace == kRecord && home_open && tid == 0) {
         // the ticket asked for one step ago
         s_next = ticket < home_size ? home_begin + int(ticket) : kHelp;
@@ -537,8 +633,9 @@ void attn_pipe_kernel(AttnArgs) {
         else it.n_sel = 0;
       }
 
-      const char* kn = k_lds + (kStage ^ 1) * kTileBytes;
-      const char* vc = v_lds + kStage * kTileBytes;
+      const int odd_pair = COPIERS ? pair & 1 : 0;
+      const char* kn = k_lds + (COPIERS ? (kStage == 0 ? 2 * odd_pair + 1 : 2 - 2 * odd_pair) : kStage ^ 1) * kTileBytes;
+      const char* vc = v_lds + (2 * odd_pair + kStage) * kTileBytes;
 
       bf16x8 kf[kQK], vf[kPV];
       if (kHasNext) clear_scores(sc_nxt);
@@ -662,14 +759,14 @@ void attn_pipe_kernel(AttnArgs) {
     int b = 0;
     for (; b + 1 < n_pairs; ++b) {
       const int j2 = block_of(b + 2);
-      step(integral_constant<int, kMid>{}, even, sc_a, sc_b, j1, j0 == i || beyond(b), beyond(b), beyond(b), false);
+      step(integral_constant<int, kMid>{}, even, sc_a, sc_b, j1, j0 == i || beyond(b), beyond(b), beyond(b), false, b);
       step(integral_constant<int, kMid>{}, odd, sc_b, sc_a, j1, j1 == i || beyond(b + 1), beyond(b + 1), beyond(b),
-           b + 2 == n_pairs);
+           b + 2 == n_pairs, b);
       j0 = j1;
       j1 = j2;
     }
-    step(integral_constant<int, kRecord>{}, even, sc_a, sc_b, 0, j0 == i || beyond(b), beyond(b), beyond(b), false);
-    step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false, beyond(b), false);
+    step(integral_constant<int, kRecord>{}, even, sc_a, sc_b, 0, j0 == i || beyond(b), beyond(b), beyond(b), false, b);
+    step(integral_constant<int, kFinal>{}, odd, sc_b, sc_a, 0, false, false, beyond(b), false, b);
 
     // ---- the next item starts before this one's results are written
     float l_tot[QG];
@@ -848,9 +945,10 @@ void attn_pipe_kernel(AttnArgs) {
   }
 }
 
-template <int BQ, int GROUPS, bool SCORES_FIRST = false>
+template <int BQ, int GROUPS, bool SCORES_FIRST = false, bool COPIERS = false>
 void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS, SCORES_FIRST>), dim3(n_wg), dim3(64 * GROUPS * BQ / 32), 0, stream, args);
+  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS, SCORES_FIRST, COPIERS>), dim3(n_wg), dim3(64 * (GROUPS * BQ / 32 + (COPIERS ? GROUPS : 0))),
+                     0, stream, args);
 }
 
 }  // namespace
@@ -904,7 +1002,8 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
     if (plan.groups == 2) launch_one<128, 2>(args, plan.grid, stream);
     else launch_one<128, 1>(args, plan.grid, stream);
   } else {
-    if (plan.groups == 2 && wq.items == nullptr) launch_one<64, 2, true>(args, plan.grid, stream);
+    if (plan.groups == 2 && wq.items == nullptr && args.rows_per_die > 0) launch_one<64, 2, true, true>(args, plan.grid, stream);
+    else if (plan.groups == 2 && wq.items == nullptr) launch_one<64, 2, true>(args, plan.grid, stream);
     else if (plan.groups == 2) launch_one<64, 2>(args, plan.grid, stream);
     else launch_one<64, 1>(args, plan.grid, stream);
   }

@@ -224,6 +224,29 @@ def test_rows_shared_by_two_groups_of_waves(n_blocks, budgets):
     full_parity(wl)
 
 
+@pytest.mark.parametrize("n_blocks, tail, heads", [(1, 5, (32, 8)), (2, 64, (8, 2)), (3, 1, (8, 2)), (5, 40, (8, 8)), (8, 63, (32, 8)), (9, 31, (8, 1)), (32, 64, (8, 8)), (250, 33, (1, 1))])
+def test_64_token_rows_with_waves_that_copy(n_blocks, tail, heads):
+    # Up to one row per compute unit: two waves copy three steps ahead.  Rows of one block up to many, odd and even, so that a
+    # group has two, four, six and more tiles, none beyond them and none of its own; ragged tails; selections that begin with
+    # another block than the sink, a single one and none.
+    hq, hkv = heads
+    T = 64 * (n_blocks - 1) + tail
+    budgets = ([2, 3, 4, 5, 6, 7, 9, 999] * 4)[:hq] if hq > 1 else [999]
+    wl = make_custom([T], hq, hkv, 64, budgets, seed=760 + n_blocks, name="copiers_%d" % n_blocks)
+    rows = None if n_blocks <= 32 else [0, 1, 2, 3, 100, 248, 249]
+    run = full_parity(wl, rows=rows)
+    assert run.rows <= run.n_wg // 4
+    pick = [lambda i: list(range(max(0, i - 2), i + 1)), lambda i: [i], lambda i: [] if i % 3 == 1 else [i // 2, i] if i else [0], lambda i: list(range(i + 1))]
+    lists = [pick[h % 4](i) for h in range(hq) for i in range(n_blocks)]
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    idx = np.concatenate([np.asarray(x, np.int32) for x in lists])
+    run.attn_step(torch.from_numpy(ptr).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"))
+    torch.cuda.synchronize()
+    at = [r for r in (range(len(lists)) if rows is None else rows) if len(lists[r])]
+    out_o, lse_o = orc.sparse_attention(wl.q, wl.k, wl.v, wl.cu_seqlens, 64, ptr, idx, None, at)
+    compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
+
+
 @pytest.mark.parametrize("n_blocks", [1, 5, 6])
 def test_groups_of_waves_keep_infinite_values_apart(n_blocks):
     # The last block's first token has an infinite value in one dim: every query of that block sees it, and no
