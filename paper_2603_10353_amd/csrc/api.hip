@@ -261,7 +261,7 @@ int32_t attention_entry(const shplb_problem* p, const void* q, const void* k, co
     // the share that rows are cut by is that of a workgroup (of 128-token rows: where two groups of waves share them there
     // are half as many; 2/1 heads x 16384 with a dense one 145 us in pieces by the larger number, 140.  With 64-token blocks
     // the two take the same time, 2/1 x 16384 dense 212.0 and 211.6, and the cuts stay)
-    if (int32_t rc = launch_order(g, sel_ptr, sel_idx, w, ws, g.meta.block == 128 ? plan.grid : n_wg, plan.grid, st)) return rc;
+    if (int32_t rc = launch_order(g, sel_ptr, sel_idx, w, ws, g.meta.block == 128 ? plan.grid : n_wg, plan.grid, plan.halves, st)) return rc;
   const WorkQueues wq{plan.ordered ? reinterpret_cast<const ItemRec*>(ws + w.items) : nullptr,
                       reinterpret_cast<const int32_t*>(ws + w.queue_begin),
                       reinterpret_cast<uint32_t*>(ws + w.tickets)};

@@ -58,6 +58,10 @@
 // heads: the launch 135 -> 121 us; 62 tiles, 32K: 1.84 -> 1.80 ms; the 128K layer, 270 tiles, 1.4%.)  With the copies
 // started one step later, between the last step and the output, these were 125 us, 1.81 ms and 0.7%.
 //
+// HALVES: items may be halves of a row's queries (16 a wave), the first 2 H of a queue being those of its H longest rows; see
+// queue_place() and halved_above().  A query's sums do not depend on it, as with QS = 2.  (Operands are fetched 6 ahead there: with
+// 8, 22 and more registers are spilled in the tile loop, 16%.)
+//
 // The two score buffers swap roles from step to step (the tile count is even, steps are
 // issued in pairs).  LDS operands are fetched kLook ahead of their use.  Fully
 // masked sub-tiles are computed like any other (their probabilities are exact zeros).
@@ -134,6 +138,7 @@ struct Item {
   int pos;                            // its place in the queues
   int n_sel, slot, head, q_block, n_blocks, kv_head, seq_begin, seq_end, first_block, second_block;
   int64_t sel_begin;
+  int half;                           // 0: the row; 1, 2: the first, second half of its queries
 };
 
 // The row of workgroup b in a launch that gives every row a workgroup of its own.  False: no row.
@@ -190,6 +195,7 @@ __device__ __forceinline__ bool row_place(ArgsPtr a, int b, Item& it) {
   it.q_block = local - it.head * it.n_blocks;
   it.kv_head = group > 0 ? quotient(it.head, group) : scalar(int(a->meta.kv_of[it.head >> 2] >> (8 * (it.head & 3)) & 0xff));
   it.slot = -1;
+  it.half = 0;
   return true;
 }
 
@@ -273,7 +279,7 @@ __device__ __forceinline__ void copy_row(ArgsPtr args, const Item& it, int grp, 
 }
 
 // BQ: tokens per block.  GROUPS: groups of BQ/32 waves that share a row, see KS, QS, SCORES_FIRST and COPIERS in the header.
-template <int BQ, int GROUPS, bool SCORES_FIRST, bool COPIERS>
+template <int BQ, int GROUPS, bool SCORES_FIRST, bool COPIERS, bool HALVES>
 __global__ __launch_bounds__(64 * (GROUPS * BQ / 32 + (COPIERS ? GROUPS : 0))) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_pipe_kernel(AttnArgs) {
   static_assert(GROUPS == 1 || GROUPS == 2, "an item's record names its first two blocks");
@@ -283,7 +289,8 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kThreads = 64 * (GROUPS * kWaves + (COPIERS ? GROUPS : 0));
   constexpr int kStages = COPIERS ? 4 : 2;           // of K and V tiles each: tile t is in stage t mod kStages
   constexpr int KT = BQ / 2;                         // keys per tile: two tiles per key block
-  constexpr int QG = 2 / QS, MT = KT / 16;           // 16-query and 16-key MFMA tiles of a tile's scores
+  static_assert(!HALVES || GROUPS == 1, "rows from queues");
+  constexpr int QGM = 2 / QS, MT = KT / 16;          // 16-query and 16-key MFMA tiles of a tile's scores
   constexpr int kTileBytes = KT * kRowBytes;
   constexpr int kRoundRows = 4 * kWaves;             // rows one round of copies moves (4 per wave)
   constexpr int kRounds = KT / kRoundRows;
@@ -291,7 +298,7 @@ void attn_pipe_kernel(AttnArgs) {
   constexpr int kPV = 8 * (KT / 32);                 // ... V operands of its second, index 8*gq + dt: QG MFMAs each
   // LDS operand fetches run this many operands ahead.  (A row to a workgroup: 12 no change.  Shared by two groups: 1/1 heads
   // x 20000 take 266 us with 4, 281 with 2, 273 with 8, 292 with 16; 2/1 x 8000 with 64-token blocks 109.5 with 4, 111.5 with 8.)
-  constexpr int kLook = GROUPS > 1 ? 4 : 8;
+  constexpr int kLook = GROUPS > 1 ? 4 : HALVES ? 6 : 8;
   constexpr float kSumLimit = 4.0f * MT * 256.0f;    // a lane's 4 MT probabilities of a query and tile can only sum to
                                                      // more if one of them exceeds 2^8
   constexpr int kHelp = -2;                          // s_next: the home queue is empty
@@ -300,6 +307,7 @@ void attn_pipe_kernel(AttnArgs) {
   __shared__ __attribute__((aligned(1024))) char lds[KS * 2 * kStages * kTileBytes];
   __shared__ float s_ml[KS > 1 ? KS * 2 * BQ : 1];   // groups' reference exponents and denominators
   __shared__ int32_t s_next, s_flag, s_empty;
+  __shared__ int32_t s_home[HALVES ? 3 : 1];         // the home queue's begin, halved rows and size (thread 0's own)
   __shared__ int32_t s_merge[kDeferredMerges];       // items whose row this workgroup still has to combine
 
   ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -309,7 +317,7 @@ void attn_pipe_kernel(AttnArgs) {
   const int team = GROUPS > 1 ? wave_all / kWaves : 0, wave = GROUPS > 1 ? wave_all % kWaves : wave_all;
   const bool computes = !COPIERS || wave_all < GROUPS * kWaves;
   const int grp = COPIERS && !computes ? wave_all - GROUPS * kWaves : KS > 1 ? team : 0, q_grp = QS > 1 ? team : 0;         // group of waves, by keys or by queries
-  const int q_wave = 16 * QG * (q_grp * kWaves + wave);                 // the wave's first query
+  const int q_wave = 16 * QGM * (q_grp * kWaves + wave);                // the wave's first query
   const int n = lane & 15, hi = lane >> 4;
   const int64_t row_bytes = args->st.kv_t * 2;
   const float scale_log2 = args->scale_log2;
@@ -339,19 +347,19 @@ void attn_pipe_kernel(AttnArgs) {
   const int home = my_xcd();
   bool home_open = false;                // the home die's queue may still hold items
   int home_begin = 0;                    // ... which starts at this place
-  uint32_t home_size = 0;                // ... and held so many
+  uint32_t home_size = 0;                // ... and held so many (HALVES: s_home, for want of scalar registers)
 
   // The record of queue place pos, one word per lane (every 16 lanes): a vector load, so that waiting
   // for it does not wait for LDS operands.
   // (No place: any words.  No branch around the load, which would make the wave wait for it on the spot.)
   auto record_words = [&](int pos) {
     ArgsPtr a = reload(args);
-    const uint32_t* at = pos >= 0 ? reinterpret_cast<const uint32_t*>(a->wq.items + pos) : reinterpret_cast<const uint32_t*>(a->q);
+    const uint32_t* at = pos >= 0 ? reinterpret_cast<const uint32_t*>(a->wq.items + (HALVES ? pos & kPlaceMask : pos)) : reinterpret_cast<const uint32_t*>(a->q);
     return at[lane & 15];
   };
   auto read_record = [&](int pos, uint32_t words, Item& it) {
     auto word = [&](int x) { return int(__builtin_amdgcn_readlane(words, x)); };
-    it.pos = pos;
+    it.pos = HALVES ? pos & kPlaceMask : pos;
     it.n_sel = word(1);
     it.sel_begin = int64_t(uint32_t(word(2))) | int64_t(word(3)) << 32;
     it.slot = word(4);
@@ -363,13 +371,14 @@ void attn_pipe_kernel(AttnArgs) {
     it.n_blocks = word(13);
     it.first_block = word(14);
     it.second_block = word(15);
+    it.half = HALVES ? pos >> kHalfShift : 0;
     // records come from the ordering kernel; a malformed one must not index out of bounds
     return it.n_sel > 0 && it.slot < reload(args)->sb.slot_capacity;
   };
   // Place of an item from another die's queue, to all threads (-1: every queue is empty).
   auto help = [&]() {
     if (wave_all == 0) {
-      const int at = help_item(reload(args)->wq.queue_begin, reload(args)->wq.tickets, home, &s_empty);
+      const int at = help_item<HALVES>(reload(args)->wq.queue_begin, reload(args)->wq.tickets, home, &s_empty);
       if (lane == 0) s_next = at;
     }
     __syncthreads();
@@ -387,16 +396,25 @@ void attn_pipe_kernel(AttnArgs) {
   } else {
     if (tid < 64) s_empty = 0;                       // (wave 0's own)
     const int x = blockIdx.x % kXcds, begin = args->wq.queue_begin[x];
-    int pos = begin + int(blockIdx.x / kXcds);
-    if (pos >= args->wq.queue_begin[x + 1]) pos = help();
+    const int halved = HALVES ? args->wq.queue_begin[kHalvedRows + x] : 0;
+    int pos = queue_place(begin, halved, int(blockIdx.x / kXcds));
+    if (int(blockIdx.x / kXcds) >= args->wq.queue_begin[x + 1] - begin + halved) pos = help();
     have = pos >= 0 && read_record(pos, record_words(pos), it);
     while (!have && pos >= 0) {                      // rows without a block (at the end of their queues)
       pos = help();
       have = pos >= 0 && read_record(pos, record_words(pos), it);
     }
     home_open = true;
-    home_begin = __builtin_amdgcn_readfirstlane(args->wq.queue_begin[home]);
-    home_size = uint32_t(__builtin_amdgcn_readfirstlane(args->wq.queue_begin[home + 1]) - home_begin);
+    if constexpr (HALVES) {
+      if (tid == 0) {
+        s_home[0] = args->wq.queue_begin[home];
+        s_home[1] = args->wq.queue_begin[kHalvedRows + home];
+        s_home[2] = args->wq.queue_begin[home + 1] - s_home[0] + s_home[1];
+      }
+    } else {
+      home_begin = __builtin_amdgcn_readfirstlane(args->wq.queue_begin[home]);
+      home_size = uint32_t(__builtin_amdgcn_readfirstlane(args->wq.queue_begin[home + 1]) - home_begin);
+    }
   }
 
   if constexpr (COPIERS) {
@@ -406,7 +424,7 @@ void attn_pipe_kernel(AttnArgs) {
     }
   }
   const char *k_head = nullptr, *v_head = nullptr;
-  bf16x8 qf[QG][4];
+  bf16x8 qf[QGM][4];
   int64_t next_off = 0;                  // byte offset (from k_head, v_head) of the tile whose K copies were issued last ...
   int next_last = 0;                     // ... and the row in it that holds the sequence's last token (or a larger number)
 
@@ -441,14 +459,15 @@ void attn_pipe_kernel(AttnArgs) {
   // Everything an item can start before its turn: its first tile copies and its Q fragments (B operand of
   // S^T = K Q^T, lane (n, hi) holds dims 32ks+8hi.. of queries n and 16 + n).  The stages must be free.
   auto load_queries = [&](ArgsPtr a) {
-    const uint16_t* src[QG];
+    const uint16_t* src[QGM];
+    const int first = HALVES && it.half > 0 ? BQ / 2 * (it.half - 1) + 16 * wave : q_wave, group = HALVES && it.half > 0 ? 0 : 16;
 #pragma unroll
-    for (int qg = 0; qg < QG; ++qg) {
-      const int tok = min(it.seq_begin + it.q_block * BQ + q_wave + 16 * qg + n, it.seq_end - 1);
+    for (int qg = 0; qg < QGM; ++qg) {
+      const int tok = min(it.seq_begin + it.q_block * BQ + first + group * qg + n, it.seq_end - 1);
       src[qg] = a->q + int64_t(tok) * a->st.q_t + int64_t(it.head) * a->st.q_h + 8 * hi;
     }
 #pragma unroll
-    for (int qg = 0; qg < QG; ++qg)
+    for (int qg = 0; qg < QGM; ++qg)
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) qf[qg][ks] = *reinterpret_cast<const bf16x8*>(src[qg] + 32 * ks);
   };
@@ -503,10 +522,13 @@ void attn_pipe_kernel(AttnArgs) {
   }
   wait_vmem_all();
 
-  while (have) {
+  // QG: query groups of a wave, one in a half of a row.
+  auto process = [&](auto qg_c) __attribute__((always_inline)) {
+    constexpr int QG = decltype(qg_c)::value;
+    const int q_first = HALVES && QG != QGM ? BQ / 2 * (it.half - 1) + 16 * wave : q_wave;
     if (my_items == 0) t_first = wall_clock64();
-    my_items += 1;
-    my_cost += uint32_t(it.n_sel);
+    my_items += HALVES && it.half == 2 ? 0 : 1;      // (a row in halves is one item, and half of its blocks to either)
+    my_cost += uint32_t(HALVES && it.half > 0 ? (it.n_sel + 2 - it.half) / 2 : it.n_sel);
     const int i = it.q_block;
     const int n_pairs = KS > 1 ? (it.n_sel + KS - 1) / KS : it.n_sel;   // tile pairs of every group
     // selected block of the group's tile pair b; read one pair ahead of its first use so
@@ -540,7 +562,7 @@ void attn_pipe_kernel(AttnArgs) {
         // key position minus query position, up to the part that depends on the register: taken
         // through an opaque move so that the comparisons are made here, on the rare diagonal
         // tile, instead of being hoisted out of the item loop into 64 scalar registers of masks
-        int d = all ? BQ : KT * half + 4 * hi - (q_wave + 16 * qg + n);
+        int d = all ? BQ : KT * half + 4 * hi - (q_first + 16 * qg + n);
         asm volatile("" : "+v"(d));
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -618,7 +640,8 @@ void attn_pipe_kernel(AttnArgs) {
       if (!COPIERS) wait_vmem_all();    // own copies of K(t+1), V(t) have landed
       if (kPlace == kRecord && home_open && tid == 0) {
         // the ticket asked for one step ago
-        s_next = ticket < home_size ? home_begin + int(ticket) : kHelp;
+        if constexpr (HALVES) s_next = ticket < uint32_t(s_home[2]) ? queue_place(s_home[0], s_home[1], int(ticket)) : kHelp;
+        else s_next = ticket < home_size ? home_begin + int(ticket) : kHelp;
       }
       __syncthreads();                  // everyone's have; stages of K(t) and V(t-1) are free
       if (kPlace == kMid && kStage == 1 && ask_now) ask();
@@ -836,7 +859,7 @@ void attn_pipe_kernel(AttnArgs) {
     }
 
     // ---- normalise and store: lane holds, for its queries, dims 16dt + 4hi + r
-    int q_in = q_wave + n;                           // + 16 qg
+    int q_in = q_first + n;                          // + 16 qg
     asm volatile("" : "+v"(q_in));                   // output addresses are made here, not carried through the loop
     ArgsPtr a = reload(args);
     const int q0 = cur.seq_begin + cur.q_block * BQ;
@@ -849,7 +872,7 @@ void attn_pipe_kernel(AttnArgs) {
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt)
           if (own(dt)) {
-            float* dst = part + slot_chunk(q_wave / 16 + qg, dt, lane);
+            float* dst = part + slot_chunk(q_first / 16 + qg, dt, lane);
             slot_store(dst, acc_o[qg][dt][0], acc_o[qg][dt][1]);
             slot_store(dst + 2, acc_o[qg][dt][2], acc_o[qg][dt][3]);
           }
@@ -900,7 +923,7 @@ void attn_pipe_kernel(AttnArgs) {
       // guide, memory model of gfx6 to gfx9 and of gfx942; flat accesses to LDS are the exception, and none is under
       // way here): with at most the stores outstanding the copies have landed.  For that the stores must stay in
       // front of the wait.
-      if (KS == 1 && q_wave + 16 * QG <= n_valid) {
+      if (KS == 1 && q_first + 16 * QG <= n_valid) {
         store_rows(true);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -912,9 +935,13 @@ void attn_pipe_kernel(AttnArgs) {
     }
     // (said to the compiler too, which would else wait for the stores in front of the first use)
 #pragma unroll
-    for (int qg = 0; qg < QG; ++qg)
+    for (int qg = 0; qg < QGM; ++qg)
       asm volatile("" : "+v"(qf[qg][0]), "+v"(qf[qg][1]), "+v"(qf[qg][2]), "+v"(qf[qg][3]));
     t_last = wall_clock64();
+  };
+  while (have) {
+    if (HALVES && it.half > 0) process(std::integral_constant<int, HALVES ? 1 : QGM>{});
+    else process(std::integral_constant<int, QGM>{});
   }
 
   // ---- rows whose pieces are all done and whose last piece this workgroup computed
@@ -945,9 +972,9 @@ void attn_pipe_kernel(AttnArgs) {
   }
 }
 
-template <int BQ, int GROUPS, bool SCORES_FIRST = false, bool COPIERS = false>
+template <int BQ, int GROUPS, bool SCORES_FIRST = false, bool COPIERS = false, bool HALVES = false>
 void launch_one(const AttnArgs& args, int n_wg, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS, SCORES_FIRST, COPIERS>), dim3(n_wg), dim3(64 * (GROUPS * BQ / 32 + (COPIERS ? GROUPS : 0))),
+  hipLaunchKernelGGL((attn_pipe_kernel<BQ, GROUPS, SCORES_FIRST, COPIERS, HALVES>), dim3(n_wg), dim3(64 * (GROUPS * BQ / 32 + (COPIERS ? GROUPS : 0))),
                      0, stream, args);
 }
 
@@ -972,6 +999,14 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // No more rows than workgroups and none to be cut: there is nothing to order, every row gets a workgroup
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).
   plan.ordered = slot_capacity > 0 || g.rows > plan.grid - plan.grid % kXcds;
+  // Whole rows from queues: the ordering kernel may have long ones worked on in halves, if a row can be that long (every row of
+  // two blocks and more selects at least two), by an instance of the kernel that has both.  Where there is nothing to halve it takes
+  // 0 to 0.8% longer (8231 tokens x 32/8 heads 168.4 and 168.0 us, 4270 x 40/8 156.4 and 157.3), on long launches, whose rows
+  // hardly reach the share, 0.9% (32K x 32/8, 64K x 8/2): up to six rows a workgroup.  With 64-token blocks, where a half has as many
+  // copies for half of the products of which there are few, 6933 x 32/8 with a dense head gains 10%, 8/8 x (1265, 6884, 1553) loses 4%.
+  const int64_t n_sh = int64_t(g.meta.n_seq) * g.meta.n_q_heads;
+  plan.halves = plan.ordered && slot_capacity == 0 && plan.groups == 1 && g.meta.block == 128 && g.rows <= 6 * n_wg &&
+                n_sh <= kPlacePairs && int64_t(g.max_nb) > halved_above(2 * g.rows - n_sh, n_wg);
   return plan;
 }
 
@@ -1000,6 +1035,7 @@ int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const voi
   args.meta = g.meta;
   if (g.meta.block == 128) {
     if (plan.groups == 2) launch_one<128, 2>(args, plan.grid, stream);
+    else if (plan.halves) launch_one<128, 1, false, false, true>(args, plan.grid, stream);
     else launch_one<128, 1>(args, plan.grid, stream);
   } else {
     if (plan.groups == 2 && wq.items == nullptr && args.rows_per_die > 0) launch_one<64, 2, true, true>(args, plan.grid, stream);

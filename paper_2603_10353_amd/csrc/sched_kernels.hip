@@ -348,7 +348,8 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 //
 // A workgroup takes 32 consecutive rows of a stream (the heads of one KV head of one sequence; with a caller's map of heads,
 // of one head), eight lanes each, which share the pairs of the die between them and write the record together.  An extra
-// workgroup at the end writes the queues' beginnings and tickets.
+// workgroup at the end writes the queues' beginnings and tickets, and with `halves` how many rows of each queue are worked on in
+// halves (the longest ones, so the first; see halved_above()).
 // What bounds it is the chain arguments -> row pointer -> first blocks, with the pairs' budgets behind the
 // arguments at the same time; nothing is sorted, and it takes as many compute units as there are rows for.  Under
 // the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.6 us, 48 sequences x 28 heads 10.2 -> 6.5, 32K x 32
@@ -356,23 +357,22 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 // listed one by one, a division each, instead of by streams the 48 sequences took 7.9.  In pieces, whole path: 16K x 32 heads
 // with four dense ones 546 -> 538 us, 3000 x 32 with a dense one 75.1 -> 70.0, 9000 x 28 with 64-token blocks 276 -> 268.
 constexpr int kPlaceThreads = 256, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes;
-constexpr int kPlacePairs = 2048;         // pairs of a launch, each of which may be on the same die
 
 template <bool kPieces>
 __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     SeqMeta meta, const int64_t* __restrict__ sel_ptr, const int32_t* __restrict__ sel_idx,
     ItemRec* __restrict__ items, int32_t* __restrict__ queue_begin, uint32_t* __restrict__ tickets, uint32_t* __restrict__ split_done,
-    int item_capacity, int slot_capacity, int n_wg, int grid) {
+    int item_capacity, int slot_capacity, int n_wg, int grid, int halves) {
   __shared__ int32_t s_blk[SHPLB_MAX_SEQ + 1], s_tok[SHPLB_MAX_SEQ + 1];
   __shared__ uint32_t s_kv[SHPLB_MAX_MAPPED_HEADS / 4];
   __shared__ uint32_t s_unit[kPlacePairs];   // units on this die: number of the first pair | blocks << 16 ...
   __shared__ int32_t s_row[kPlacePairs];     // ... and first row
   __shared__ uint32_t s_pair[kPlacePairs];   // their pairs: number | blocks << 16 ...
   __shared__ int32_t s_k[kPlacePairs];       // ... and blocks of the last row
-  __shared__ int32_t s_count, s_before, s_total[kXcds];
+  __shared__ int32_t s_count, s_before, s_total[kXcds], s_halved[kXcds];
   // pieces: of all pairs the blocks of the last row | blocks << 13 | die << 26 (0 the workgroup's, 1 before it, 2 behind it);
   // all blocks selected; slots and split rows on the dies before
-  __shared__ uint32_t s_all[kPieces ? kPlacePairs : 1];
+  __shared__ uint32_t s_all[kPlacePairs];
   __shared__ unsigned long long s_cost;
   __shared__ int32_t s_slots, s_splits;
   static_assert(SHPLB_MAX_BLOCKS < 1 << 13, "");
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     s_tok[tid] = my_tok;
   }
   if (tid < SHPLB_MAX_MAPPED_HEADS / 4) s_kv[tid] = my_kv;
-  if (tid < kXcds) s_total[tid] = 0;
+  if (tid < kXcds) s_total[tid] = s_halved[tid] = 0;
   if (tid == 0) {
     s_count = s_before = s_slots = s_splits = 0;
     s_cost = 0;
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     for (int d = 1; d < 64; d <<= 1) cost += __shfl_xor(cost, d);
     if (lane == 0 && cost != 0) atomicAdd(&s_cost, cost);
     __syncthreads();
-    len = int(min(split_length(int64_t(s_cost), slot_capacity, n_wg, meta.block), int64_t(1 << 30)));
+    if (kPieces) len = int(min(split_length(int64_t(s_cost), slot_capacity, n_wg, meta.block), int64_t(1 << 30)));
   };
   // f(t) for t = 0, len, 2 len .. below k: a row of more than t blocks has a piece more than one of t
   auto each_piece = [&](int k, auto&& f) {
@@ -453,7 +453,18 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
       else
         for (int r = 0; r < mod; ++r) atomicAdd(&s_total[e.stream * mod + r], group * ((e.nb + mod - 1 - r) >> log_mod));
     }
+    if (!kPieces && halves) {
+      // rows of more blocks than `above`, the first of every queue
+      load_pairs(0);
+      const int above = int(min(halved_above(int64_t(s_cost), n_wg), int64_t(SHPLB_MAX_BLOCKS)));
+      for (int p = tid; p < n_pairs; p += kPlaceThreads) {
+        const int k = int(s_all[p] & 0x1fff), nb = int(s_all[p] >> 13 & 0x1fff), s = quotient(p, hq), stream = s * hkv + kv_head(p - s * hq);
+        for (int r = 0; k > above && r < mod; ++r)
+          atomicAdd(&s_halved[mod == 1 ? stream % kXcds : stream * mod + r], ((nb + mod - 1 - r) >> log_mod) - ((above + mod - 1 - r) >> log_mod));
+      }
+    }
     __syncthreads();
+    if (!kPieces && halves && tid < kXcds) queue_begin[kHalvedRows + tid] = s_halved[tid];
     if (tid <= kXcds) {
       int begin = 0;
       for (int x = 0; x < tid; ++x) begin += s_total[x];
@@ -632,7 +643,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
 }  // namespace
 
 int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* sel_idx, const WorkspaceLayout& w,
-                     char* workspace, int32_t n_wg, int32_t grid, hipStream_t stream) {
+                     char* workspace, int32_t n_wg, int32_t grid, bool halves, hipStream_t stream) {
   const SeqMeta& m = g.meta;
   if (int64_t(m.n_seq) * m.n_q_heads <= kPlacePairs) {
     const int units = m.kv_map ? m.n_q_heads : m.n_kv_heads, group = m.n_q_heads / units;
@@ -642,7 +653,7 @@ int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* s
     hipLaunchKernelGGL(w.slot_capacity >= 2 ? place_kernel<true> : place_kernel<false>, dim3(uint32_t(parts + 1)), dim3(kPlaceThreads), 0,
                        stream, m, sel_ptr, sel_idx, reinterpret_cast<ItemRec*>(workspace + w.items),
                        reinterpret_cast<int32_t*>(workspace + w.queue_begin), reinterpret_cast<uint32_t*>(workspace + w.tickets),
-                       reinterpret_cast<uint32_t*>(workspace + w.split_done), int(w.item_capacity), int(w.slot_capacity), n_wg, grid);
+                       reinterpret_cast<uint32_t*>(workspace + w.split_done), int(w.item_capacity), int(w.slot_capacity), n_wg, grid, int(halves));
     return hipGetLastError() == hipSuccess ? SHPLB_OK : SHPLB_E_HIP;
   }
   hipLaunchKernelGGL(order_kernel, dim3(kXcds), dim3(kOrderThreads), 0, stream, g.meta, sel_ptr, sel_idx,

@@ -57,7 +57,7 @@ struct WorkspaceLayout {
   int64_t part_o;            // float [slot_capacity][128][kHeadDim]: partial results of the pieces
   int64_t part_ml;           // float [slot_capacity][2][128]
   int64_t item_capacity, slot_capacity;   // counts, not offsets
-  int64_t queue_begin;       // int32 [kXcds + 1]: queue x is items[queue_begin[x] .. queue_begin[x+1])
+  int64_t queue_begin;       // int32 [kXcds + 1]: queue x is items[queue_begin[x] .. queue_begin[x+1]); from kHalvedRows on [kXcds] more
   int64_t tickets;           // uint32 [kXcds * kTicketStride]
   int64_t total;
 };
@@ -76,7 +76,7 @@ int32_t launch_pool_scores(const Geometry& g, const void* q, const void* k, floa
 int32_t launch_select(const Geometry& g, const float* scores, const int64_t* sel_ptr,
                       int32_t* sel_idx, hipStream_t stream);
 int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* sel_idx, const WorkspaceLayout& w,
-                     char* workspace, int32_t n_wg, int32_t grid, hipStream_t stream);
+                     char* workspace, int32_t n_wg, int32_t grid, bool halves, hipStream_t stream);
 int32_t launch_mfma_rate(int random_operands, int iters, int n_workgroups, void* scratch, hipStream_t stream);
 int32_t launch_block_mass(const Geometry& g, const void* q, const void* k, float* mass, hipStream_t stream);
 int32_t launch_token_recovery(const Geometry& g, const void* q, const void* k, const int32_t* budgets,
@@ -125,6 +125,26 @@ __host__ __device__ inline int pieces_of(int64_t n_sel, int64_t split_len) {
 // piece c of a row of n selected blocks cut into p pieces covers [piece_begin(c), piece_begin(c + 1))
 __host__ __device__ inline int64_t piece_begin(int64_t n_sel, int p, int c) { return n_sel * c / p; }
 
+constexpr int kPlacePairs = 2048;     // (sequence, head) pairs of a launch whose rows work out their own places
+
+// A queue's item `at` where the first `halved` rows of the queue, its longest, are worked on in halves: the row's place in the
+// queues, with the half (0: whole row, 1, 2) above it.
+constexpr int kHalfShift = 28, kPlaceMask = (1 << kHalfShift) - 1;
+constexpr int kHalvedRows = 16;       // halved rows of queue x: queue_begin[kHalvedRows + x] (launches with AttentionPlan::halves)
+__host__ __device__ inline int queue_place(int begin, int halved, int at) {
+  return at < 2 * halved ? (begin + (at >> 1)) | ((at & 1) + 1) << kHalfShift : begin + at - halved;
+}
+// Rows of more blocks than this are worked on in halves, given what all rows select together and the persistent workgroups.
+// A half takes some 0.65 of the row's time (its waves have half of the products and exponentials but all of the copies), so halves pay where
+// a row is longer than a workgroup's average share and the launch waits for it: 28/4 heads x 5971 with two dense ones 142 -> 112 us,
+// 8/2 x 16903 with one 332 -> 255, 32/8 x 10000 239 -> 201, 32/8 x 3000 82 -> 70.  From 1.0 times the share on 16/4 x 12000 with two dense
+// ones takes 292 us for 276 (in whole rows 293), from 0.8 on 28/4 x (3107, 2525, 392) 129 for 119; with rows of 10 to 16
+// blocks in halves too 40/8 x 2155 takes 72 us for 69.
+__host__ __device__ inline int64_t halved_above(int64_t total_cost, int n_wg) {
+  const int64_t above = total_cost * 6 / (int64_t(n_wg) * 5);
+  return above < 16 ? 16 : above;
+}
+
 // The per-XCD work queues the ordering kernel builds (device pointers into the workspace).
 struct WorkQueues {
   const ItemRec* items;        // items, queue after queue, each by descending row cost
@@ -147,6 +167,7 @@ struct AttentionPlan {
   int32_t grid;         // workgroups
   int32_t compute_units;
   bool ordered;         // items come from queues; else every row has a workgroup
+  bool halves;          // of which the longest may be halves of rows, see queue_place()
 };
 AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capacity);
 int32_t launch_attention(const Geometry& g, const AttentionPlan& plan, const void* q, const void* k, const void* v,
@@ -197,11 +218,12 @@ __device__ __forceinline__ void decode_row(const SeqMeta& m, int32_t row, int& s
 // (Now two memory round trips; with one thread going through the queues, load after load, it was ten: 48 sequences
 // x 28 heads, whose dies hold unequal work, 172 -> 165 us for the whole path, an 8K prompt 189 -> 187 us.  Asked
 // for behind the item's last steps they cost the tile loop registers, and 2% at 32K and 128K.)
+template <bool kHalves>
 __device__ __attribute__((noinline)) int help_item(const int32_t* queue_begin, uint32_t* tickets, int home, int* empty_mask) {
   static_assert(kXcds == 8, "the largest of eight lanes in three exchanges");
   int empty = *empty_mask;
   const int lane = threadIdx.x & 63, x = (home + lane) % kXcds;
-  const int begin = queue_begin[x], size = queue_begin[x + 1] - begin;
+  const int begin = queue_begin[x], halved = kHalves ? queue_begin[kHalvedRows + x] : 0, size = queue_begin[x + 1] - begin + halved;
   for (;;) {
     const uint32_t taken = __hip_atomic_load(tickets + x * kTicketStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int left = taken < uint32_t(size) && !(empty >> x & 1) ? size - int(taken) : 0;
@@ -217,7 +239,7 @@ __device__ __attribute__((noinline)) int help_item(const int32_t* queue_begin, u
     t = __builtin_amdgcn_readlane(t, pick);
     if (t < uint32_t(__builtin_amdgcn_readlane(size, pick))) {
       *empty_mask = empty;
-      return __builtin_amdgcn_readlane(begin, pick) + int(t);
+      return queue_place(__builtin_amdgcn_readlane(begin, pick), kHalves ? __builtin_amdgcn_readlane(halved, pick) : 0, int(t));
     }
     empty |= 1 << __builtin_amdgcn_readlane(x, pick);
   }

@@ -370,3 +370,31 @@ def test_a_128_token_sequence_alone_and_in_a_larger_call(n_blocks, tail, heads, 
         at = slice(x * T, (x + 1) * T)
         assert torch.equal(a.sel_idx, b.sel_idx[x * len(a.sel_idx):(x + 1) * len(a.sel_idx)])
         assert torch.equal(a.out.view(torch.int16), b.out[at].view(torch.int16)) and torch.equal(a.lse, b.lse[:, at])
+
+
+@pytest.mark.parametrize("n_blocks, tail, heads, budgets", [(70, 128, (8, 2), [999] + [2] * 7), (70, 1, (8, 2), [2, 2, 999, 2, 2, 40, 2, 2]), (66, 64, (8, 8), [999, 3] * 4),
+                                                           (65, 65, (8, 4), [2] * 7 + [50]), (520, 30, (1, 1), [200]), (131, 90, (4, 1), [2, 9, 999, 2])])
+def test_long_rows_in_halves(n_blocks, tail, heads, budgets):
+    # Launches of up to six 128-token rows a workgroup have rows of more than 1.2 times the average share worked on in halves of
+    # 64 queries: the same bits as whole rows, which they are among seven copies of the sequence; every row counted once; a last
+    # block whose second half has no query, and references raised in one of the halves only (a later key's component 9).
+    hq, hkv = heads
+    T = 128 * (n_blocks - 1) + tail
+    one = make_custom([T], hq, hkv, 128, budgets, seed=640 + n_blocks + tail, name="halves_%d_%d" % (n_blocks, tail))
+    one.q[:, ::2, 9] = np.where(np.arange(T) % 128 < 64, 0x4000, 0xc000).astype(np.uint16)[:, None]     # 2 and -2
+    one.k[128 * np.arange(1, n_blocks), :, 9] = (0x4200 + 2 * (np.arange(1, n_blocks) % 64)).astype(np.uint16)[:, None]   # from 32 on
+    many = make_custom([T] * 7, hq, hkv, 128, budgets, seed=1, name="whole_%d" % n_blocks)
+    for name in ("q", "k", "v"):
+        setattr(many, name, np.tile(getattr(one, name), (7, 1, 1)))
+    a, b = DevicePass(one).run_all(), DevicePass(many).run_all()
+    n = np.diff(a.sel_ptr_host)
+    above = max(16, n.sum() * 6 // (a.n_wg * 5))
+    print("case", one.name, "rows", a.rows, b.rows, "in halves", int((n > above).sum()), flush=True)
+    assert a.n_wg < a.rows <= 6 * a.n_wg < b.rows and (n > above).any()
+    st = a.stats_host()
+    assert st["n_items"].sum() == a.rows and st["cost_blocks"].sum() == n.sum()
+    assert torch.equal(a.sel_idx, b.sel_idx[:len(a.sel_idx)])
+    assert torch.equal(a.out.view(torch.int16), b.out[:T].view(torch.int16)) and torch.equal(a.lse, b.lse[:, :T])
+    rows = np.flatnonzero(n > above)[[0, 1, -2, -1]].tolist() + [0, n_blocks - 1]
+    out_o, lse_o = orc.sparse_attention(one.q, one.k, one.v, one.cu_seqlens, 128, a.sel_ptr_host, a.sel_idx_host(), None, rows)
+    compare_output(a.out_host(), out_o, a.lse_host(), lse_o)
