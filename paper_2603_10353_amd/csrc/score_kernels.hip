@@ -317,7 +317,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3, 
 // registers, and the parts trade dims before their sums meet (each part working out all 8 dims' planes, and tests for all
 // tokens, 777 tokens took 26.6 us for 25.8 and 8/2 x 1000 at 64-token blocks 21.3 for 19.3).  All 32 columns of the
 // product are the one query block; its 24 dependent MFMAs, on a wave for each accumulator, take 0.4 us.
-// Whole path, passes back to back on one card: 32/8 heads x 777 tokens 29.4 -> 25.4 us, x 300 tokens 23.9 -> 19.9, 4/2 x 60
+// Whole path, passes back to back on one card: 32/8 heads x 777 tokens 29.4 -> 25.4 us (24.2 with the arguments
+// loaded together and a lane per sequence, 2048 x 8/8 29.9 -> 28.9), x 300 tokens 23.9 -> 19.9, 4/2 x 60
 // 23.7 -> 19.8, 28/4 x (513, 129) 26.5 -> 22.0, eight sequences of 250 x 32/8 31.3 -> 26.7.  Workgroups of 16 waves, of which
 // one fits a compute unit, are the faster ones only where eight waves take two turns and more at 64-token blocks (16/4 heads
 // x 1000: 25.9 for 26.3 us, 8/8 x 2048 29.1 for 29.9).

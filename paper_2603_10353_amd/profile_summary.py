@@ -71,6 +71,14 @@ def counter_means(dirname: str):
     return {c: {k: (len(v), sum(v) / len(v)) for k, v in per.items()} for c, per in agg.items()}
 
 
+def instance_of(kernel: str, runs):
+    """Full name of the one instance of `kernel` in the counter runs."""
+    names = {k for run in runs if run for per in run.values() for k in per if k.split("<")[0] == kernel}
+    if len(names) != 1:
+        raise SystemExit("counter runs hold %s of kernel %s" % (sorted(names) or "no instance", kernel))
+    return names.pop()
+
+
 def last_json_line(path: str):
     try:
         lines = [l for l in open(path) if l.startswith("{")]
@@ -84,7 +92,8 @@ def main():
     ap.add_argument("--workload", required=True, help="bench.py --workload value the runs were made with")
     ap.add_argument("--warmup", type=int, default=2, help="--warmup of the kernel-trace run")
     ap.add_argument("--dir", default="gpurun_out", help="where the rocprofv3 output directories are")
-    ap.add_argument("--kernel", default="attn_pipe_kernel<128, 1, false>", help="dominant kernel (traffic line, SQ counters)")
+    ap.add_argument("--kernel", default="attn_pipe_kernel",
+                    help="dominant kernel (traffic line, SQ counters): its name, the template arguments are those of the runs")
     ap.add_argument("--out", required=True)
     args = ap.parse_args()
     wl, d = args.workload, args.dir
@@ -116,6 +125,10 @@ def main():
 
     fetch = counter_means(os.path.join(d, "pmc_fetch_" + wl))
     write = counter_means(os.path.join(d, "pmc_write_" + wl))
+    sq_dirs = sorted(glob.glob(os.path.join(d, "pmc_sq*_" + wl)))
+    sq_runs = [counter_means(sd) for sd in sq_dirs]
+    if any([fetch, write] + sq_runs):
+        args.kernel = instance_of(args.kernel, [fetch, write] + sq_runs)
     if fetch and write:
         f, w = fetch["FETCH_SIZE"], write["WRITE_SIZE"]
         out.append("")
@@ -129,7 +142,7 @@ def main():
             out.append("  scale from the 1 GiB copy (reads 1 GiB, writes 1 GiB): FETCH_SIZE x%.3f, WRITE_SIZE x%.3f" % (ff, wf))
         else:
             ff, wf = 2.0, 1.0
-            out.append("  no copy kernel in the runs: scale factors of earlier runs on this pool, FETCH_SIZE x2, WRITE_SIZE x1")
+            out.append("  no copy kernel in the runs: scale factors of earlier runs, FETCH_SIZE x2, WRITE_SIZE x1")
         out.append("  %-28s %14s %14s %16s" % ("kernel", "FETCH_SIZE", "WRITE_SIZE", "bytes (scaled)"))
         for k in f:
             if k in w and not k.startswith("void") and (k.split("<")[0].endswith("_kernel") or k == "copy_1GiB"):
@@ -139,9 +152,7 @@ def main():
                                                              1024 * (ff * f[args.kernel][1] + wf * w[args.kernel][1])))
 
     sq = {}
-    sq_dirs = sorted(glob.glob(os.path.join(d, "pmc_sq*_" + wl)))
-    for sd in sq_dirs:
-        cm = counter_means(sd)
+    for cm in sq_runs:
         for c, per in (cm or {}).items():
             if args.kernel in per:
                 sq[c] = per[args.kernel][1]
