@@ -228,7 +228,7 @@ class Pass:
         select_bytes = tri + 4 * int(self.sel_ptr_h[-1])
         st = np.frombuffer(self.stats.cpu().numpy().tobytes(), dtype=self.stats_dtype)
         busy = (st["t_last"] - st["t_first"]).astype(np.float64)
-        active = st["n_items"] > 0
+        active = st["t_last"] > 0             # (a workgroup that only worked on second halves of rows has no item)
         imb_time = float(busy[active].max() / busy[active].mean() - 1.0) if active.any() else None
         cost = st["cost_blocks"].astype(np.float64)
         span = float(st["t_last"][active].max() - st["t_first"][active].min())

@@ -87,10 +87,11 @@ typedef struct {
 typedef struct {
   uint32_t xcc_id;        /* accelerator die the workgroup ran on */
   uint32_t cu_id;         /* (shader engine << 8) | compute unit inside the die */
-  uint32_t n_items;       /* (head, query block) items it processed (one worked on in halves counts for one of the two) */
+  uint32_t n_items;       /* (head, query block) items it processed; one worked on in halves counts where its first half
+                           * was, so a workgroup that only had second halves has none: t_last tells who worked */
   uint32_t cost_blocks;   /* selected key blocks over those items (half of them to either half) */
-  uint64_t t_first;       /* constant-rate device clock at its first item */
-  uint64_t t_last;        /* ... after its last item */
+  uint64_t t_first;       /* constant-rate device clock at its first item (or half); 0: it had none */
+  uint64_t t_last;        /* ... after its last item; 0: it had none */
 } shplb_wg_stats;
 
 /* ---- host-side shape helpers (no device work) --------------------------- */

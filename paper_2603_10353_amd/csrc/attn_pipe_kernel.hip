@@ -526,7 +526,7 @@ void attn_pipe_kernel(AttnArgs) {
   auto process = [&](auto qg_c) __attribute__((always_inline)) {
     constexpr int QG = decltype(qg_c)::value;
     const int q_first = HALVES && QG != QGM ? BQ / 2 * (it.half - 1) + 16 * wave : q_wave;
-    if (my_items == 0) t_first = wall_clock64();
+    if (t_first == 0) t_first = wall_clock64();      // (my_items may still be 0: a second half is not counted)
     my_items += HALVES && it.half == 2 ? 0 : 1;      // (a row in halves is one item, and half of its blocks to either)
     my_cost += uint32_t(HALVES && it.half > 0 ? (it.n_sel + 2 - it.half) / 2 : it.n_sel);
     const int i = it.q_block;

@@ -393,6 +393,13 @@ def test_long_rows_in_halves(n_blocks, tail, heads, budgets):
     assert a.n_wg < a.rows <= 6 * a.n_wg < b.rows and (n > above).any()
     st = a.stats_host()
     assert st["n_items"].sum() == a.rows and st["cost_blocks"].sum() == n.sum()
+    # Every workgroup that worked says when, and all start with the launch, those that begin with a second half too: at its end such a
+    # half has taken more than half of an average share, about as much of the launch.  (Workgroups start within some microseconds.)
+    worked = st["cost_blocks"] > 0
+    assert (worked == (st["t_last"] > 0)).all() and (st["t_first"][worked] > 0).all() and (st["t_first"] < st["t_last"])[worked].all()
+    late = (st["t_first"] - st["t_first"][worked].min())[worked].astype(np.float64) / (st["t_last"].max() - st["t_first"][worked].min())
+    print("latest start %.3f of the launch" % late.max(), flush=True)
+    assert late.max() < 0.3
     assert torch.equal(a.sel_idx, b.sel_idx[:len(a.sel_idx)])
     assert torch.equal(a.out.view(torch.int16), b.out[:T].view(torch.int16)) and torch.equal(a.lse, b.lse[:, :T])
     rows = np.flatnonzero(n > above)[[0, 1, -2, -1]].tolist() + [0, n_blocks - 1]
