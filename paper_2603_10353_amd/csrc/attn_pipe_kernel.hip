@@ -1006,7 +1006,7 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // copies for half of the products of which there are few, 6933 x 32/8 with a dense head gains 10%, 8/8 x (1265, 6884, 1553) loses 4%.
   const int64_t n_sh = int64_t(g.meta.n_seq) * g.meta.n_q_heads;
   plan.halves = plan.ordered && slot_capacity == 0 && plan.groups == 1 && g.meta.block == 128 && g.rows <= 6 * n_wg &&
-                n_sh <= kPlacePairs && int64_t(g.max_nb) > halved_above(2 * g.rows - n_sh, n_wg);
+                places_counted(g, false) && int64_t(g.max_nb) > halved_above(2 * g.rows - n_sh, n_wg);
   return plan;
 }
 

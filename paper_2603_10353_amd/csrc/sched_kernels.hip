@@ -10,8 +10,8 @@
 // has the most items left (see help_item()), which keeps the greedy's balance when the dies'
 // queues hold very different amounts of work.
 //
-// Rows of up to 2048 (sequence, head) pairs find their places without a sort: see place_kernel.  Launches of more pairs
-// go through one launch of eight workgroups (order_kernel); workgroup x builds the queue of die x with a counting sort
+// Launches of up to 65536 rows (16384 where rows may be cut) and 2048 (sequence, head) pairs find their places without a sort: see
+// place_kernel.  Larger ones go through one launch of eight workgroups (order_kernel); workgroup x builds the queue of die x with a counting sort
 // whose histogram (one entry per possible cost) lies in LDS: count, scan, place.  It looks
 // only at the rows that live on its die; where its queue begins follows from the shapes
 // alone, so the workgroups need nothing from each other.  Rows of equal cost are placed in
@@ -22,11 +22,11 @@
 // longer than split_length() are cut along their selected key blocks into near-equal pieces,
 // each an item of its own (the pieces of a row sit next to each other, where the row would).
 // A piece leaves a partial result in a slot of the workspace; the piece of a row that finishes
-// last combines them (count_piece() and merge_row() in attn_common.h).  Slots and counter
-// entries are handed out in the same arbitrary order; what is computed does not depend on it.
+// last combines them (count_piece() and merge_row() in attn_common.h).  Which slots and counter
+// entries a row gets depends on the kernel and, in order_kernel, on arrival; what is computed does not.
 //
-// Launches without splitting that have no more rows than workgroups skip all this: see row_place() in
-// attn_pipe_kernel.hip.
+// Launches that cut no row (through the splitting entry point too, where all are short) and have no more rows than workgroups skip all
+// this: see row_place() in attn_pipe_kernel.hip.
 //
 // What bounds order_kernel: a chain of dependent memory round trips (geometry, row pointer, first
 // selected blocks, record) on eight compute units.  A thread works out one (sequence, head)
@@ -331,67 +331,62 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
   }
 }
 
-// The queues without a sort: where a row goes follows from its own number of blocks and
-// from the budgets of the heads on its die, and every row works it out for itself.
+// The queues without a sort: every row counts the rows in front of it in its queue, those of its die that select more blocks, and of those
+// that select as many the ones before it.
 //
-// A row of query block i selects c = min(k, i + 1) blocks, k being what the last row of its (sequence, head) pair
-// selects.  So the rows with more than c blocks are counted pair by pair, nb - c of each pair with k > c, and so are those with
-// as many in front of it (pairs in order, then query blocks).  Keys are taken from k and i alone, never from a row's own entry in sel_ptr: the
-// places are then a permutation whatever sel_ptr holds (a caller may list other blocks than a budget's), only
-// the order is by cost just where rows are those of a budget.  The record holds what sel_ptr says.
+// A workgroup takes 64 consecutive rows of one die and one stream (the heads of one KV head of one sequence; with a caller's map of
+// heads, of one head).  It goes through all rows of the die and counts them per number of selected blocks, in LDS, and apart those
+// in front of its own 64; a sum over the bins from the longest rows on, and its rows' places are known.  All workgroups of a die
+// count the same, so none waits for another one.  A row has eight lanes, which write its record together.  An extra workgroup at the
+// end writes the queues' beginnings and tickets, and with `halves` how many rows of each queue are worked on in halves (the
+// longest ones, so the first; see halved_above()).
 //
-// Pieces (kPieces): a row of c blocks is cut into one piece more for every m with m len < c, so the items in front of a row are
-// the rows with more than max(c, m len) blocks, summed over m.  The length is split_length() of the budgets' cost, which is the selection's where
-// rows are those of a budget: never more pieces than slots.  Split rows are the first of their queues, so slots and counters are
-// numbered like items and rows, behind those of the dies before.  A row that is not its budget's is cut into as many pieces
-// as its place has room for, or as it has blocks.
+// Pieces (kPieces): a row is cut into pieces_of() its own number of blocks, and the items in front of it are the pieces of the rows
+// in front.  The workgroups go through all rows, as the items of the dies before come first.  Split rows are the first of their queues, so slots and
+// counters are numbered like items and rows, behind those of the dies before.
 //
-// A workgroup takes 32 consecutive rows of a stream (the heads of one KV head of one sequence; with a caller's map of heads,
-// of one head), eight lanes each, which share the pairs of the die between them and write the record together.  An extra
-// workgroup at the end writes the queues' beginnings and tickets, and with `halves` how many rows of each queue are worked on in
-// halves (the longest ones, so the first; see halved_above()).
-// What bounds it is the chain arguments -> row pointer -> first blocks, with the pairs' budgets behind the
-// arguments at the same time; nothing is sorted, and it takes as many compute units as there are rows for.  Under
-// the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.6 us, 48 sequences x 28 heads 10.2 -> 6.5, 32K x 32
-// heads 12.0 -> 5.2, 128K 26 -> 5.7 (whole path: 8K 180.6 -> 175.1 us, the 48 sequences 145.4 -> 143.3).  With the pairs
-// listed one by one, a division each, instead of by streams the 48 sequences took 7.9.  In pieces, whole path: 16K x 32 heads
-// with four dense ones 546 -> 538 us, 3000 x 32 with a dense one 75.1 -> 70.0, 9000 x 28 with 64-token blocks 276 -> 268.
-constexpr int kPlaceThreads = 256, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes;
+// What bounds it is the chain arguments -> row pointers -> first blocks, on as many compute units as there are rows for.  Every
+// workgroup reads the row pointers of its die (with pieces of all rows), rows / 64 times in all: that is why larger launches are
+// sorted (places_counted()).  Under the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 6.1 us, 48 sequences x 28 heads 10.2
+// -> 5.8, 32K x 32 heads 12.0 -> 6.4, 128K 26 -> 9.7, 16K in pieces 18 -> 11.6.  Workgroups of 256 threads take 7.5, 6.5, 7.0,
+// 14.0 and 16.1 us, of 1024 6.3, 7.0, 7.6, 9.5 and 11.2.  (Counted in closed form from what the last row of every head selects, 5.3,
+// 6.7, 5.6, 7.4 and 6.6: but then a list that is no budget's, say a different number of blocks for every query block, is neither ordered nor
+// cut by its length; attention call of 8231 tokens x 32/8 heads with such lists 176 us, ordered 148.)
+constexpr int kPlaceThreads = 512, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes, kPlaceWaves = kPlaceThreads / 64;
+constexpr int kPlaceInFlight = 4;         // rows a thread has in flight
 
 template <bool kPieces>
 __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     SeqMeta meta, const int64_t* __restrict__ sel_ptr, const int32_t* __restrict__ sel_idx,
     ItemRec* __restrict__ items, int32_t* __restrict__ queue_begin, uint32_t* __restrict__ tickets, uint32_t* __restrict__ split_done,
-    int item_capacity, int slot_capacity, int n_wg, int grid, int halves) {
+    int rows, int n_bins, int item_capacity, int slot_capacity, int n_wg, int grid, int halves) {
+  // per number of selected blocks the rows of the die, later those with more blocks | those in front of the workgroup's own << 32;
+  // pieces: behind them the items of the rows with more blocks (int32)
+  extern __shared__ unsigned long long s_bins[];
   __shared__ int32_t s_blk[SHPLB_MAX_SEQ + 1], s_tok[SHPLB_MAX_SEQ + 1];
   __shared__ uint32_t s_kv[SHPLB_MAX_MAPPED_HEADS / 4];
-  __shared__ uint32_t s_unit[kPlacePairs];   // units on this die: number of the first pair | blocks << 16 ...
-  __shared__ int32_t s_row[kPlacePairs];     // ... and first row
-  __shared__ uint32_t s_pair[kPlacePairs];   // their pairs: number | blocks << 16 ...
-  __shared__ int32_t s_k[kPlacePairs];       // ... and blocks of the last row
-  __shared__ int32_t s_count, s_before, s_total[kXcds], s_halved[kXcds];
-  // pieces: of all pairs the blocks of the last row | blocks << 13 | die << 26 (0 the workgroup's, 1 before it, 2 behind it);
-  // all blocks selected; slots and split rows on the dies before
-  __shared__ uint32_t s_all[kPlacePairs];
-  __shared__ unsigned long long s_cost;
-  __shared__ int32_t s_slots, s_splits;
-  static_assert(SHPLB_MAX_BLOCKS < 1 << 13, "");
-  static_assert(SHPLB_MAX_SEQ < kPlaceThreads && SHPLB_MAX_BLOCKS < 1 << 16 && kPlacePairs <= 1 << 16, "");
-  const int tid = threadIdx.x, lane = tid & 63;
+  __shared__ int32_t s_pre[kPlacePairs];     // listed units: listed rows before its own ...
+  __shared__ int32_t s_row[kPlacePairs];     // ... first row ...
+  __shared__ uint32_t s_unit[kPlacePairs];   // ... blocks | stream << 16
+  __shared__ int32_t s_listed;               // rows listed | units listed << 20
+  __shared__ int32_t s_before, s_slots, s_splits;   // items, slots and split rows on the dies before
+  __shared__ int32_t s_total[kXcds], s_halved[kXcds], s_wave[2][kPlaceWaves], s_n[kPlaceRows];
+  static_assert(SHPLB_MAX_SEQ < kPlaceThreads && SHPLB_MAX_BLOCKS < 1 << 16 && kPlaceCounted < 1 << 20 && kPlacePairs < 1 << 12, "");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // asked for together: the geometry, of which a lane-dependent index is read
   const int my_blk = meta.blk_begin[min(tid, SHPLB_MAX_SEQ)], my_tok = meta.tok_begin[min(tid, SHPLB_MAX_SEQ)];
   const uint32_t my_kv = meta.kv_of[min(tid, SHPLB_MAX_MAPPED_HEADS / 4 - 1)];
+  const int64_t first_sel = sel_ptr[0], end_sel = sel_ptr[rows];
   const int n_seq = meta.n_seq, hq = meta.n_q_heads, hkv = meta.n_kv_heads;
   const bool map = meta.kv_map != 0;
   auto scalar = [](int v) { return int(__builtin_amdgcn_readfirstlane(v)); };
-  // x / y of non-negative numbers below 2^24, quotients below 2^16
+  // x / y of non-negative numbers, x below 2^25, quotients below 2^16
   auto quotient = [](int x, int y) {
     const int q = int(float(x) * __builtin_amdgcn_rcpf(float(y))), r = x - q * y;
     return q + (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
   };
   const int group = map ? 1 : scalar(quotient(hq, hkv));      // heads of a unit, whose K/V is one stream ...
   const int units = map ? hq : hkv, n_units = n_seq * units;  // ... and how many units a sequence has, and all have
-  const int n_pairs = n_seq * hq;
   const int n_streams = n_seq * hkv;
   const int mod = n_streams < kXcds ? scalar(quotient(kXcds, n_streams)) : 1;   // dies of a stream: 1, 2, 4 or 8
   const int log_mod = 31 - __builtin_clz(mod);
@@ -401,66 +396,108 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   }
   if (tid < SHPLB_MAX_MAPPED_HEADS / 4) s_kv[tid] = my_kv;
   if (tid < kXcds) s_total[tid] = s_halved[tid] = 0;
-  if (tid == 0) {
-    s_count = s_before = s_slots = s_splits = 0;
-    s_cost = 0;
-  }
+  if (tid == 0) s_listed = s_before = s_slots = s_splits = 0;
+  for (int b = tid; b < n_bins; b += kPlaceThreads) s_bins[b] = 0;
   __syncthreads();
   auto kv_head = [&](int h) { return map ? int(s_kv[h >> 2] >> (8 * (h & 3)) & 0xff) : quotient(h, group); };
-  struct Unit { int stream, nb, pair, row; };                 // (pair, row: its first)
+  struct Unit { int stream, nb, row; };                       // (row: its first)
   auto unit_of = [&](int u) {
     const int s = quotient(u, units), first = (u - s * units) * group, b0 = s_blk[s], nb = s_blk[s + 1] - b0;
-    return Unit{map ? s * hkv + kv_head(first) : u, nb, s * hq + first, b0 * hq + first * nb};
+    return Unit{map ? s * hkv + kv_head(first) : u, nb, b0 * hq + first * nb};
   };
+  // The die of query block i of a stream is (stream << log_mod) + (i & (mod - 1)), or stream % 8: first_die() + the block's residue.
+  auto first_die = [&](int stream) { return mod == 1 ? stream % kXcds : stream << log_mod; };
+  // Query blocks of nb with residue r, and with one below r (r: 0 .. mod).
+  auto with_residue = [&](int nb, int r) { return (nb + mod - 1 - r) >> log_mod; };
+  auto below_residue = [&](int nb, int r) { return (nb >> log_mod) * r + min(nb & (mod - 1), r); };
 
-  // ---- pieces: what the pairs' last rows select, and the length that rows are cut at
-  int len = 1 << 30;
-  auto load_pairs = [&](int own_stream) {
-    unsigned long long cost = 0;
-    for (int p = tid; p < n_pairs; p += kPlaceThreads) {
-      const int s = quotient(p, hq), h = p - s * hq, b0 = s_blk[s], nb = s_blk[s + 1] - b0, end = b0 * hq + (h + 1) * nb;
-      const int k = int(min(max(sel_ptr[end] - sel_ptr[end - 1], int64_t(1)), int64_t(nb))), stream = s * hkv + kv_head(h);
-      const int a = mod == 1 ? stream % kXcds : stream, b = mod == 1 ? own_stream % kXcds : own_stream;
-      s_all[p] = uint32_t(k | nb << 13 | (a == b ? 0 : a < b ? 1 : 2) << 26);
-      cost += uint32_t(k) * uint32_t(nb) - uint32_t(k) * uint32_t(k - 1) / 2;
+  // List the units that have rows on `die` (all units where it is negative), in any order.  Returns a thread's sum of the rows on the dies before.
+  auto list_units = [&](int die) {
+    int before = 0;
+    for (int u0 = 0; u0 < n_units; u0 += kPlaceThreads) {
+      const int u = u0 + tid;
+      Unit e{0, 0, 0};
+      int n = 0;
+      if (u < n_units) {
+        e = unit_of(u);
+        const int r = die - first_die(e.stream);              // the residue that lives on the die, if it is one
+        n = group * (die < 0 ? e.nb : r >= 0 && r < mod ? with_residue(e.nb, r) : 0);
+        before += group * below_residue(e.nb, min(max(r, 0), mod));
+      }
+      const uint32_t own = n > 0 ? uint32_t(n) | 1u << 20 : 0u;
+      const uint32_t to = uint32_t(wave_scan(int(own)));
+      uint32_t at = 0;
+      if (lane == 63 && to != 0) at = uint32_t(atomicAdd(&s_listed, int(to)));
+      at = uint32_t(__builtin_amdgcn_readlane(int(at), 63)) + to - own;
+      if (n > 0) {
+        s_pre[at >> 20] = int(at & 0xfffff);
+        s_row[at >> 20] = e.row;
+        s_unit[at >> 20] = uint32_t(e.nb | e.stream << 16);
+      }
     }
+    return before;
+  };
+  // f(row, die, blocks it selects, whether there is a row) for the listed rows (those of residue `res`; negative: of all), by whole waves
+  auto each_row = [&](int res, auto&& f) {
+    const int n_rows = s_listed & 0xfffff, n_list = int(uint32_t(s_listed) >> 20);
+    const int top = n_list > 1 ? 1 << (31 - __builtin_clz(n_list - 1)) : 0;
+    for (int r0 = 0; r0 < n_rows; r0 += kPlaceInFlight * kPlaceThreads) {
+      int row[kPlaceInFlight], die[kPlaceInFlight];
+      int64_t begin[kPlaceInFlight], end[kPlaceInFlight];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) cost += __shfl_xor(cost, d);
-    if (lane == 0 && cost != 0) atomicAdd(&s_cost, cost);
-    __syncthreads();
-    if (kPieces) len = int(min(split_length(int64_t(s_cost), slot_capacity, n_wg, meta.block), int64_t(1 << 30)));
+      for (int u = 0; u < kPlaceInFlight; ++u) {
+        row[u] = -1;
+        die[u] = 0;
+        if (r0 + u * kPlaceThreads >= n_rows) continue;       // (the same for all)
+        const int r = r0 + u * kPlaceThreads + tid;
+        int x = 0;
+        for (int d = top; d > 0; d >>= 1)
+          if (x + d < n_list && s_pre[x + d] <= r) x += d;
+        const int nb = int(s_unit[x] & 0xffff), stream = int(s_unit[x] >> 16), local = r - s_pre[x];
+        int at = local;
+        die[u] = first_die(stream);
+        if (mod > 1) {
+          const int per_head = res < 0 ? nb : with_residue(nb, res), h = quotient(local, per_head), i = local - h * per_head;
+          at = res < 0 ? local : h * nb + (i << log_mod) + res;
+          die[u] += res < 0 ? i & (mod - 1) : res;
+        }
+        if (r < n_rows) row[u] = s_row[x] + at;
+        begin[u] = sel_ptr[max(row[u], 0)];
+        end[u] = sel_ptr[max(row[u], 0) + 1];
+      }
+#pragma unroll
+      for (int u = 0; u < kPlaceInFlight; ++u)
+        if (r0 + u * kPlaceThreads < n_rows)
+          f(row[u], die[u], int(min(max(end[u] - begin[u], int64_t(0)), int64_t(n_bins - 1))), row[u] >= 0);
+    }
   };
-  // f(t) for t = 0, len, 2 len .. below k: a row of more than t blocks has a piece more than one of t
-  auto each_piece = [&](int k, auto&& f) {
-    int t = 0;
-    for (int m = 0; m < kSplitMaxPieces && t < k; ++m, t += len) f(t);
-  };
+  const int len = kPieces ? int(min(split_length(end_sel - first_sel, slot_capacity, n_wg, meta.block), int64_t(1 << 24))) : 0;
+  auto pieces_here = [&](int n) { return !kPieces || n <= len ? 1 : min(quotient(n + len - 1, len), kSplitMaxPieces); };   // pieces_of()
 
   if (blockIdx.x == gridDim.x - 1) {                          // the queues' beginnings
-    if constexpr (kPieces) {
-      load_pairs(0);
-      for (int p = tid; p < n_pairs; p += kPlaceThreads) {
-        const int k = int(s_all[p] & 0x1fff), nb = int(s_all[p] >> 13 & 0x1fff), s = quotient(p, hq), stream = s * hkv + kv_head(p - s * hq);
-        for (int r = 0; r < mod; ++r) {
-          int n = 0;
-          each_piece(k, [&](int t) { n += ((nb + mod - 1 - r) >> log_mod) - ((t + mod - 1 - r) >> log_mod); });
-          atomicAdd(&s_total[mod == 1 ? stream % kXcds : stream * mod + r], n);
+    if (kPieces || halves) {
+      list_units(-1);
+      __syncthreads();
+      const int above = int(min(halved_above(end_sel - first_sel, n_wg), int64_t(SHPLB_MAX_BLOCKS)));
+      each_row(-1, [&](int, int die, int n, bool live) {
+        const int add = !live ? 0 : kPieces ? pieces_here(n) : int(n > above);
+        int32_t* const sums = kPieces ? s_total : s_halved;
+        if (mod > 1) {
+          if (add != 0) atomicAdd(&sums[die], add);
+          return;
         }
-      }
-    } else for (int u = tid; u < n_units; u += kPlaceThreads) {
-      const Unit e = unit_of(u);
-      if (mod == 1) atomicAdd(&s_total[e.stream % kXcds], group * e.nb);
-      else
-        for (int r = 0; r < mod; ++r) atomicAdd(&s_total[e.stream * mod + r], group * ((e.nb + mod - 1 - r) >> log_mod));
+        for (uint64_t open = __ballot(add != 0); open != 0;) {        // neighbours are mostly on one die: LDS atomics on one address go one by one
+          const int d = __builtin_amdgcn_readlane(die, __builtin_ctzll(open));
+          const int sum = wave_scan(die == d ? add : 0);
+          if (lane == 63) atomicAdd(&sums[d], sum);
+          open &= __ballot(die != d);
+        }
+      });
     }
-    if (!kPieces && halves) {
-      // rows of more blocks than `above`, the first of every queue
-      load_pairs(0);
-      const int above = int(min(halved_above(int64_t(s_cost), n_wg), int64_t(SHPLB_MAX_BLOCKS)));
-      for (int p = tid; p < n_pairs; p += kPlaceThreads) {
-        const int k = int(s_all[p] & 0x1fff), nb = int(s_all[p] >> 13 & 0x1fff), s = quotient(p, hq), stream = s * hkv + kv_head(p - s * hq);
-        for (int r = 0; k > above && r < mod; ++r)
-          atomicAdd(&s_halved[mod == 1 ? stream % kXcds : stream * mod + r], ((nb + mod - 1 - r) >> log_mod) - ((above + mod - 1 - r) >> log_mod));
+    if constexpr (!kPieces) {
+      for (int u = tid; u < n_units; u += kPlaceThreads) {
+        const Unit e = unit_of(u);
+        for (int r = 0; r < mod; ++r) atomicAdd(&s_total[first_die(e.stream) + r], group * with_residue(e.nb, r));
       }
     }
     __syncthreads();
@@ -475,154 +512,131 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   }
 
   // ---- the workgroup's sequence, heads and rows
+  auto parts_of = [&](int nb) { return (group * with_residue(nb, 0) + kPlaceRows - 1) / kPlaceRows << log_mod; };   // of a unit: of every residue as many
   int s = 0, part = int(blockIdx.x);
   if (n_seq > 1) {
     const int at = min(lane, n_seq - 1), nb = s_blk[at + 1] - s_blk[at];
-    const int parts = lane < n_seq ? units * ((group * nb + kPlaceRows - 1) / kPlaceRows) : 0;
-    const int end = wave_scan(parts);
+    const int end = wave_scan(lane < n_seq ? units * parts_of(nb) : 0);
     s = min(int(__builtin_popcountll(__ballot(lane < n_seq && part >= end))), n_seq - 1);
     part -= s > 0 ? __builtin_amdgcn_readlane(end, s - 1) : 0;
   }
   const int b0 = scalar(s_blk[s]), nb = scalar(s_blk[s + 1]) - b0;
-  const int parts = (group * nb + kPlaceRows - 1) / kPlaceRows;
-  const int unit = scalar(quotient(part, parts));
-  const int at = (part - unit * parts) * kPlaceRows + tid / kPlaceLanes, e8 = tid % kPlaceLanes;
-  const bool live = at < group * nb;
-  const int head_in = live ? quotient(at, nb) : 0, i = live ? at - head_in * nb : 0;
-  const int h = unit * group + head_in, row = b0 * hq + h * nb + i, own_pair = s * hq + h;
+  const int parts = parts_of(nb), unit = scalar(quotient(part, parts));
+  part -= unit * parts;
+  const int res = part & (mod - 1), per_head = with_residue(nb, res), n_unit = group * per_head;   // rows of the unit on the die
+  const int first = (part >> log_mod) * kPlaceRows;
+  if (first >= n_unit) return;
+  const int kv = map ? scalar(kv_head(unit)) : unit, die = first_die(s * hkv + kv) + res;
+  auto head_of = [&](int at) { return quotient(at, per_head); };
+  const int first_head = head_of(first), first_row = b0 * hq + (unit * group + first_head) * nb + ((first - first_head * per_head) << log_mod) + res;
+  const int slot_row = tid / kPlaceLanes, at = first + slot_row, e8 = tid % kPlaceLanes;
+  const bool live = at < n_unit;
+  const int head_in = live ? head_of(at) : first_head, i = live ? ((at - head_in * per_head) << log_mod) + res : res;
+  const int h = unit * group + head_in, row = b0 * hq + h * nb + i;
   const int64_t begin = sel_ptr[row], end = sel_ptr[row + 1];
-  const int kv = map ? scalar(kv_head(unit)) : unit, stream = s * hkv + kv;
-  const int res = i & (mod - 1);                              // the row's die is stream * mod + res, or stream % 8
-  // query blocks below v whose rows are on the row's die
-  auto below = [&](int v) { return (v + mod - 1 - res) >> log_mod; };
 
-  // ---- the units of the die, and the rows of the dies before it
-  int before = 0, slots = 0, splits = 0;
-  for (int u0 = 0; !kPieces && u0 < n_units; u0 += kPlaceThreads) {
-    const int u = u0 + tid;
-    bool own = false;
-    Unit e{0, 0, 0, 0};
-    if (u < n_units) {
-      e = unit_of(u);
-      own = mod == 1 ? e.stream % kXcds == stream % kXcds : e.stream == stream;
-      before += (mod == 1 ? e.stream % kXcds < stream % kXcds : e.stream < stream) ? group * e.nb : 0;
-    }
-    const uint64_t mask = __ballot(own);
-    int first = 0;
-    if (mask != 0) {
-      if (lane == 0) first = atomicAdd(&s_count, __builtin_popcountll(mask));
-      first = scalar(first);
-    }
-    if (own) {
-      const int x = first + int(__builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u)));
-      s_unit[x] = uint32_t(e.pair | e.nb << 16);
-      s_row[x] = e.row;
-    }
-  }
-  if constexpr (kPieces) {
-    load_pairs(stream);
-    for (int p0 = 0; p0 < n_pairs; p0 += kPlaceThreads) {
-      const int p = p0 + tid;
-      const uint32_t e = p < n_pairs ? s_all[p] : 2u << 26;
-      const int k = int(e & 0x1fff), rows = int(e >> 13 & 0x1fff);
-      if (e >> 26 == 1) {
-        each_piece(k, [&](int t) {
-          before += rows - t;
-          slots += max(t, len) < k ? rows - max(t, len) : 0;
-        });
-        splits += len < k ? rows - len : 0;
-      }
-      const uint64_t mask = __ballot(e >> 26 == 0);
-      int first = 0;
-      if (mask != 0) {
-        if (lane == 0) first = atomicAdd(&s_count, __builtin_popcountll(mask));
-        first = scalar(first);
-      }
-      if (e >> 26 == 0) {
-        const int x = first + int(__builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u)));
-        s_pair[x] = uint32_t(p | rows << 16);
-        s_k[x] = k;
-      }
-    }
-    slots = wave_scan(slots);
-    splits = wave_scan(splits);
-    if (lane == 63 && splits != 0) {
-      atomicAdd(&s_slots, slots);
-      atomicAdd(&s_splits, splits);
-    }
-  }
-  before = wave_scan(before);
-  if (lane == 63 && before != 0) atomicAdd(&s_before, before);
-  const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1)));
-  const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
+  // ---- count
+  int before = list_units(kPieces ? -1 : die), slots = 0, splits = 0;
   __syncthreads();
-  const int n_own = kPieces ? s_count : s_count * group;
-  for (int x = tid; !kPieces && x < n_own; x += kPlaceThreads) {
-    const int u = quotient(x, group), head = x - u * group, rows = int(s_unit[u] >> 16);
-    const int end = s_row[u] + (head + 1) * rows;
-    s_pair[x] = s_unit[u] + head;
-    s_k[x] = int(min(max(sel_ptr[end] - sel_ptr[end - 1], int64_t(1)), int64_t(rows)));
+  if constexpr (kPieces) before = 0;
+  each_row(kPieces ? -1 : res, [&](int r, int die_of, int n, bool there) {
+    bool active = there && (!kPieces || die_of == die);
+    if (kPieces && there && die_of < die) {
+      const int pieces = pieces_here(n);
+      before += pieces;
+      slots += pieces > 1 ? pieces : 0;
+      splits += pieces > 1;
+    }
+    // rows of a wave are mostly neighbours of one head: two bins are counted by ballot, the rest lane by lane (see take_places())
+    const uint64_t front = __ballot(r < first_row);
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+      const uint64_t open = __ballot(active);
+      if (open == 0) break;
+      const int lead = round == 0 ? 63 - __builtin_clzll(open) : __builtin_ctzll(open);
+      const int b = __builtin_amdgcn_readlane(n, lead);
+      const uint64_t same = __ballot(active && n == b);
+      if (lane == lead)
+        atomicAdd(&s_bins[b], (unsigned long long)(__builtin_popcountll(same)) | (unsigned long long)(__builtin_popcountll(same & front)) << 32);
+      if (n == b) active = false;
+    }
+    if (active) atomicAdd(&s_bins[n], r < first_row ? 1ull | 1ull << 32 : 1ull);
+  });
+  auto add_up = [&](int v, int32_t* sum) {
+    v = wave_scan(v);
+    if (lane == 63 && v != 0) atomicAdd(sum, v);
+  };
+  add_up(before, &s_before);
+  if constexpr (kPieces) {
+    add_up(slots, &s_slots);
+    add_up(splits, &s_splits);
+  }
+  const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1))), key = min(n_sel, n_bins - 1);
+  const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
+  if (e8 == 0) s_n[slot_row] = live ? key : -1;
+  __syncthreads();
+
+  // ---- rows (and items) with more blocks, a thread owns a run of bins
+  int32_t* const s_items = reinterpret_cast<int32_t*>(s_bins + n_bins);
+  const int per = (n_bins + kPlaceThreads - 1) / kPlaceThreads;
+  const int k0 = min(tid * per, n_bins), k1 = min(k0 + per, n_bins);
+  int more = 0, more_items = 0;
+  for (int k = k0; k < k1; ++k) {
+    const int c = int(uint32_t(s_bins[n_bins - 1 - k]));
+    more += c;
+    if constexpr (kPieces) more_items += c * pieces_here(n_bins - 1 - k);
+  }
+  const int more_inc = wave_scan(more), items_inc = kPieces ? wave_scan(more_items) : 0;
+  if (lane == 63) {
+    s_wave[0][wave] = more_inc;
+    s_wave[1][wave] = items_inc;
+  }
+  __syncthreads();
+  auto waves_before = [&](const int32_t (&sums)[kPlaceWaves]) {
+    const int to = wave_scan(lane < kPlaceWaves ? sums[lane] : 0);
+    return wave > 0 ? __builtin_amdgcn_readlane(to, wave - 1) : 0;
+  };
+  more = more_inc - more + waves_before(s_wave[0]);
+  if constexpr (kPieces) more_items = items_inc - more_items + waves_before(s_wave[1]);
+  for (int k = k0; k < k1; ++k) {
+    const int b = n_bins - 1 - k, c = int(uint32_t(s_bins[b]));
+    s_bins[b] = (s_bins[b] >> 32 << 32) | uint32_t(more);
+    more += c;
+    if constexpr (kPieces) {
+      s_items[b] = more_items;
+      more_items += c * pieces_here(b);
+    }
   }
   __syncthreads();
 
   // ---- the row's place
-  const int own_end = b0 * hq + (h + 1) * nb;
-  const int k = int(min(max(sel_ptr[own_end] - sel_ptr[own_end - 1], int64_t(1)), int64_t(nb)));
-  const int c = min(k, i + 1), below_c = below(c), at_c = below_c - below(c - 1);
-  // rows of the same stream's dies before this one: those of the first v query blocks
-  auto earlier = [&](int v) { return (v >> log_mod) * res + min(v & (mod - 1), res); };
-  const int pieces = kPieces ? pieces_of(c, len) : 1;
-  int place = 0;                              // items in front of the row, on this die and those before
-  int slot = 0, entry = 0;                    // its first slot and its counter: split rows are the first of a queue
-  for (int x = e8; x < n_own; x += kPlaceLanes) {
-    const int p = int(s_pair[x] & 0xffff), rows = int(s_pair[x] >> 16), k_p = s_k[x], all = below(rows);
-    const int same = p < own_pair ? (c < k_p ? at_c : c == k_p ? all - below_c + at_c : 0) : p == own_pair && c == k_p ? below(i) - below(k_p - 1) : 0;
-    if constexpr (kPieces) {
-      each_piece(k_p, [&](int t) {
-        place += earlier(rows) - earlier(t);
-        if (max(t, len) < k_p) slot += earlier(rows) - earlier(max(t, len));
-        if (max(t, c) < k_p) {
-          place += all - below(max(t, c));
-          slot += all - below(max(t, c));
-        }
-      });
-      if (len < k_p) entry += earlier(rows) - earlier(len);
-      place += pieces * same;
-      slot += pieces * same;
-      entry += (c < k_p ? all - below_c : 0) + same;
-    } else {
-      place += earlier(rows) + (c < k_p ? all - below_c : 0) + same;
-    }
-  }
-  auto of_row = [](int v) {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    return v + __shfl_xor(v, 4);
-  };
-  place = of_row(place) + s_before;
-  if constexpr (kPieces) {
-    slot = of_row(slot) + s_slots;
-    entry = of_row(entry) + s_splits;
-  }
+  int same = 0;                                               // rows of the workgroup in front with as many blocks
+#pragma unroll
+  for (int x = e8; x < kPlaceRows; x += kPlaceLanes) same += x < slot_row && s_n[x] == key;
+  same += __shfl_xor(same, 1);
+  same += __shfl_xor(same, 2);
+  same += __shfl_xor(same, 4);
+  same += int(s_bins[key] >> 32);
+  const int rows_above = int(uint32_t(s_bins[key])), items_above = kPieces ? s_items[key] : rows_above;
+  const int pieces = pieces_here(key);
+  const int place = s_before + items_above + pieces * same;
   if (!live || uint32_t(place) + uint32_t(pieces) > uint32_t(item_capacity)) return;      // (the latter never: keeps stores in bounds)
   if constexpr (kPieces) {
     if (pieces > 1) {
-      // A row that is not its budget's may have fewer blocks than pieces are reserved for it: the others are items without a block.
-      const int real = min(pieces, n_sel);
+      const int slot = s_slots + items_above + pieces * same, entry = s_splits + rows_above + same;   // split rows are the first of a queue
       if (slot + pieces > slot_capacity || entry >= slot_capacity / 2 + 1) return;        // likewise
       if (e8 == 0) split_done[entry] = 0;
       for (int x = 0; x < pieces; ++x) {
-        const int64_t from = x < real ? piece_begin(n_sel, real, x) : 0, to = x < real ? piece_begin(n_sel, real, x + 1) : 0;
-        const int n = int(to - from);
-        const int64_t at = begin + from;
+        const int64_t from = piece_begin(n_sel, pieces, x), from_sel = begin + from;
+        const int n = int(piece_begin(n_sel, pieces, x + 1) - from);
         int lo = 0, hi = n;
-        if (e8 == 1) lo = int(uint32_t(at)), hi = int(at >> 32);
-        if (e8 == 2) lo = real > 1 ? slot + x : -1, hi = max(real, 1);                    // slot, pieces
-        if (e8 == 3) lo = real > 1 ? slot : -1, hi = real > 1 ? entry : -1;               // first_slot, split_index
+        if (e8 == 1) lo = int(uint32_t(from_sel)), hi = int(from_sel >> 32);
+        if (e8 == 2) lo = slot + x, hi = pieces;                        // slot, pieces
+        if (e8 == 3) lo = slot, hi = entry;                             // first_slot, split_index
         if (e8 == 4) lo = s_tok[s], hi = s_tok[s + 1];
         if (e8 == 5) lo = h, hi = kv;
         if (e8 == 6) lo = i, hi = nb;
-        if (e8 == 7 && n > 0) lo = sel_idx[at], hi = sel_idx[at + min(1, n - 1)];
+        if (e8 == 7) lo = sel_idx[from_sel], hi = sel_idx[from_sel + min(1, n - 1)];
         reinterpret_cast<int2*>(items + place + x)[e8] = int2{lo, hi};
       }
       return;
@@ -645,15 +659,20 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
 int32_t launch_order(const Geometry& g, const int64_t* sel_ptr, const int32_t* sel_idx, const WorkspaceLayout& w,
                      char* workspace, int32_t n_wg, int32_t grid, bool halves, hipStream_t stream) {
   const SeqMeta& m = g.meta;
-  if (int64_t(m.n_seq) * m.n_q_heads <= kPlacePairs) {
-    const int units = m.kv_map ? m.n_q_heads : m.n_kv_heads, group = m.n_q_heads / units;
+  const bool pieces = w.slot_capacity >= 2;
+  if (places_counted(g, pieces)) {
+    const int units = m.kv_map ? m.n_q_heads : m.n_kv_heads, group = m.n_q_heads / units, n_streams = m.n_seq * m.n_kv_heads;
+    const int mod = n_streams < kXcds ? kXcds / n_streams : 1;          // dies of a stream
     int64_t parts = 0;
-    for (int s = 0; s < m.n_seq; ++s)
-      parts += units * ((int64_t(group) * (m.blk_begin[s + 1] - m.blk_begin[s]) + kPlaceRows - 1) / kPlaceRows);
-    hipLaunchKernelGGL(w.slot_capacity >= 2 ? place_kernel<true> : place_kernel<false>, dim3(uint32_t(parts + 1)), dim3(kPlaceThreads), 0,
-                       stream, m, sel_ptr, sel_idx, reinterpret_cast<ItemRec*>(workspace + w.items),
+    for (int s = 0; s < m.n_seq; ++s) {
+      const int64_t per_head = (m.blk_begin[s + 1] - m.blk_begin[s] + mod - 1) / mod;   // rows of a head on a die, at most
+      parts += units * mod * ((group * per_head + kPlaceRows - 1) / kPlaceRows);
+    }
+    hipLaunchKernelGGL(pieces ? place_kernel<true> : place_kernel<false>, dim3(uint32_t(parts + 1)), dim3(kPlaceThreads),
+                       (g.max_nb + 1) * (pieces ? 12 : 8), stream, m, sel_ptr, sel_idx, reinterpret_cast<ItemRec*>(workspace + w.items),
                        reinterpret_cast<int32_t*>(workspace + w.queue_begin), reinterpret_cast<uint32_t*>(workspace + w.tickets),
-                       reinterpret_cast<uint32_t*>(workspace + w.split_done), int(w.item_capacity), int(w.slot_capacity), n_wg, grid, int(halves));
+                       reinterpret_cast<uint32_t*>(workspace + w.split_done), int(g.rows), int(g.max_nb + 1), int(w.item_capacity),
+                       int(w.slot_capacity), n_wg, grid, int(halves));
     return hipGetLastError() == hipSuccess ? SHPLB_OK : SHPLB_E_HIP;
   }
   hipLaunchKernelGGL(order_kernel, dim3(kXcds), dim3(kOrderThreads), 0, stream, g.meta, sel_ptr, sel_idx,

@@ -125,7 +125,13 @@ __host__ __device__ inline int pieces_of(int64_t n_sel, int64_t split_len) {
 // piece c of a row of n selected blocks cut into p pieces covers [piece_begin(c), piece_begin(c + 1))
 __host__ __device__ inline int64_t piece_begin(int64_t n_sel, int p, int c) { return n_sel * c / p; }
 
-constexpr int kPlacePairs = 2048;     // (sequence, head) pairs of a launch whose rows work out their own places
+// Launches whose rows count their own places (place_kernel); others are sorted by a workgroup per die (order_kernel).  A die's row
+// pointers (with pieces all) are read by each of its workgroups: 57344 rows of four sequences take 26 us, and the sort as long from
+// 32768 on; with pieces 4096 rows 11.6 us against 18.
+constexpr int kPlacePairs = 2048, kPlaceCounted = 1 << 16, kPlaceCountedCut = 1 << 14;
+inline bool places_counted(const Geometry& g, bool pieces) {
+  return int64_t(g.meta.n_seq) * g.meta.n_q_heads <= kPlacePairs && g.rows <= (pieces ? kPlaceCountedCut : kPlaceCounted);
+}
 
 // A queue's item `at` where the first `halved` rows of the queue, its longest, are worked on in halves: the row's place in the
 // queues, with the half (0: whole row, 1, 2) above it.

@@ -21,6 +21,18 @@ def bf16_tensor_to_f64(t: torch.Tensor) -> np.ndarray:
     return t.to(torch.float32).cpu().numpy().astype(np.float64)
 
 
+def queues_of(ws: torch.Tensor, rows: int, slots: int = 0):
+    """What the ordering kernel left in a workspace: the items' records (sixteen words each), the queues' beginnings and, of
+    launches that work on long rows in halves, how many rows of each queue those are.  The workspace ends with the items, the counters and results of
+    pieces, the queues' beginnings and eight tickets 64 bytes apart, each from a multiple of 256 bytes on."""
+    up = lambda x: -(-x // 256) * 256
+    left = ws.cpu().numpy()
+    queues = left.size - 512 - 256
+    at = queues - up(slots * 1024) - up(slots * 65536) - up((slots // 2 + 1) * 4) - up((rows + slots) * 64)
+    words = left[queues:queues + 96].view(np.int32)
+    return left[at:at + 64 * (rows + slots)].view(np.int32).reshape(-1, 16), words[:9], words[16:24]
+
+
 class DevicePass:
     """Device-resident state of one pass of the path over a workload."""
 

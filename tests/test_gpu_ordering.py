@@ -12,7 +12,7 @@ from oracle import shplb_oracle as orc
 from workloads import make_custom
 
 from checks import compare_output
-from harness import DevicePass
+from harness import DevicePass, queues_of
 from test_gpu_parity import _split_against_whole_rows, full_parity
 
 pytestmark = pytest.mark.gpu
@@ -57,65 +57,144 @@ def test_every_row_is_dealt_once_from_queues(block, seqlens, heads):
     assert (run.lse != 0).all()
 
 
+class QueueCase:
+    """A launch whose queues are looked at: its rows, their dies, and all-zero inputs."""
+
+    def __init__(self, block, seqlens, heads, kv_of, budget_choice):
+        self.block, (hq, hkv) = block, heads
+        self.rng = rng = np.random.default_rng(len(seqlens) + hq + block)
+        self.lens = [block * nb - int(rng.integers(0, block)) for nb in seqlens]
+        n_seq, self.nbs = len(self.lens), np.array(seqlens)
+        budgets = rng.choice(budget_choice, size=n_seq * hq).astype(np.int32)
+        self.p = S.Problem(np.concatenate([[0], np.cumsum(self.lens)]), hq, hkv, block, 128, kv_head_of=kv_of)
+        self.n_wg = S.shplb_sched_num_workgroups(self.p)
+        self.ptr = S.shplb_sel_row_ptr(self.p, budgets)
+        self.kv_of = np.array(kv_of or [h // (hq // hkv) for h in range(hq)])
+        self.what = np.array([(s, h, i) for s in range(n_seq) for h in range(hq) for i in range(self.nbs[s])])
+        self.rows, n_streams = len(self.what), n_seq * hkv
+        stream = self.what[:, 0] * hkv + self.kv_of[self.what[:, 1]]
+        spread = 8 // n_streams if n_streams < 8 else 1
+        self.die = stream % 8 if n_streams >= 8 else stream * spread + self.what[:, 2] % spread
+        total = int(self.p.cu[-1])
+        self.q = torch.zeros((total, hq, 128), dtype=torch.bfloat16, device="cuda:0")
+        self.kv = torch.zeros((total, hkv, 128), dtype=torch.bfloat16, device="cuda:0")
+        self.out = torch.zeros_like(self.q)
+
+    def any_lists(self, long=None):
+        """Rows of any number of blocks, the last of a head like the others: of all it sees, or 0 to 2 and, one in `long`, all."""
+        n = np.array([int(self.rng.integers(0, i + 2)) for _, _, i in self.what])
+        if long is not None:
+            n = np.where(self.rng.integers(0, long, size=self.rows) == 0, self.what[:, 2] + 1, np.minimum(n, self.rng.integers(0, 3, size=self.rows)))
+        return np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+
+    def lists(self, sel, ascending=True):
+        draw = lambda i, n: np.sort(self.rng.permutation(i + 1)[:n]) if ascending else self.rng.permutation(i + 1)[:n]
+        return np.concatenate([draw(i, n) for (_, _, i), n in zip(self.what, np.diff(sel))] + [np.zeros(0)]).astype(np.int32)
+
+    def launch(self, sel, idx, slots=0):
+        args = (self.p, self.q, self.kv, self.kv, torch.from_numpy(sel).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"), self.out, None, None)
+        stream = torch.cuda.current_stream()
+        size = S.shplb_split_workspace_bytes(self.p, slots) if slots else S.shplb_workspace_bytes(self.p)
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        if slots:
+            S.shplb_sparse_attn_prefill_split(*args, ws, slots, stream)
+        else:
+            S.shplb_sparse_attn_prefill(*args, ws, stream)
+        torch.cuda.synchronize()
+        return queues_of(ws, self.rows, slots)
+
+    def rows_of(self, item):
+        """Row of every item, by its sequence, head and query block."""
+        at_token = np.concatenate([[0], np.cumsum(self.lens)])
+        first_row = np.concatenate([[0], np.cumsum(self.nbs)]) * self.p.n_q_heads
+        s_of = np.searchsorted(at_token, item[:, 8])
+        assert (at_token[s_of] == item[:, 8]).all() and (at_token[s_of + 1] == item[:, 9]).all()
+        assert (item[:, 10] < self.p.n_q_heads).all() and (item[:, 12] < self.nbs[s_of]).all() and (item[:, [10, 12]] >= 0).all()
+        assert (item[:, 11] == self.kv_of[item[:, 10]]).all() and (item[:, 13] == self.nbs[s_of]).all()
+        return first_row[s_of] + item[:, 10] * self.nbs[s_of] + item[:, 12]
+
+
+def queues_of_whole_rows(block, seqlens, heads, kv_of, long=None):
+    c = QueueCase(block, seqlens, heads, kv_of, [2, 3, 5, 11, 999] if long is None else [2, 3, 5])
+    halves_seen = 0
+    for by_budget, sel in ((True, c.ptr), (False, c.any_lists(long))):
+        idx = c.lists(sel, ascending=False)
+        print("case", block, seqlens[:4], heads, "rows", c.rows, "by budget", by_budget, flush=True)
+        item, begin, halved = c.launch(sel, idx)
+        assert c.rows > c.n_wg                                    # (so there are queues)
+        assert begin.tolist() == np.concatenate([[0], np.cumsum(np.bincount(c.die, minlength=8))]).tolist()
+        row = c.rows_of(item)
+        assert (np.sort(row) == np.arange(c.rows)).all()
+        assert (c.die[row] == np.repeat(np.arange(8), np.diff(begin))).all()
+        n = np.diff(sel)[row]
+        full = np.append(idx, 0)
+        assert (item[:, 0] == 0).all() and (item[:, 1] == n).all() and (item[:, 2] == sel[row]).all() and (item[:, 3] == 0).all()
+        assert (item[:, [4, 6, 7]] == -1).all() and (item[:, 5] == 1).all()
+        assert (item[:, 14] == np.where(n > 0, full[sel[row]], 0)).all()
+        assert (item[:, 15] == np.where(n > 0, full[sel[row] + np.minimum(1, np.maximum(n - 1, 0))], 0)).all()
+        for x in range(8):
+            assert (np.diff(n[begin[x]:begin[x + 1]]) <= 0).all()
+        # which launches have halves at all is decided by the shapes: what the rows of any budgets select at least
+        n_sh = len(seqlens) * heads[0]
+        if block == 128 and c.rows <= 6 * c.n_wg and n_sh <= 2048 and max(seqlens) > max(16, (2 * c.rows - n_sh) * 6 // (c.n_wg * 5)):
+            above = max(16, int(sel[-1]) * 6 // (c.n_wg * 5))
+            assert halved.tolist() == np.bincount(c.die[np.diff(sel) > above], minlength=8).tolist()
+            halves_seen += int(halved.sum())
+    return halves_seen
+
+
 @pytest.mark.parametrize("block, seqlens, heads, kv_of", [
     (128, [230], (6, 1), None), (128, [181], (6, 3), None), (64, [300], (10, 5), None), (128, [70, 67], (8, 4), None),
     (128, [33, 1, 64], (28, 4), None), (64, [97, 31, 32], (16, 8), None), (64, [17] * 64, (32, 8), None),
     (128, [90, 40], (8, 2), [0, 1, 1, 1, 1, 1, 1, 1]), (64, [131, 9], (24, 9), [x % 9 for x in range(24)])])
 def test_queues_hold_every_row_by_cost(block, seqlens, heads, kv_of):
-    # What the ordering kernel leaves in the workspace, where rows work their places out for themselves (up to 2048
+    # What the ordering kernel leaves in the workspace, where rows count their places for themselves (up to 2048
     # (sequence, head) pairs: the seventh shape): 1, 3, 5, 8, 12 .. 512 K/V streams on eight dies, heads of a stream and mapped ones, runs of 32 rows
-    # that end inside a head; for rows of a budget and for rows of any number of blocks, none among them.
-    hq, hkv = heads
-    rng = np.random.default_rng(len(seqlens) + hq + block)
-    lens = [block * nb - int(rng.integers(0, block)) for nb in seqlens]
-    n_seq, nbs = len(lens), np.array(seqlens)
-    budgets = rng.choice([2, 3, 5, 11, 999], size=n_seq * hq).astype(np.int32)
-    p = S.Problem(np.concatenate([[0], np.cumsum(lens)]), hq, hkv, block, 128, kv_head_of=kv_of)
-    ptr = S.shplb_sel_row_ptr(p, budgets)
-    kv_of = kv_of or [h // (hq // hkv) for h in range(hq)]
-    what = np.array([(s, h, i) for s in range(n_seq) for h in range(hq) for i in range(nbs[s])])
-    rows, n_streams = len(what), n_seq * hkv
-    stream = what[:, 0] * hkv + np.array(kv_of)[what[:, 1]]
-    spread = 8 // n_streams if n_streams < 8 else 1
-    die = stream % 8 if n_streams >= 8 else stream * spread + what[:, 2] % spread
-    odd = np.concatenate([[0], np.cumsum([int(rng.integers(0, i + 2)) for _, _, i in what])]).astype(np.int64)
-    total = int(p.cu[-1])
-    q = torch.zeros((total, hq, 128), dtype=torch.bfloat16, device="cuda:0")
-    kv = torch.zeros((total, hkv, 128), dtype=torch.bfloat16, device="cuda:0")
-    out = torch.zeros_like(q)
-    size = S.shplb_workspace_bytes(p)
-    for by_budget, sel in ((True, ptr), (False, odd)):
-        idx = np.concatenate([rng.permutation(i + 1)[:n] for (_, _, i), n in zip(what, np.diff(sel))]).astype(np.int32)
-        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda:0")
-        print("case", block, seqlens[:4], heads, "rows", rows, "by budget", by_budget, flush=True)
-        S.shplb_sparse_attn_prefill(p, q, kv, kv, torch.from_numpy(sel).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"), out, None,
-                                    None, ws, torch.cuda.current_stream())
-        torch.cuda.synchronize()
-        assert rows > S.shplb_sched_num_workgroups(p)             # (so there are queues)
-        left = ws.cpu().numpy()
-        # the workspace ends with the items, an unused piece of 256 bytes, where the queues begin, and eight tickets 64 bytes apart
-        at = size - 512 - 256 - 256 - -(-rows * 64 // 256) * 256
-        item = left[at:at + 64 * rows].view(np.int32).reshape(rows, 16)
-        begin = left[size - 768:size - 768 + 36].view(np.int32)
-        assert begin.tolist() == np.concatenate([[0], np.cumsum(np.bincount(die, minlength=8))]).tolist()
-        index = {tuple(w): r for r, w in enumerate(what)}
-        at_token = np.concatenate([[0], np.cumsum(lens)])
-        s_of = np.searchsorted(at_token, item[:, 8])
-        row = np.array([index[(int(s), int(x[10]), int(x[12]))] for s, x in zip(s_of, item)])
-        assert (np.sort(row) == np.arange(rows)).all()
-        assert (die[row] == np.repeat(np.arange(8), np.diff(begin))).all()
-        n = np.diff(sel)[row]
-        expect = np.zeros((rows, 16), np.int64)
-        expect[:, 1], expect[:, 2], expect[:, 4], expect[:, 5], expect[:, 6], expect[:, 7] = n, sel[row], -1, 1, -1, -1
-        expect[:, 8], expect[:, 9], expect[:, 10], expect[:, 11] = at_token[s_of], at_token[s_of + 1], what[row, 1], np.array(kv_of)[what[row, 1]]
-        expect[:, 12], expect[:, 13] = what[row, 2], nbs[s_of]
-        full = np.append(idx, 0)
-        expect[:, 14] = np.where(n > 0, full[sel[row]], 0)
-        expect[:, 15] = np.where(n > 0, full[sel[row] + np.minimum(1, np.maximum(n - 1, 0))], 0)
-        assert (item == expect).all()
-        if by_budget:
-            for x in range(8):
-                assert (np.diff(n[begin[x]:begin[x + 1]]) <= 0).all()
+    # that end inside a head; for rows of a budget and for rows of any number of blocks, none among them.  The long rows that
+    # are worked on in halves are counted per queue, in ragged batches and with mapped heads too.
+    halves = queues_of_whole_rows(block, seqlens, heads, kv_of)
+    assert halves > 0 or block == 64
+
+
+def queues_of_pieces(block, seqlens, heads, kv_of, slots, long=None):
+    # Every block of a row is in one of its pieces, in order; slots and counters are a split row's own and within what the workspace
+    # holds; items lie by the cost of their rows, whose pieces are as many as split_length() makes of what they select.
+    c = QueueCase(block, seqlens, heads, kv_of, [2, 3, 11, 999, 999] if long is None else [2] * 9 + [999])
+    rows, share_wg = c.rows, c.n_wg // 2 if block == 128 and c.rows <= c.n_wg // 2 else c.n_wg
+    cut_rows = 0
+    for by_budget, sel in ((True, c.ptr), (False, c.any_lists(long))):
+        idx = c.lists(sel)
+        cost = int(sel[-1])
+        cut = max(32 * 64 // block, -(-2 * cost // slots), -(-cost // (share_wg * 2)))
+        wanted = np.clip(-(-np.diff(sel) // cut), 1, 64)              # pieces of a row
+        print("case", block, seqlens[:4], heads, "rows", rows, "cut at", cut, "split rows", int((wanted > 1).sum()), "by budget", by_budget, flush=True)
+        item, begin, _ = c.launch(sel, idx, slots)
+        assert begin.tolist() == np.concatenate([[0], np.cumsum(np.bincount(c.die, weights=wanted, minlength=8))]).astype(int).tolist()
+        item = item[:int(wanted.sum())]
+        row = c.rows_of(item)
+        assert (np.bincount(row, minlength=rows) == wanted).all()
+        assert (c.die[row] == np.repeat(np.arange(8), np.diff(begin))).all()
+        n_of = np.diff(sel)[row]
+        for x in range(8):
+            assert (np.diff(n_of[begin[x]:begin[x + 1]]) <= 0).all()
+        whole = wanted[row] == 1
+        assert (item[whole, 1] == n_of[whole]).all() and (item[whole, 2] == sel[row[whole]]).all()
+        assert (item[whole][:, [4, 6, 7]] == -1).all() and (item[whole, 5] == 1).all()
+        some = item[:, 1] > 0
+        assert (item[some, 14] == idx[item[some, 2]]).all() and (item[some, 15] == idx[item[some, 2] + np.minimum(1, item[some, 1] - 1)]).all()
+        used, counters = [], []
+        for r in np.flatnonzero(wanted > 1):
+            pieces = item[row == r]
+            assert (pieces[:, 1] > 0).all() and int(pieces[:, 1].sum()) == sel[r + 1] - sel[r]
+            assert (pieces[:, 2] == sel[r] + np.concatenate([[0], np.cumsum(pieces[:, 1])])[:-1]).all()
+            assert (pieces[:, 5] == len(pieces)).all() and (pieces[:, 6] == pieces[0, 6]).all() and (pieces[:, 7] == pieces[0, 7]).all()
+            assert (pieces[:, 4] == pieces[0, 6] + np.arange(len(pieces))).all()
+            used += pieces[:, 4].tolist()
+            counters.append(int(pieces[0, 7]))
+        assert len(set(used)) == len(used) and len(set(counters)) == len(counters)
+        assert not used or (min(used) >= 0 and max(used) < slots and min(counters) >= 0 and max(counters) <= slots // 2)
+        cut_rows += len(counters)
+    return cut_rows
 
 
 @pytest.mark.parametrize("block, seqlens, heads, kv_of, slots", [
@@ -123,73 +202,42 @@ def test_queues_hold_every_row_by_cost(block, seqlens, heads, kv_of):
     (128, [33, 1, 64], (28, 4), None, 2048), (64, [97, 31, 32], (16, 8), None, 3), (128, [17] * 64, (32, 8), None, 4096),
     (128, [90, 40], (8, 2), [0, 1, 1, 1, 1, 1, 1, 1], 2048), (64, [131, 9], (24, 9), [x % 9 for x in range(24)], 2048), (128, [40], (4, 4), None, 2048)])
 def test_queues_hold_every_piece_of_cut_rows(block, seqlens, heads, kv_of, slots):
-    # The same with pieces: every block of a row is in one of them, in order; slots and counters are a split row's own and within
-    # what the workspace holds; items lie by the cost of their rows.  For rows of a budget, cut at split_length(), and for rows
-    # of any number of blocks, where a row may have fewer blocks than pieces.
+    # The same with pieces, for rows of a budget and for rows of any number of blocks.
+    queues_of_pieces(block, seqlens, heads, kv_of, slots)
+
+
+@pytest.mark.parametrize("block, n_blocks, heads", [(128, 70, (8, 2)), (64, 140, (10, 5))])
+def test_lists_that_follow_no_budget(block, n_blocks, heads):
+    # Lists of a caller's own whose last row of a head is short and whose earlier ones are long, and the other way round: long rows
+    # are in halves or cut, short ones whole, and the outputs are the oracle's.
     hq, hkv = heads
-    rng = np.random.default_rng(len(seqlens) + hq + block)
-    lens = [block * nb - int(rng.integers(0, block)) for nb in seqlens]
-    n_seq, nbs = len(lens), np.array(seqlens)
-    budgets = rng.choice([2, 3, 11, 999, 999], size=n_seq * hq).astype(np.int32)
-    p = S.Problem(np.concatenate([[0], np.cumsum(lens)]), hq, hkv, block, 128, kv_head_of=kv_of)
-    ptr = S.shplb_sel_row_ptr(p, budgets)
-    kv_of = kv_of or [h // (hq // hkv) for h in range(hq)]
-    what = np.array([(s, h, i) for s in range(n_seq) for h in range(hq) for i in range(nbs[s])])
-    rows, n_streams = len(what), n_seq * hkv
-    stream = what[:, 0] * hkv + np.array(kv_of)[what[:, 1]]
-    spread = 8 // n_streams if n_streams < 8 else 1
-    die = stream % 8 if n_streams >= 8 else stream * spread + what[:, 2] % spread
-    last = (what[:, 2] == nbs[what[:, 0]] - 1)
-    odd = np.concatenate([[0], np.cumsum([n if end else int(rng.integers(0, i + 2)) for n, end, (_, _, i) in zip(np.diff(ptr), last, what)])]).astype(np.int64)
-    total = int(p.cu[-1])
-    q = torch.zeros((total, hq, 128), dtype=torch.bfloat16, device="cuda:0")
-    kv = torch.zeros((total, hkv, 128), dtype=torch.bfloat16, device="cuda:0")
-    out = torch.zeros_like(q)
-    size = S.shplb_split_workspace_bytes(p, slots)
-    up = lambda x: -(-x // 256) * 256
-    n_wg = S.shplb_sched_num_workgroups(p)
-    few = rows <= n_wg // 2 if block == 128 else False
-    share_wg = n_wg // 2 if few else n_wg
-    cost = int(ptr[-1])
-    cut = max(32 * 64 // block, -(-2 * cost // slots), -(-cost // (share_wg * 2)))
-    wanted = np.minimum(-(-np.diff(ptr) // cut), 64)                  # pieces of a row of its budget
-    for by_budget, sel in ((True, ptr), (False, odd)):
-        idx = np.concatenate([np.sort(rng.permutation(i + 1)[:n]) for (_, _, i), n in zip(what, np.diff(sel))]).astype(np.int32)
-        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda:0")
-        print("case", block, seqlens[:4], heads, "rows", rows, "cut at", cut, "split rows", int((wanted > 1).sum()), "by budget", by_budget, flush=True)
-        S.shplb_sparse_attn_prefill_split(p, q, kv, kv, torch.from_numpy(sel).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"), out, None,
-                                          None, ws, slots, torch.cuda.current_stream())
+    wl = make_custom([block * n_blocks - 9], hq, hkv, block, [2] * hq, seed=910 + block, name="no_budget_%d" % block)
+    rng = np.random.default_rng(911)
+    run = DevicePass(wl)
+    lists = []
+    for h in range(hq):
+        for i in range(n_blocks):
+            long = i < n_blocks - 1 and i % 7 == 5 if h % 2 == 0 else i == n_blocks - 1
+            lists.append(np.arange(i + 1) if long else np.union1d(rng.integers(0, i + 1, size=(i + h) % 5 // 2), [i]))
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    idx = np.concatenate(lists).astype(np.int32)
+    n = np.diff(ptr)
+    rows = sorted(set(np.argsort(n)[-6:].tolist()) | set(rng.integers(0, run.rows, size=60).tolist()) | {n_blocks - 1, 2 * n_blocks - 1})
+    out_o, lse_o = orc.sparse_attention(wl.q, wl.k, wl.v, wl.cu_seqlens, block, ptr, idx, None, rows)
+    run.sel_ptr, run.sel_idx = torch.from_numpy(ptr).to("cuda:0"), torch.from_numpy(idx).to("cuda:0")
+    cut = max(32 * 64 // block, -(-int(ptr[-1]) // (run.n_wg * 2)))
+    wanted = np.clip(-(-n // cut), 1, 64)
+    print("case", wl.name, "rows", run.rows, "blocks", int(ptr[-1]), "cut at", cut, "split rows", int((wanted > 1).sum()), flush=True)
+    assert (wanted > 1).any() and wanted[n_blocks - 1] == 1
+    for step, items in ((run.attn_step, run.rows), (lambda: run.attn_split_step(2048), int(wanted.sum()))):
+        run.out.zero_()
+        run.lse.zero_()
+        step()
         torch.cuda.synchronize()
-        left = ws.cpu().numpy()
-        n_items = int(wanted.sum())
-        at = size - 512 - 256 - up(slots * 1024) - up(slots * 65536) - up((slots // 2 + 1) * 4) - up((rows + slots) * 64)
-        begin = left[size - 768:size - 768 + 36].view(np.int32)
-        assert begin.tolist() == np.concatenate([[0], np.cumsum(np.bincount(die, weights=wanted, minlength=8))]).astype(int).tolist()
-        item = left[at:at + 64 * n_items].view(np.int32).reshape(n_items, 16)
-        index = {tuple(w): r for r, w in enumerate(what)}
-        s_of = np.searchsorted(np.concatenate([[0], np.cumsum(lens)]), item[:, 8])
-        row = np.array([index[(int(s), int(x[10]), int(x[12]))] for s, x in zip(s_of, item)])
-        assert (np.bincount(row, minlength=rows) == wanted).all()
-        assert (die[row] == np.repeat(np.arange(8), np.diff(begin))).all()
-        n_of = np.diff(ptr)[row]
-        for x in range(8):
-            assert (np.diff(n_of[begin[x]:begin[x + 1]]) <= 0).all()  # (by the budgets' costs in either case)
-        used, counters = [], []
-        for r in range(rows):
-            mine = item[row == r] if wanted[r] > 1 else item[np.flatnonzero(row == r)]
-            pieces = mine[mine[:, 1] > 0]
-            assert int(pieces[:, 1].sum()) == sel[r + 1] - sel[r]
-            assert (pieces[:, 2] == sel[r] + np.concatenate([[0], np.cumsum(pieces[:, 1])])[:-1]).all()
-            assert (pieces[:, 14] == idx[pieces[:, 2]]).all() and (pieces[:, 15] == idx[pieces[:, 2] + np.minimum(1, pieces[:, 1] - 1)]).all()
-            if len(pieces) <= 1:
-                assert (pieces[:, 4] == -1).all() and (pieces[:, 5] == 1).all()
-                continue
-            assert (pieces[:, 5] == len(pieces)).all() and (pieces[:, 6] == pieces[0, 6]).all() and (pieces[:, 7] == pieces[0, 7]).all()
-            assert (pieces[:, 4] == pieces[0, 6] + np.arange(len(pieces))).all()
-            used += pieces[:, 4].tolist()
-            counters.append(int(pieces[0, 7]))
-        assert len(set(used)) == len(used) and len(set(counters)) == len(counters)
-        assert not used or (min(used) >= 0 and max(used) < slots and min(counters) >= 0 and max(counters) <= slots // 2)
+        st = run.stats_host()
+        assert st["n_items"].sum() == items and st["cost_blocks"].sum() == ptr[-1]
+        compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
+        assert (run.lse != 0).all()
 
 
 @pytest.mark.parametrize("block, n_blocks, heads", [(128, 16, (32, 8)), (128, 17, (32, 8)), (64, 32, (40, 8)), (64, 33, (40, 8)), (128, 3, (8, 2))])
