@@ -1000,13 +1000,14 @@ AttentionPlan plan_attention(const Geometry& g, int32_t n_wg, int64_t slot_capac
   // of its own (777 tokens x 32 heads: 42.6 us for the whole path with the ordering launch, 35.5 without).
   plan.ordered = slot_capacity > 0 || g.rows > plan.grid - plan.grid % kXcds;
   // Whole rows from queues: the ordering kernel may have long ones worked on in halves, if a row can be that long (every row of
-  // two blocks and more selects at least two), by an instance of the kernel that has both.  Where there is nothing to halve it takes
-  // 0 to 0.8% longer (8231 tokens x 32/8 heads 168.4 and 168.0 us, 4270 x 40/8 156.4 and 157.3), on long launches, whose rows
+  // two blocks and more selects at least two), by an instance of the kernel that has both.  Where there is nothing to halve, the
+  // attention call takes 0.2 to 3% longer by it (8231 tokens x 32/8 heads 144.9 -> 148.1 us, x 28/4 130.4 -> 131.4, 12000 x 32/8 263.9 -> 271.0,
+  // 6000 x 40/8 109.4 -> 113.1), on long launches, whose rows
   // hardly reach the share, 0.9% (32K x 32/8, 64K x 8/2): up to six rows a workgroup.  With 64-token blocks, where a half has as many
   // copies for half of the products of which there are few, 6933 x 32/8 with a dense head gains 10%, 8/8 x (1265, 6884, 1553) loses 4%.
   const int64_t n_sh = int64_t(g.meta.n_seq) * g.meta.n_q_heads;
   plan.halves = plan.ordered && slot_capacity == 0 && plan.groups == 1 && g.meta.block == 128 && g.rows <= 6 * n_wg &&
-                places_counted(g, false) && int64_t(g.max_nb) > halved_above(2 * g.rows - n_sh, n_wg);
+                places_counted(g, false) && worth_halves(g.max_nb, 2 * g.rows - n_sh, n_wg);
   return plan;
 }
 

@@ -339,7 +339,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 // in front of its own 64; a sum over the bins from the longest rows on, and its rows' places are known.  All workgroups of a die
 // count the same, so none waits for another one.  A row has eight lanes, which write its record together.  An extra workgroup at the
 // end writes the queues' beginnings and tickets, and with `halves` how many rows of each queue are worked on in halves (the
-// longest ones, so the first; see halved_above()).
+// longest ones, so the first; see halved_above() and worth_halves()).
 //
 // Pieces (kPieces): a row is cut into pieces_of() its own number of blocks, and the items in front of it are the pieces of the rows
 // in front.  The workgroups go through all rows, as the items of the dies before come first.  Split rows are the first of their queues, so slots and
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   __shared__ uint32_t s_unit[kPlacePairs];   // ... blocks | stream << 16
   __shared__ int32_t s_listed;               // rows listed | units listed << 20
   __shared__ int32_t s_before, s_slots, s_splits;   // items, slots and split rows on the dies before
-  __shared__ int32_t s_total[kXcds], s_halved[kXcds], s_wave[2][kPlaceWaves], s_n[kPlaceRows];
+  __shared__ int32_t s_total[kXcds], s_halved[kXcds], s_longest, s_wave[2][kPlaceWaves], s_n[kPlaceRows];
   static_assert(SHPLB_MAX_SEQ < kPlaceThreads && SHPLB_MAX_BLOCKS < 1 << 16 && kPlaceCounted < 1 << 20 && kPlacePairs < 1 << 12, "");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // asked for together: the geometry, of which a lane-dependent index is read
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   }
   if (tid < SHPLB_MAX_MAPPED_HEADS / 4) s_kv[tid] = my_kv;
   if (tid < kXcds) s_total[tid] = s_halved[tid] = 0;
-  if (tid == 0) s_listed = s_before = s_slots = s_splits = 0;
+  if (tid == 0) s_listed = s_before = s_slots = s_splits = s_longest = 0;
   for (int b = tid; b < n_bins; b += kPlaceThreads) s_bins[b] = 0;
   __syncthreads();
   auto kv_head = [&](int h) { return map ? int(s_kv[h >> 2] >> (8 * (h & 3)) & 0xff) : quotient(h, group); };
@@ -482,6 +482,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
       each_row(-1, [&](int, int die, int n, bool live) {
         const int add = !live ? 0 : kPieces ? pieces_here(n) : int(n > above);
         int32_t* const sums = kPieces ? s_total : s_halved;
+        if (!kPieces && add != 0) atomicMax(&s_longest, n);
         if (mod > 1) {
           if (add != 0) atomicAdd(&sums[die], add);
           return;
@@ -501,7 +502,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
       }
     }
     __syncthreads();
-    if (!kPieces && halves && tid < kXcds) queue_begin[kHalvedRows + tid] = s_halved[tid];
+    if (!kPieces && halves && tid < kXcds) queue_begin[kHalvedRows + tid] = worth_halves(s_longest, end_sel - first_sel, n_wg) ? s_halved[tid] : 0;
     if (tid <= kXcds) {
       int begin = 0;
       for (int x = 0; x < tid; ++x) begin += s_total[x];

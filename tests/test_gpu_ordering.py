@@ -114,6 +114,12 @@ class QueueCase:
         return first_row[s_of] + item[:, 10] * self.nbs[s_of] + item[:, 12]
 
 
+def halved_rows(n, total, n_wg):
+    """Which of rows of n blocks are worked on in halves: those of more than 1.2 times a workgroup's share, and 16 blocks, where the longest has 5/3 of
+    it."""
+    return (n > max(16, total * 6 // (n_wg * 5))) & (n.max() * 3 * n_wg >= total * 5)
+
+
 def queues_of_whole_rows(block, seqlens, heads, kv_of, long=None):
     c = QueueCase(block, seqlens, heads, kv_of, [2, 3, 5, 11, 999] if long is None else [2, 3, 5])
     halves_seen = 0
@@ -136,9 +142,8 @@ def queues_of_whole_rows(block, seqlens, heads, kv_of, long=None):
             assert (np.diff(n[begin[x]:begin[x + 1]]) <= 0).all()
         # which launches have halves at all is decided by the shapes: what the rows of any budgets select at least
         n_sh = len(seqlens) * heads[0]
-        if block == 128 and c.rows <= 6 * c.n_wg and n_sh <= 2048 and max(seqlens) > max(16, (2 * c.rows - n_sh) * 6 // (c.n_wg * 5)):
-            above = max(16, int(sel[-1]) * 6 // (c.n_wg * 5))
-            assert halved.tolist() == np.bincount(c.die[np.diff(sel) > above], minlength=8).tolist()
+        if block == 128 and c.rows <= 6 * c.n_wg and n_sh <= 2048 and halved_rows(np.array(seqlens), 2 * c.rows - n_sh, c.n_wg).any():
+            assert halved.tolist() == np.bincount(c.die[halved_rows(np.diff(sel), int(sel[-1]), c.n_wg)], minlength=8).tolist()
             halves_seen += int(halved.sum())
     return halves_seen
 
@@ -154,6 +159,20 @@ def test_queues_hold_every_row_by_cost(block, seqlens, heads, kv_of):
     # are worked on in halves are counted per queue, in ragged batches and with mapped heads too.
     halves = queues_of_whole_rows(block, seqlens, heads, kv_of)
     assert halves > 0 or block == 64
+
+
+def test_rows_hardly_longer_than_the_share_stay_whole():
+    # 1280 rows of up to 20 blocks, the share of a workgroup being 13 to 16: the longest rows stay whole, with others of 40 blocks they do not.
+    for extra in (20, 40):
+        c = QueueCase(128, [40], (32, 8), None, [2, 3, 4, 20])
+        budgets = np.array([2, 3, 4, 20] * 7 + [20, 2, 2, extra], np.int32)
+        sel = S.shplb_sel_row_ptr(c.p, budgets)
+        n, share = np.diff(sel), sel[-1] / c.n_wg
+        expect = halved_rows(n, int(sel[-1]), c.n_wg)
+        print("share %.1f longest %d" % (share, n.max()), flush=True)
+        assert (n > 1.2 * share).any() and expect.any() == (extra == 40)
+        _, _, halved = c.launch(sel, c.lists(sel))
+        assert halved.tolist() == np.bincount(c.die[expect], minlength=8).tolist()
 
 
 def queues_of_pieces(block, seqlens, heads, kv_of, slots, long=None):
@@ -437,10 +456,10 @@ def test_a_128_token_sequence_alone_and_in_a_larger_call(n_blocks, tail, heads, 
 
 
 @pytest.mark.parametrize("n_blocks, tail, heads, budgets", [(70, 128, (8, 2), [999] + [2] * 7), (70, 1, (8, 2), [2, 2, 999, 2, 2, 40, 2, 2]), (66, 64, (8, 8), [999, 3] * 4),
-                                                           (65, 65, (8, 4), [2] * 7 + [50]), (520, 30, (1, 1), [200]), (131, 90, (4, 1), [2, 9, 999, 2])])
+                                                           (65, 65, (8, 4), [2] * 7 + [50]), (520, 30, (1, 1), [999]), (131, 90, (4, 1), [2, 9, 999, 2])])
 def test_long_rows_in_halves(n_blocks, tail, heads, budgets):
     # Launches of up to six 128-token rows a workgroup have rows of more than 1.2 times the average share worked on in halves of
-    # 64 queries: the same bits as whole rows, which they are among seven copies of the sequence; every row counted once; a last
+    # 64 queries, where the longest has 5/3 of it: the same bits as whole rows, which they are among seven copies of the sequence; every row counted once; a last
     # block whose second half has no query, and references raised in one of the halves only (a later key's component 9).
     hq, hkv = heads
     T = 128 * (n_blocks - 1) + tail
@@ -454,7 +473,7 @@ def test_long_rows_in_halves(n_blocks, tail, heads, budgets):
     n = np.diff(a.sel_ptr_host)
     above = max(16, n.sum() * 6 // (a.n_wg * 5))
     print("case", one.name, "rows", a.rows, b.rows, "in halves", int((n > above).sum()), flush=True)
-    assert a.n_wg < a.rows <= 6 * a.n_wg < b.rows and (n > above).any()
+    assert a.n_wg < a.rows <= 6 * a.n_wg < b.rows and halved_rows(n, int(n.sum()), a.n_wg).any()
     st = a.stats_host()
     assert st["n_items"].sum() == a.rows and st["cost_blocks"].sum() == n.sum()
     # Every workgroup that worked says when, and all start with the launch, those that begin with a second half too: at its end such a
