@@ -213,6 +213,7 @@ __device__ __attribute__((noinline)) void merge_row(const SplitBuffers& sb, int 
   // pass 2: the slots hold O in the order the attention kernels keep it in registers (slot_chunk()):
   // chunk e = (queries * 8 + dt) * 64 + lane is dims 16 dt + 4 (lane / 16) .. +3 of query
   // 16 queries + lane % 16.  A thread owns chunks threadIdx.x + THREADS * u; a wave reads 1 KB runs.
+  static_assert(BQ * (kHeadDim / 4) % THREADS == 0, "every chunk is a thread's");
   constexpr int kChunks = BQ * (kHeadDim / 4) / THREADS;
   f32x4 acc[kChunks];
   const SlotBuffer slots = slot_buffer(part_o, pieces * kSlotFloatsO);

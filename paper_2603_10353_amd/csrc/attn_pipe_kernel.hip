@@ -863,7 +863,7 @@ void attn_pipe_kernel(AttnArgs) {
     asm volatile("" : "+v"(q_in));                   // output addresses are made here, not carried through the loop
     ArgsPtr a = reload(args);
     const int q0 = cur.seq_begin + cur.q_block * BQ;
-    if (cur.slot >= 0) {
+    if (!COPIERS && cur.slot >= 0) {
       // a piece of a split row: O and l as they stand (relative to 2^m_ref), for merge_row()
       float* part = a->sb.part_o + int64_t(cur.slot) * kSlotFloatsO;
       float* ml = a->sb.part_ml + int64_t(cur.slot) * kSlotFloatsML;
@@ -944,8 +944,8 @@ void attn_pipe_kernel(AttnArgs) {
     else process(std::integral_constant<int, QGM>{});
   }
 
-  // ---- rows whose pieces are all done and whose last piece this workgroup computed
-  for (int x = 0; x < n_merge; ++x) {
+  // ---- rows whose pieces are all done and whose last piece this workgroup computed (COPIERS: rows are whole)
+  if constexpr (!COPIERS) for (int x = 0; x < n_merge; ++x) {
     __syncthreads();                                   // s_merge as thread 0 left it
     ArgsPtr a = reload(args);
     const ItemRec* item = a->wq.items + s_merge[x];
