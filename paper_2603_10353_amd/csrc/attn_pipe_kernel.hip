@@ -59,7 +59,7 @@
 // started one step later, between the last step and the output, these were 125 us, 1.81 ms and 0.7%.
 //
 // HALVES: items may be halves of a row's queries (16 a wave), the first 2 H of a queue being those of its H longest rows; see
-// queue_place() and halved_above().  A query's sums do not depend on it, as with QS = 2.  (Operands are fetched 6 ahead there: with
+// queue_place() and in_halves().  A query's sums do not depend on it, as with QS = 2.  (Operands are fetched 6 ahead there: with
 // 8, 22 and more registers are spilled in the tile loop, 16%.)
 //
 // The two score buffers swap roles from step to step (the tile count is even, steps are

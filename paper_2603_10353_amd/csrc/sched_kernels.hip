@@ -339,21 +339,22 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 // in front of its own 64; a sum over the bins from the longest rows on, and its rows' places are known.  All workgroups of a die
 // count the same, so none waits for another one.  A row has eight lanes, which write its record together.  An extra workgroup at the
 // end writes the queues' beginnings and tickets, and with `halves` how many rows of each queue are worked on in halves (the
-// longest ones, so the first; see halved_above() and worth_halves()).
+// longest ones, so the first; see in_halves() and worth_halves()).
 //
 // Pieces (kPieces): a row is cut into pieces_of() its own number of blocks, and the items in front of it are the pieces of the rows
 // in front.  The workgroups go through all rows, as the items of the dies before come first.  Split rows are the first of their queues, so slots and
 // counters are numbered like items and rows, behind those of the dies before.
 //
-// What bounds it is the chain arguments -> row pointers -> first blocks, on as many compute units as there are rows for.  Every
-// workgroup reads the row pointers of its die (with pieces of all rows), rows / 64 times in all: that is why larger launches are
-// sorted (places_counted()).  Under the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 6.1 us, 48 sequences x 28 heads 10.2
-// -> 5.8, 32K x 32 heads 12.0 -> 6.4, 128K 26 -> 9.7, 16K in pieces 18 -> 11.6.  Workgroups of 256 threads take 7.5, 6.5, 7.0,
-// 14.0 and 16.1 us, of 1024 6.3, 7.0, 7.6, 9.5 and 11.2.  (Counted in closed form from what the last row of every head selects, 5.3,
-// 6.7, 5.6, 7.4 and 6.6: but then a list that is no budget's, say a different number of blocks for every query block, is neither ordered nor
-// cut by its length; attention call of 8231 tokens x 32/8 heads with such lists 176 us, ordered 148.)
+// What bounds it is the chain arguments -> row pointers -> first blocks, on as many compute units as there are rows for, with code that is not in
+// the instruction cache.  Every workgroup reads the row pointers of its die (with pieces of all rows), rows / 64 times in all: that is why
+// larger launches are sorted (places_counted()).  Under the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.4 us, 48
+// sequences x 28 heads 10.2 -> 5.7, 32K x 32 heads 12.0 -> 6.3, 128K 26 -> 10.2, 16K in pieces 18 -> 12.4.  (Workgroups of 256 threads take
+// 1 to 5 us longer, of 1024 as long or up to 1 us longer.  With the extra workgroup going through the dies of all rows, not only of those in halves, the 8K
+// prompt took 6.6; twice the code by four rows in flight, 0.4.)  Counted in closed form from what the last row of every head selects it
+// took 5.3, 6.7, 5.7, 7.3 and 6.8 us, but then a list that is no budget's, say a different number of blocks for every query block, is neither
+// ordered nor cut by its length: attention call of 8231 tokens x 32/8 heads with such lists 176 us, ordered 148.
 constexpr int kPlaceThreads = 512, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes, kPlaceWaves = kPlaceThreads / 64;
-constexpr int kPlaceInFlight = 4;         // rows a thread has in flight
+constexpr int kPlaceInFlight = 2;         // rows a thread has in flight
 
 template <bool kPieces>
 __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
@@ -474,47 +475,11 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   const int len = kPieces ? int(min(split_length(end_sel - first_sel, slot_capacity, n_wg, meta.block), int64_t(1 << 24))) : 0;
   auto pieces_here = [&](int n) { return !kPieces || n <= len ? 1 : min(quotient(n + len - 1, len), kSplitMaxPieces); };   // pieces_of()
 
-  if (blockIdx.x == gridDim.x - 1) {                          // the queues' beginnings
-    if (kPieces || halves) {
-      list_units(-1);
-      __syncthreads();
-      const int above = int(min(halved_above(end_sel - first_sel, n_wg), int64_t(SHPLB_MAX_BLOCKS)));
-      each_row(-1, [&](int, int die, int n, bool live) {
-        const int add = !live ? 0 : kPieces ? pieces_here(n) : int(n > above);
-        int32_t* const sums = kPieces ? s_total : s_halved;
-        if (!kPieces && add != 0) atomicMax(&s_longest, n);
-        if (mod > 1) {
-          if (add != 0) atomicAdd(&sums[die], add);
-          return;
-        }
-        for (uint64_t open = __ballot(add != 0); open != 0;) {        // neighbours are mostly on one die: LDS atomics on one address go one by one
-          const int d = __builtin_amdgcn_readlane(die, __builtin_ctzll(open));
-          const int sum = wave_scan(die == d ? add : 0);
-          if (lane == 63) atomicAdd(&sums[d], sum);
-          open &= __ballot(die != d);
-        }
-      });
-    }
-    if constexpr (!kPieces) {
-      for (int u = tid; u < n_units; u += kPlaceThreads) {
-        const Unit e = unit_of(u);
-        for (int r = 0; r < mod; ++r) atomicAdd(&s_total[first_die(e.stream) + r], group * with_residue(e.nb, r));
-      }
-    }
-    __syncthreads();
-    if (!kPieces && halves && tid < kXcds) queue_begin[kHalvedRows + tid] = worth_halves(s_longest, end_sel - first_sel, n_wg) ? s_halved[tid] : 0;
-    if (tid <= kXcds) {
-      int begin = 0;
-      for (int x = 0; x < tid; ++x) begin += s_total[x];
-      queue_begin[tid] = begin;
-    }
-    if (tid < kXcds) tickets[tid * kTicketStride] = uint32_t(grid - tid + kXcds - 1) / kXcds;   // see order_kernel
-    return;
-  }
+  const bool extra = blockIdx.x == gridDim.x - 1;             // writes the queues' beginnings, and has no rows
 
   // ---- the workgroup's sequence, heads and rows
   auto parts_of = [&](int nb) { return (group * with_residue(nb, 0) + kPlaceRows - 1) / kPlaceRows << log_mod; };   // of a unit: of every residue as many
-  int s = 0, part = int(blockIdx.x);
+  int s = 0, part = extra ? 0 : int(blockIdx.x);
   if (n_seq > 1) {
     const int at = min(lane, n_seq - 1), nb = s_blk[at + 1] - s_blk[at];
     const int end = wave_scan(lane < n_seq ? units * parts_of(nb) : 0);
@@ -526,7 +491,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   part -= unit * parts;
   const int res = part & (mod - 1), per_head = with_residue(nb, res), n_unit = group * per_head;   // rows of the unit on the die
   const int first = (part >> log_mod) * kPlaceRows;
-  if (first >= n_unit) return;
+  if (!extra && first >= n_unit) return;
   const int kv = map ? scalar(kv_head(unit)) : unit, die = first_die(s * hkv + kv) + res;
   auto head_of = [&](int at) { return quotient(at, per_head); };
   const int first_head = head_of(first), first_row = b0 * hq + (unit * group + first_head) * nb + ((first - first_head * per_head) << log_mod) + res;
@@ -537,10 +502,23 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   const int64_t begin = sel_ptr[row], end = sel_ptr[row + 1];
 
   // ---- count
-  int before = list_units(kPieces ? -1 : die), slots = 0, splits = 0;
+  int before = 0, slots = 0, splits = 0;
+  if (!extra || kPieces) before = list_units(kPieces ? -1 : die);
+  const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1))), key = min(n_sel, n_bins - 1);
+  const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
   __syncthreads();
   if constexpr (kPieces) before = 0;
   each_row(kPieces ? -1 : res, [&](int r, int die_of, int n, bool there) {
+    if (kPieces && extra) {
+      const int add = there ? pieces_here(n) : 0;
+      for (uint64_t open = __ballot(add != 0); open != 0;) {  // neighbours are mostly on one die: LDS atomics on one address go one by one
+        const int d = __builtin_amdgcn_readlane(die_of, __builtin_ctzll(open));
+        const int sum = wave_scan(die_of == d ? add : 0);
+        if (lane == 63) atomicAdd(&s_total[d], sum);
+        open &= __ballot(die_of != d);
+      }
+      return;
+    }
     bool active = there && (!kPieces || die_of == die);
     if (kPieces && there && die_of < die) {
       const int pieces = pieces_here(n);
@@ -563,6 +541,48 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     }
     if (active) atomicAdd(&s_bins[n], r < first_row ? 1ull | 1ull << 32 : 1ull);
   });
+  if (extra) {
+    if constexpr (!kPieces) {
+      // (a row's die is looked for only where it is worked on in halves)
+      for (int r0 = 0; halves && r0 < rows; r0 += 8 * kPlaceThreads) {
+        int64_t n[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int at = min(r0 + u * kPlaceThreads + tid, rows - 1);
+          n[u] = sel_ptr[at + 1] - sel_ptr[at];
+        }
+        uint32_t cut = 0;
+        int longest = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (r0 + u * kPlaceThreads + tid < rows && in_halves(n[u], end_sel - first_sel, n_wg)) {
+            cut |= 1u << u;
+            longest = max(longest, int(min(n[u], int64_t(kCostBins))));
+          }
+        if (cut != 0) atomicMax(&s_longest, longest);
+        for (; cut != 0; cut &= cut - 1) {
+          const int r = r0 + __builtin_ctz(cut) * kPlaceThreads + tid;
+          int of = 0;
+          while (r >= s_blk[of + 1] * hq) ++of;
+          const int its_nb = s_blk[of + 1] - s_blk[of], local = r - s_blk[of] * hq, its_h = quotient(local, its_nb);
+          atomicAdd(&s_halved[first_die(of * hkv + kv_head(its_h)) + ((local - its_h * its_nb) & (mod - 1))], 1);
+        }
+      }
+      for (int u = tid; u < n_units; u += kPlaceThreads) {
+        const Unit e = unit_of(u);
+        for (int r = 0; r < mod; ++r) atomicAdd(&s_total[first_die(e.stream) + r], group * with_residue(e.nb, r));
+      }
+    }
+    __syncthreads();
+    if (!kPieces && halves && tid < kXcds) queue_begin[kHalvedRows + tid] = worth_halves(s_longest, end_sel - first_sel, n_wg) ? s_halved[tid] : 0;
+    if (tid <= kXcds) {
+      int begin = 0;
+      for (int x = 0; x < tid; ++x) begin += s_total[x];
+      queue_begin[tid] = begin;
+    }
+    if (tid < kXcds) tickets[tid * kTicketStride] = uint32_t(grid - tid + kXcds - 1) / kXcds;   // see order_kernel
+    return;
+  }
   auto add_up = [&](int v, int32_t* sum) {
     v = wave_scan(v);
     if (lane == 63 && v != 0) atomicAdd(sum, v);
@@ -572,8 +592,6 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     add_up(slots, &s_slots);
     add_up(splits, &s_splits);
   }
-  const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1))), key = min(n_sel, n_bins - 1);
-  const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
   if (e8 == 0) s_n[slot_row] = live ? key : -1;
   __syncthreads();
 

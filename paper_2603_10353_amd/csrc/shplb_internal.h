@@ -140,15 +140,14 @@ constexpr int kHalvedRows = 16;       // halved rows of queue x: queue_begin[kHa
 __host__ __device__ inline int queue_place(int begin, int halved, int at) {
   return at < 2 * halved ? (begin + (at >> 1)) | ((at & 1) + 1) << kHalfShift : begin + at - halved;
 }
-// Rows of more blocks than this are worked on in halves, given what all rows select together and the persistent workgroups.
+// Whether a row is worked on in halves, given what all rows select together and the persistent workgroups: from 1.2 times the average share on.
 // A half takes some 0.65 of the row's time (its waves have half of the products and exponentials but all of the copies), so halves pay where
 // a row is longer than a workgroup's average share and the launch waits for it: 28/4 heads x 5971 with two dense ones 142 -> 112 us,
 // 8/2 x 16903 with one 332 -> 255, 32/8 x 3000 82 -> 70.  From 1.0 times the share on 16/4 x 12000 with two dense
 // ones takes 292 us for 276 (in whole rows 293), from 0.8 on 28/4 x (3107, 2525, 392) 129 for 119; with rows of 10 to 16
 // blocks in halves too 40/8 x 2155 takes 72 us for 69.
-__host__ __device__ inline int64_t halved_above(int64_t total_cost, int n_wg) {
-  const int64_t above = total_cost * 6 / (int64_t(n_wg) * 5);
-  return above < 16 ? 16 : above;
+__host__ __device__ inline bool in_halves(int64_t n_sel, int64_t total_cost, int n_wg) {
+  return n_sel > 16 && n_sel * 5 * n_wg > total_cost * 6;
 }
 // ... and whether any are: where the longest row of the launch is less than 5/3 of the share, all stay whole.  Halves are more work in all, and they
 // come before whole rows that take longer than they.  Attention calls in whole rows and in halves, longest row against the share: 32/8 heads x
@@ -156,7 +155,7 @@ __host__ __device__ inline int64_t halved_above(int64_t total_cost, int n_wg) {
 // 6000 with four 1.66 times 136 -> 153; of 33 calls from 5/3 on 31 are 6 to 25% faster and two 2% slower.  In between some
 // gain and lose this: 28/4 x 8231 with four dense ones 1.47 times 194 -> 182, 32/8 x 8231 with two 1.64 times 184 -> 169.
 __host__ __device__ inline bool worth_halves(int64_t longest, int64_t total_cost, int n_wg) {
-  return longest > halved_above(total_cost, n_wg) && longest * 3 * n_wg >= total_cost * 5;
+  return in_halves(longest, total_cost, n_wg) && longest * 3 * n_wg >= total_cost * 5;
 }
 
 // The per-XCD work queues the ordering kernel builds (device pointers into the workspace).
