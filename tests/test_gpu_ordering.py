@@ -9,7 +9,7 @@ import torch
 
 import paper_2603_10353_amd as S
 from oracle import shplb_oracle as orc
-from workloads import make_custom
+from workloads import make_custom, one_kv_head_per_query_head
 
 from checks import compare_output
 from harness import DevicePass, queues_of
@@ -488,3 +488,40 @@ def test_long_rows_in_halves(n_blocks, tail, heads, budgets):
     rows = np.flatnonzero(n > above)[[0, 1, -2, -1]].tolist() + [0, n_blocks - 1]
     out_o, lse_o = orc.sparse_attention(one.q, one.k, one.v, one.cu_seqlens, 128, a.sel_ptr_host, a.sel_idx_host(), None, rows)
     compare_output(a.out_host(), out_o, a.lse_host(), lse_o)
+
+
+@pytest.mark.parametrize("lens, heads, kv_of", [([128 * 50 - 9, 128 * 20 - 100, 130], (8, 2), None), ([128 * 66 - 1, 300], (8, 2), [0, 1, 1, 1, 1, 1, 1, 1]),
+                                                ([200, 128 * 40 - 64, 128 * 35 - 127], (9, 3), [2, 0, 0, 0, 1, 0, 2, 2, 0])])
+def test_halves_of_batches_and_mapped_heads(lens, heads, kv_of):
+    # Long rows in halves where the sequences are of unequal length or the heads have a map, for the lists of budgets, and for lists
+    # of which every third row has no block (its output stays as it is).
+    hq, hkv = heads
+    wl = make_custom(lens, hq, hkv, 128, ([999] + [2] * (hq - 2) + [3]), seed=670 + len(lens) + hq, name="halves_batch")
+    if kv_of:
+        wl.kv_head_of = np.array(kv_of, np.int32)
+    run = DevicePass(wl).run_all()
+    plain = one_kv_head_per_query_head(wl) if kv_of else wl
+    n = np.diff(run.sel_ptr_host)
+    rng = np.random.default_rng(671)
+    some = rng.permutation(run.rows)[:40].tolist()
+    print("case", lens, heads, "rows", run.rows, "in halves", int(halved_rows(n, int(n.sum()), run.n_wg).sum()), flush=True)
+    for empty in (False, True):
+        keep = np.arange(run.rows) % 3 != 1 if empty else np.ones(run.rows, bool)
+        idx = np.concatenate([run.sel_idx_host()[run.sel_ptr_host[r]:run.sel_ptr_host[r + 1]] for r in range(run.rows) if keep[r]])
+        ptr = np.concatenate([[0], np.cumsum(n * keep)]).astype(np.int64)
+        halved = np.flatnonzero(halved_rows(n * keep, int(ptr[-1]), run.n_wg))
+        assert run.n_wg < run.rows <= 6 * run.n_wg and len(halved) > 4
+        run.out.zero_()
+        run.lse.zero_()
+        run.attn_step(torch.from_numpy(ptr).to("cuda:0"), torch.from_numpy(idx).to("cuda:0"))
+        torch.cuda.synchronize()
+        st = run.stats_host()
+        assert st["n_items"].sum() == keep.sum() and st["cost_blocks"].sum() == ptr[-1]
+        rows = [r for r in set(some) | set(halved[[0, 1, -2, -1]].tolist()) if keep[r]]
+        out_o, lse_o = orc.sparse_attention(plain.q, plain.k, plain.v, wl.cu_seqlens, 128, ptr, idx, None, rows)
+        compare_output(run.out_host(), out_o, run.lse_host(), lse_o)
+        written = np.zeros((hq, int(wl.cu_seqlens[-1])), bool)
+        for r in np.flatnonzero(keep):
+            s, h, i = orc.row_decode(wl.cu_seqlens, 128, hq, r)
+            written[h, wl.cu_seqlens[s] + 128 * i:min(wl.cu_seqlens[s] + 128 * (i + 1), wl.cu_seqlens[s + 1])] = True
+        assert ((run.lse.cpu().numpy() != 0) == written).all()
