@@ -226,17 +226,19 @@ def test_queues_hold_every_piece_of_cut_rows(block, seqlens, heads, kv_of, slots
 
 
 # Beyond 2048 (sequence, head) pairs or 65536 rows (16384 with pieces) a workgroup per die sorts its rows: eight streams and more, three and one
-# (spread by query block), mapped heads, sequences of one block among long ones; the two limits by themselves too.
+# (spread by query block), mapped heads, sequences of one block among long ones.  On the other side of the limits too: 2048 pairs, as many rows
+# as are counted, on all dies and on one, and the most blocks of a sequence.
 @pytest.mark.parametrize("block, seqlens, heads, kv_of, long", [
     (64, [150, 3, 140] + [1] * 61, (40, 8), None, 9), (128, [9], (2100, 3), None, 9), (128, [9], (2100, 1), None, 9),
-    (64, [40, 3] + [2] * 62, (40, 9), [x % 9 for x in range(40)], 9), (64, [4096], (17, 1), None, 200), (64, [32], (2048, 8), None, 9)])
+    (64, [40, 3] + [2] * 62, (40, 9), [x % 9 for x in range(40)], 9), (64, [4096], (17, 1), None, 200), (64, [4096], (16, 1), None, 200),
+    (64, [4000] + [1] * 7, (16, 1), None, 200), (64, [32], (2048, 8), None, 9)])
 def test_queues_of_larger_launches(block, seqlens, heads, kv_of, long):
     queues_of_whole_rows(block, seqlens, heads, kv_of, long)
 
 
 @pytest.mark.parametrize("block, seqlens, heads, kv_of, slots, long", [
     (64, [150, 3, 140] + [1] * 61, (40, 8), None, 2048, 50), (64, [33], (2052, 3), None, 65536, 300), (128, [2100], (8, 1), None, 2048, 50),
-    (64, [90, 70] + [1] * 62, (40, 9), [x % 9 for x in range(40)], 300, 50), (128, [2048], (8, 1), None, 2048, 50)])
+    (64, [90, 70] + [1] * 62, (40, 9), [x % 9 for x in range(40)], 300, 50), (128, [2048], (8, 1), None, 2048, 50), (64, [4096], (4, 1), None, 2048, 50)])
 def test_queues_of_pieces_of_larger_launches(block, seqlens, heads, kv_of, slots, long):
     assert queues_of_pieces(block, seqlens, heads, kv_of, slots, long) > 0
 
