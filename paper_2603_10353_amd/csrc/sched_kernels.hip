@@ -342,17 +342,17 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(
 // longest ones, so the first; see in_halves() and worth_halves()).
 //
 // Pieces (kPieces): a row is cut into pieces_of() its own number of blocks, and the items in front of it are the pieces of the rows
-// in front.  The workgroups go through all rows, as the items of the dies before come first.  Split rows are the first of their queues, so slots and
-// counters are numbered like items and rows, behind those of the dies before.
+// in front.  Items of the dies before come first: their rows follow from the shapes, and all rows of the launch are looked at for those that are cut.
+// Split rows are the first of their queues, so slots and counters are numbered like items and rows, behind those of the dies before.
 //
 // What bounds it is the chain arguments -> row pointers -> first blocks, on as many compute units as there are rows for, with code that is not in
 // the instruction cache.  Every workgroup reads the row pointers of its die (with pieces of all rows), rows / 64 times in all: that is why
-// larger launches are sorted (places_counted()).  Under the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.4 us, 48
-// sequences x 28 heads 10.2 -> 5.7, 32K x 32 heads 12.0 -> 6.3, 128K 26 -> 10.2, 16K in pieces 18 -> 12.4.  (Workgroups of 256 threads take
-// 1 to 5 us longer, of 1024 as long or up to 1 us longer.  With the extra workgroup going through the dies of all rows, not only of those in halves, the 8K
-// prompt took 6.6; twice the code by four rows in flight, 0.4.)  Counted in closed form from what the last row of every head selects it
-// took 5.3, 6.7, 5.7, 7.3 and 6.8 us, but then a list that is no budget's, say a different number of blocks for every query block, is neither
-// ordered nor cut by its length: attention call of 8231 tokens x 32/8 heads with such lists 176 us, ordered 148.
+// larger launches are sorted (places_counted()).  Under the tracer, order_kernel against this: 8K prompt x 32 heads 9.7 -> 5.5 us, 48
+// sequences x 28 heads 10.2 -> 5.8, 32K x 32 heads 12.0 -> 6.5, 128K 26 -> 10.2, 16K in pieces 18 -> 9.2.  (Workgroups of 256 threads take
+// 1 to 5 us longer, of 1024 as long or up to 1 us longer.  With the dies of all rows worked out, not only of the long ones, the extra workgroup took
+// 6.6 at 8K and the pieces 12.4; four rows in flight, and so twice the code, 0.4 longer.)  Counted in closed form from what the last row of
+// every head selects it took 5.3, 6.7, 5.7, 7.3 and 6.8 us, but then a list that is no budget's, say a different number of blocks for every query
+// block, is neither ordered nor cut by its length: attention call of 8231 tokens x 32/8 heads with such lists 176 us, ordered 148.
 constexpr int kPlaceThreads = 512, kPlaceLanes = 8, kPlaceRows = kPlaceThreads / kPlaceLanes, kPlaceWaves = kPlaceThreads / 64;
 constexpr int kPlaceInFlight = 2;         // rows a thread has in flight
 
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   __shared__ uint32_t s_kv[SHPLB_MAX_MAPPED_HEADS / 4];
   __shared__ int32_t s_pre[kPlacePairs];     // listed units: listed rows before its own ...
   __shared__ int32_t s_row[kPlacePairs];     // ... first row ...
-  __shared__ uint32_t s_unit[kPlacePairs];   // ... blocks | stream << 16
+  __shared__ int32_t s_nb[kPlacePairs];      // ... blocks (streams on several dies)
   __shared__ int32_t s_listed;               // rows listed | units listed << 20
   __shared__ int32_t s_before, s_slots, s_splits;   // items, slots and split rows on the dies before
   __shared__ int32_t s_total[kXcds], s_halved[kXcds], s_longest, s_wave[2][kPlaceWaves], s_n[kPlaceRows];
@@ -391,6 +391,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   const int n_streams = n_seq * hkv;
   const int mod = n_streams < kXcds ? scalar(quotient(kXcds, n_streams)) : 1;   // dies of a stream: 1, 2, 4 or 8
   const int log_mod = 31 - __builtin_clz(mod);
+  const int top_seq = n_seq > 1 ? 1 << (31 - __builtin_clz(n_seq - 1)) : 0;
   if (tid <= SHPLB_MAX_SEQ) {
     s_blk[tid] = my_blk;
     s_tok[tid] = my_tok;
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
   auto with_residue = [&](int nb, int r) { return (nb + mod - 1 - r) >> log_mod; };
   auto below_residue = [&](int nb, int r) { return (nb >> log_mod) * r + min(nb & (mod - 1), r); };
 
-  // List the units that have rows on `die` (all units where it is negative), in any order.  Returns a thread's sum of the rows on the dies before.
+  // List the units that have rows on `die`, in any order.  Returns a thread's sum of the rows on the dies before.
   auto list_units = [&](int die) {
     int before = 0;
     for (int u0 = 0; u0 < n_units; u0 += kPlaceThreads) {
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
       if (u < n_units) {
         e = unit_of(u);
         const int r = die - first_die(e.stream);              // the residue that lives on the die, if it is one
-        n = group * (die < 0 ? e.nb : r >= 0 && r < mod ? with_residue(e.nb, r) : 0);
+        n = r >= 0 && r < mod ? group * with_residue(e.nb, r) : 0;
         before += group * below_residue(e.nb, min(max(r, 0), mod));
       }
       const uint32_t own = n > 0 ? uint32_t(n) | 1u << 20 : 0u;
@@ -433,34 +434,30 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
       if (n > 0) {
         s_pre[at >> 20] = int(at & 0xfffff);
         s_row[at >> 20] = e.row;
-        s_unit[at >> 20] = uint32_t(e.nb | e.stream << 16);
+        if (mod > 1) s_nb[at >> 20] = e.nb;
       }
     }
     return before;
   };
-  // f(row, die, blocks it selects, whether there is a row) for the listed rows (those of residue `res`; negative: of all), by whole waves
+  // f(row, blocks it selects, whether there is a row) for the listed rows, of residue `res`, by whole waves
   auto each_row = [&](int res, auto&& f) {
     const int n_rows = s_listed & 0xfffff, n_list = int(uint32_t(s_listed) >> 20);
     const int top = n_list > 1 ? 1 << (31 - __builtin_clz(n_list - 1)) : 0;
     for (int r0 = 0; r0 < n_rows; r0 += kPlaceInFlight * kPlaceThreads) {
-      int row[kPlaceInFlight], die[kPlaceInFlight];
+      int row[kPlaceInFlight];
       int64_t begin[kPlaceInFlight], end[kPlaceInFlight];
 #pragma unroll
       for (int u = 0; u < kPlaceInFlight; ++u) {
         row[u] = -1;
-        die[u] = 0;
         if (r0 + u * kPlaceThreads >= n_rows) continue;       // (the same for all)
         const int r = r0 + u * kPlaceThreads + tid;
         int x = 0;
         for (int d = top; d > 0; d >>= 1)
           if (x + d < n_list && s_pre[x + d] <= r) x += d;
-        const int nb = int(s_unit[x] & 0xffff), stream = int(s_unit[x] >> 16), local = r - s_pre[x];
-        int at = local;
-        die[u] = first_die(stream);
+        int at = r - s_pre[x];
         if (mod > 1) {
-          const int per_head = res < 0 ? nb : with_residue(nb, res), h = quotient(local, per_head), i = local - h * per_head;
-          at = res < 0 ? local : h * nb + (i << log_mod) + res;
-          die[u] += res < 0 ? i & (mod - 1) : res;
+          const int nb = s_nb[x], per_head = with_residue(nb, res), h = quotient(at, per_head);
+          at = h * nb + ((at - h * per_head) << log_mod) + res;
         }
         if (r < n_rows) row[u] = s_row[x] + at;
         begin[u] = sel_ptr[max(row[u], 0)];
@@ -469,7 +466,32 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
 #pragma unroll
       for (int u = 0; u < kPlaceInFlight; ++u)
         if (r0 + u * kPlaceThreads < n_rows)
-          f(row[u], die[u], int(min(max(end[u] - begin[u], int64_t(0)), int64_t(n_bins - 1))), row[u] >= 0);
+          f(row[u], int(min(max(end[u] - begin[u], int64_t(0)), int64_t(n_bins - 1))), row[u] >= 0);
+    }
+  };
+  // f(die, blocks it selects) for every row of the launch for which is_long(blocks) holds.  (Only those are decoded.)
+  auto each_long = [&](auto&& is_long, auto&& f) {
+    constexpr int kRun = 8;
+    for (int r0 = 0; r0 < rows; r0 += kRun * kPlaceThreads) {
+      int n[kRun];
+      uint32_t found = 0;
+#pragma unroll
+      for (int u = 0; u < kRun; ++u) {
+        const int at = min(r0 + u * kPlaceThreads + tid, rows - 1);
+        n[u] = int(min(max(sel_ptr[at + 1] - sel_ptr[at], int64_t(0)), int64_t(n_bins - 1)));
+      }
+#pragma unroll
+      for (int u = 0; u < kRun; ++u) found |= r0 + u * kPlaceThreads + tid < rows && is_long(n[u]) ? 1u << u : 0u;
+      for (; found != 0; found &= found - 1) {
+        const int u = __builtin_ctz(found), r = r0 + u * kPlaceThreads + tid;
+        int n_u = n[0], of = 0;
+#pragma unroll
+        for (int x = 1; x < kRun; ++x) n_u = u == x ? n[x] : n_u;
+        for (int d = top_seq; d > 0; d >>= 1)
+          if (of + d < n_seq && s_blk[of + d] * hq <= r) of += d;
+        const int nb = s_blk[of + 1] - s_blk[of], local = r - s_blk[of] * hq, h = quotient(local, nb);
+        f(first_die(of * hkv + kv_head(h)) + ((local - h * nb) & (mod - 1)), n_u);
+      }
     }
   };
   const int len = kPieces ? int(min(split_length(end_sel - first_sel, slot_capacity, n_wg, meta.block), int64_t(1 << 24))) : 0;
@@ -503,29 +525,23 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
 
   // ---- count
   int before = 0, slots = 0, splits = 0;
-  if (!extra || kPieces) before = list_units(kPieces ? -1 : die);
+  if (!extra) before = list_units(die);
   const int n_sel = int(min(max(end - begin, int64_t(0)), int64_t(kCostBins - 1))), key = min(n_sel, n_bins - 1);
   const int first_j = n_sel > 0 ? sel_idx[begin] : 0, second_j = n_sel > 0 ? sel_idx[begin + min(1, n_sel - 1)] : 0;
   __syncthreads();
-  if constexpr (kPieces) before = 0;
-  each_row(kPieces ? -1 : res, [&](int r, int die_of, int n, bool there) {
-    if (kPieces && extra) {
-      const int add = there ? pieces_here(n) : 0;
-      for (uint64_t open = __ballot(add != 0); open != 0;) {  // neighbours are mostly on one die: LDS atomics on one address go one by one
-        const int d = __builtin_amdgcn_readlane(die_of, __builtin_ctzll(open));
-        const int sum = wave_scan(die_of == d ? add : 0);
-        if (lane == 63) atomicAdd(&s_total[d], sum);
-        open &= __ballot(die_of != d);
-      }
-      return;
-    }
-    bool active = there && (!kPieces || die_of == die);
-    if (kPieces && there && die_of < die) {
+  // Pieces: every row is an item and rows of more than `len` blocks are more than one, of which the dies before matter
+  if constexpr (kPieces)
+    each_long([&](int n) { return n > len; }, [&](int of, int n) {
       const int pieces = pieces_here(n);
-      before += pieces;
-      slots += pieces > 1 ? pieces : 0;
-      splits += pieces > 1;
-    }
+      if (extra) {
+        atomicAdd(&s_total[of], pieces - 1);
+      } else if (of < die) {
+        before += pieces - 1;
+        slots += pieces;
+        splits += 1;
+      }
+    });
+  each_row(res, [&](int r, int n, bool active) {
     // rows of a wave are mostly neighbours of one head: two bins are counted by ballot, the rest lane by lane (see take_places())
     const uint64_t front = __ballot(r < first_row);
 #pragma unroll
@@ -542,36 +558,14 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
     if (active) atomicAdd(&s_bins[n], r < first_row ? 1ull | 1ull << 32 : 1ull);
   });
   if (extra) {
-    if constexpr (!kPieces) {
-      // (a row's die is looked for only where it is worked on in halves)
-      for (int r0 = 0; halves && r0 < rows; r0 += 8 * kPlaceThreads) {
-        int64_t n[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int at = min(r0 + u * kPlaceThreads + tid, rows - 1);
-          n[u] = sel_ptr[at + 1] - sel_ptr[at];
-        }
-        uint32_t cut = 0;
-        int longest = 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (r0 + u * kPlaceThreads + tid < rows && in_halves(n[u], end_sel - first_sel, n_wg)) {
-            cut |= 1u << u;
-            longest = max(longest, int(min(n[u], int64_t(kCostBins))));
-          }
-        if (cut != 0) atomicMax(&s_longest, longest);
-        for (; cut != 0; cut &= cut - 1) {
-          const int r = r0 + __builtin_ctz(cut) * kPlaceThreads + tid;
-          int of = 0;
-          while (r >= s_blk[of + 1] * hq) ++of;
-          const int its_nb = s_blk[of + 1] - s_blk[of], local = r - s_blk[of] * hq, its_h = quotient(local, its_nb);
-          atomicAdd(&s_halved[first_die(of * hkv + kv_head(its_h)) + ((local - its_h * its_nb) & (mod - 1))], 1);
-        }
-      }
-      for (int u = tid; u < n_units; u += kPlaceThreads) {
-        const Unit e = unit_of(u);
-        for (int r = 0; r < mod; ++r) atomicAdd(&s_total[first_die(e.stream) + r], group * with_residue(e.nb, r));
-      }
+    if (!kPieces && halves)
+      each_long([&](int n) { return in_halves(n, end_sel - first_sel, n_wg); }, [&](int of, int n) {
+        atomicAdd(&s_halved[of], 1);
+        atomicMax(&s_longest, n);
+      });
+    for (int u = tid; u < n_units; u += kPlaceThreads) {
+      const Unit e = unit_of(u);
+      for (int r = 0; r < mod; ++r) atomicAdd(&s_total[first_die(e.stream) + r], group * with_residue(e.nb, r));
     }
     __syncthreads();
     if (!kPieces && halves && tid < kXcds) queue_begin[kHalvedRows + tid] = worth_halves(s_longest, end_sel - first_sel, n_wg) ? s_halved[tid] : 0;
